@@ -362,7 +362,7 @@ int moe_attention_workspace_bytes(const moe_config* cfg, const moe_encoder_dims*
 int moe_encoder_workspace_bytes(const moe_config* cfg, const moe_encoder_dims* dims, size_t* bytes);
 
 /* out = Attention(u) (no residual): u [B,L,M], wqkv [M,3A], wo_att [A,M] -> out [B,L,M].
- * The flash-style MFMA kernel serves bf16 with d in {64,128} and L % 128 == 0; other
+ * The flash-style MFMA kernel serves bf16 with d in {64,128}, any L; other
  * shapes use a plain kernel that needs (L + d) * 16 bytes of LDS <= 64 KB. */
 int moe_self_attention(const moe_config* cfg, const moe_encoder_dims* dims, const void* u,
                        const void* wqkv, const void* wo_att, void* out,
@@ -414,7 +414,7 @@ int moe_encoder_pair_forward_train(const moe_config* cfg, const moe_encoder_dims
  * moe_encoder_pair_forward_train.  out: dx [B,L,M]; every member of g (fully overwritten).
  * ws >= moe_encoder_backward_workspace_bytes, 256-byte aligned.  Errors as the other calls;
  * MOE_EUNSUPPORTED also when the attention shape is served by neither form of the core's
- * derivative: the MFMA kernels take bf16 with d in {64,128} and L % 128 == 0, the plain kernels
+ * derivative: the MFMA kernels take bf16 with d in {64,128}, the plain kernels
  * need (2 L + 2 d) * 16 bytes of LDS <= 64 KB; and when M * 16 bytes > 64 KB (layer-norm
  * parameter sums).  Results are bit-reproducible (no atomics). */
 int moe_encoder_pair_backward(const moe_config* cfg, const moe_encoder_dims* dims, const void* x,

@@ -1,5 +1,4 @@
-// Backward of the scaled dot-product attention core on the matrix cores (bf16, d = 64 or 128,
-// L a multiple of 128).  Section 2.1 of the paper names the self-attention sub-layer; the
+// Backward of the scaled dot-product attention core on the matrix cores (bf16, d = 64 or 128).  Section 2.1 of the paper names the self-attention sub-layer; the
 // derivative is the chain rule of ctx = softmax(q k^T / sqrt(d)) v, with the probabilities
 // recomputed from q, k and the stored row statistic lse = log sum_k exp(score):
 //
@@ -18,6 +17,11 @@
 //               S = Q K^T and dP = dO V^T (queries x keys; Q, dO rows from LDS, K^T and V^T
 //               fragments in registers), P and dS in registers become the B operands of
 //               dV^T += dO^T P and dK^T += Q^T dS.
+//
+// RAGGED (both): L is no multiple of 128.  Rows past the end are read from row L - 1 and their part of
+// P and dS is made 0 (dq kernel: keys >= L; dkv kernel: queries >= L, through lse = +inf and D = 0);
+// rows past the end of the block's own side are not stored.  L % 128 == 0 keeps the form without
+// these tests.
 //
 // MFMA register layout (v_mfma_f32_32x32x16_bf16): lane (r = lane % 32, hf = lane / 32) supplies
 // row r of the first operand and column r of the second, k = 8 hf .. 8 hf + 7 of the step; it
@@ -82,7 +86,7 @@ __device__ __forceinline__ bf16x8_t read_transposed(uint32_t block, int row16, i
 }
 
 // ---------------------------------------------------------------- dq (and D)
-template <int D>
+template <int D, bool RAGGED>
 __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
     const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
     const float* __restrict__ lse, bf16_t* __restrict__ dqkv, float* __restrict__ dvec, int L,
@@ -94,7 +98,7 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
   extern __shared__ __attribute__((aligned(16))) unsigned char att_bwd_lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, hf = lane >> 5;
-  const int qblocks = L / 128;
+  const int qblocks = (L + 127) / 128;
   const unsigned work = xcd_contiguous(blockIdx.x, gridDim.x);
   const int qb = work % qblocks;
   const long long bh = work / qblocks;
@@ -108,8 +112,10 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
   const int q = qb * 128 + wave * 32 + r;
 
   // Q^T and dO^T fragments of this wavefront's queries, D of the lane's query
-  const bf16_t* qrow = base + (size_t)q * ld;
-  const size_t crow = ((size_t)b * L + q) * A + (size_t)h * D;
+  const int qc = RAGGED && q >= L ? L - 1 : q;
+  const bool live = !RAGGED || qb * 128 + __builtin_amdgcn_readfirstlane(wave) * 32 < L;
+  const bf16_t* qrow = base + (size_t)qc * ld;
+  const size_t crow = ((size_t)b * L + qc) * A + (size_t)h * D;
   u32x4_t qf[KS], dof[KS];
   float dd = 0.f;
 #pragma unroll
@@ -124,8 +130,8 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
     for (int i = 0; i < 8; ++i) dd = fmaf(g[i], o[i], dd);
   }
   dd += __shfl_xor(dd, 32, 64);
-  if (hf == 0) dvec[(size_t)bh * L + q] = dd;
-  const float lse2 = lse[(size_t)bh * L + q] * 1.4426950408889634f;
+  if (hf == 0 && (!RAGGED || q < L)) dvec[(size_t)bh * L + q] = dd;
+  const float lse2 = lse[(size_t)bh * L + qc] * 1.4426950408889634f;
   const float scale = 1.0f / sqrtf((float)D);
   const float sl2 = 1.4426950408889634f * scale;
 
@@ -139,9 +145,11 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
   u32x4_t kreg[VV], vreg[VV];
 #define MOE_ATTB_LOAD(kb)                                                                     \
   _Pragma("unroll") for (int i = 0; i < VV; ++i) {                                            \
-    const int f = tid + 256 * i, key = f / VPR, c = f % VPR;                                  \
-    kreg[i] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)((kb) * 64 + key) * ld + 8 * c); \
-    vreg[i] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)((kb) * 64 + key) * ld + 8 * c); \
+    const int f = tid + 256 * i, c = f % VPR;                                                 \
+    int key = (kb) * 64 + f / VPR;                                                            \
+    if (RAGGED) key = key < L ? key : L - 1;                                                  \
+    kreg[i] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)key * ld + 8 * c);            \
+    vreg[i] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)key * ld + 8 * c);            \
   }
 #define MOE_ATTB_STORE(stage)                                                                 \
   _Pragma("unroll") for (int i = 0; i < VV; ++i) {                                            \
@@ -151,7 +159,7 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
     *reinterpret_cast<u32x4_t*>(sb + kVRows + key * GM::kRowPitch + 16 * c) = vreg[i];        \
     *reinterpret_cast<u32x4_t*>(sb + kKPerm + swap_bits_2_3(key) * GM::kTrPitch + 16 * c) = kreg[i]; \
   }
-  const int nkb = L / 64;
+  const int nkb = RAGGED ? (L + 63) / 64 : L / 64;
   const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_ptr)att_bwd_lds);
   for (int kb = 0; kb < nkb; ++kb) {
     // one LDS stage, two blocks per CU: the other block multiplies while this one stages
@@ -159,6 +167,7 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
     __syncthreads();                         // the previous key block has been read by everyone
     MOE_ATTB_STORE(0)
     __syncthreads();
+    if (!live) continue;                     // (both barriers of the next block are still reached)
     const uint32_t kst = lds0, vst = kst + kVRows, kpst = kst + kKPerm;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -177,6 +186,11 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
 #pragma unroll
       for (int i = 0; i < 16; ++i)
         ds[i] = __builtin_amdgcn_exp2f(fmaf(sacc[i], sl2, -lse2)) * (dpacc[i] - dd);
+      if (RAGGED && kb * 64 + 64 > L) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (kb * 64 + 32 * t + 8 * (i >> 2) + 4 * hf + (i & 3) >= L) ds[i] = 0.f;
+      }
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         const u32x4_t dsf = pack8(ds + 8 * s);
@@ -190,6 +204,7 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
   }
 #undef MOE_ATTB_LOAD
 #undef MOE_ATTB_STORE
+  if (RAGGED && q >= L) return;
   // dq[dt][i]: d = 32 dt + 8 (i/4) + 4 hf + i%4 of query r
   bf16_t* orow = dqkv + ((size_t)b * L + q) * ld + (size_t)h * D;
 #pragma unroll
@@ -203,7 +218,7 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
 }
 
 // ---------------------------------------------------------------- dk, dv
-template <int D>
+template <int D, bool RAGGED>
 __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
     const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
     const float* __restrict__ dvec, bf16_t* __restrict__ dqkv, int L, int heads) {
@@ -216,7 +231,7 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
   extern __shared__ __attribute__((aligned(16))) unsigned char att_bwd_lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, hf = lane >> 5;
-  const int kblocks = L / 128;
+  const int kblocks = (L + 127) / 128;
   const unsigned work = xcd_contiguous(blockIdx.x, gridDim.x);
   const int kblk = work % kblocks;
   const long long bh = work / kblocks;
@@ -231,7 +246,8 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
   const int key = kblk * 128 + wave * 32 + r;
 
   // K and V fragments of this wavefront's keys: lane (r, hf) holds d = 16 s + 8 hf .. + 7
-  const bf16_t* krow = qbase + (size_t)key * ld + A;
+  const bool live = !RAGGED || kblk * 128 + __builtin_amdgcn_readfirstlane(wave) * 32 < L;
+  const bf16_t* krow = qbase + (size_t)(RAGGED && key >= L ? L - 1 : key) * ld + A;
   u32x4_t kf[KS], vf[KS];
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
@@ -253,12 +269,17 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
 #define MOE_ATTB_LOAD(qb)                                                                     \
   {                                                                                           \
     _Pragma("unroll") for (int i = 0; i < VV; ++i) {                                          \
-      const int f = tid + 256 * i, row = f / VPR, c = f % VPR;                                \
-      qreg[i] = *reinterpret_cast<const u32x4_t*>(qbase + (size_t)((qb) * 64 + row) * ld + 8 * c); \
-      greg[i] = *reinterpret_cast<const u32x4_t*>(gbase + (size_t)((qb) * 64 + row) * A + 8 * c); \
+      const int f = tid + 256 * i, c = f % VPR;                                               \
+      int row = (qb) * 64 + f / VPR;                                                          \
+      if (RAGGED) row = row < L ? row : L - 1;                                                \
+      qreg[i] = *reinterpret_cast<const u32x4_t*>(qbase + (size_t)row * ld + 8 * c);          \
+      greg[i] = *reinterpret_cast<const u32x4_t*>(gbase + (size_t)row * A + 8 * c);           \
     }                                                                                         \
-    if (tid < 64) st_reg = lse_h[(qb) * 64 + tid] * 1.4426950408889634f;                      \
-    else if (tid < 128) st_reg = dvec_h[(qb) * 64 + tid - 64];                                \
+    if (tid < 128) {                                                                          \
+      const int row = (qb) * 64 + (tid & 63);                                                 \
+      if (RAGGED && row >= L) st_reg = tid < 64 ? INFINITY : 0.f;                             \
+      else st_reg = tid < 64 ? lse_h[row] * 1.4426950408889634f : dvec_h[row];                \
+    }                                                                                         \
   }
 #define MOE_ATTB_STORE(stage)                                                                 \
   {                                                                                           \
@@ -273,7 +294,7 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
     }                                                                                         \
     if (tid < 128) *reinterpret_cast<float*>(sb + kStats + 4 * tid) = st_reg;                 \
   }
-  const int nqb = L / 64;
+  const int nqb = RAGGED ? (L + 63) / 64 : L / 64;
   MOE_ATTB_LOAD(0)
   MOE_ATTB_STORE(0)
   __syncthreads();
@@ -284,6 +305,7 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
     const uint32_t qpst = qst + kQPerm, gpst = qst + kGPerm, sst = qst + kStats;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
+      if (!live) break;
       f32x16_t sacc, dpacc;
 #pragma unroll
       for (int i = 0; i < 16; ++i) { sacc[i] = 0.f; dpacc[i] = 0.f; }
@@ -328,6 +350,7 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
   }
 #undef MOE_ATTB_LOAD
 #undef MOE_ATTB_STORE
+  if (RAGGED && key >= L) return;
   // dk[dt][i], dv[dt][i]: d = 32 dt + 8 (i/4) + 4 hf + i%4 of key r
   bf16_t* orow = dqkv + ((size_t)b * L + key) * ld + A + (size_t)h * D;
 #pragma unroll
@@ -343,28 +366,28 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
     }
 }
 
-template <int D>
+template <int D, bool RAGGED>
 int prepare_bwd() {
   using GM = AttBwdGeom<D>;
   constexpr int kLdsQ = 2 * GM::kRowBlock + GM::kTrBlock;      // one stage
   constexpr int kLdsKV = 2 * (2 * GM::kRowBlock + 2 * GM::kTrBlock + 512);
   static_assert(kLdsKV <= 160 * 1024, "two stages must fit the 160 KB of LDS");
   static LdsLimitOnce once_q, once_kv;
-  const int rc = ensure_lds_limit(once_q, reinterpret_cast<const void*>(attention_bwd_dq_mfma_kernel<D>), kLdsQ);
+  const int rc = ensure_lds_limit(once_q, reinterpret_cast<const void*>(attention_bwd_dq_mfma_kernel<D, RAGGED>), kLdsQ);
   if (rc != MOE_OK) return rc;
-  return ensure_lds_limit(once_kv, reinterpret_cast<const void*>(attention_bwd_dkv_mfma_kernel<D>), kLdsKV);
+  return ensure_lds_limit(once_kv, reinterpret_cast<const void*>(attention_bwd_dkv_mfma_kernel<D, RAGGED>), kLdsKV);
 }
 
-template <int D>
+template <int D, bool RAGGED>
 int launch_bwd(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse,
                bf16_t* dqkv, float* dvec, long long B, int L, int heads, hipStream_t st) {
   using GM = AttBwdGeom<D>;
   constexpr int kLdsQ = 2 * GM::kRowBlock + GM::kTrBlock;      // one stage
   constexpr int kLdsKV = 2 * (2 * GM::kRowBlock + 2 * GM::kTrBlock + 512);
-  auto kq = attention_bwd_dq_mfma_kernel<D>;
-  auto kkv = attention_bwd_dkv_mfma_kernel<D>;
-  if (prepare_bwd<D>() != MOE_OK) return MOE_EHIP;
-  const long long blocks = B * heads * (L / 128);
+  auto kq = attention_bwd_dq_mfma_kernel<D, RAGGED>;
+  auto kkv = attention_bwd_dkv_mfma_kernel<D, RAGGED>;
+  if (prepare_bwd<D, RAGGED>() != MOE_OK) return MOE_EHIP;
+  const long long blocks = B * heads * ((L + 127) / 128);
   if (blocks > 0x7fffffffLL) return MOE_EUNSUPPORTED;
   hipLaunchKernelGGL(kq, dim3((unsigned)blocks), dim3(256), kLdsQ, st, qkv, ctx, dctx, lse, dqkv, dvec,
                      L, heads);
@@ -375,25 +398,31 @@ int launch_bwd(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const f
 
 }  // namespace
 
-bool attention_bwd_mfma_ok(int act_dtype, int L, int d) {
-  return act_dtype == MOE_BF16 && (d == 64 || d == 128) && L % 128 == 0;
+bool attention_bwd_mfma_ok(int act_dtype, int d) {
+  return act_dtype == MOE_BF16 && (d == 64 || d == 128);
 }
 
 int prepare_attention_bwd() {
-  const int rc = prepare_bwd<64>();
-  return rc != MOE_OK ? rc : prepare_bwd<128>();
+  const int rcs[] = {prepare_bwd<64, false>(), prepare_bwd<64, true>(), prepare_bwd<128, false>(),
+                     prepare_bwd<128, true>()};
+  for (int rc : rcs)
+    if (rc != MOE_OK) return rc;
+  return MOE_OK;
 }
 
 int launch_attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, const float* lse,
                               void* dqkv, float* dvec, long long B, int L, int heads, int d,
                               hipStream_t st) {
-  if (!attention_bwd_mfma_ok(MOE_BF16, L, d)) return MOE_EUNSUPPORTED;
+  if (!attention_bwd_mfma_ok(MOE_BF16, d)) return MOE_EUNSUPPORTED;
   auto q = static_cast<const bf16_t*>(qkv);
   auto c = static_cast<const bf16_t*>(ctx);
   auto g = static_cast<const bf16_t*>(dctx);
   auto o = static_cast<bf16_t*>(dqkv);
-  return d == 64 ? launch_bwd<64>(q, c, g, lse, o, dvec, B, L, heads, st)
-                 : launch_bwd<128>(q, c, g, lse, o, dvec, B, L, heads, st);
+  if (L % 128 != 0)
+    return d == 64 ? launch_bwd<64, true>(q, c, g, lse, o, dvec, B, L, heads, st)
+                   : launch_bwd<128, true>(q, c, g, lse, o, dvec, B, L, heads, st);
+  return d == 64 ? launch_bwd<64, false>(q, c, g, lse, o, dvec, B, L, heads, st)
+                 : launch_bwd<128, false>(q, c, g, lse, o, dvec, B, L, heads, st);
 }
 
 }  // namespace moe

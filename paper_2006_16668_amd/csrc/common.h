@@ -248,8 +248,8 @@ int dense_wgrad_splits(int act_dtype, long long rows, int in, int out);
 size_t dense_wgrad_partial_bytes(int act_dtype, long long rows, int in, int out);
 int launch_dense_wgrad(const moe_config& c, long long rows, int in, int out, const void* X,
                        const void* dY, void* dW, float* partial, hipStream_t st);
-// MFMA form (attention_bwd_mfma.hip): bf16, d = 64 or 128, L % 128 == 0
-bool attention_bwd_mfma_ok(int act_dtype, int L, int d);
+// MFMA form (attention_bwd_mfma.hip): bf16, d = 64 or 128
+bool attention_bwd_mfma_ok(int act_dtype, int d);
 int launch_attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, const float* lse,
                               void* dqkv, float* dvec, long long B, int L, int heads, int d,
                               hipStream_t st);
