@@ -182,7 +182,7 @@ int moe_dispatch(const moe_config* cfg, const void* x, const int32_t* src_token,
  * buffer position holds a token or nothing).  With fill and ws, and when
  * moe_forward_packs_rows(cfg) says the kernels take the shape, only the occupied slots are
  * multiplied: the kernels pack each expert's occupied rows to the front of its block (row maps
- * in ws), multiply whole 256-row tiles of them and store each result row at its slot of out;
+ * in ws), multiply the row tiles that hold them and store each result row at its slot of out;
  * the slots c >= fill[g,e] of out are then NOT written (combine never reads them).  Occupied
  * rows get bit-identical results either way.
  */
@@ -213,9 +213,9 @@ int moe_forward(const moe_config* cfg, const void* x, const float* wg, const flo
 /*
  * Whether moe_forward folds the dispatch into the first expert GEMM for this config
  * (Section 3.2's gather form: the GEMM's operand copies pick the rows of x through
- * src_token, and the [E,G,C,M] buffer is never written).  It does so for bf16 layers
- * with G*C % 256 == 0, H % 256 == 0, M % 32 == 0 and M >= 128; other shapes run the
- * dispatch kernel.  The results are bit-identical either way.
+ * row indices, and the [E,G,C,M] buffer is never written).  It does so for bf16 layers
+ * with M >= 128 and E <= 2048; other shapes run the dispatch kernel.  The results are
+ * bit-identical either way.
  * Pure host function: *fused = 1 or 0; returns MOE_OK or the config's error.
  */
 int moe_forward_fuses_dispatch(const moe_config* cfg, int* fused);
@@ -223,9 +223,9 @@ int moe_forward_fuses_dispatch(const moe_config* cfg, int* fused);
 /*
  * Whether moe_forward (and moe_expert_ffn with fill and ws) multiplies only the occupied
  * expert rows for this config (Section 2.2, "Expert capacity"): the kept rows of an expert
- * are packed to the front of its block of G*C rows and only the ceil(kept / 256) row tiles
- * that hold them go through the two GEMMs.  It does so for bf16 layers with G*C, M and H
- * all multiples of 256.  moe_forward_train keeps every slot in place.
+ * are packed to the front of its block of G*C rows and only the row tiles that hold them go
+ * through the two GEMMs.  It does so for bf16 layers with M >= 128 and E <= 2048;
+ * moe_forward_train does the same.
  * Pure host function: *packed = 1 or 0; returns MOE_OK or the config's error.
  */
 int moe_forward_packs_rows(const moe_config* cfg, int* packed);

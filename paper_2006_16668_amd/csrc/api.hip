@@ -69,8 +69,8 @@ ForwardWs carve(const moe_config& c, bool train) {
   w.zero_row = take((size_t)c.M * elt);
   w.packing = take(moe::expert_ffn_can_pack(c) ? moe::row_packing_bytes(c) : 0);
   w.gates = take(train ? N * c.E * 4 : 0);
-  w.signbits = take(train && moe::expert_gemm1_can_gather(c) ? moe::expert_signbits_bytes(c) : 0);
-  w.buf = take(moe::expert_gemm1_can_gather(c) ? 0 : rows * c.M * elt);   // gathered from x instead
+  w.signbits = take(train ? moe::expert_signbits_bytes(c) : 0);
+  w.buf = take(moe::expert_ffn_can_pack(c) ? 0 : rows * c.M * elt);   // gathered from x instead
   w.h = take(rows * c.H * elt);
   w.out = take(rows * c.M * elt);
   w.gate_ws = take(moe::gate_workspace_bytes(c));
@@ -129,10 +129,9 @@ int forward_impl(const moe_config* cfg, const void* x, const float* wg, const fl
   int32_t* slot = reinterpret_cast<int32_t*>(base + w.slot);
   float* weight = reinterpret_cast<float*>(base + w.weight);
   int32_t* src_token = reinterpret_cast<int32_t*>(base + w.src_token);
-  // bf16 layers whose shape the persistent GEMM takes skip the dispatched buffer: the first
-  // GEMM gathers its rows from x (then the dispatch mark coincides with the gate mark)
-  const bool gather = moe::expert_gemm1_can_gather(*cfg);
-  // ... and multiply only the occupied rows of each expert, packed to the front of its block
+  // bf16 layers multiply only the occupied rows of each expert, packed to the front of its block, and
+  // skip the dispatched buffer: the first GEMM gathers its rows from x (then the dispatch mark
+  // coincides with the gate mark)
   const bool packed = moe::expert_ffn_can_pack(*cfg);
   const moe::RowPacking pk = moe::carve_row_packing(*cfg, base + w.packing);
   if (!mark(0)) return MOE_EHIP;
@@ -141,23 +140,21 @@ int forward_impl(const moe_config* cfg, const void* x, const float* wg, const fl
                         reinterpret_cast<int32_t*>(base + w.c1),
                         reinterpret_cast<float*>(base + w.mean_gate), aux,
                         keep_gates ? reinterpret_cast<float*>(base + w.gates) : nullptr,
-                        base + w.gate_ws, gather ? base + w.zero_row : nullptr,
+                        base + w.gate_ws, packed ? base + w.zero_row : nullptr,
                         packed ? &pk : nullptr, wg_packed, st);
   if (rc != MOE_OK) return rc;
   if (!mark(1)) return MOE_EHIP;
-  if (!gather) rc = moe::launch_dispatch(*cfg, x, src_token, base + w.buf, nullptr, st);
+  if (!packed) rc = moe::launch_dispatch(*cfg, x, src_token, base + w.buf, nullptr, st);
   if (rc != MOE_OK) return rc;
   if (!mark(2)) return MOE_EHIP;
   if (packed) {
     rc = moe::launch_expert_ffn_packed(*cfg, x, pk, base + w.zero_row, wi, wo, base + w.h,
-                                       base + w.out, false, keep_gates ? base + w.signbits : nullptr,
+                                       base + w.out, false, keep_gates,
+                                       keep_gates ? base + w.signbits : nullptr,
                                        st, events != nullptr ? events[3] : nullptr);
     if (rc != MOE_OK) return rc;
   } else {
-    rc = gather ? moe::launch_expert_gemm1_gather(*cfg, x, src_token, base + w.zero_row, wi,
-                                                  base + w.h, keep_gates ? base + w.signbits : nullptr,
-                                                  st)
-                : moe::launch_expert_gemm1(*cfg, base + w.buf, wi, base + w.h, st);
+    rc = moe::launch_expert_gemm1(*cfg, base + w.buf, wi, base + w.h, st);
     if (rc != MOE_OK) return rc;
     if (!mark(3)) return MOE_EHIP;
     rc = moe::launch_expert_gemm2(*cfg, base + w.h, wo, base + w.out, st);
@@ -375,7 +372,7 @@ int moe_forward_fuses_dispatch(const moe_config* cfg, int* fused) {
   const int rc = check_config(cfg);
   if (rc != MOE_OK) return rc;
   if (fused == nullptr) return MOE_EINVAL;
-  *fused = moe::expert_gemm1_can_gather(*cfg) ? 1 : 0;
+  *fused = moe::expert_ffn_can_pack(*cfg) ? 1 : 0;
   return MOE_OK;
 }
 
@@ -517,7 +514,7 @@ int moe_expert_ffn(const moe_config* cfg, const void* buf, const int32_t* fill, 
     void* zero_row = static_cast<char*>(ws) + maps;
     int r = moe::launch_row_maps_from_fill(*cfg, fill, pk, zero_row, st);
     if (r != MOE_OK) return r;
-    return moe::launch_expert_ffn_packed(*cfg, buf, pk, zero_row, wi, wo, h_ws, out, true, nullptr, st,
+    return moe::launch_expert_ffn_packed(*cfg, buf, pk, zero_row, wi, wo, h_ws, out, true, false, nullptr, st,
                                          nullptr);
   }
   const int rc1 = moe::launch_expert_gemm1(*cfg, buf, wi, h_ws, st);
@@ -602,7 +599,7 @@ int moe_backward_events(const moe_config* cfg, const void* x, const float* wg, c
   if (rc != MOE_OK) return rc;
   if (!mark(1)) return MOE_EHIP;
   rc = moe::launch_expert_dgrad2(*cfg, base + b.dout, wo, fb + f.h,
-                                 moe::expert_gemm1_can_gather(*cfg) ? fb + f.signbits : nullptr,
+                                 packed ? fb + f.signbits : nullptr,
                                  base + b.dh, kept, st);
   if (rc != MOE_OK) return rc;
   if (!mark(2)) return MOE_EHIP;

@@ -117,7 +117,7 @@ inline RowPacking carve_row_packing(const moe_config& c, void* base) {
 }
 
 // host-side launchers (each returns a moe_status)
-// zero_row: NULL, or M bf16 elements that the gate also clears (see launch_expert_gemm1_gather)
+// zero_row: NULL, or M bf16 elements that the gate also clears (see launch_expert_ffn_packed)
 // packing: NULL, or the arrays of the packed row layout that the gate also fills (packed_src
 // then holds token rows g*S + s of x)
 int launch_gate(const moe_config& c, const void* x, const float* wg, const float* u,
@@ -145,23 +145,17 @@ int launch_expert_gemm1(const moe_config& c, const void* buf, const void* wi, vo
                         hipStream_t st);
 int launch_expert_gemm2(const moe_config& c, const void* h, const void* wo, void* out,
                         hipStream_t st);
-// h = relu(dispatch(x) . wi) without materialising the dispatched buffer: the GEMM's copies
-// gather the rows of x through src_token (zero_row: M zeros of the activation type).
-bool expert_gemm1_can_gather(const moe_config& c);
-// signbits: NULL, or expert_signbits_bytes(c) bytes that receive one bit per element of h
-// (set where h > 0) in the GEMM kernel's private tile order, for launch_expert_dgrad2
-int launch_expert_gemm1_gather(const moe_config& c, const void* x, const int32_t* src_token,
-                               const void* zero_row, const void* wi, void* h, void* signbits,
-                               hipStream_t st);
-// both GEMMs over the packed row layout (bf16 layers the persistent kernel takes, M >= 128)
+// Both GEMMs over the packed row layout: the first gathers its rows of `a` (x, or an expert buffer)
+// through pk.packed_src, so the dispatched buffer is never materialised (zero_row: M zeros of the
+// activation type).  train: the rows of h behind the occupied ones are what the backward pass expects.
+// signbits: NULL, or expert_signbits_bytes(c) bytes that may receive one bit per element of h (set
+// where h > 0) in the persistent kernel's private tile order, for launch_expert_dgrad2.
 bool expert_ffn_can_pack(const moe_config& c);
 int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPacking& pk,
                              const void* zero_row, const void* wi, const void* wo, void* h,
-                             void* out, bool scatter_out, void* signbits, hipStream_t st,
+                             void* out, bool scatter_out, bool train, void* signbits, hipStream_t st,
                              void* event_between);
-inline size_t expert_signbits_bytes(const moe_config& c) {
-  return (size_t)c.E * c.G * c.C * c.H / 8;
-}
+size_t expert_signbits_bytes(const moe_config& c);
 
 // backward pass (backward.hip); epi of the strided GEMM: 0 none, 1 relu, 2 zero where mask <= 0
 int launch_combine_bwd(const moe_config& c, const void* dy, const void* out,
@@ -195,7 +189,7 @@ int launch_gemm_strided(const moe_config& c, int epi, const void* A, long long a
                         void* Cout, const void* mask, int R, int N, int K, hipStream_t st);
 // expert GEMMs of the backward pass (expert_gemm.hip), per expert with rows = G*C:
 //   dgrad2: dh   = (dout . wo^T) masked by h > 0     [rows,M] x [H,M]^T -> [rows,H]
-//           (signbits as written by launch_expert_gemm1_gather when that path ran, else NULL)
+//           (signbits as launch_expert_ffn_packed got them, else NULL)
 //   wgrad2: dwo  = h^T . dout                        [rows,H]^T x [rows,M] -> [H,M]
 //   dgrad1: dbuf = dh . wi^T                         [rows,H] x [M,H]^T -> [rows,M]
 //   wgrad1: dwi  = buf^T . dh                        [rows,M]^T x [rows,H] -> [M,H]

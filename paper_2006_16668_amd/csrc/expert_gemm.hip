@@ -8,13 +8,13 @@
 // bf16, v_mfma_f32_32x32x16_bf16 with fp32 accumulation, in two kernels:
 //
 //   expert_gemm_bf16_dma_kernel   shapes made of whole 256x256 tiles with K % 32 == 0
-//     (every benchmarked layer): persistent, one block per CU walks its share of the
+//     (the large layers): persistent, one block per CU walks its share of the
 //     tiles as one stream of K steps; operands travel global -> LDS without passing
 //     the registers; either operand in either layout; gathered rows, packed rows,
 //     scattered result rows and a per-expert k range as template options.
-//   expert_gemm_bf16_kernel       every other shape: one block per tile, operands
-//     staged global -> registers -> LDS (double buffered, one barrier per K step),
-//     clamped addresses and select masks at the ragged edges.
+//   expert_gemm_bf16_edge_kernel  every other shape: one block per 128 x 256 or 128 x 128
+//     tile, two or three blocks per CU, the same register-bypassing copies with per-lane
+//     source addresses (pieces past an edge come from a zero line).
 //
 // In both, activation tiles (K contiguous) sit in LDS as [m][k] and are read with
 // 16-byte loads; weight tiles are [k][n] in memory (N contiguous), stay that way in
@@ -40,197 +40,6 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblk) {
   const int q = nblk / kXcds, r = nblk % kXcds;
   const int xcd = bid % kXcds, idx = bid / kXcds;
   return xcd * q + (xcd < r ? xcd : r) + idx;
-}
-
-// LDS staging of one operand tile of ROWS output rows (or columns) x BK.  "K-contiguous"
-// (KC): the operand is stored [rows][K]; staged as [ROWS][BK + 8] (16 B pad: conflict-free
-// 16-byte reads).  "row-of-k" (MNC): stored [K][rows]; staged as [BK][ROWS + 16] (32 B pad:
-// 4 consecutive k rows hit distinct banks) and read with the transposing LDS load.
-template <int ROWS, int BK, bool MNC>
-struct OperandSmem {
-  static constexpr int kPitch = MNC ? ROWS + 16 : BK + 8;
-  static constexpr int kElems = MNC ? BK * kPitch : ROWS * kPitch;
-  static constexpr int kVecs = ROWS * BK / 8 / 256;             // 16-byte vectors per thread
-  static constexpr int kVecsPerLine = MNC ? ROWS / 8 : BK / 8;  // along the contiguous dimension
-  static constexpr int kLinesPerPass = 256 / kVecsPerLine;
-};
-
-template <int BM, int BN, int BK, bool A_MNC, bool B_KC>
-struct GemmSmem {
-  using SA = OperandSmem<BM, BK, A_MNC>;
-  using SB = OperandSmem<BN, BK, !B_KC>;
-  static constexpr size_t kBytes = (size_t)2 * (SA::kElems + SB::kElems) * sizeof(bf16_t);
-};
-
-// One block per 256x256 or 128x128 tile of C, any shape (clamped addresses and select masks at
-// the ragged edges; EXACT drops them), either operand in either layout (the same three products
-// as the persistent kernel below):
-//   C = A . B      A KC [R,K], B MNC [K,N]      C = A . B^T    A KC, B KC [N,K]
-//   C = A^T . B    A MNC [K,R], B MNC [K,N]
-// EPI: 0 plain, 1 relu, 2 zero every element whose `mask` element (same index as C) is <= 0.
-// Contiguous dimensions are multiples of 8 elements (16-byte loads are whole or masked whole).
-template <int BM, int BN, int BK, int WM, int WN, int EPI, bool A_MNC, bool B_KC, bool EXACT>
-__global__ __launch_bounds__(256) void expert_gemm_bf16_kernel(
-    const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ Cout,
-    const bf16_t* __restrict__ mask, int R, int N, int K, int tiles_m, int tiles_n, int nblk) {
-  using SM = GemmSmem<BM, BN, BK, A_MNC, B_KC>;
-  using SA = typename SM::SA;
-  using SB = typename SM::SB;
-  constexpr int WTM = BM / WM, WTN = BN / WN;      // wave tile
-  constexpr int TM = WTM / 32, TN = WTN / 32;      // 32x32 MFMA tiles per wave
-  static_assert(WM * WN == 4, "four wavefronts per block");
-  static_assert(SA::kVecs >= 1 && SB::kVecs >= 1, "tile too small for 256 threads");
-
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  bf16_t* As = reinterpret_cast<bf16_t*>(smem_raw);            // two stages
-  bf16_t* Bs = As + 2 * SA::kElems;                            // two stages
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int logical = xcd_remap(blockIdx.x, nblk);
-  const int per_e = tiles_m * tiles_n;
-  const int e = logical / per_e;
-  const int t = logical - e * per_e;
-  const int m0 = (t % tiles_m) * BM, n0 = (t / tiles_m) * BN;
-  const int wm0 = (wave / WN) * WTM, wn0 = (wave % WN) * WTN;
-
-  const bf16_t* Ae = A + (size_t)e * R * K;
-  const bf16_t* Be = B + (size_t)e * K * N;
-  const size_t c_e = (size_t)e * R * N;
-
-  // One 16-byte vector of an operand tile: `line` counts rows of the operand's memory layout
-  // (output rows / columns for KC, k for MNC), `vec` the position along the contiguous
-  // dimension.  Out-of-range pieces are read from a clamped address and replaced by zeros;
-  // surplus output rows of a KC operand are clamped only (their results are never stored).
-  typedef u32x4_t vec_t;
-#define MOE_LOAD_OPERAND(REGS, SX, MNC, BASE, EXTENT, ORIGIN, k0)                              \
-  _Pragma("unroll") for (int i = 0; i < SX::kVecs; ++i) {                                    \
-    const int line_ = tid / SX::kVecsPerLine + i * SX::kLinesPerPass;                        \
-    const int vec_ = (tid % SX::kVecsPerLine) * 8;                                           \
-    if (MNC) {                                                                               \
-      int gk = (k0) + line_, gx = (ORIGIN) + vec_;                                           \
-      const bool ok = EXACT || (gk < K && gx < (EXTENT));                                    \
-      if (!EXACT) { gk = gk < K ? gk : K - 1; gx = gx < (EXTENT) ? gx : (EXTENT) - 8; }     \
-      const vec_t v = *reinterpret_cast<const vec_t*>((BASE) + (size_t)gk * (EXTENT) + gx);  \
-      REGS[i] = ok ? v : vec_t{0u, 0u, 0u, 0u};                                              \
-    } else {                                                                                 \
-      int gx = (ORIGIN) + line_, gk = (k0) + vec_;                                           \
-      const bool ok = EXACT || gk < K;                                                       \
-      if (!EXACT) { gx = gx < (EXTENT) ? gx : (EXTENT) - 1; gk = gk < K ? gk : K - 8; }     \
-      const vec_t v = *reinterpret_cast<const vec_t*>((BASE) + (size_t)gx * K + gk);         \
-      REGS[i] = ok ? v : vec_t{0u, 0u, 0u, 0u};                                              \
-    }                                                                                        \
-  }
-#define MOE_STORE_OPERAND(REGS, SX, XS, buf)                                                    \
-  _Pragma("unroll") for (int i = 0; i < SX::kVecs; ++i) {                                    \
-    const int line_ = tid / SX::kVecsPerLine + i * SX::kLinesPerPass;                        \
-    const int vec_ = (tid % SX::kVecsPerLine) * 8;                                           \
-    *reinterpret_cast<vec_t*>(XS + (buf) * SX::kElems + line_ * SX::kPitch + vec_) = REGS[i]; \
-  }
-  vec_t areg[SA::kVecs], breg[SB::kVecs];          // staging registers of the tile in flight
-#define MOE_LOAD_TILES(k0)                                                                   \
-  MOE_LOAD_OPERAND(areg, SA, A_MNC, Ae, R, m0, k0)                                           \
-  MOE_LOAD_OPERAND(breg, SB, !B_KC, Be, N, n0, k0)
-#define MOE_STORE_TILES(buf)                                                                 \
-  MOE_STORE_OPERAND(areg, SA, As, buf)                                                       \
-  MOE_STORE_OPERAND(breg, SB, Bs, buf)
-
-  f32x16_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // MFMA operands of one 16-wide k step: each lane gets the 8 consecutive k of one output row
-  // (A) / column (B).  KC: one 16-byte read; MNC: two transposing 8-byte reads.
-  typedef s16x4_t __attribute__((address_space(3))) * lds_s16x4_ptr;
-  const int kc_off_a = (wm0 + (lane & 31)) * SA::kPitch + 8 * (lane >> 5);
-  const int kc_off_b = (wn0 + (lane & 31)) * SB::kPitch + 8 * (lane >> 5);
-  const int mnc_line = 8 * (lane >> 5) + ((lane & 15) >> 2);
-  const int mnc_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  struct Frags { bf16x8_t a[TM]; bf16x8_t b[TN]; };
-#define MOE_READ_OPERAND(DST, CNT, SX, MNC, XS, KC_OFF, W0, buf, kk)                           \
-  _Pragma("unroll") for (int i = 0; i < CNT; ++i) {                                          \
-    if (MNC) {                                                                               \
-      const bf16_t* p_ = XS + (buf) * SX::kElems + ((kk) * 16 + mnc_line) * SX::kPitch + (W0) + mnc_col + i * 32; \
-      const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)p_);         \
-      const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p_ + 4 * SX::kPitch)); \
-      DST[i] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7)); \
-    } else {                                                                                 \
-      DST[i] = *reinterpret_cast<const bf16x8_t*>(XS + (buf) * SX::kElems + (KC_OFF) + (kk) * 16 + i * 32 * SX::kPitch); \
-    }                                                                                        \
-  }
-#define MOE_READ_FRAGS(F, buf, kk)                                                           \
-  MOE_READ_OPERAND((F).a, TM, SA, A_MNC, As, kc_off_a, wm0, buf, kk)                         \
-  MOE_READ_OPERAND((F).b, TN, SB, !B_KC, Bs, kc_off_b, wn0, buf, kk)
-  // The B fragment goes in as the first MFMA operand: the 32x32 result is then
-  // the transposed tile, i.e. a lane owns 4 consecutive columns of one row of C.
-#define MOE_MFMA_STEP(F)                                                                     \
-  _Pragma("unroll") for (int i = 0; i < TM; ++i)                                             \
-    _Pragma("unroll") for (int j = 0; j < TN; ++j)                                           \
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16((F).b[j], (F).a[i], acc[i][j], 0, 0, 0);
-
-  const int KT = (K + BK - 1) / BK;
-  constexpr int KK = BK / 16;
-  Frags fr[2];
-  // Pipeline: tile kt is consumed from LDS stage kt&1 while tile kt+1 travels
-  // through the staging registers (loaded right after the barrier, written to the
-  // other LDS stage during the last k step).
-  MOE_LOAD_TILES(0)
-  MOE_STORE_TILES(0)
-  __syncthreads();
-  if (KT > 1) { MOE_LOAD_TILES(BK) }
-  MOE_READ_FRAGS(fr[0], 0, 0)
-  for (int kt = 0; kt < KT; ++kt) {
-    const int cur = kt & 1;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      if (kk + 1 < KK) { MOE_READ_FRAGS(fr[(kk + 1) & 1], cur, kk + 1) }
-      if (kk + 1 == KK && kt + 1 < KT) { MOE_STORE_TILES(cur ^ 1) }
-      MOE_MFMA_STEP(fr[kk & 1])
-    }
-    __syncthreads();
-    if (kt + 2 < KT) { MOE_LOAD_TILES((kt + 2) * BK) }
-    if (kt + 1 < KT) { MOE_READ_FRAGS(fr[0], cur ^ 1, 0) }
-  }
-
-  // epilogue: acc[i][j][r] = C[row][col .. col+3 for r%4 = 0..3] with
-  //   row = 32 i + lane%32,  col = 32 j + 8 (r/4) + 4 (lane/32)
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int row = m0 + wm0 + 32 * i + (lane & 31);
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = n0 + wn0 + 32 * j + 8 * q + 4 * (lane >> 5);
-        if (!(EXACT || (row < R && col < N))) continue;   // N % 8 == 0: the 4 columns are in or out together
-        const size_t o = c_e + (size_t)row * N + col;
-        float v[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          v[r] = acc[i][j][4 * q + r];
-          if (EPI == 1) v[r] = fmaxf(v[r], 0.f);
-        }
-        if (EPI == 2) {
-          const uint2 mk = *reinterpret_cast<const uint2*>(mask + o);
-          // a bf16 is positive iff its bits, read as a 16-bit integer, are positive
-          if ((int16_t)(mk.x & 0xffffu) <= 0) v[0] = 0.f;
-          if ((int16_t)(mk.x >> 16) <= 0) v[1] = 0.f;
-          if ((int16_t)(mk.y & 0xffffu) <= 0) v[2] = 0.f;
-          if ((int16_t)(mk.y >> 16) <= 0) v[3] = 0.f;
-        }
-        *reinterpret_cast<uint2*>(Cout + o) = uint2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-      }
-  }
-#undef MOE_READ_OPERAND
-#undef MOE_READ_FRAGS
-#undef MOE_MFMA_STEP
-#undef MOE_LOAD_OPERAND
-#undef MOE_STORE_OPERAND
-#undef MOE_LOAD_TILES
-#undef MOE_STORE_TILES
 }
 
 // ----------------------------------------------------------------------------
@@ -267,9 +76,9 @@ struct DmaSmem {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"     \
                :: "s"(LDS_U32), "v"(VOFF_U32), "s"(SBASE) : "memory")
 
-// GATHER: the A rows are not a dense [E,R,K] buffer but rows of x picked by the dispatch
-// indices (A = x [G,S,K]; row r of expert e is x[r / C, src_token[e,r], :], a zero row when
-// the slot is empty), i.e. the dispatch of Algorithm 2 folded into the first GEMM's copies.
+// GATHER: the A rows are not a dense [E,R,K] buffer but rows of the matrix A ([rows, K]) picked by
+// index (row p of expert e is A[src_token[e R + p], :], a zero row from kept[e] on), i.e. the
+// dispatch of Algorithm 2 folded into the first GEMM's copies.
 //
 // Operand layouts.  "K-contiguous" (KC): the operand is stored [rows][K] (row = its index in
 // the output) and staged as [256 rows][4 chunks]; "row-of-k" (MNC): stored [K][rows] and
@@ -289,8 +98,6 @@ struct DmaSmem {
 // are the same tiling of the same [E,R,N] matrix, so no lane ever needs another lane's bits.
 // The reader fetches a tile's 8 KB into spare LDS with two register-bypassing copies issued
 // in the tile's first K step; the waits of the next two steps cover them.
-// GATHER 2: the indices are absolute rows of the matrix A ([rows, K], row p of expert e comes
-// from row src_token[e * R + p], -1 = zero row): the packed row layout (RowPacking).
 // PACKED: expert e has only its first ceil(kept[e] / 256) row tiles multiplied (kept[e] = its
 // occupied rows): every block copies kept to LDS and forms the running tile counts there when it
 // starts; the tiles of all experts are numbered consecutively in expert order, and since a
@@ -299,14 +106,14 @@ struct DmaSmem {
 // the rows of C go to the absolute rows src_token[e * R + p] of Cout ([rows, N]), -1 = not stored.
 // DYNK: the sum over k of expert e stops at 256 ceil(kept[e] / 256) instead of K (the weight
 // gradients, whose k runs over an expert's packed rows); an expert with no rows gets zeros.
-template <int ST, int EPI, int GATHER, bool A_MNC, bool B_KC, bool PACKED, bool SCATTER, bool DYNK>
+template <int ST, int EPI, bool GATHER, bool A_MNC, bool B_KC, bool PACKED, bool SCATTER, bool DYNK>
 __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ Cout,
     int R, int N, int K, int tiles_m, int tiles_n, int ntiles_static,
-    const int32_t* __restrict__ src_token, const bf16_t* __restrict__ zero_row, int S,
-    uint32_t c_magic, int c_shift, const bf16_t* __restrict__ mask,
-    unsigned char* __restrict__ signbits, const int32_t* __restrict__ kept, int E) {
+    const int32_t* __restrict__ src_token, const bf16_t* __restrict__ zero_row,
+    const bf16_t* __restrict__ mask, unsigned char* __restrict__ signbits, const int32_t* __restrict__ kept, int E) {
   static_assert(!(GATHER && A_MNC), "the gather form addresses whole rows of a K-contiguous A");
+  static_assert(!GATHER || PACKED, "gathered rows are packed rows");
   static_assert(!SCATTER || (PACKED && EPI == 0), "scattered rows: plain bf16 result of a packed launch");
   static_assert(!(DYNK && (PACKED || GATHER)), "a shortened k range comes with the full list of output tiles");
   constexpr bool RELU = EPI == 1 || EPI == 4;
@@ -443,14 +250,7 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
       const int tok_ = *(lds_int_ptr)(uintptr_t)(lds_tok + 4 * rl_);                         \
       const int row_ = 64 * wave + rl_;                                                      \
       const int ca_ = (lane & 3) ^ ((row_ >> 2) & 3);                                        \
-      const bf16_t* src_;                                                                    \
-      if (GATHER == 2) {                                                                     \
-        src_ = (m0_) + row_ < kept_s[e_] && tok_ >= 0 ? A + (size_t)tok_ * K : zero_row;     \
-      } else {                                                                               \
-        const uint32_t n_ = (uint32_t)((m0_) + row_);                                        \
-        const uint32_t g_ = c_magic ? __umulhi(n_, c_magic) >> c_shift : n_; /* n_ / C */    \
-        src_ = tok_ >= 0 ? A + ((size_t)g_ * S + tok_) * K : zero_row;                       \
-      }                                                                                      \
+      const bf16_t* src_ = (m0_) + row_ < kept_s[e_] && tok_ >= 0 ? A + (size_t)tok_ * K : zero_row; \
       a_addr[q] = (uint64_t)(uintptr_t)(src_ + 8 * ca_);                                     \
     }                                                                                        \
   }
@@ -738,9 +538,292 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
 #undef MOE_DMA_MFMA_ROW
 }
 
+// ----------------------------------------------------------------------------
+// Tiles of any shape: C [E,R,N] with R, N, K arbitrary (contiguous dimensions multiples of 8
+// elements), either operand in either layout (the products of the table above).
+//
+// One block of four wavefronts (2 x 2) per 128 x BN tile, wavefront tile 64 x BN/2, 32-wide K
+// steps in ST = 3 LDS stages.  The copies are those of the persistent kernel (1 KB per wavefront
+// instruction, the same source permutation against bank conflicts), but every lane carries its own
+// 64-bit source address: a row, column or k past an edge, an unoccupied packed row, reads a zero
+// line instead, so the inner loop knows no edges and nothing outside an operand is touched.
+// Two (BN = 256) or three (BN = 128) blocks share a compute unit: while one waits for its step or
+// stores its tile the others multiply, and the dispatcher evens out tiles of different length,
+// which a persistent block cannot.
+//
+// gather: NULL, or the rows of A (K-contiguous) are the absolute rows gather[e R + p].
+// kept:   NULL, or occupied rows of each expert (packed layout): row tiles past them are left
+//         alone; row_pad 255: up to 255 rows of zeros follow them, to the next multiple of 256, which
+//         the persistent kernel's DYNK sums run over.  K_KEPT: kept[e] limits the sum over k instead
+//         (weight gradients).
+// scatter: NULL, or row p of expert e goes to the absolute row scatter[e R + p] of C.
+// EPI: 0 plain, 1 relu, 2 zero every element whose `mask` element (same index as C) is <= 0.
+//
+// The k order of a sum is the persistent kernel's, so a layer gets the same bits from either.
+//
+// Bound: the copies of a step (24 KB for 2 x 128 x 256 x 32 flop, a third more per flop than 256 x 256
+// tiles) and the power they draw; 0.95 PFLOP/s on shapes of whole tiles where the persistent kernel
+// reaches 1.07.  Layer of 5 x 700 tokens, M 768, H 3072, 24 experts of 295 positions: 299 us with the
+// kernel it replaced (256 x 256 tiles through registers, one block per unit, every position
+// multiplied), 146 us with this one, 145 us over the occupied rows only.
+// ----------------------------------------------------------------------------
+static __device__ const u32x4_t edge_zero_line = {0u, 0u, 0u, 0u};
+
+template <int BN>
+struct EdgeSmem {
+  static constexpr int kStages = 3;
+  static constexpr int kAStage = 128 * 32 * 2, kBStage = BN * 32 * 2;
+  static constexpr int kStage = kAStage + kBStage;
+  static constexpr size_t kBytes = (size_t)kStages * kStage;
+};
+
+template <int BN, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
+__global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void expert_gemm_bf16_edge_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ Cout,
+    const bf16_t* __restrict__ mask, int R, int N, int K, int tiles_m, int tiles_n, int nblk,
+    const int32_t* __restrict__ gather, const int32_t* __restrict__ kept,
+    int row_pad, const int32_t* __restrict__ scatter) {
+  using SM = EdgeSmem<BN>;
+  constexpr int BM = 128, BK = 32, ST = SM::kStages, TM = 2, TN = BN / 64;
+  constexpr int WN = BN / 2;                                   // columns of a wavefront tile
+  constexpr int AC = 2, BC = BN / 64;                          // copies per wavefront and step
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  typedef unsigned char __attribute__((address_space(3))) * lds_ptr;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_ptr)smem_raw);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * WN;
+
+  // Neighbouring tiles on one XCD; inside an expert bands of 8 row tiles, row tile fastest, so
+  // that the tiles an XCD works on at a time share row and column panels in its L2.
+  const int logical = xcd_remap(blockIdx.x, nblk);
+  const int per_e = tiles_m * tiles_n;
+  const int e = logical / per_e;
+  const int t = logical - e * per_e;
+  constexpr int kBand = 8;
+  const int band = t / (kBand * tiles_n), rem = t - band * kBand * tiles_n;
+  const int left = tiles_m - band * kBand, brows = left < kBand ? left : kBand;
+  const int ct = rem / brows, rt = band * kBand + (rem - ct * brows);
+  const int m0 = rt * BM, n0 = ct * BN;
+  int rows = R, rows_out = R;                                  // rows of A that count, of C that are stored
+  if (kept != nullptr && !K_KEPT) {
+    rows = kept[e];
+    rows_out = (rows + row_pad) & ~row_pad;
+    rows_out = rows_out < R ? rows_out : R;
+  }
+  if (m0 >= rows_out) return;                                  // block-uniform
+  const int KE = K_KEPT ? kept[e] : K;                         // length of the sum
+  const int KT = (KE + BK - 1) / BK;
+
+  // Per-lane source addresses of the copies and their advance per K step (0 for a lane that reads
+  // the zero line).  k_of: the lane's first k inside a step.
+  const uint64_t zline = (uint64_t)(uintptr_t)&edge_zero_line;
+  uint64_t a_addr[AC], b_addr[BC];
+  uint32_t a_inc[AC], b_inc[BC];
+#pragma unroll
+  for (int q = 0; q < AC; ++q) {
+    const int c = wave * AC + q;
+    bool ok;
+    const bf16_t* src;
+    if (A_MNC) {                                               // 4 k rows of 16 chunks per copy
+      const int kr = 4 * c + (lane >> 4), col = m0 + 8 * ((lane & 15) ^ (4 * (kr & 3)));
+      ok = col < R && kr < KE;
+      src = A + ((size_t)e * K + kr) * R + col;
+    } else {                                                   // 16 rows of 4 chunks per copy
+      const int row = 16 * c + (lane >> 2), ch = (lane & 3) ^ ((row >> 2) & 3);
+      ok = m0 + row < rows && 8 * ch < KE;
+      long long arow = (long long)e * R + m0 + row;
+      if (gather != nullptr) {
+        const int tok = ok ? gather[arow] : -1;
+        ok = tok >= 0;
+        arow = tok;
+      }
+      src = A + arow * K + 8 * ch;
+    }
+    a_addr[q] = ok ? (uint64_t)(uintptr_t)src : zline;
+    a_inc[q] = ok ? (A_MNC ? (uint32_t)R * BK * 2 : BK * 2) : 0u;
+  }
+#pragma unroll
+  for (int q = 0; q < BC; ++q) {
+    const int c = wave * BC + q;
+    bool ok;
+    const bf16_t* src;
+    if (B_KC) {
+      const int row = 16 * c + (lane >> 2), ch = (lane & 3) ^ ((row >> 2) & 3);
+      ok = n0 + row < N && 8 * ch < KE;
+      src = B + ((size_t)e * N + n0 + row) * K + 8 * ch;
+    } else {                                                   // 1024 / (2 BN) k rows of BN / 8 chunks
+      constexpr int CH = BN / 8, RPC = 64 / CH;
+      const int kr = RPC * c + lane / CH, col = n0 + 8 * ((lane % CH) ^ (4 * (kr & 3)));
+      ok = col < N && kr < KE;
+      src = B + ((size_t)e * K + kr) * N + col;
+    }
+    b_addr[q] = ok ? (uint64_t)(uintptr_t)src : zline;
+    b_inc[q] = ok ? (B_KC ? BK * 2 : (uint32_t)N * BK * 2) : 0u;
+  }
+#define MOE_EDGE_COPY(LDS_U32, ADDR_U64)                                                     \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"            \
+               :: "s"(LDS_U32), "v"(ADDR_U64) : "memory")
+  // start the copies of step `p` (the next one in order) and move the addresses on; lanes whose
+  // k is past the end in the last step go to the zero line
+  auto start_step = [&](int p, int stage) {
+    if (p > 0) {
+#pragma unroll
+      for (int q = 0; q < AC; ++q) a_addr[q] += a_inc[q];
+#pragma unroll
+      for (int q = 0; q < BC; ++q) b_addr[q] += b_inc[q];
+      const int kl = KE - p * BK;                              // k left, this step's included
+      if (kl < BK) {                                           // block-uniform, last step only
+#pragma unroll
+        for (int q = 0; q < AC; ++q) {
+          const int c = wave * AC + q;
+          const int k = A_MNC ? 4 * c + (lane >> 4)
+                              : 8 * ((lane & 3) ^ (((16 * c + (lane >> 2)) >> 2) & 3));
+          if (k >= kl) a_addr[q] = zline;
+        }
+#pragma unroll
+        for (int q = 0; q < BC; ++q) {
+          const int c = wave * BC + q;
+          constexpr int CH = BN / 8, RPC = 64 / CH;
+          const int k = B_KC ? 8 * ((lane & 3) ^ (((16 * c + (lane >> 2)) >> 2) & 3)) : RPC * c + lane / CH;
+          if (k >= kl) b_addr[q] = zline;
+        }
+      }
+    }
+    const uint32_t la = lds0 + stage * SM::kStage + wave * (AC * 1024);
+    const uint32_t lb = lds0 + stage * SM::kStage + SM::kAStage + wave * (BC * 1024);
+#pragma unroll
+    for (int q = 0; q < AC; ++q) MOE_EDGE_COPY(la + q * 1024, a_addr[q]);
+#pragma unroll
+    for (int q = 0; q < BC; ++q) MOE_EDGE_COPY(lb + q * 1024, b_addr[q]);
+  };
+
+  // fragment read offsets, as in the persistent kernel (row pitch of a row-of-k stage: 2 x rows)
+  const int ar = lane & 31;
+  const int p16 = lane & 15, bb = lane >> 4;
+  const int bk = 8 * (bb >> 1) + (p16 >> 2);
+  const int bsw = 4 * (bk & 3);
+  const int kcc0 = (lane >> 5) ^ ((ar >> 2) & 3), kcc1 = (2 + (lane >> 5)) ^ ((ar >> 2) & 3);
+  uint32_t a_rd[2], b_rd[TN > 2 ? TN : 2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int ca = (wm0 >> 3) + 4 * j + 2 * (bb & 1) + ((p16 & 3) >> 1);
+    a_rd[j] = A_MNC ? (uint32_t)(bk * (BM * 2) + ((ca ^ bsw) * 16) + (p16 & 1) * 8)
+                    : (uint32_t)((wm0 + ar) * 64 + (j ? kcc1 : kcc0) * 16);
+  }
+#pragma unroll
+  for (int j = 0; j < (B_KC ? 2 : TN); ++j) {
+    const int cb = (wn0 >> 3) + 4 * j + 2 * (bb & 1) + ((p16 & 3) >> 1);
+    b_rd[j] = B_KC ? (uint32_t)(SM::kAStage + (wn0 + ar) * 64 + (j ? kcc1 : kcc0) * 16)
+                   : (uint32_t)(SM::kAStage + bk * (BN * 2) + ((cb ^ bsw) * 16) + (p16 & 1) * 8);
+  }
+  typedef s16x4_t __attribute__((address_space(3))) * lds_s16x4_ptr;
+  typedef bf16x8_t __attribute__((address_space(3))) * lds_bf16x8_ptr;
+  auto read_kc = [&](uint32_t stage_base, uint32_t rd, int i) {
+    return *(lds_bf16x8_ptr)(uintptr_t)(stage_base + rd + i * 32 * 64);
+  };
+  auto read_mnc = [&](uint32_t stage_base, uint32_t rd, int kk, int pitch) {
+    const uint32_t p = stage_base + rd + kk * 16 * pitch;
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)p);
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(p + 4 * pitch));
+    return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  int p = 0, pstage = 0;
+  for (; p < ST - 1 && p < KT; ++p) {
+    start_step(p, pstage);
+    ++pstage;
+  }
+  int stage = 0;
+  for (int g = 0; g < KT; ++g) {
+    // own copies of step g landed (step g + 1 may still fly), then everybody's; the stage of step
+    // g - 1 is free after the barrier
+    if (g + 1 < KT) {
+      if (BC == 4) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    __syncthreads();
+    if (p < KT) {
+      start_step(p, pstage);
+      pstage = pstage + 1 == ST ? 0 : pstage + 1;
+      ++p;
+    }
+    const uint32_t sb = lds0 + stage * SM::kStage;
+    stage = stage + 1 == ST ? 0 : stage + 1;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      bf16x8_t fa[TM], fb[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[i] = A_MNC ? read_mnc(sb, a_rd[i], kk, BM * 2) : read_kc(sb, a_rd[kk], i);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[j] = B_KC ? read_kc(sb, b_rd[kk], j) : read_mnc(sb, b_rd[j], kk, BN * 2);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+    }
+  }
+  __syncthreads();                                             // the stages are free
+
+  // acc[i][j][4 q + r] = C[32 i + r32][32 j + 8 q + 4 h + r] of the wavefront tile: 32 rows at a time
+  // through the wavefront's own LDS into whole-row 16-byte stores.  Chunk c of row r sits at
+  // position c ^ (r % chunks), its 8-byte halves swapped in every other group of rows.
+  constexpr int CH = WN / 8, RPP = 64 / CH;                    // chunks per row, rows per store
+  const uint32_t st_base = lds0 + wave * (32 * WN * 2);
+  const int r32 = lane & 31, hh = lane >> 5;
+  const uint32_t st_wr = st_base + r32 * (WN * 2) + 8 * (hh ^ ((r32 / CH) & 1));
+  typedef u32x2_t __attribute__((address_space(3))) * lds_u2_ptr;
+  typedef u32x4_t __attribute__((address_space(3))) * lds_u4_ptr;
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        uint32_t lo = pack_bf16x2(acc[i][j][4 * q], acc[i][j][4 * q + 1]);
+        uint32_t hi = pack_bf16x2(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+        if (EPI == 1) { lo = relu_bf16x2(lo); hi = relu_bf16x2(hi); }
+        *(lds_u2_ptr)(uintptr_t)(st_wr + (((4 * j + q) ^ (r32 & (CH - 1))) * 16)) = u32x2_t{lo, hi};
+      }
+#pragma unroll
+    for (int ps = 0; ps < 32 / RPP; ++ps) {
+      const int rr = RPP * ps + lane / CH, c = lane % CH;
+      u32x4_t d = *(lds_u4_ptr)(uintptr_t)(st_base + rr * (WN * 2) + ((c ^ (rr & (CH - 1))) * 16));
+      if ((rr / CH) & 1) d = u32x4_t{d[2], d[3], d[0], d[1]};
+      const int row = m0 + wm0 + 32 * i + rr, col = n0 + wn0 + 8 * c;
+      if (row < rows_out && col < N) {
+        const size_t o = ((size_t)e * R + row) * N + col;
+        if (EPI == 2) {
+          const u32x4_t mk = *reinterpret_cast<const u32x4_t*>(mask + o);
+#pragma unroll
+          for (int w = 0; w < 4; ++w)          // a bf16 is positive iff its bits, as an integer, are
+            d[w] &= ((int16_t)(mk[w] & 0xffffu) > 0 ? 0xffffu : 0u) |
+                    ((int16_t)(mk[w] >> 16) > 0 ? 0xffff0000u : 0u);
+        }
+        if (scatter != nullptr)
+          *reinterpret_cast<u32x4_t*>(Cout + (size_t)scatter[(size_t)e * R + row] * N + col) = d;
+        else
+          *reinterpret_cast<u32x4_t*>(Cout + o) = d;
+      }
+    }
+  }
+#undef MOE_EDGE_COPY
+}
+
 // LDS limit of one instantiation of the persistent kernel on the current device (all of the
 // 160 KB when the size depends on the number of experts)
-template <int ST, int EPI, int GATHER, bool A_MNC = false, bool B_KC = false, bool PACKED = false,
+template <int ST, int EPI, bool GATHER, bool A_MNC = false, bool B_KC = false, bool PACKED = false,
           bool SCATTER = false, bool DYNK = false>
 int prepare_dma() {
   static LdsLimitOnce once;
@@ -751,10 +834,10 @@ int prepare_dma() {
       PACKED || DYNK ? 160 * 1024 : kFixed);
 }
 
-template <int ST, int EPI, int GATHER, bool A_MNC = false, bool B_KC = false, bool PACKED = false,
+template <int ST, int EPI, bool GATHER, bool A_MNC = false, bool B_KC = false, bool PACKED = false,
           bool SCATTER = false, bool DYNK = false>
 int launch_bf16_dma(const bf16_t* A, const bf16_t* B, bf16_t* Cout, int E, int R, int N, int K,
-                    const int32_t* src_token, const bf16_t* zero_row, int S, int C, hipStream_t st,
+                    const int32_t* src_token, const bf16_t* zero_row, hipStream_t st,
                     const bf16_t* mask = nullptr, unsigned char* signbits = nullptr,
                     const int32_t* kept = nullptr) {
   using SM = DmaSmem<ST>;
@@ -763,16 +846,6 @@ int launch_bf16_dma(const bf16_t* A, const bf16_t* B, bf16_t* Cout, int E, int R
   const size_t kLds = SM::kBytes + (GATHER ? 4 * 64 * sizeof(int32_t) : 0) + (EPI == 5 ? 8192 : 0) +
                       (PACKED || DYNK ? align_up(((size_t)2 * E + 1) * sizeof(int32_t), 16) : 0);
   if (kLds > 160 * 1024) return MOE_EUNSUPPORTED;
-  // n / C for n < 2^31 as (n * c_magic) >> (32 + c_shift), c_magic = ceil(2^(31+l) / C) with
-  // l = ceil(log2 C); C == 1 is flagged by c_magic == 0
-  uint32_t c_magic = 0;
-  int c_shift = 0;
-  if (GATHER == 1 && C > 1) {
-    int l = 0;
-    while ((1LL << l) < C) ++l;
-    c_magic = (uint32_t)((((unsigned long long)1 << (31 + l)) + C - 1) / C);
-    c_shift = l - 1;
-  }
   if ((PACKED || DYNK) && kept == nullptr) return MOE_EINVAL;
   auto kern = expert_gemm_bf16_dma_kernel<ST, EPI, GATHER, A_MNC, B_KC, PACKED, SCATTER, DYNK>;
   int cus = 0;
@@ -784,7 +857,7 @@ int launch_bf16_dma(const bf16_t* A, const bf16_t* B, bf16_t* Cout, int E, int R
   if (ntiles > 0x7fffffffLL) return MOE_EUNSUPPORTED;
   const unsigned grid = (unsigned)(ntiles < cus ? ntiles : cus);   // one block per CU (LDS-bound)
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), kLds, st, A, B, Cout, R, N, K, tiles_m,
-                     tiles_n, (int)ntiles, src_token, zero_row, S, c_magic, c_shift, mask, signbits,
+                     tiles_n, (int)ntiles, src_token, zero_row, mask, signbits,
                      kept, E);
   return check_launch();
 }
@@ -795,52 +868,91 @@ inline bool dma_shape_ok(int R, int N, int K) {
   return R % 256 == 0 && N % 256 == 0 && K % 32 == 0 && 256 * big * 2 < (1LL << 31);
 }
 
-template <int BM, int BN, int BK, int EPI, bool A_MNC, bool B_KC, bool EXACT>
-int prepare_tiled() {
-  static LdsLimitOnce once;
-  return ensure_lds_limit(
-      once,
-      reinterpret_cast<const void*>(expert_gemm_bf16_kernel<BM, BN, BK, 2, 2, EPI, A_MNC, B_KC, EXACT>),
-      (int)GemmSmem<BM, BN, BK, A_MNC, B_KC>::kBytes);
+// Which kernel multiplies C [E,R,N]: the persistent one on 256 x 256 tiles (shapes it takes), the
+// edge kernel on 128 x 256 or on 128 x 128 tiles.  All have the same k order, so the choice changes no
+// bit; it compares the time the fullest compute unit needs, counted in 128 x 128 tiles at the
+// persistent kernel's rate: that kernel's tile = 4 of them, one at a time; of 128 x 256 tiles two
+// share a unit at 0.9 of that rate, a lone one reaches 0.6; of 128 x 128 tiles three share it at 0.7,
+// two at 0.5, a lone one 0.4.  (h = relu(buf wi), out = h wo of E experts of R rows, in us,
+// persistent / 128 x 256 / 128 x 128, one form for both products:
+//   E 32 R 2048 M 1024 H 8192   2065 / 2304 / 2693      E 128 R 1024 M 1024 H 4096  2141 / 2345 / 2764
+//   E 24 R 512  M 768  H 3072    172 /  174 /  191      E 64  R 256  M 1024 H 2048   166 /  182 /  223
+//   E 32 R 256  M 1024 H 8192    373 /  348 /  432      E 16  R 512  M 512  H 2048  69.6 / 58.8 / 48.1)
+enum GemmForm { kPersistent, kEdge256, kEdge128 };
+GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int cus) {
+  auto tiles = [&](int bm, int bn) {
+    return (long long)E * ((R + bm - 1) / bm) * ((N + bn - 1) / bn);
+  };
+  // `full` rounds of `res` tiles per unit, then what is left of the last round
+  auto shared = [&](long long n, int res, double tile, const double* rate) {
+    const long long full = n / ((long long)res * cus), rem = n - full * res * cus;
+    const int left = (int)((rem + cus - 1) / cus);
+    return full * res * tile / rate[res - 1] + (left > 0 ? left * tile / rate[left - 1] : 0.0);
+  };
+  static const double rate256[] = {0.6, 0.9}, rate128[] = {0.4, 0.5, 0.7};
+  const double t256 = shared(tiles(128, 256), 2, 2.0, rate256);
+  const double t128 = shared(tiles(128, 128), 3, 1.0, rate128);
+  if (persistent_ok && 4.0 * ((tiles(256, 256) + cus - 1) / cus) <= (t256 < t128 ? t256 : t128))
+    return kPersistent;
+  return t256 <= t128 ? kEdge256 : kEdge128;
+}
+// the form of this shape on the current device; k_kept: the sum over k runs over packed rows, of
+// which the persistent kernel takes whole 256-row tiles
+int choose_form(int E, int R, int N, int K, GemmForm* form, bool k_kept = false) {
+  int cus = 0;
+  if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
+  *form = gemm_form(dma_shape_ok(R, N, K) && (!k_kept || K % 256 == 0), E, R, N, cus);
+  return MOE_OK;
 }
 
-template <int BM, int BN, int BK, int EPI, bool A_MNC, bool B_KC, bool EXACT>
-int launch_bf16_kernel(const bf16_t* A, const bf16_t* B, bf16_t* Cout, const bf16_t* mask, int E,
-                       int R, int N, int K, hipStream_t st) {
-  using SM = GemmSmem<BM, BN, BK, A_MNC, B_KC>;
-  auto kern = expert_gemm_bf16_kernel<BM, BN, BK, 2, 2, EPI, A_MNC, B_KC, EXACT>;
-  if (prepare_tiled<BM, BN, BK, EPI, A_MNC, B_KC, EXACT>() != MOE_OK) return MOE_EHIP;
-  const int tiles_m = (R + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+// operands and result of one launch of the edge kernel (see there)
+struct EdgeArgs {
+  const void *A, *B;
+  void* C;
+  const void* mask = nullptr;
+  const int32_t *gather = nullptr, *kept = nullptr;
+  int row_pad = 0;
+  const int32_t* scatter = nullptr;
+};
+
+template <int BN, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
+int prepare_edge() {
+  static LdsLimitOnce once;
+  return ensure_lds_limit(
+      once, reinterpret_cast<const void*>(expert_gemm_bf16_edge_kernel<BN, EPI, A_MNC, B_KC, K_KEPT>),
+      (int)EdgeSmem<BN>::kBytes);
+}
+
+template <int BN, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
+int launch_edge(const EdgeArgs& a, int E, int R, int N, int K, hipStream_t st) {
+  if (prepare_edge<BN, EPI, A_MNC, B_KC, K_KEPT>() != MOE_OK) return MOE_EHIP;
+  const int tiles_m = (R + 127) / 128, tiles_n = (N + BN - 1) / BN;
   const long long nblk = (long long)E * tiles_m * tiles_n;
-  if (nblk > 0x7fffffffLL) return MOE_EUNSUPPORTED;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), SM::kBytes, st, A, B, Cout, mask, R, N, K,
-                     tiles_m, tiles_n, (int)nblk);
+  if (nblk > 0x7fffffffLL || (K_KEPT && a.kept == nullptr)) return MOE_EUNSUPPORTED;
+  hipLaunchKernelGGL((expert_gemm_bf16_edge_kernel<BN, EPI, A_MNC, B_KC, K_KEPT>), dim3((unsigned)nblk),
+                     dim3(256), EdgeSmem<BN>::kBytes, st, static_cast<const bf16_t*>(a.A),
+                     static_cast<const bf16_t*>(a.B), static_cast<bf16_t*>(a.C),
+                     static_cast<const bf16_t*>(a.mask), R, N, K, tiles_m, tiles_n, (int)nblk, a.gather,
+                     a.kept, a.row_pad, a.scatter);
   return check_launch();
 }
 
 // C [E,R,N] for any R, N, K with N % 8 == 0 and the operands' contiguous dimensions % 8 == 0
-// (K for a K-contiguous operand, R / N for a row-of-k one): 256x256 tiles when the output is
-// large enough, else 128x128.
-template <int EPI, bool A_MNC, bool B_KC>
-int gemm_bf16_tiled(const bf16_t* A, const bf16_t* B, bf16_t* Cout, const bf16_t* mask, int E, int R,
-                    int N, int K, hipStream_t st) {
-  if (R > 128 && N >= 256) {
-    if (R % 256 == 0 && N % 256 == 0 && K % 64 == 0)
-      return launch_bf16_kernel<256, 256, 64, EPI, A_MNC, B_KC, true>(A, B, Cout, mask, E, R, N, K, st);
-    return launch_bf16_kernel<256, 256, 64, EPI, A_MNC, B_KC, false>(A, B, Cout, mask, E, R, N, K, st);
-  }
-  if (R % 128 == 0 && N % 128 == 0 && K % 64 == 0)
-    return launch_bf16_kernel<128, 128, 64, EPI, A_MNC, B_KC, true>(A, B, Cout, mask, E, R, N, K, st);
-  return launch_bf16_kernel<128, 128, 64, EPI, A_MNC, B_KC, false>(A, B, Cout, mask, E, R, N, K, st);
+// (K for a K-contiguous operand, R / N for a row-of-k one)
+template <int EPI, bool A_MNC, bool B_KC, bool K_KEPT = false>
+int gemm_bf16_edge(GemmForm form, const EdgeArgs& a, int E, int R, int N, int K, hipStream_t st) {
+  return form == kEdge128 ? launch_edge<128, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st)
+                          : launch_edge<256, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
 }
 
 template <bool RELU>
 int gemm_bf16(const bf16_t* A, const bf16_t* B, bf16_t* Cout, int E, int R, int N, int K,
               hipStream_t st) {
-  if (dma_shape_ok(R, N, K))
-    return launch_bf16_dma<4, RELU ? 1 : 0, 0>(A, B, Cout, E, R, N, K, nullptr, nullptr, 0, 0,
-                                                   st);
-  return gemm_bf16_tiled<RELU ? 1 : 0, false, false>(A, B, Cout, nullptr, E, R, N, K, st);
+  GemmForm form;
+  if (choose_form(E, R, N, K, &form) != MOE_OK) return MOE_EHIP;
+  if (form == kPersistent)
+    return launch_bf16_dma<4, RELU ? 1 : 0, false>(A, B, Cout, E, R, N, K, nullptr, nullptr, st);
+  return gemm_bf16_edge<RELU ? 1 : 0, false, false>(form, EdgeArgs{A, B, Cout}, E, R, N, K, st);
 }
 
 // ---------------------------------------------------------------- fp32 path
@@ -876,23 +988,22 @@ int compute_units(int* cus) {
 int prepare_expert_gemm() {
   const int rcs[] = {
       // forward
-      prepare_dma<4, 1, 0>(), prepare_dma<4, 0, 0>(), prepare_dma<4, 1, 1>(), prepare_dma<4, 4, 1>(),
-      prepare_dma<4, 1, 2, false, false, true>(), prepare_dma<4, 4, 2, false, false, true>(),
-      prepare_dma<4, 0, 0, false, false, true, false>(), prepare_dma<4, 0, 0, false, false, true, true>(),
+      prepare_dma<4, 1, false>(), prepare_dma<4, 0, false>(),
+      prepare_dma<4, 1, true, false, false, true>(), prepare_dma<4, 4, true, false, false, true>(),
+      prepare_dma<4, 0, false, false, false, true, false>(), prepare_dma<4, 0, false, false, false, true, true>(),
       // fp32 results (gate logits and gate gradients)
-      prepare_dma<4, 3, 0, true, false>(), prepare_dma<4, 3, 0, false, true>(),
+      prepare_dma<4, 3, false, true, false>(), prepare_dma<4, 3, false, false, true>(),
       // backward
-      prepare_dma<4, 5, 0, false, true>(), prepare_dma<4, 2, 0, false, true>(),
-      prepare_dma<4, 0, 0, true, false>(), prepare_dma<4, 0, 0, false, true>(),
-      prepare_dma<4, 5, 0, false, true, true>(), prepare_dma<4, 0, 0, false, true, true>(),
-      prepare_dma<4, 0, 0, true, false, false, false, true>(),
-      // ragged shapes: forward (relu / plain), data gradients (plain / masked), weight gradients
-#define MOE_TILED_BOTH(EPI, AM, BK_)                                                              \
-      prepare_tiled<256, 256, 64, EPI, AM, BK_, true>(), prepare_tiled<256, 256, 64, EPI, AM, BK_, false>(), \
-      prepare_tiled<128, 128, 64, EPI, AM, BK_, true>(), prepare_tiled<128, 128, 64, EPI, AM, BK_, false>()
-      MOE_TILED_BOTH(1, false, false), MOE_TILED_BOTH(0, false, false), MOE_TILED_BOTH(0, false, true),
-      MOE_TILED_BOTH(2, false, true), MOE_TILED_BOTH(0, true, false)};
-#undef MOE_TILED_BOTH
+      prepare_dma<4, 2, false, false, true>(),
+      prepare_dma<4, 0, false, true, false>(), prepare_dma<4, 0, false, false, true>(),
+      prepare_dma<4, 5, false, false, true, true>(), prepare_dma<4, 0, false, false, true, true>(),
+      prepare_dma<4, 0, false, true, false, false, false, true>(),
+      // other shapes: forward (relu / plain), data gradients (plain / masked), weight gradients
+#define MOE_EDGE_BOTH(...) prepare_edge<256, __VA_ARGS__>(), prepare_edge<128, __VA_ARGS__>()
+      MOE_EDGE_BOTH(1, false, false, false), MOE_EDGE_BOTH(0, false, false, false),
+      MOE_EDGE_BOTH(0, false, true, false), MOE_EDGE_BOTH(2, false, true, false),
+      MOE_EDGE_BOTH(0, true, false, false), MOE_EDGE_BOTH(0, true, false, true)};
+#undef MOE_EDGE_BOTH
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
   for (int rc : rcs)
@@ -931,67 +1042,79 @@ int launch_gemm_bf16_f32out(bool transposed_a, const void* A, const void* B, flo
   auto c = reinterpret_cast<bf16_t*>(Cout);
   // transposed_a: C = A^T . B with A [K,R], B [K,N];  else C = A . B^T with A [R,K], B [N,K]
   return transposed_a
-             ? launch_bf16_dma<4, 3, 0, true, false>(a, b, c, batch, R, N, K, nullptr, nullptr, 0, 0, st)
-             : launch_bf16_dma<4, 3, 0, false, true>(a, b, c, batch, R, N, K, nullptr, nullptr, 0, 0, st);
+             ? launch_bf16_dma<4, 3, false, true, false>(a, b, c, batch, R, N, K, nullptr, nullptr, st)
+             : launch_bf16_dma<4, 3, false, false, true>(a, b, c, batch, R, N, K, nullptr, nullptr, st);
 }
 
-bool expert_gemm1_can_gather(const moe_config& c) {
-  const long long rows = (long long)c.G * c.C;
-  // the kernel fetches a tile's dispatch indices 4 K-steps (of 32) ahead of its first copy
-  return c.act_dtype == MOE_BF16 && rows <= 0x7fffffffLL && c.M >= 128 &&
-         dma_shape_ok((int)rows, c.H, c.M);
+// Which layers take the packed row layout, gathering the rows of x in the first GEMM: bf16 layers with
+// M >= 128 (the persistent kernel fetches a tile's row indices 4 K steps of 32 ahead of its first copy)
+// and row counts of the experts that fit the LDS left over by its stages.
+bool expert_ffn_can_pack(const moe_config& c) {
+  return c.act_dtype == MOE_BF16 && (long long)c.G * c.C <= 0x7fffffffLL && c.M >= 128 && c.E <= 2048;
 }
 
-int launch_expert_gemm1_gather(const moe_config& c, const void* x, const int32_t* src_token,
-                               const void* zero_row, const void* wi, void* h, void* signbits,
-                               hipStream_t st) {
-  if (!expert_gemm1_can_gather(c)) return MOE_EUNSUPPORTED;
-  if (signbits != nullptr)
-    return launch_bf16_dma<4, 4, 1>(static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(wi),
-                                       static_cast<bf16_t*>(h), c.E, c.G * c.C, c.H, c.M, src_token,
-                                       static_cast<const bf16_t*>(zero_row), c.S, c.C, st, nullptr,
-                                       static_cast<unsigned char*>(signbits));
-  return launch_bf16_dma<4, 1, 1>(static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(wi),
-                                        static_cast<bf16_t*>(h), c.E, c.G * c.C, c.H, c.M, src_token,
-                                        static_cast<const bf16_t*>(zero_row), c.S, c.C, st);
+size_t expert_signbits_bytes(const moe_config& c) {
+  return expert_ffn_can_pack(c) && dma_shape_ok(c.G * c.C, c.H, c.M) ? (size_t)c.E * c.G * c.C * c.H / 8 : 0;
 }
 
-// Packed row layout: both GEMMs walk the list of occupied row tiles.  The first gathers its rows
+// The weight gradients sum over whole 256-row tiles when the persistent kernel forms them: the rows of
+// h and dh behind the occupied ones then have to be zeros up to there.
+static int packed_row_pad(const moe_config& c) {
+  GemmForm f1, f2;
+  const int R = c.G * c.C;
+  if (choose_form(c.E, c.H, c.M, R, &f1, true) != MOE_OK || choose_form(c.E, c.M, c.H, R, &f2, true) != MOE_OK)
+    return 255;
+  return f1 == kPersistent || f2 == kPersistent ? 255 : 0;
+}
+
+// Packed row layout: both GEMMs walk the occupied row tiles.  The first gathers its rows
 // through pk.packed_src (absolute rows of `a`: token rows of x, or rows of an [E,G,C,M] buffer),
 // h and (scatter_out == false) out hold packed rows; scatter_out sends the rows of out back to
 // the absolute rows pk.packed_src names.
 int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPacking& pk,
                              const void* zero_row, const void* wi, const void* wo, void* h,
-                             void* out, bool scatter_out, void* signbits, hipStream_t st,
+                             void* out, bool scatter_out, bool train, void* signbits, hipStream_t st,
                              void* event_between) {
   if (!expert_ffn_can_pack(c)) return MOE_EUNSUPPORTED;
   const int R = c.G * c.C;
-  int rc = signbits != nullptr
-               ? launch_bf16_dma<4, 4, 2, false, false, true>(
-                     static_cast<const bf16_t*>(a), static_cast<const bf16_t*>(wi),
-                     static_cast<bf16_t*>(h), c.E, R, c.H, c.M, pk.packed_src,
-                     static_cast<const bf16_t*>(zero_row), c.S, c.C, st, nullptr,
-                     static_cast<unsigned char*>(signbits), pk.kept)
-               : launch_bf16_dma<4, 1, 2, false, false, true>(
-                     static_cast<const bf16_t*>(a), static_cast<const bf16_t*>(wi),
-                     static_cast<bf16_t*>(h), c.E, R, c.H, c.M, pk.packed_src,
-                     static_cast<const bf16_t*>(zero_row), c.S, c.C, st, nullptr, nullptr, pk.kept);
+  GemmForm f1, f2;
+  if (choose_form(c.E, R, c.H, c.M, &f1) != MOE_OK || choose_form(c.E, R, c.M, c.H, &f2) != MOE_OK)
+    return MOE_EHIP;
+  int rc;
+  if (f1 != kPersistent) {
+    EdgeArgs g{a, wi, h};
+    g.gather = pk.packed_src;
+    g.kept = pk.kept;
+    g.row_pad = train ? packed_row_pad(c) : 0;
+    rc = gemm_bf16_edge<1, false, false>(f1, g, c.E, R, c.H, c.M, st);
+  } else if (signbits != nullptr) {
+    rc = launch_bf16_dma<4, 4, true, false, false, true>(
+        static_cast<const bf16_t*>(a), static_cast<const bf16_t*>(wi), static_cast<bf16_t*>(h), c.E, R,
+        c.H, c.M, pk.packed_src, static_cast<const bf16_t*>(zero_row), st, nullptr,
+        static_cast<unsigned char*>(signbits), pk.kept);
+  } else {
+    rc = launch_bf16_dma<4, 1, true, false, false, true>(
+        static_cast<const bf16_t*>(a), static_cast<const bf16_t*>(wi), static_cast<bf16_t*>(h), c.E, R,
+        c.H, c.M, pk.packed_src, static_cast<const bf16_t*>(zero_row), st, nullptr, nullptr,
+        pk.kept);
+  }
   if (rc != MOE_OK) return rc;
   if (event_between != nullptr &&
       hipEventRecord(static_cast<hipEvent_t>(event_between), st) != hipSuccess)
     return MOE_EHIP;
+  if (f2 != kPersistent) {
+    EdgeArgs g{h, wo, out};
+    g.kept = pk.kept;
+    g.scatter = scatter_out ? pk.packed_src : nullptr;
+    return gemm_bf16_edge<0, false, false>(f2, g, c.E, R, c.M, c.H, st);
+  }
   if (scatter_out)
-    return launch_bf16_dma<4, 0, 0, false, false, true, true>(
+    return launch_bf16_dma<4, 0, false, false, false, true, true>(
         static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(wo), static_cast<bf16_t*>(out), c.E,
-        R, c.M, c.H, pk.packed_src, nullptr, 0, 0, st, nullptr, nullptr, pk.kept);
-  return launch_bf16_dma<4, 0, 0, false, false, true, false>(
+        R, c.M, c.H, pk.packed_src, nullptr, st, nullptr, nullptr, pk.kept);
+  return launch_bf16_dma<4, 0, false, false, false, true, false>(
       static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(wo), static_cast<bf16_t*>(out), c.E, R,
-      c.M, c.H, nullptr, nullptr, 0, 0, st, nullptr, nullptr, pk.kept);
-}
-
-bool expert_ffn_can_pack(const moe_config& c) {
-  // E: the kernels keep 2 E + 1 integers in the LDS left over by the stages
-  return expert_gemm1_can_gather(c) && dma_shape_ok(c.G * c.C, c.M, c.H) && c.E <= 2048;
+      c.M, c.H, nullptr, nullptr, st, nullptr, nullptr, pk.kept);
 }
 
 int launch_expert_gemm2(const moe_config& c, const void* h, const void* wo, void* out,
@@ -1010,90 +1133,84 @@ int launch_expert_gemm2(const moe_config& c, const void* h, const void* wo, void
 int launch_expert_dgrad2(const moe_config& c, const void* dout, const void* wo, const void* h,
                          const void* signbits, void* dh, const int32_t* kept, hipStream_t st) {
   const long long R = (long long)c.G * c.C;
-  if (kept != nullptr) {
-    if (signbits == nullptr || !expert_ffn_can_pack(c)) return MOE_EINVAL;
-    return launch_bf16_dma<4, 5, 0, false, true, true>(
-        static_cast<const bf16_t*>(dout), static_cast<const bf16_t*>(wo), static_cast<bf16_t*>(dh),
-        c.E, (int)R, c.H, c.M, nullptr, nullptr, 0, 0, st, nullptr,
-        const_cast<unsigned char*>(static_cast<const unsigned char*>(signbits)), kept);
+  if (c.act_dtype != MOE_BF16 || R > 0x7fffffffLL)
+    return launch_gemm_strided(c, 2, dout, R * c.M, c.M, 1, wo, (long long)c.H * c.M, 1, c.M, dh, h,
+                               (int)R, c.H, c.M, st);
+  auto a = static_cast<const bf16_t*>(dout);
+  auto b = static_cast<const bf16_t*>(wo);
+  auto o = static_cast<bf16_t*>(dh);
+  auto sign = const_cast<unsigned char*>(static_cast<const unsigned char*>(signbits));
+  GemmForm form;
+  if (choose_form(c.E, (int)R, c.H, c.M, &form) != MOE_OK) return MOE_EHIP;
+  if (form != kPersistent) {
+    EdgeArgs g{dout, wo, dh, h};
+    g.kept = kept;
+    g.row_pad = kept != nullptr ? packed_row_pad(c) : 0;
+    return gemm_bf16_edge<2, false, true>(form, g, c.E, (int)R, c.H, c.M, st);
   }
-  // the forward pass recorded the sign bits exactly when its first GEMM gathered (K >= 128)
-  if (signbits != nullptr && expert_gemm1_can_gather(c))
-    return launch_bf16_dma<4, 5, 0, false, true>(
-        static_cast<const bf16_t*>(dout), static_cast<const bf16_t*>(wo), static_cast<bf16_t*>(dh),
-        c.E, (int)R, c.H, c.M, nullptr, nullptr, 0, 0, st, nullptr,
-        const_cast<unsigned char*>(static_cast<const unsigned char*>(signbits)));
-  if (c.act_dtype == MOE_BF16 && R <= 0x7fffffffLL && dma_shape_ok((int)R, c.H, c.M))
-    return launch_bf16_dma<4, 2, 0, false, true>(
-        static_cast<const bf16_t*>(dout), static_cast<const bf16_t*>(wo), static_cast<bf16_t*>(dh),
-        c.E, (int)R, c.H, c.M, nullptr, nullptr, 0, 0, st, static_cast<const bf16_t*>(h));
-  // other bf16 shapes: the tiled MFMA kernel, A . B^T with the mask epilogue
-  if (c.act_dtype == MOE_BF16 && R <= 0x7fffffffLL)
-    return gemm_bf16_tiled<2, false, true>(static_cast<const bf16_t*>(dout), static_cast<const bf16_t*>(wo),
-                                           static_cast<bf16_t*>(dh), static_cast<const bf16_t*>(h), c.E,
-                                           (int)R, c.H, c.M, st);
-  return launch_gemm_strided(c, 2, dout, R * c.M, c.M, 1, wo, (long long)c.H * c.M, 1, c.M, dh, h,
-                             (int)R, c.H, c.M, st);
+  if (kept != nullptr) {
+    if (signbits == nullptr) return MOE_EINVAL;
+    return launch_bf16_dma<4, 5, false, false, true, true>(a, b, o, c.E, (int)R, c.H, c.M, nullptr, nullptr,
+                                                       st, nullptr, sign, kept);
+  }
+  return launch_bf16_dma<4, 2, false, false, true>(a, b, o, c.E, (int)R, c.H, c.M, nullptr, nullptr, st,
+                                               static_cast<const bf16_t*>(h));
+}
+
+// C = A^T . B of a weight gradient, [N1,N2] per expert summed over its rows (kept: packed rows)
+static int wgrad(const moe_config& c, const void* A, const void* B, void* dw, int N1, int N2,
+                 const int32_t* kept, hipStream_t st) {
+  const long long R = (long long)c.G * c.C;
+  if (c.act_dtype != MOE_BF16 || R > 0x7fffffffLL)
+    return launch_gemm_strided(c, 0, A, R * N1, 1, N1, B, R * N2, N2, 1, dw, nullptr, N1, N2, (int)R, st);
+  GemmForm form;
+  if (choose_form(c.E, N1, N2, (int)R, &form, kept != nullptr) != MOE_OK) return MOE_EHIP;
+  if (form != kPersistent) {
+    EdgeArgs g{A, B, dw};
+    g.kept = kept;
+    return kept != nullptr ? gemm_bf16_edge<0, true, false, true>(form, g, c.E, N1, N2, (int)R, st)
+                           : gemm_bf16_edge<0, true, false>(form, g, c.E, N1, N2, (int)R, st);
+  }
+  auto a = static_cast<const bf16_t*>(A);
+  auto b = static_cast<const bf16_t*>(B);
+  auto o = static_cast<bf16_t*>(dw);
+  if (kept != nullptr)
+    return launch_bf16_dma<4, 0, false, true, false, false, false, true>(a, b, o, c.E, N1, N2, (int)R, nullptr,
+                                                                     nullptr, st, nullptr, nullptr,
+                                                                     kept);
+  return launch_bf16_dma<4, 0, false, true, false>(a, b, o, c.E, N1, N2, (int)R, nullptr, nullptr, st);
 }
 
 int launch_expert_wgrad2(const moe_config& c, const void* h, const void* dout, void* dwo,
                          const int32_t* kept, hipStream_t st) {
-  const long long R = (long long)c.G * c.C;
-  if (kept != nullptr) {
-    if (!expert_ffn_can_pack(c)) return MOE_EINVAL;
-    return launch_bf16_dma<4, 0, 0, true, false, false, false, true>(
-        static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(dout), static_cast<bf16_t*>(dwo),
-        c.E, c.H, c.M, (int)R, nullptr, nullptr, 0, 0, st, nullptr, nullptr, kept);
-  }
-  if (c.act_dtype == MOE_BF16 && R <= 0x7fffffffLL && dma_shape_ok(c.H, c.M, (int)R))
-    return launch_bf16_dma<4, 0, 0, true, false>(
-        static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(dout), static_cast<bf16_t*>(dwo),
-        c.E, c.H, c.M, (int)R, nullptr, nullptr, 0, 0, st);
-  if (c.act_dtype == MOE_BF16 && R <= 0x7fffffffLL)       // A^T . B on the tiled MFMA kernel
-    return gemm_bf16_tiled<0, true, false>(static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(dout),
-                                           static_cast<bf16_t*>(dwo), nullptr, c.E, c.H, c.M, (int)R, st);
-  return launch_gemm_strided(c, 0, h, R * c.H, 1, c.H, dout, R * c.M, c.M, 1, dwo, nullptr, c.H,
-                             c.M, (int)R, st);
+  return wgrad(c, h, dout, dwo, c.H, c.M, kept, st);
 }
 
 int launch_expert_dgrad1(const moe_config& c, const void* dh, const void* wi, void* dbuf,
                          const int32_t* kept, hipStream_t st) {
   const long long R = (long long)c.G * c.C;
-  if (kept != nullptr) {
-    if (!expert_ffn_can_pack(c)) return MOE_EINVAL;
-    return launch_bf16_dma<4, 0, 0, false, true, true>(
-        static_cast<const bf16_t*>(dh), static_cast<const bf16_t*>(wi), static_cast<bf16_t*>(dbuf),
-        c.E, (int)R, c.M, c.H, nullptr, nullptr, 0, 0, st, nullptr, nullptr, kept);
+  if (c.act_dtype != MOE_BF16 || R > 0x7fffffffLL)
+    return launch_gemm_strided(c, 0, dh, R * c.H, c.H, 1, wi, (long long)c.M * c.H, 1, c.H, dbuf,
+                               nullptr, (int)R, c.M, c.H, st);
+  auto a = static_cast<const bf16_t*>(dh);
+  auto b = static_cast<const bf16_t*>(wi);
+  auto o = static_cast<bf16_t*>(dbuf);
+  GemmForm form;
+  if (choose_form(c.E, (int)R, c.M, c.H, &form) != MOE_OK) return MOE_EHIP;
+  if (form != kPersistent) {
+    EdgeArgs g{dh, wi, dbuf};
+    g.kept = kept;
+    return gemm_bf16_edge<0, false, true>(form, g, c.E, (int)R, c.M, c.H, st);
   }
-  if (c.act_dtype == MOE_BF16 && R <= 0x7fffffffLL && dma_shape_ok((int)R, c.M, c.H))
-    return launch_bf16_dma<4, 0, 0, false, true>(
-        static_cast<const bf16_t*>(dh), static_cast<const bf16_t*>(wi), static_cast<bf16_t*>(dbuf),
-        c.E, (int)R, c.M, c.H, nullptr, nullptr, 0, 0, st);
-  if (c.act_dtype == MOE_BF16 && R <= 0x7fffffffLL)       // A . B^T on the tiled MFMA kernel
-    return gemm_bf16_tiled<0, false, true>(static_cast<const bf16_t*>(dh), static_cast<const bf16_t*>(wi),
-                                           static_cast<bf16_t*>(dbuf), nullptr, c.E, (int)R, c.M, c.H, st);
-  return launch_gemm_strided(c, 0, dh, R * c.H, c.H, 1, wi, (long long)c.M * c.H, 1, c.H, dbuf,
-                             nullptr, (int)R, c.M, c.H, st);
+  if (kept != nullptr)
+    return launch_bf16_dma<4, 0, false, false, true, true>(a, b, o, c.E, (int)R, c.M, c.H, nullptr, nullptr,
+                                                       st, nullptr, nullptr, kept);
+  return launch_bf16_dma<4, 0, false, false, true>(a, b, o, c.E, (int)R, c.M, c.H, nullptr, nullptr, st);
 }
 
 int launch_expert_wgrad1(const moe_config& c, const void* buf, const void* dh, void* dwi,
                          const int32_t* kept, hipStream_t st) {
-  const long long R = (long long)c.G * c.C;
-  if (kept != nullptr) {
-    if (!expert_ffn_can_pack(c)) return MOE_EINVAL;
-    return launch_bf16_dma<4, 0, 0, true, false, false, false, true>(
-        static_cast<const bf16_t*>(buf), static_cast<const bf16_t*>(dh), static_cast<bf16_t*>(dwi),
-        c.E, c.M, c.H, (int)R, nullptr, nullptr, 0, 0, st, nullptr, nullptr, kept);
-  }
-  if (c.act_dtype == MOE_BF16 && R <= 0x7fffffffLL && dma_shape_ok(c.M, c.H, (int)R))
-    return launch_bf16_dma<4, 0, 0, true, false>(
-        static_cast<const bf16_t*>(buf), static_cast<const bf16_t*>(dh), static_cast<bf16_t*>(dwi),
-        c.E, c.M, c.H, (int)R, nullptr, nullptr, 0, 0, st);
-  if (c.act_dtype == MOE_BF16 && R <= 0x7fffffffLL)       // A^T . B on the tiled MFMA kernel
-    return gemm_bf16_tiled<0, true, false>(static_cast<const bf16_t*>(buf), static_cast<const bf16_t*>(dh),
-                                           static_cast<bf16_t*>(dwi), nullptr, c.E, c.M, c.H, (int)R, st);
-  return launch_gemm_strided(c, 0, buf, R * c.M, 1, c.M, dh, R * c.H, c.H, 1, dwi, nullptr, c.M,
-                             c.H, (int)R, st);
+  return wgrad(c, buf, dh, dwi, c.M, c.H, kept, st);
 }
 
 }  // namespace moe
