@@ -17,9 +17,10 @@
 // differs from a plain fp32 dot product.  wg is repacked (by the caller once per
 // weight update, else once per call) into the lane order of the
 // v_mfma_f32_32x32x16_bf16 B operand, so each B load is one contiguous 1 KB read.
-// Gates wider than 512 experts and fp32 activations with GEMM-friendly shapes get
-// their logits from the persistent GEMM kernel; everything else keeps the plain FMA
-// kernel.
+// Gates that leave compute units idle and fp32 gates take gate_chunk_kernel (one chunk
+// per block, the features split over its wavefronts).  Gates wider than 512 experts and
+// fp32 gates wider than 128 with GEMM-friendly shapes get their logits from the
+// persistent GEMM kernel; everything else keeps the plain FMA kernel.
 //
 // Positions never come from atomics: they are exact counts of earlier tokens, so
 // the result equals the sequential two-pass loop of Algorithm 1 bit for bit.
@@ -225,9 +226,9 @@ __device__ __forceinline__ Top2 top2_merge(const Top2& a, const Top2& b) {
 // per token; a wavefront holds 64/TPT tokens (lane % (64/TPT)) and thread `sub` = lane / (64/TPT)
 // of a token owns the 4-expert groups sub, sub + TPT, ...: its 16-byte reads and those of the
 // 15 lanes around it fall into different banks.  A token's logits are processed in registers
-// and its gates written back for the column sums.  Must be called by all threads of the block;
-// ends with a barrier.
-template <int NT, int EPAD>
+// and its gates written back for the column sums.  EXACT: library exponentials (fp32 layers).  Must be
+// called by all threads of the block; ends with a barrier.
+template <int NT, int EPAD, bool EXACT = false>
 __device__ __forceinline__ void gate_chunk_epilogue(
     float* zs, int pitch, int g, int ch, int S, int E, int nch, const float* __restrict__ u,
     int32_t* __restrict__ expert_idx, int32_t* __restrict__ slot, float* __restrict__ weight,
@@ -278,7 +279,8 @@ __device__ __forceinline__ void gate_chunk_epilogue(
   for (int i = 0; i < NG; ++i)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const float p = 4 * (sub + TPT * i) + k < E ? __expf(z[4 * i + k] - t2.v1) : 0.f;
+      const float d = z[4 * i + k] - t2.v1;
+      const float p = 4 * (sub + TPT * i) + k < E ? (EXACT ? expf(d) : __expf(d)) : 0.f;
       z[4 * i + k] = p;
       psum += p;
     }
@@ -835,6 +837,218 @@ __global__ __launch_bounds__(512) void gate_mfma_cols_split_kernel(
     }
   }
 }
+// What gate_scan_kernel and gate_slots_kernel do, for a single chunk in all (G == 1, S <= 64): the block
+// that routed the chunk has every count in LDS.  h1 / h2: its histograms (LDS), ms: its gate sums;
+// the routing record is the one the block has just written (a barrier in between).  NT threads.
+template <int NT>
+__device__ __forceinline__ void gate_single_chunk_finish(
+    int S, int E, int C, const int* h1, const int* h2, const float* __restrict__ ms,
+    int32_t* expert_idx, int32_t* slot, float* weight, int32_t* __restrict__ src_token,
+    int32_t* __restrict__ c1, float* __restrict__ mean_gate, int32_t* __restrict__ fill,
+    float* __restrict__ aux, uint32_t* __restrict__ zero_fill, int zero_words, const RowPacking& pk) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const bool packing = pk.packed_src != nullptr;
+  for (int i = tid; i < zero_words; i += NT) zero_fill[i] = 0u;
+  for (int e = tid; e < E; e += NT) {
+    const int tot = h1[e] + h2[e], f = tot < C ? tot : C;
+    c1[e] = h1[e];
+    mean_gate[e] = ms[e] / (float)S;
+    fill[e] = f;
+    if (packing) {
+      pk.row_base[e] = 0;
+      pk.kept[e] = f;
+    }
+  }
+  for (long long i = tid; i < (long long)E * C; i += NT) {
+    const int e = (int)(i / C), c = (int)(i - (long long)e * C);
+    if (c >= h1[e] + h2[e]) src_token[i] = -1;
+  }
+  if (tid >= 64) return;                               // one wavefront = the chunk's tokens
+  float part = 0.f;
+  for (int e = lane; e < E; e += 64) part += ((float)h1[e] / (float)S) * (ms[e] / (float)S);
+  part = wave_sum(part);
+  if (lane == 0) aux[0] = part / (float)E;
+  const bool valid = lane < S;
+  int e1 = -1, e2 = -1;
+  bool sampled = false;
+  if (valid) {
+    e1 = expert_idx[2 * lane];
+    sampled = slot[2 * lane + 1] != MOE_SLOT_NOT_SAMPLED;
+    if (sampled) e2 = expert_idx[2 * lane + 1];
+  }
+  unsigned long long peers1 = __ballot(e1 >= 0), peers2 = __ballot(e2 >= 0);
+  for (int bit = 0; (E - 1) >> bit; ++bit) {           // ranks as in gate_slots_kernel
+    const bool b1 = (e1 >> bit) & 1, b2 = (e2 >> bit) & 1;
+    const unsigned long long m1 = __ballot(b1), m2 = __ballot(b2);
+    peers1 &= b1 ? m1 : ~m1;
+    peers2 &= b2 ? m2 : ~m2;
+  }
+  if (!valid) return;
+  const unsigned long long earlier = (1ull << lane) - 1;
+  const int p1 = __popcll(peers1 & earlier);
+  const int s1 = p1 < C ? p1 : MOE_SLOT_OVERFLOW;
+  int s2 = MOE_SLOT_NOT_SAMPLED;
+  if (sampled) {
+    const int p2 = h1[e2] + __popcll(peers2 & earlier);
+    s2 = p2 < C ? p2 : MOE_SLOT_OVERFLOW;
+  }
+  slot[2 * lane] = s1;
+  slot[2 * lane + 1] = s2;
+  if (s1 < 0) weight[2 * lane] = 0.f;
+  if (s2 < 0) weight[2 * lane + 1] = 0.f;
+  if (s1 >= 0) {
+    src_token[(size_t)e1 * C + s1] = lane;
+    if (packing) pk.packed_src[(size_t)e1 * C + s1] = lane;
+  }
+  if (s2 >= 0) {
+    src_token[(size_t)e2 * C + s2] = lane;
+    if (packing) pk.packed_src[(size_t)e2 * C + s2] = lane;
+  }
+}
+
+// One 64-token chunk per block, eight wavefronts: KW of them share the features, 8 / KW the column
+// tiles of 32 experts (ETW each).  Takes the gates that would leave compute units idle or have no
+// matrix form otherwise:
+//   bf16, E <= 64, at most one chunk per compute unit: the 128-token blocks of gate_mfma_rows_kernel
+//     (their weight traffic pays once the chip is full) would use half the units and walk a quarter
+//     of the features serially.  Whole gate, launches included: 3500 tokens, M 768, E 24: 19.9 ->
+//     14.8 us; 16384 tokens, M 1024, E 32 (a chunk on every unit): 22.7 -> 18.5 us; 8192 tokens,
+//     E 64: 27.6 -> 22.2 us.
+//   fp32, E <= 128: full fp32 products on v_mfma_f32_32x32x2_f32, wg read as it is.  64 tokens, M 32,
+//     E 4: 68.6 us with the FMA kernel (a wavefront walks the features for one token at a time) ->
+//     6.9 us; 3000 tokens, M 1024, E 100: 3378 -> 56 us; 32 768 tokens, M 1024, E 32: 250 us with x
+//     split into bf16 terms, a logit GEMM and a softmax pass -> 45 us.
+// A call with a single chunk in all (a server's step) finishes here, no scan and no slots kernel: 64
+// tokens, M 1024, E 32: 16.9 -> 10.6 us.
+template <typename T, int ETW, int KW>
+__global__ __launch_bounds__(512) void gate_chunk_kernel(
+    const T* __restrict__ x, const uint4* __restrict__ wgP, const float* __restrict__ wg,
+    const float* __restrict__ u, int S, int M, int E, int C, int nch, int32_t* expert_idx, int32_t* slot,
+    float* weight, float* __restrict__ gates_opt, int32_t* __restrict__ hist1,
+    int32_t* __restrict__ hist2, float* msum, int32_t* __restrict__ src_token,
+    int32_t* __restrict__ c1, float* __restrict__ mean_gate, int32_t* __restrict__ fill,
+    float* __restrict__ aux, uint32_t* __restrict__ zero_fill, int zero_words, RowPacking pk, int single) {
+  constexpr int NT = 512, CW = 8 / KW, T32 = ETW * CW, Epad = 32 * T32, pitch = Epad + 8;  // 8 mod 32
+  constexpr bool F32 = sizeof(T) == 4;
+  extern __shared__ __attribute__((aligned(16))) unsigned char gate_smem[];
+  float* part = reinterpret_cast<float*>(gate_smem);             // [KW][64 * pitch]
+  int* hh = reinterpret_cast<int*>(part + (size_t)KW * 64 * pitch);
+  const int g = blockIdx.x / nch, ch = blockIdx.x % nch;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 31, h = lane >> 5;
+  const int kw = wave % KW, cw = wave / KW;
+
+  const T* xrow[2];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    int s = ch * kChunk + 32 * rt + r;
+    s = s < S ? s : S - 1;                              // clamp: surplus rows are ignored later
+    xrow[rt] = x + ((size_t)g * S + s) * M;
+  }
+  f32x16_t acc[2][ETW];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+    for (int t = 0; t < ETW; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[rt][t][i] = 0.f;
+
+  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  typedef float f32x4_t __attribute__((ext_vector_type(4)));
+  // feature blocks: 64 bf16 (lane half h owns 32, in the packed operand's order) or 32 fp32 (half h
+  // owns 16), 64 bytes of the token row per lane; features past M read the row start and meet zeros
+  constexpr int FB = F32 ? 32 : 64, PV = 16 / sizeof(T);
+  const int KB = (M + FB - 1) / FB, per = (KB + KW - 1) / KW;
+  const int kb0 = kw * per, kb1 = kb0 + per < KB ? kb0 + per : KB;
+  // the loads of NB feature blocks go out together, behind a fence that keeps the compiler from moving
+  // them to their uses (a block past the range is read again and not multiplied)
+  constexpr int NB = !F32 && ETW == 2 ? 1 : 2;
+  for (int kb = kb0; kb < kb1; kb += NB) {
+    u32x4_t a[NB][2][4];
+    float bf[NB][16][ETW];
+    u32x4_t bp[NB][4][ETW * 3];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      const int cur = kb + n < kb1 ? kb + n : kb;
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int col = cur * FB + FB / 2 * h + PV * j;
+          a[n][rt][j] = *reinterpret_cast<const u32x4_t*>(xrow[rt] + (col < M ? col : 0));
+        }
+      if constexpr (F32) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+#pragma unroll
+          for (int t = 0; t < ETW; ++t) {
+            const int m = cur * FB + 16 * h + q, e = 32 * (cw * ETW + t) + r;
+            bf[n][q][t] = wg[m < M && e < E ? (size_t)m * E + e : 0];
+          }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const u32x4_t* p = reinterpret_cast<const u32x4_t*>(wgP) +
+                             ((size_t)(cur * 4 + j) * T32 + cw * ETW) * 3 * 64 + lane;
+#pragma unroll
+          for (int t = 0; t < ETW * 3; ++t) bp[n][j][t] = p[t * 64];
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      if (kb + n >= kb1) break;                         // wave-uniform
+      if constexpr (F32) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+#pragma unroll
+          for (int t = 0; t < ETW; ++t) {
+            const float b = (kb + n) * FB + 16 * h + q < M && 32 * (cw * ETW + t) + r < E ? bf[n][q][t] : 0.f;
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+              acc[rt][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[n][rt][q >> 2][q & 3]), b,
+                                                                acc[rt][t], 0, 0, 0);
+          }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int t = 0; t < ETW; ++t)
+#pragma unroll
+            for (int sp = 2; sp >= 0; --sp)             // smallest term first
+#pragma unroll
+              for (int rt = 0; rt < 2; ++rt)
+                acc[rt][t] = MOE_GATE_MFMA(a[n][rt][j], bp[n][j][t * 3 + sp], acc[rt][t]);
+      }
+    }
+  }
+  // acc[rt][t][i]: token row 32 rt + 8 (i/4) + 4 h + i%4, expert 32 (cw ETW + t) + r
+  float* dst = part + (size_t)kw * 64 * pitch;
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+    for (int t = 0; t < ETW; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        dst[(32 * rt + 8 * (i >> 2) + 4 * h + (i & 3)) * pitch + 32 * (cw * ETW + t) + r] = acc[rt][t][i];
+  __syncthreads();
+  // the KW partial sums in a fixed order, into the first
+  for (int i = threadIdx.x; i < 64 * (Epad / 4); i += NT) {
+    float* p = part + (i / (Epad / 4)) * pitch + 4 * (i % (Epad / 4));
+    f32x4_t v = *reinterpret_cast<const f32x4_t*>(p);
+#pragma unroll
+    for (int k = 1; k < KW; ++k) v += *reinterpret_cast<const f32x4_t*>(p + (size_t)k * 64 * pitch);
+    *reinterpret_cast<f32x4_t*>(p) = v;
+  }
+  __syncthreads();
+  gate_chunk_epilogue<NT, Epad, F32>(part, pitch, g, ch, S, E, nch, u, expert_idx, slot, weight, gates_opt,
+                                     hist1, hist2, msum, hh, hh + Epad);
+  if (single)
+    gate_single_chunk_finish<NT>(S, E, C, hh, hh + Epad, msum, expert_idx, slot, weight, src_token, c1,
+                                 mean_gate, fill, aux, zero_fill, zero_words, pk);
+}
 #undef MOE_GATE_MFMA
 
 // One block per (group, 32 experts); thread (e, k) owns expert e and the k-th of 8
@@ -1114,8 +1328,11 @@ __global__ __launch_bounds__(256) void gate_split_x_kernel(
 }
 }  // namespace
 
-// Logits as one GEMM on the matrix cores, for bf16 gates wider than 512 experts and for fp32
-// activations (x split into three bf16 terms, K = 3 M): needs the persistent GEMM's shapes (token
+// fp32 gates of up to 128 experts: gate_chunk_kernel, nothing to pack
+static bool gate_f32_chunks(const moe_config& c) { return c.act_dtype == MOE_F32 && c.E <= 128; }
+
+// Logits as one GEMM on the matrix cores, for bf16 gates wider than 512 experts and for wider fp32
+// gates (x split into three bf16 terms, K = 3 M): needs the persistent GEMM's shapes (token
 // count a multiple of 256, K of 32) and at most 2048 experts (registers of the epilogue kernel).
 struct WideGeom { int cols, k; size_t z_bytes, w_bytes, x_bytes; };
 static WideGeom wide_geom(const moe_config& c) {
@@ -1123,7 +1340,7 @@ static WideGeom wide_geom(const moe_config& c) {
   const long long tokens = (long long)c.G * c.S;
   const long long cols = ((long long)3 * c.E + 255) / 256 * 256;
   const long long k = c.act_dtype == MOE_F32 ? (long long)3 * c.M : c.M;
-  if ((c.act_dtype == MOE_BF16 && c.E <= 512) || c.E > 2048 || tokens > 0x7fffffffLL ||
+  if (gate_f32_chunks(c) || (c.act_dtype == MOE_BF16 && c.E <= 512) || c.E > 2048 || tokens > 0x7fffffffLL ||
       k > 0x7fffffffLL || !gemm_bf16_f32out_ok((int)tokens, (int)cols, (int)k))
     return w;
   w.cols = (int)cols;
@@ -1181,10 +1398,25 @@ int launch_gate_pack(const moe_config& c, const float* wg, void* packed, hipStre
 // partial logits [4][128][Epad + 4], per-wavefront gate sums [4][Epad], histograms [4][Epad]
 constexpr size_t kGateRowsLds1 = (4 * 128 * 36 + 8 * 32) * 4, kGateRowsLds2 = (4 * 128 * 68 + 8 * 64) * 4;
 
+// partial logits [KW][64][Epad + 8] and two histograms [Epad]
+template <int ETW, int KW> constexpr int kGateChunkLds = (KW * 64 * (32 * ETW * 8 / KW + 8) + 2 * 32 * ETW * 8 / KW) * 4;
+
+template <typename T, int ETW, int KW>
+static int prepare_gate_chunk() {
+  static LdsLimitOnce once;
+  return ensure_lds_limit(once, reinterpret_cast<const void*>(gate_chunk_kernel<T, ETW, KW>),
+                          kGateChunkLds<ETW, KW>);
+}
+
 int prepare_gate() {
   static LdsLimitOnce once1, once2;
-  const int rc = ensure_lds_limit(once1, reinterpret_cast<const void*>(gate_mfma_rows_kernel<1>),
-                                  (int)kGateRowsLds1);
+  int rc = ensure_lds_limit(once1, reinterpret_cast<const void*>(gate_mfma_rows_kernel<1>),
+                            (int)kGateRowsLds1);
+  if (rc == MOE_OK) rc = prepare_gate_chunk<bf16_t, 1, 8>();
+  if (rc == MOE_OK) rc = prepare_gate_chunk<bf16_t, 2, 8>();
+  if (rc == MOE_OK) rc = prepare_gate_chunk<float, 1, 8>();
+  if (rc == MOE_OK) rc = prepare_gate_chunk<float, 2, 8>();
+  if (rc == MOE_OK) rc = prepare_gate_chunk<float, 2, 4>();
   if (rc != MOE_OK) return rc;
   return ensure_lds_limit(once2, reinterpret_cast<const void*>(gate_mfma_rows_kernel<2>),
                           (int)kGateRowsLds2);
@@ -1205,9 +1437,29 @@ int launch_gate(const moe_config& c, const void* x, const float* wg, const float
   uint4* wgP = wg_prepacked != nullptr ? static_cast<uint4*>(const_cast<void*>(wg_prepacked))
                                         : reinterpret_cast<uint4*>(own);
   const PackGeom pg = pack_geom(c);
-  int rc;
+  int rc, cus = 0;
+  if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
+  const long long chunks = (long long)c.G * nch;
+  const bool chunk_form = gate_f32_chunks(c) || (c.act_dtype == MOE_BF16 && c.E <= 64 && chunks <= cus);
+  const bool single = chunk_form && chunks == 1;
+  const int zero_words = zero_row != nullptr ? c.M / 2 : 0;
+  const RowPacking pk = packing != nullptr ? *packing : RowPacking{nullptr, nullptr, nullptr};
   if (wg_prepacked == nullptr && (rc = launch_gate_pack(c, wg, own, st)) != MOE_OK) return rc;
-  if (wide_geom(c).cols != 0) {
+  if (chunk_form) {
+    if (prepare_gate() != MOE_OK) return MOE_EHIP;
+#define MOE_GATE_CHUNK(T, ETW, KW)                                                                      \
+  hipLaunchKernelGGL((gate_chunk_kernel<T, ETW, KW>), dim3((unsigned)chunks), dim3(512),                \
+                     (kGateChunkLds<ETW, KW>), st, static_cast<const T*>(x), wgP, wg, u, c.S, c.M, c.E, c.C, \
+                     nch, expert_idx, slot, weight, gates_opt, hist1, hist2, msum, src_token, c1,       \
+                     mean_gate, fill, aux, static_cast<uint32_t*>(zero_row), zero_words, pk, single)
+    if (c.act_dtype == MOE_BF16) {
+      if (c.E <= 32) MOE_GATE_CHUNK(bf16_t, 1, 8); else MOE_GATE_CHUNK(bf16_t, 2, 8);
+    } else if (c.E <= 32) MOE_GATE_CHUNK(float, 1, 8);
+    else if (c.E <= 64) MOE_GATE_CHUNK(float, 2, 8);
+    else MOE_GATE_CHUNK(float, 2, 4);
+#undef MOE_GATE_CHUNK
+    if ((rc = check_launch()) != MOE_OK || single) return rc;
+  } else if (wide_geom(c).cols != 0) {
     // pg.bytes == 0 here: the packed-operand region is empty; wgk, the logits and (fp32) the
     // split activations follow it
     const WideGeom w = wide_geom(c);
@@ -1248,8 +1500,6 @@ int launch_gate(const moe_config& c, const void* x, const float* wg, const float
     }
     else if (c.E <= 128) {
       // 256-token blocks once they give every compute unit a block
-      int cus = 0;
-      if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
       const long long blocks256 = (long long)c.G * ((nch + 3) / 4);
       if (blocks256 >= cus)
         hipLaunchKernelGGL((gate_mfma_cols_split_kernel<1, 6, 8, 8>), dim3((unsigned)blocks256), dim3(512), 0, st, MOE_GATE_ARGS);
@@ -1267,9 +1517,7 @@ int launch_gate(const moe_config& c, const void* x, const float* wg, const float
   if ((rc = check_launch()) != MOE_OK) return rc;
   hipLaunchKernelGGL(gate_slots_kernel, dim3((unsigned)(c.G * nch)), dim3(64), 0, st, c.S, c.E,
                      c.C, c.G, nch, hist1, hist2, expert_idx, slot, weight, src_token, c1,
-                     mean_gate, aux, static_cast<uint32_t*>(zero_row),
-                     zero_row != nullptr ? c.M / 2 : 0, fill,
-                     packing != nullptr ? *packing : RowPacking{nullptr, nullptr, nullptr});
+                     mean_gate, aux, static_cast<uint32_t*>(zero_row), zero_words, fill, pk);
   return check_launch();
 }
 
