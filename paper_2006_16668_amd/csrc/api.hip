@@ -129,7 +129,7 @@ int forward_impl(const moe_config* cfg, const void* x, const float* wg, const fl
   int32_t* slot = reinterpret_cast<int32_t*>(base + w.slot);
   float* weight = reinterpret_cast<float*>(base + w.weight);
   int32_t* src_token = reinterpret_cast<int32_t*>(base + w.src_token);
-  // bf16 layers multiply only the occupied rows of each expert, packed to the front of its block, and
+  // layers that pack multiply only the occupied rows of each expert, packed to the front of its block, and
   // skip the dispatched buffer: the first GEMM gathers its rows from x (then the dispatch mark
   // coincides with the gate mark)
   const bool packed = moe::expert_ffn_can_pack(*cfg);
@@ -509,7 +509,7 @@ int moe_expert_ffn(const moe_config* cfg, const void* buf, const int32_t* fill, 
     // the second sends its rows back to their slots of out
     if ((reinterpret_cast<uintptr_t>(ws) & 255u) != 0) return MOE_EINVAL;
     const size_t maps = moe::row_packing_bytes(*cfg);
-    if (ws_bytes < maps + align_up((size_t)cfg->M * 2, 256)) return MOE_EWORKSPACE;
+    if (ws_bytes < maps + align_up((size_t)cfg->M * (cfg->act_dtype == MOE_F32 ? 4 : 2), 256)) return MOE_EWORKSPACE;
     const moe::RowPacking pk = moe::carve_row_packing(*cfg, ws);
     void* zero_row = static_cast<char*>(ws) + maps;
     int r = moe::launch_row_maps_from_fill(*cfg, fill, pk, zero_row, st);

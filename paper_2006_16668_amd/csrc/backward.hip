@@ -14,9 +14,6 @@
 //   dwg           dwg[m,e] = sum_tokens x[t,m] dz[t,e]
 //   dx            dx[g,s,:] = sum_k dbuf[e_k,g,c_k,:] + sum_e dz[g,s,e] wg[:,e]
 //                 (dispatch transposed + the gate projection)
-//
-// plus a generic strided GEMM that serves the expert GEMMs of the backward pass for
-// shapes and element types the MFMA kernels do not take.
 #include "common.h"
 
 namespace moe {
@@ -294,93 +291,7 @@ __global__ __launch_bounds__(256) void dx_kernel(
   }
 }
 
-// C[e,r,n] = epi( sum_k A[e*a_e + r*a_r + k*a_k] * B[e*b_e + k*b_k + n*b_n] ), C row-major
-// [E,R,N]; fp32 accumulation; EPI 0: none, 1: relu, 2: zero where mask[e,r,n] <= 0.
-template <typename T, int EPI>
-__global__ __launch_bounds__(256) void gemm_strided_kernel(
-    const T* __restrict__ A, long long a_e, long long a_r, long long a_k,
-    const T* __restrict__ B, long long b_e, long long b_k, long long b_n,
-    T* __restrict__ Cout, const T* __restrict__ mask, int R, int N, int K) {
-  __shared__ float as[16][65];
-  __shared__ float bs[16][65];
-  const int n0 = blockIdx.x * 64, r0 = blockIdx.y * 64, e = blockIdx.z;
-  const T* Ae = A + (size_t)e * a_e;
-  const T* Be = B + (size_t)e * b_e;
-  const int tid = threadIdx.x, tr = tid & 15, tn = tid >> 4;
-  const int lr = tid >> 2, lc = 4 * (tid & 3);
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = k0 + lc + i;
-      const int r = r0 + lr, n = n0 + lr;
-      as[lc + i][lr] = (r < R && k < K) ? Elt<T>::load(Ae + (long long)r * a_r + (long long)k * a_k) : 0.f;
-      bs[lc + i][lr] = (n < N && k < K) ? Elt<T>::load(Be + (long long)k * b_k + (long long)n * b_n) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = as[k][4 * tr + i]; b[i] = bs[k][4 * tn + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = r0 + 4 * tr + i, n = n0 + 4 * tn + j;
-      if (r >= R || n >= N) continue;
-      const size_t o = ((size_t)e * R + r) * N + n;
-      float v = acc[i][j];
-      if (EPI == 1) v = fmaxf(v, 0.f);
-      if (EPI == 2) v = Elt<T>::load(mask + o) > 0.f ? v : 0.f;
-      Elt<T>::store(Cout + o, v);
-    }
-}
-
-template <typename T>
-int gemm_strided(int epi, const void* A, long long a_e, long long a_r, long long a_k, const void* B,
-                 long long b_e, long long b_k, long long b_n, void* Cout, const void* mask, int E,
-                 int R, int N, int K, hipStream_t st) {
-  if (E > 65535 || (R + 63) / 64 > 65535) return MOE_EUNSUPPORTED;
-  const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((R + 63) / 64), (unsigned)E);
-  auto a = static_cast<const T*>(A);
-  auto b = static_cast<const T*>(B);
-  auto c = static_cast<T*>(Cout);
-  auto m = static_cast<const T*>(mask);
-  if (epi == 0)
-    hipLaunchKernelGGL((gemm_strided_kernel<T, 0>), grid, dim3(256), 0, st, a, a_e, a_r, a_k, b, b_e,
-                       b_k, b_n, c, m, R, N, K);
-  else if (epi == 1)
-    hipLaunchKernelGGL((gemm_strided_kernel<T, 1>), grid, dim3(256), 0, st, a, a_e, a_r, a_k, b, b_e,
-                       b_k, b_n, c, m, R, N, K);
-  else
-    hipLaunchKernelGGL((gemm_strided_kernel<T, 2>), grid, dim3(256), 0, st, a, a_e, a_r, a_k, b, b_e,
-                       b_k, b_n, c, m, R, N, K);
-  return check_launch();
-}
-
 }  // namespace
-
-int launch_gemm_strided(const moe_config& c, int epi, const void* A, long long a_e, long long a_r,
-                        long long a_k, const void* B, long long b_e, long long b_k, long long b_n,
-                        void* Cout, const void* mask, int R, int N, int K, hipStream_t st) {
-  if (c.act_dtype == MOE_F32 && R > 0 && N > 0 && K > 0 && a_e % 4 == 0 && b_e % 4 == 0 &&
-      gemm_f32_mfma_ok(a_r, a_k, b_k, b_n, c.E, R, N, K))
-    return launch_gemm_f32_mfma(epi, static_cast<const float*>(A), a_e, a_r, a_k,
-                                static_cast<const float*>(B), b_e, b_k, b_n,
-                                static_cast<float*>(Cout), static_cast<const float*>(mask), c.E, R,
-                                N, K, st);
-  return c.act_dtype == MOE_F32
-             ? gemm_strided<float>(epi, A, a_e, a_r, a_k, B, b_e, b_k, b_n, Cout, mask, c.E, R, N, K, st)
-             : gemm_strided<bf16_t>(epi, A, a_e, a_r, a_k, B, b_e, b_k, b_n, Cout, mask, c.E, R, N, K, st);
-}
 
 int launch_combine_bwd(const moe_config& c, const void* dy, const void* out,
                        const int32_t* src_token, const int32_t* expert_idx, const float* weight,

@@ -116,6 +116,20 @@ inline RowPacking carve_row_packing(const moe_config& c, void* base) {
   return pk;
 }
 
+// Operands and result of one grouped GEMM launch: C [E,R,N] per expert.
+//   gather:  NULL, or row p of expert e of a K-contiguous A is the absolute row gather[e R + p]
+//   kept:    NULL, or the occupied rows of each expert (packed layout)
+//   row_pad: 255: zero rows follow the occupied ones in C up to the next multiple of 256 (bf16)
+//   scatter: NULL, or row p of expert e of C goes to the absolute row scatter[e R + p]
+struct GemmArgs {
+  const void *A, *B;
+  void* C;
+  const void* mask = nullptr;          // same shape as C
+  const int32_t *gather = nullptr, *kept = nullptr;
+  int row_pad = 0;
+  const int32_t* scatter = nullptr;
+};
+
 // host-side launchers (each returns a moe_status)
 // zero_row: NULL, or M bf16 elements that the gate also clears (see launch_expert_ffn_packed)
 // packing: NULL, or the arrays of the packed row layout that the gate also fills (packed_src
@@ -157,7 +171,7 @@ int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPackin
                              void* event_between);
 size_t expert_signbits_bytes(const moe_config& c);
 
-// backward pass (backward.hip); epi of the strided GEMM: 0 none, 1 relu, 2 zero where mask <= 0
+// backward pass (backward.hip)
 int launch_combine_bwd(const moe_config& c, const void* dy, const void* out,
                        const int32_t* src_token, const int32_t* expert_idx, const float* weight,
                        void* dout, float* dweight, const int32_t* kept, hipStream_t st);
@@ -184,9 +198,6 @@ int launch_gate_bwd(const moe_config& c, const void* x, const float* wg, const f
 int launch_dx(const moe_config& c, const float* wg, const void* dbuf, const int32_t* expert_idx,
               const int32_t* slot, const GateBwdWs& w, void* dx, const int32_t* row_base,
               hipStream_t st);
-int launch_gemm_strided(const moe_config& c, int epi, const void* A, long long a_e, long long a_r,
-                        long long a_k, const void* B, long long b_e, long long b_k, long long b_n,
-                        void* Cout, const void* mask, int R, int N, int K, hipStream_t st);
 // expert GEMMs of the backward pass (expert_gemm.hip), per expert with rows = G*C:
 //   dgrad2: dh   = (dout . wo^T) masked by h > 0     [rows,M] x [H,M]^T -> [rows,H]
 //           (signbits as launch_expert_ffn_packed got them, else NULL)
@@ -210,13 +221,11 @@ bool gemm_bf16_f32out_ok(int R, int N, int K);
 int launch_gemm_bf16_f32out(bool transposed_a, const void* A, const void* B, float* Cout,
                             int batch, int R, int N, int K, hipStream_t st);
 
-// fp32 GEMM on the matrix cores (gemm_f32.hip), strides as in launch_gemm_strided; every operand
-// needs one unit stride and 16-byte alignment along it (gemm_f32_mfma_ok says whether it fits)
-bool gemm_f32_mfma_ok(long long a_r, long long a_k, long long b_k, long long b_n, int E, int R, int N,
-                      int K);
-int launch_gemm_f32_mfma(int epi, const float* A, long long a_e, long long a_r, long long a_k,
-                         const float* B, long long b_e, long long b_k, long long b_n, float* Cout,
-                         const float* mask, int E, int R, int N, int K, hipStream_t st);
+// fp32 GEMM on the matrix cores (gemm_f32.hip), dense operands as in the bf16 table above:
+//   kForward(Relu) C = A . B, kDataGrad(Mask) C = A . B^T (zero where mask <= 0), kWeightGrad C = A^T . B
+// kept with kWeightGrad is the length of each expert's sum, else its rows.
+enum GemmKind { kForward, kForwardRelu, kDataGrad, kDataGradMask, kWeightGrad };
+int launch_gemm_f32(GemmKind kind, const GemmArgs& a, int E, int R, int N, int K, hipStream_t st);
 
 // Transformer encoder sub-layers around the MoE layer (encoder.hip)
 int launch_add_layer_norm(int act_dtype, const void* x, const void* delta, const float* gamma,
@@ -270,6 +279,14 @@ inline int ensure_lds_limit(LdsLimitOnce& once, const void* kernel, int bytes) {
   return MOE_OK;
 }
 int compute_units(int* cus);      // of the current device (cached per device)
+
+// Time the fullest compute unit needs for n equal tiles when `res` of them share a unit at a time:
+// rate[i] is what the unit delivers with i + 1 tiles on it (1 = one tile of `size` per time `size`).
+inline double tiles_time(long long n, int cus, int res, double size, const double* rate) {
+  const long long full = n / ((long long)res * cus), rem = n - full * res * cus;
+  const int left = (int)((rem + cus - 1) / cus);
+  return full * res * size / rate[res - 1] + (left > 0 ? left * size / rate[left - 1] : 0.0);
+}
 int prepare_expert_gemm();        // expert_gemm.hip
 int prepare_gate();               // gate.hip
 int prepare_attention_bwd();      // attention_bwd_mfma.hip

@@ -883,15 +883,9 @@ GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int cus) {
   auto tiles = [&](int bm, int bn) {
     return (long long)E * ((R + bm - 1) / bm) * ((N + bn - 1) / bn);
   };
-  // `full` rounds of `res` tiles per unit, then what is left of the last round
-  auto shared = [&](long long n, int res, double tile, const double* rate) {
-    const long long full = n / ((long long)res * cus), rem = n - full * res * cus;
-    const int left = (int)((rem + cus - 1) / cus);
-    return full * res * tile / rate[res - 1] + (left > 0 ? left * tile / rate[left - 1] : 0.0);
-  };
   static const double rate256[] = {0.6, 0.9}, rate128[] = {0.4, 0.5, 0.7};
-  const double t256 = shared(tiles(128, 256), 2, 2.0, rate256);
-  const double t128 = shared(tiles(128, 128), 3, 1.0, rate128);
+  const double t256 = tiles_time(tiles(128, 256), cus, 2, 2.0, rate256);
+  const double t128 = tiles_time(tiles(128, 128), cus, 3, 1.0, rate128);
   if (persistent_ok && 4.0 * ((tiles(256, 256) + cus - 1) / cus) <= (t256 < t128 ? t256 : t128))
     return kPersistent;
   return t256 <= t128 ? kEdge256 : kEdge128;
@@ -905,16 +899,6 @@ int choose_form(int E, int R, int N, int K, GemmForm* form, bool k_kept = false)
   return MOE_OK;
 }
 
-// operands and result of one launch of the edge kernel (see there)
-struct EdgeArgs {
-  const void *A, *B;
-  void* C;
-  const void* mask = nullptr;
-  const int32_t *gather = nullptr, *kept = nullptr;
-  int row_pad = 0;
-  const int32_t* scatter = nullptr;
-};
-
 template <int BN, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
 int prepare_edge() {
   static LdsLimitOnce once;
@@ -924,7 +908,7 @@ int prepare_edge() {
 }
 
 template <int BN, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
-int launch_edge(const EdgeArgs& a, int E, int R, int N, int K, hipStream_t st) {
+int launch_edge(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
   if (prepare_edge<BN, EPI, A_MNC, B_KC, K_KEPT>() != MOE_OK) return MOE_EHIP;
   const int tiles_m = (R + 127) / 128, tiles_n = (N + BN - 1) / BN;
   const long long nblk = (long long)E * tiles_m * tiles_n;
@@ -940,7 +924,7 @@ int launch_edge(const EdgeArgs& a, int E, int R, int N, int K, hipStream_t st) {
 // C [E,R,N] for any R, N, K with N % 8 == 0 and the operands' contiguous dimensions % 8 == 0
 // (K for a K-contiguous operand, R / N for a row-of-k one)
 template <int EPI, bool A_MNC, bool B_KC, bool K_KEPT = false>
-int gemm_bf16_edge(GemmForm form, const EdgeArgs& a, int E, int R, int N, int K, hipStream_t st) {
+int gemm_bf16_edge(GemmForm form, const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
   return form == kEdge128 ? launch_edge<128, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st)
                           : launch_edge<256, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
 }
@@ -952,19 +936,7 @@ int gemm_bf16(const bf16_t* A, const bf16_t* B, bf16_t* Cout, int E, int R, int 
   if (choose_form(E, R, N, K, &form) != MOE_OK) return MOE_EHIP;
   if (form == kPersistent)
     return launch_bf16_dma<4, RELU ? 1 : 0, false>(A, B, Cout, E, R, N, K, nullptr, nullptr, st);
-  return gemm_bf16_edge<RELU ? 1 : 0, false, false>(form, EdgeArgs{A, B, Cout}, E, R, N, K, st);
-}
-
-// ---------------------------------------------------------------- fp32 path
-// fp32 layers multiply on the matrix cores in full fp32 (gemm_f32.hip); M and H are multiples
-// of 8, so every operand meets that kernel's 16-byte rule.
-template <bool RELU>
-int gemm_f32(const float* A, const float* B, float* Cout, int E, int R, int N, int K,
-             hipStream_t st) {
-  const long long ae = (long long)R * K, be = (long long)K * N;
-  if (ae % 4 != 0 || be % 4 != 0 || !gemm_f32_mfma_ok(K, 1, N, 1, E, R, N, K))
-    return MOE_EUNSUPPORTED;
-  return launch_gemm_f32_mfma(RELU ? 1 : 0, A, ae, K, 1, B, be, N, 1, Cout, nullptr, E, R, N, K, st);
+  return gemm_bf16_edge<RELU ? 1 : 0, false, false>(form, GemmArgs{A, B, Cout}, E, R, N, K, st);
 }
 
 }  // namespace
@@ -1024,8 +996,7 @@ int launch_expert_gemm1(const moe_config& c, const void* buf, const void* wi, vo
   const int rc = rows_per_expert(c, &R);
   if (rc != MOE_OK) return rc;
   if (c.act_dtype == MOE_F32)
-    return gemm_f32<true>(static_cast<const float*>(buf), static_cast<const float*>(wi),
-                          static_cast<float*>(h), c.E, R, c.H, c.M, st);
+    return launch_gemm_f32(kForwardRelu, GemmArgs{buf, wi, h}, c.E, R, c.H, c.M, st);
   return gemm_bf16<true>(static_cast<const bf16_t*>(buf), static_cast<const bf16_t*>(wi),
                          static_cast<bf16_t*>(h), c.E, R, c.H, c.M, st);
 }
@@ -1046,15 +1017,15 @@ int launch_gemm_bf16_f32out(bool transposed_a, const void* A, const void* B, flo
              : launch_bf16_dma<4, 3, false, false, true>(a, b, c, batch, R, N, K, nullptr, nullptr, st);
 }
 
-// Which layers take the packed row layout, gathering the rows of x in the first GEMM: bf16 layers with
+// Which layers take the packed row layout, gathering the rows of x in the first GEMM: those with
 // M >= 128 (the persistent kernel fetches a tile's row indices 4 K steps of 32 ahead of its first copy)
 // and row counts of the experts that fit the LDS left over by its stages.
 bool expert_ffn_can_pack(const moe_config& c) {
-  return c.act_dtype == MOE_BF16 && (long long)c.G * c.C <= 0x7fffffffLL && c.M >= 128 && c.E <= 2048;
+  return (long long)c.G * c.C <= 0x7fffffffLL && c.M >= 128 && c.E <= 2048;
 }
 
 size_t expert_signbits_bytes(const moe_config& c) {
-  return expert_ffn_can_pack(c) && dma_shape_ok(c.G * c.C, c.H, c.M) ? (size_t)c.E * c.G * c.C * c.H / 8 : 0;
+  return c.act_dtype == MOE_BF16 && expert_ffn_can_pack(c) && dma_shape_ok(c.G * c.C, c.H, c.M) ? (size_t)c.E * c.G * c.C * c.H / 8 : 0;
 }
 
 // The weight gradients sum over whole 256-row tiles when the persistent kernel forms them: the rows of
@@ -1077,16 +1048,26 @@ int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPackin
                              void* event_between) {
   if (!expert_ffn_can_pack(c)) return MOE_EUNSUPPORTED;
   const int R = c.G * c.C;
+  auto between = [&] {
+    return event_between == nullptr || hipEventRecord(static_cast<hipEvent_t>(event_between), st) == hipSuccess;
+  };
+  GemmArgs g1{a, wi, h}, g2{h, wo, out};
+  g1.gather = pk.packed_src;
+  g1.kept = g2.kept = pk.kept;
+  g2.scatter = scatter_out ? pk.packed_src : nullptr;
+  int rc;
+  if (c.act_dtype == MOE_F32) {
+    rc = launch_gemm_f32(kForwardRelu, g1, c.E, R, c.H, c.M, st);
+    if (rc != MOE_OK) return rc;
+    if (!between()) return MOE_EHIP;
+    return launch_gemm_f32(kForward, g2, c.E, R, c.M, c.H, st);
+  }
   GemmForm f1, f2;
   if (choose_form(c.E, R, c.H, c.M, &f1) != MOE_OK || choose_form(c.E, R, c.M, c.H, &f2) != MOE_OK)
     return MOE_EHIP;
-  int rc;
   if (f1 != kPersistent) {
-    EdgeArgs g{a, wi, h};
-    g.gather = pk.packed_src;
-    g.kept = pk.kept;
-    g.row_pad = train ? packed_row_pad(c) : 0;
-    rc = gemm_bf16_edge<1, false, false>(f1, g, c.E, R, c.H, c.M, st);
+    g1.row_pad = train ? packed_row_pad(c) : 0;
+    rc = gemm_bf16_edge<1, false, false>(f1, g1, c.E, R, c.H, c.M, st);
   } else if (signbits != nullptr) {
     rc = launch_bf16_dma<4, 4, true, false, false, true>(
         static_cast<const bf16_t*>(a), static_cast<const bf16_t*>(wi), static_cast<bf16_t*>(h), c.E, R,
@@ -1099,15 +1080,8 @@ int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPackin
         pk.kept);
   }
   if (rc != MOE_OK) return rc;
-  if (event_between != nullptr &&
-      hipEventRecord(static_cast<hipEvent_t>(event_between), st) != hipSuccess)
-    return MOE_EHIP;
-  if (f2 != kPersistent) {
-    EdgeArgs g{h, wo, out};
-    g.kept = pk.kept;
-    g.scatter = scatter_out ? pk.packed_src : nullptr;
-    return gemm_bf16_edge<0, false, false>(f2, g, c.E, R, c.M, c.H, st);
-  }
+  if (!between()) return MOE_EHIP;
+  if (f2 != kPersistent) return gemm_bf16_edge<0, false, false>(f2, g2, c.E, R, c.M, c.H, st);
   if (scatter_out)
     return launch_bf16_dma<4, 0, false, false, false, true, true>(
         static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(wo), static_cast<bf16_t*>(out), c.E,
@@ -1123,8 +1097,7 @@ int launch_expert_gemm2(const moe_config& c, const void* h, const void* wo, void
   const int rc = rows_per_expert(c, &R);
   if (rc != MOE_OK) return rc;
   if (c.act_dtype == MOE_F32)
-    return gemm_f32<false>(static_cast<const float*>(h), static_cast<const float*>(wo),
-                           static_cast<float*>(out), c.E, R, c.M, c.H, st);
+    return launch_gemm_f32(kForward, GemmArgs{h, wo, out}, c.E, R, c.M, c.H, st);
   return gemm_bf16<false>(static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(wo),
                           static_cast<bf16_t*>(out), c.E, R, c.M, c.H, st);
 }
@@ -1133,9 +1106,10 @@ int launch_expert_gemm2(const moe_config& c, const void* h, const void* wo, void
 int launch_expert_dgrad2(const moe_config& c, const void* dout, const void* wo, const void* h,
                          const void* signbits, void* dh, const int32_t* kept, hipStream_t st) {
   const long long R = (long long)c.G * c.C;
-  if (c.act_dtype != MOE_BF16 || R > 0x7fffffffLL)
-    return launch_gemm_strided(c, 2, dout, R * c.M, c.M, 1, wo, (long long)c.H * c.M, 1, c.M, dh, h,
-                               (int)R, c.H, c.M, st);
+  if (R > 0x7fffffffLL) return MOE_EUNSUPPORTED;
+  GemmArgs g{dout, wo, dh, h};
+  g.kept = kept;
+  if (c.act_dtype == MOE_F32) return launch_gemm_f32(kDataGradMask, g, c.E, (int)R, c.H, c.M, st);
   auto a = static_cast<const bf16_t*>(dout);
   auto b = static_cast<const bf16_t*>(wo);
   auto o = static_cast<bf16_t*>(dh);
@@ -1143,8 +1117,6 @@ int launch_expert_dgrad2(const moe_config& c, const void* dout, const void* wo, 
   GemmForm form;
   if (choose_form(c.E, (int)R, c.H, c.M, &form) != MOE_OK) return MOE_EHIP;
   if (form != kPersistent) {
-    EdgeArgs g{dout, wo, dh, h};
-    g.kept = kept;
     g.row_pad = kept != nullptr ? packed_row_pad(c) : 0;
     return gemm_bf16_edge<2, false, true>(form, g, c.E, (int)R, c.H, c.M, st);
   }
@@ -1161,16 +1133,15 @@ int launch_expert_dgrad2(const moe_config& c, const void* dout, const void* wo, 
 static int wgrad(const moe_config& c, const void* A, const void* B, void* dw, int N1, int N2,
                  const int32_t* kept, hipStream_t st) {
   const long long R = (long long)c.G * c.C;
-  if (c.act_dtype != MOE_BF16 || R > 0x7fffffffLL)
-    return launch_gemm_strided(c, 0, A, R * N1, 1, N1, B, R * N2, N2, 1, dw, nullptr, N1, N2, (int)R, st);
+  if (R > 0x7fffffffLL) return MOE_EUNSUPPORTED;
+  GemmArgs g{A, B, dw};
+  g.kept = kept;
+  if (c.act_dtype == MOE_F32) return launch_gemm_f32(kWeightGrad, g, c.E, N1, N2, (int)R, st);
   GemmForm form;
   if (choose_form(c.E, N1, N2, (int)R, &form, kept != nullptr) != MOE_OK) return MOE_EHIP;
-  if (form != kPersistent) {
-    EdgeArgs g{A, B, dw};
-    g.kept = kept;
+  if (form != kPersistent)
     return kept != nullptr ? gemm_bf16_edge<0, true, false, true>(form, g, c.E, N1, N2, (int)R, st)
                            : gemm_bf16_edge<0, true, false>(form, g, c.E, N1, N2, (int)R, st);
-  }
   auto a = static_cast<const bf16_t*>(A);
   auto b = static_cast<const bf16_t*>(B);
   auto o = static_cast<bf16_t*>(dw);
@@ -1189,19 +1160,16 @@ int launch_expert_wgrad2(const moe_config& c, const void* h, const void* dout, v
 int launch_expert_dgrad1(const moe_config& c, const void* dh, const void* wi, void* dbuf,
                          const int32_t* kept, hipStream_t st) {
   const long long R = (long long)c.G * c.C;
-  if (c.act_dtype != MOE_BF16 || R > 0x7fffffffLL)
-    return launch_gemm_strided(c, 0, dh, R * c.H, c.H, 1, wi, (long long)c.M * c.H, 1, c.H, dbuf,
-                               nullptr, (int)R, c.M, c.H, st);
+  if (R > 0x7fffffffLL) return MOE_EUNSUPPORTED;
+  GemmArgs g{dh, wi, dbuf};
+  g.kept = kept;
+  if (c.act_dtype == MOE_F32) return launch_gemm_f32(kDataGrad, g, c.E, (int)R, c.M, c.H, st);
   auto a = static_cast<const bf16_t*>(dh);
   auto b = static_cast<const bf16_t*>(wi);
   auto o = static_cast<bf16_t*>(dbuf);
   GemmForm form;
   if (choose_form(c.E, (int)R, c.M, c.H, &form) != MOE_OK) return MOE_EHIP;
-  if (form != kPersistent) {
-    EdgeArgs g{dh, wi, dbuf};
-    g.kept = kept;
-    return gemm_bf16_edge<0, false, true>(form, g, c.E, (int)R, c.M, c.H, st);
-  }
+  if (form != kPersistent) return gemm_bf16_edge<0, false, true>(form, g, c.E, (int)R, c.M, c.H, st);
   if (kept != nullptr)
     return launch_bf16_dma<4, 0, false, false, true, true>(a, b, o, c.E, (int)R, c.M, c.H, nullptr, nullptr,
                                                        st, nullptr, nullptr, kept);

@@ -3,13 +3,24 @@
 // this library's fast path, this kernel is the fp32 one for all six expert GEMMs of the forward
 // and backward pass and the dense layers around them.
 //
-//   C[e,r,n] = epi( sum_k A[e*a_e + r*a_r + k*a_k] * B[e*b_e + k*b_k + n*b_n] ),  C row-major
+// Built like the bf16 kernel of expert_gemm.hip that takes any shape: one block of four wavefronts
+// (2 x 2) per tile, operands travel global -> LDS without passing the registers
+// (global_load_lds_dwordx4, 1 KB per wavefront instruction, three stages of 16 k), every lane with its
+// own source address, and a row, column or k past an edge, or an unoccupied packed row, reads a zero
+// line.  Unit strides run along dimensions that are multiples of 4 elements.
 //
-// Each operand must have one unit stride (K-contiguous or row-contiguous); the kernel reads it
-// with 16-byte loads along that direction and stages it K-major in LDS ([k][row], padded), so
-// that the MFMA operands (lane l: row l % 32, k = l / 32) are conflict-free 4-byte reads.
-// Block = 128 x 128 tile, 4 wavefronts of 64 x 64 (2 x 2 MFMA tiles), 16-wide K steps, double
-// buffered through registers.  Dimensions along a unit stride must be multiples of 4.
+//   K-contiguous operand [rows][K]: stage [rows][4 chunks of 4 k], chunk c of row r at position
+//     c ^ ((r>>2)&3); a lane reads 16 bytes = the 4 k of four MFMA steps.
+//   row-of-k operand [K][rows]: stage [16 k][rows / 4 chunks], chunk c of row k at c ^ (8 ((k>>2)&1));
+//     one 4-byte read per step.  (64 banks: both reads touch every bank once)
+// Lane half h of step j of an 8-wide group of k takes k = 4 h + j in both operands.
+//
+// Bound: the matrix pipes (one instruction occupies its pipe for 64 cycles, so LDS and issue rates
+// are far from binding); what the kernel has to do is keep them fed across the barrier and the tile's
+// ends, which takes several blocks per compute unit.  The 128 x 128 kernel before this one staged
+// through registers and waited for each load where it was issued.
+// Forward products of 8 experts of 2048 rows, M 1024, H 4096: 111 TFLOP/s with that kernel, 132 with
+// this one (0.84 of the fp32 matrix peak); 16 experts of 512 rows, M 1024, H 2048: 97 -> 129.
 #include "common.h"
 
 namespace moe {
@@ -18,180 +29,241 @@ namespace {
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kT = 128, kBK = 16, kPitch = kT + 4;
+static __device__ const f32x4_t f32_zero_line = {0.f, 0.f, 0.f, 0.f};
 
-// one operand tile: 128 rows x 16 k; thread t fetches two 16-byte vectors
-struct TileRegs { f32x4_t v[2]; };
+constexpr int kF32Stages = 3, kBK = 16;
 
-// UNIT_K: the operand is K-contiguous (thread: row t/2, k 8 (t%2) .. +7)
-//         else row-contiguous          (thread: k t/16, rows 8 (t%16) .. +7)
-template <bool UNIT_K>
-__device__ __forceinline__ void load_tile(TileRegs& r, const float* __restrict__ base,
-                                          long long s_row, long long s_k, int row0, int k0,
-                                          int rows, int K, int tid) {
-  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
-  if (UNIT_K) {
-    const int row = row0 + (tid >> 1), k = k0 + 8 * (tid & 1);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const bool ok = row < rows && k + 4 * i < K;          // K % 4 == 0: no straddling
-      const float* p = base + (long long)(ok ? row : 0) * s_row + (ok ? k + 4 * i : 0);
-      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(p);
-      r.v[i] = ok ? v : zero;
-    }
-  } else {
-    const int k = k0 + (tid >> 4), row = row0 + 8 * (tid & 15);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const bool ok = k < K && row + 4 * i < rows;          // rows % 4 == 0
-      const float* p = base + (long long)(ok ? k : 0) * s_k + (ok ? row + 4 * i : 0);
-      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(p);
-      r.v[i] = ok ? v : zero;
-    }
-  }
-}
-
-template <bool UNIT_K>
-__device__ __forceinline__ void store_tile(const TileRegs& r, float* s, int tid) {   // s: [16][kPitch]
-  if (UNIT_K) {
-    const int row = tid >> 1, k = 8 * (tid & 1);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) s[(k + 4 * i + j) * kPitch + row] = r.v[i][j];
-  } else {
-    const int k = tid >> 4, row = 8 * (tid & 15);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4_t*>(&s[k * kPitch + row + 4 * i]) = r.v[i];
-  }
-}
-
-// EPI 0: plain, 1: relu, 2: zero where mask[e,r,n] <= 0
-template <int EPI, bool A_UNIT_K, bool B_UNIT_K>
-__global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(
-    const float* __restrict__ A, long long a_e, long long a_r, long long a_k,
-    const float* __restrict__ B, long long b_e, long long b_k, long long b_n,
-    float* __restrict__ Cout, const float* __restrict__ mask, int R, int N, int K, int tiles_r,
-    int tiles_n) {
-  __shared__ __attribute__((aligned(16))) float As[2][kBK * kPitch];
-  __shared__ __attribute__((aligned(16))) float Bs[2][kBK * kPitch];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// T: 64 T x 64 T tile, 32 T x 32 T per wavefront.  The other parameters are those of GemmArgs and of
+// the bf16 kernel: EPI 0 plain, 1 relu, 2 zero where mask[e,r,n] <= 0; gathered rows of A, kept rows
+// of an expert (or, K_KEPT, the length of its sum), scattered rows of C.
+template <int T, int EPI, bool A_KC, bool B_KC, bool K_KEPT>
+__global__ __launch_bounds__(256, T == 2 ? 3 : 4) void gemm_f32_mfma_kernel(
+    const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ Cout,
+    const float* __restrict__ mask, int R, int N, int K, int tiles_r, int tiles_n,
+    const int32_t* __restrict__ gather, const int32_t* __restrict__ kept,
+    const int32_t* __restrict__ scatter) {
+  constexpr int kTile = 64 * T, kAStage = kTile * kBK * 4, kStage = 2 * kAStage, ST = kF32Stages;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[ST * kStage];
+  typedef unsigned char __attribute__((address_space(3))) * lds_ptr;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_ptr)smem);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // Consecutive workgroups go to different XCDs (8, each with its own L2).  Give every XCD a
-  // contiguous range of tiles, row tiles fastest, so that the tiles that share a panel of B
-  // run next to each other under one L2.
-  unsigned t = blockIdx.x;
+  // contiguous range of tiles, in bands of 8 row tiles with the row tile fastest, so that the tiles
+  // that share panels run next to each other under one L2.
+  unsigned blk = blockIdx.x;
   const unsigned per_xcd = gridDim.x / 8;
-  if (t < per_xcd * 8) t = (t % 8) * per_xcd + t / 8;
-  const unsigned per_e = (unsigned)tiles_r * tiles_n;
-  const int e = t / per_e;
-  t -= e * per_e;
-  const int r0 = (int)(t % tiles_r) * kT, n0 = (int)(t / tiles_r) * kT;
-  const float* Ae = A + (size_t)e * a_e;
-  const float* Be = B + (size_t)e * b_e;
-  const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
+  if (blk < per_xcd * 8) blk = (blk % 8) * per_xcd + blk / 8;
+  const int per_e = tiles_r * tiles_n;
+  const int e = (int)(blk / per_e), t = (int)(blk - (unsigned)e * per_e);
+  const int band = t / (8 * tiles_n), rem = t - band * 8 * tiles_n;
+  const int left = tiles_r - 8 * band, brows = left < 8 ? left : 8;
+  const int ct = rem / brows, rt = 8 * band + (rem - ct * brows);
+  const int r0 = rt * kTile, n0 = ct * kTile;
+  const int rows = kept != nullptr && !K_KEPT ? kept[e] : R;
+  if (r0 >= rows) return;                                      // block-uniform
+  const int KE = K_KEPT ? kept[e] : K;
+  const int KT = (KE + kBK - 1) / kBK;
+  const int wm0 = (wave >> 1) * 32 * T, wn0 = (wave & 1) * 32 * T;
   const int l32 = lane & 31, hf = lane >> 5;
 
-  f32x16_t acc[2][2];
+  // per-lane sources: T copies of each operand per wavefront and step.  A copy fills 16 rows of 4
+  // chunks (K-contiguous) or 4 / T k rows of 16 T chunks (row-of-k)
+  constexpr int CH = 16 * T, RPC = 64 / CH;
+  const uint64_t zline = (uint64_t)(uintptr_t)&f32_zero_line;
+  uint64_t a_addr[T], b_addr[T];
+  uint32_t a_inc[T], b_inc[T];
+  int a_k[T], b_k[T];                                          // the lane's first k inside a step
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int q = 0; q < T; ++q) {
+    const int c = wave * T + q;
+    const int krow = RPC * c + lane / CH, kcol = 4 * ((lane % CH) ^ (8 * ((krow >> 2) & 1)));
+    const int row = 16 * c + (lane >> 2), kch = 4 * ((lane & 3) ^ ((row >> 2) & 3));
+    bool ok;
+    const float* src;
+    if (A_KC) {
+      a_k[q] = kch;
+      ok = r0 + row < rows && kch < KE;
+      long long arow = (long long)e * R + r0 + row;
+      if (gather != nullptr) {
+        const int tok = ok ? gather[arow] : -1;
+        ok = tok >= 0;
+        arow = tok;
+      }
+      src = A + arow * K + kch;
+    } else {
+      a_k[q] = krow;
+      ok = r0 + kcol < R && krow < KE;
+      src = A + ((size_t)e * K + krow) * R + r0 + kcol;
+    }
+    a_addr[q] = ok ? (uint64_t)(uintptr_t)src : zline;
+    a_inc[q] = ok ? (A_KC ? kBK * 4 : (uint32_t)R * kBK * 4) : 0u;
+    if (B_KC) {
+      b_k[q] = kch;
+      ok = n0 + row < N && kch < KE;
+      src = B + ((size_t)e * N + n0 + row) * K + kch;
+    } else {
+      b_k[q] = krow;
+      ok = n0 + kcol < N && krow < KE;
+      src = B + ((size_t)e * K + krow) * N + n0 + kcol;
+    }
+    b_addr[q] = ok ? (uint64_t)(uintptr_t)src : zline;
+    b_inc[q] = ok ? (B_KC ? kBK * 4 : (uint32_t)N * kBK * 4) : 0u;
+  }
+#define MOE_F32_COPY(LDS_U32, ADDR_U64)                                                      \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"            \
+               :: "s"(LDS_U32), "v"(ADDR_U64) : "memory")
+  auto start_step = [&](int p, int stage) {                    // the next step in order
+    if (p > 0) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+      for (int q = 0; q < T; ++q) { a_addr[q] += a_inc[q]; b_addr[q] += b_inc[q]; }
+      const int kl = KE - p * kBK;                             // k left, this step's included
+      if (kl < kBK) {                                          // block-uniform, last step only
+#pragma unroll
+        for (int q = 0; q < T; ++q) {
+          if (a_k[q] >= kl) a_addr[q] = zline;
+          if (b_k[q] >= kl) b_addr[q] = zline;
+        }
+      }
+    }
+    const uint32_t la = lds0 + stage * kStage + wave * (T * 1024);
+#pragma unroll
+    for (int q = 0; q < T; ++q) {
+      MOE_F32_COPY(la + q * 1024, a_addr[q]);
+      MOE_F32_COPY(la + kAStage + q * 1024, b_addr[q]);
+    }
+  };
+
+  // fragment reads of k group kg (8 k): value j is step j's operand
+  typedef f32x4_t __attribute__((address_space(3))) * lds_f4_ptr;
+  typedef float __attribute__((address_space(3))) * lds_f_ptr;
+  auto read_frag = [&](bool kc, uint32_t base, int w0, int i, int kg) {
+    const int row = w0 + 32 * i + l32;
+    if (kc)
+      return *(lds_f4_ptr)(uintptr_t)(base + row * 64 + (((2 * kg + hf) ^ ((row >> 2) & 3)) * 16));
+    f32x4_t v;
+    const uint32_t p = base + (8 * kg + 4 * hf) * (kTile * 4) + (((row >> 2) ^ (8 * hf)) * 16) + 4 * (row & 3);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = *(lds_f_ptr)(uintptr_t)(p + j * (kTile * 4));
+    return v;
+  };
+
+  f32x16_t acc[T][T];
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  TileRegs ra, rb;
-  load_tile<A_UNIT_K>(ra, Ae, a_r, a_k, r0, 0, R, K, tid);
-  load_tile<B_UNIT_K>(rb, Be, b_n, b_k, n0, 0, N, K, tid);
-  store_tile<A_UNIT_K>(ra, As[0], tid);
-  store_tile<B_UNIT_K>(rb, Bs[0], tid);
-  __syncthreads();
-  const int steps = (K + kBK - 1) / kBK;
-  for (int s = 0; s < steps; ++s) {
-    const int cur = s & 1;
-    if (s + 1 < steps) {
-      load_tile<A_UNIT_K>(ra, Ae, a_r, a_k, r0, (s + 1) * kBK, R, K, tid);
-      load_tile<B_UNIT_K>(rb, Be, b_n, b_k, n0, (s + 1) * kBK, N, K, tid);
-    }
-#pragma unroll
-    for (int kk = 0; kk < kBK / 2; ++kk) {
-      float a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        a[i] = As[cur][(2 * kk + hf) * kPitch + wm0 + 32 * i + l32];
-        b[i] = Bs[cur][(2 * kk + hf) * kPitch + wn0 + 32 * i + l32];
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    if (s + 1 < steps) {
-      store_tile<A_UNIT_K>(ra, As[cur ^ 1], tid);        // last read two barriers ago
-      store_tile<B_UNIT_K>(rb, Bs[cur ^ 1], tid);
+  int p = 0, pstage = 0;
+  for (; p < ST - 1 && p < KT; ++p) {
+    start_step(p, pstage);
+    ++pstage;
+  }
+  int stage = 0;
+  for (int s = 0; s < KT; ++s) {
+    // own copies of step s landed (step s + 1 may still fly), then everybody's; the stage of step
+    // s - 1 is free after the barrier
+    if (s + 1 < KT) {
+      if (T == 2) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
+    if (p < KT) {
+      start_step(p, pstage);
+      pstage = pstage + 1 == ST ? 0 : pstage + 1;
+      ++p;
+    }
+    const uint32_t sb = lds0 + stage * kStage;
+    stage = stage + 1 == ST ? 0 : stage + 1;
+#pragma unroll
+    for (int kg = 0; kg < 2; ++kg) {
+      f32x4_t a[T], b[T];
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        a[i] = read_frag(A_KC, sb, wm0, i, kg);
+        b[i] = read_frag(B_KC, sb + kAStage, wn0, i, kg);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+          for (int j = 0; j < T; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][q], b[j][q], acc[i][j], 0, 0, 0);
+    }
   }
-  // acc[i][j][v]: row 32 i + 8 (v/4) + 4 hf + v%4, column 32 j + lane%32 of the wavefront tile
+  // acc[i][j][v]: row 32 i + 8 (v/4) + 4 hf + v%4, column 32 j + lane%32 of the wavefront tile: a store
+  // covers whole 128-byte pieces of two rows
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < T; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int v = 0; v < 16; ++v) {
+      const int r = r0 + wm0 + 32 * i + 8 * (v >> 2) + 4 * hf + (v & 3);
+      if (r >= rows) continue;
+      const size_t o = ((size_t)e * R + r) * N;
+      float* crow = Cout + (scatter != nullptr ? (size_t)scatter[(size_t)e * R + r] * N : o);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = r0 + wm0 + 32 * i + 8 * (v >> 2) + 4 * hf + (v & 3);
+      for (int j = 0; j < T; ++j) {
         const int n = n0 + wn0 + 32 * j + l32;
-        if (r >= R || n >= N) continue;
-        const size_t o = ((size_t)e * R + r) * N + n;
+        if (n >= N) continue;
         float x = acc[i][j][v];
         if (EPI == 1) x = fmaxf(x, 0.f);
-        if (EPI == 2) x = mask[o] > 0.f ? x : 0.f;
-        Cout[o] = x;
+        if (EPI == 2) x = mask[o + n] > 0.f ? x : 0.f;
+        crow[n] = x;
       }
+    }
+#undef MOE_F32_COPY
 }
 
-template <bool A_UNIT_K, bool B_UNIT_K>
-int launch_layout(int epi, const float* A, long long a_e, long long a_r, long long a_k,
-                  const float* B, long long b_e, long long b_k, long long b_n, float* Cout,
-                  const float* mask, int E, int R, int N, int K, hipStream_t st) {
-  const int tiles_r = (R + kT - 1) / kT, tiles_n = (N + kT - 1) / kT;
-  const dim3 grid((unsigned)((long long)E * tiles_r * tiles_n));
-#define MOE_F32_CASE(EP)                                                                       \
-  hipLaunchKernelGGL((gemm_f32_mfma_kernel<EP, A_UNIT_K, B_UNIT_K>), grid, dim3(256), 0, st, A, \
-                     a_e, a_r, a_k, B, b_e, b_k, b_n, Cout, mask, R, N, K, tiles_r, tiles_n)
-  if (epi == 0) MOE_F32_CASE(0);
-  else if (epi == 1) MOE_F32_CASE(1);
-  else MOE_F32_CASE(2);
-#undef MOE_F32_CASE
+template <int T, int EPI, bool A_KC, bool B_KC, bool K_KEPT>
+int launch_tiles(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
+  const int tiles_r = (R + 64 * T - 1) / (64 * T), tiles_n = (N + 64 * T - 1) / (64 * T);
+  const long long nblk = (long long)E * tiles_r * tiles_n;
+  if (nblk > 0x7fffffffLL) return MOE_EUNSUPPORTED;
+  hipLaunchKernelGGL((gemm_f32_mfma_kernel<T, EPI, A_KC, B_KC, K_KEPT>), dim3((unsigned)nblk), dim3(256), 0,
+                     st, static_cast<const float*>(a.A), static_cast<const float*>(a.B),
+                     static_cast<float*>(a.C), static_cast<const float*>(a.mask), R, N, K, tiles_r,
+                     tiles_n, a.gather, a.kept, a.scatter);
   return check_launch();
+}
+
+// 128 x 128 or 64 x 64 tiles: whichever keeps the fullest compute unit busy for a shorter time.  Of the
+// larger three share a unit, one alone reaches 0.74 of the fp32 matrix rate, three 0.84; of the smaller
+// six share it, 0.5 for one, 0.74 from four on.  (h = relu(buf wi), out = h wo, 128 / 64, us:
+//   E 16 R 512 M 1024 H 2048  533 / 604    E 8  R 2048 M 1024 H 4096  2090 / 2365
+//   E 24 R 295 M 768  H 3072  732 / 663    E 16 R 128  M 512  H 1024   114 / 48.7
+//   E 4  R 512 M 512  H 2048  183 / 90.3   E 32 R 64   M 1024 H 2048   278 / 174)
+template <int EPI, bool A_KC, bool B_KC, bool K_KEPT = false>
+int launch_form(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
+  int cus = 0;
+  if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
+  auto tiles = [&](int edge) { return (long long)E * ((R + edge - 1) / edge) * ((N + edge - 1) / edge); };
+  static const double rate128[] = {0.74, 0.80, 0.84}, rate64[] = {0.5, 0.65, 0.7, 0.74, 0.74, 0.74};
+  const bool small = tiles_time(tiles(64), cus, 6, 1.0, rate64) < tiles_time(tiles(128), cus, 3, 4.0, rate128);
+  return small ? launch_tiles<1, EPI, A_KC, B_KC, K_KEPT>(a, E, R, N, K, st)
+               : launch_tiles<2, EPI, A_KC, B_KC, K_KEPT>(a, E, R, N, K, st);
 }
 
 }  // namespace
 
-// true when the fp32 MFMA kernel takes these strides and sizes
-bool gemm_f32_mfma_ok(long long a_r, long long a_k, long long b_k, long long b_n, int E, int R, int N,
-                      int K) {
-  if (E < 1 || R < 1 || N < 1 || K < 1) return false;
-  if ((long long)E * ((R + kT - 1) / kT) * ((N + kT - 1) / kT) > 0x7fffffffLL) return false;
-  const bool a_unit_k = a_k == 1, b_unit_k = b_k == 1;
-  if (!a_unit_k && a_r != 1) return false;
-  if (!b_unit_k && b_n != 1) return false;
-  // 16-byte loads: the dimension along the unit stride and the other stride are multiples of 4
-  if (a_unit_k ? (K % 4 != 0 || a_r % 4 != 0) : (R % 4 != 0 || a_k % 4 != 0)) return false;
-  if (b_unit_k ? (K % 4 != 0 || b_n % 4 != 0) : (N % 4 != 0 || b_k % 4 != 0)) return false;
-  return true;
-}
-
-int launch_gemm_f32_mfma(int epi, const float* A, long long a_e, long long a_r, long long a_k,
-                         const float* B, long long b_e, long long b_k, long long b_n, float* Cout,
-                         const float* mask, int E, int R, int N, int K, hipStream_t st) {
-  if (!gemm_f32_mfma_ok(a_r, a_k, b_k, b_n, E, R, N, K) || a_e % 4 != 0 || b_e % 4 != 0)
+int launch_gemm_f32(GemmKind kind, const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
+  // unit strides along K (kForward: A; kDataGrad: A and B), N and R in whole 16-byte pieces
+  if (E < 1 || R < 1 || N < 1 || K < 1 || N % 4 != 0 || (kind == kWeightGrad ? R : K) % 4 != 0)
     return MOE_EUNSUPPORTED;
-  const bool ak = a_k == 1, bk = b_k == 1;
-  if (ak && bk) return launch_layout<true, true>(epi, A, a_e, a_r, a_k, B, b_e, b_k, b_n, Cout, mask, E, R, N, K, st);
-  if (ak) return launch_layout<true, false>(epi, A, a_e, a_r, a_k, B, b_e, b_k, b_n, Cout, mask, E, R, N, K, st);
-  if (bk) return launch_layout<false, true>(epi, A, a_e, a_r, a_k, B, b_e, b_k, b_n, Cout, mask, E, R, N, K, st);
-  return launch_layout<false, false>(epi, A, a_e, a_r, a_k, B, b_e, b_k, b_n, Cout, mask, E, R, N, K, st);
+  switch (kind) {
+    case kForward: return launch_form<0, true, false>(a, E, R, N, K, st);
+    case kForwardRelu: return launch_form<1, true, false>(a, E, R, N, K, st);
+    case kDataGrad: return launch_form<0, true, true>(a, E, R, N, K, st);
+    case kDataGradMask: return launch_form<2, true, true>(a, E, R, N, K, st);
+    case kWeightGrad:
+      return a.kept != nullptr ? launch_form<0, false, false, true>(a, E, R, N, K, st)
+                               : launch_form<0, false, false>(a, E, R, N, K, st);
+  }
+  return MOE_EINVAL;
 }
 
 }  // namespace moe
