@@ -70,15 +70,19 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
   if (lane == 0) dweight[2 * n + k] = dot;
 }
 
-// one wavefront per token; dweight of a choice that is not kept is never read
+// LPT lanes per token (16, 32 or 64: no more than the experts need); dweight of a choice that is not
+// kept is never read.  dz: NULL, or [tokens, ez] fp32 with zeros behind the E columns; dzp: NULL, or the
+// three bf16 terms side by side in `cols` columns.
+template <int LPT>
 __global__ __launch_bounds__(256) void gate_bwd_kernel(
     const float* __restrict__ gates, const int32_t* __restrict__ expert_idx,
     const int32_t* __restrict__ slot, const float* __restrict__ dweight,
-    const int32_t* __restrict__ c1, const float* __restrict__ daux, float* __restrict__ dz,
+    const int32_t* __restrict__ c1, const float* __restrict__ daux, float* __restrict__ dz, int ez,
     bf16_t* __restrict__ dzp, int cols, int S, int E, long long tokens) {
-  const long long n = (long long)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-  if (n >= tokens) return;
-  const int lane = threadIdx.x & 63;
+  const long long n0 = (long long)blockIdx.x * (256 / LPT) + threadIdx.x / LPT;
+  const bool live = n0 < tokens;
+  const long long n = live ? n0 : tokens - 1;            // idle lanes take part in the shuffles
+  const int lane = threadIdx.x % LPT;
   const int g = (int)(n / S);
   const float* p = gates + n * E;
   const int e1 = expert_idx[2 * n], e2 = expert_idx[2 * n + 1];
@@ -90,15 +94,17 @@ __global__ __launch_bounds__(256) void gate_bwd_kernel(
   const float scale = daux[g] / ((float)E * (float)S * (float)S);
   const int32_t* cg = c1 + (long long)g * E;
   float dot = 0.f;
-  for (int e = lane; e < E; e += 64) {
+  for (int e = lane; e < E; e += LPT) {
     const float dp = scale * (float)cg[e] + (e == e1 ? t1 : 0.f) + (e == e2 ? t2 : 0.f);
     dot = fmaf(p[e], dp, dot);
   }
-  dot = wave_sum(dot);
-  for (int e = lane; e < E; e += 64) {
+#pragma unroll
+  for (int o = LPT / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, 64);
+  if (!live) return;
+  for (int e = lane; e < E; e += LPT) {
     const float dp = scale * (float)cg[e] + (e == e1 ? t1 : 0.f) + (e == e2 ? t2 : 0.f);
     const float v = p[e] * (dp - dot);
-    if (dz != nullptr) dz[n * E + e] = v;
+    if (dz != nullptr) dz[n * ez + e] = v;
     if (dzp != nullptr) {
       // v = hi + mid + lo exactly (three bf16 terms cover the 24 mantissa bits), stored side
       // by side so that a bf16 matrix product over these columns is an fp32-faithful one
@@ -110,8 +116,10 @@ __global__ __launch_bounds__(256) void gate_bwd_kernel(
       d[0] = hi; d[1] = mid; d[2] = lo;
     }
   }
+  if (dz != nullptr)
+    for (int e = E + lane; e < ez; e += LPT) dz[n * ez + e] = 0.f;
   if (dzp != nullptr)
-    for (int cidx = 3 * E + lane; cidx < cols; cidx += 64) dzp[n * cols + cidx] = 0;
+    for (int cidx = 3 * E + lane; cidx < cols; cidx += LPT) dzp[n * cols + cidx] = 0;
 }
 
 // wgp[m, 3e+p] = bf16(wg[m,e]) for the three terms p of dz, zero in the padding columns
@@ -165,49 +173,151 @@ __global__ __launch_bounds__(256) void dx_rows_kernel(
   }
 }
 
-// dwg[m,e] = sum_t x[t,m] dz[t,e]: partial sums over a range of tokens per block, then a
-// reduction over the ranges in a fixed order (no atomics: the result is reproducible).
-template <typename T>
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+static __device__ const f32x4_t bwd_zero_line = {0.f, 0.f, 0.f, 0.f};
+
+// dwg[m,e] = sum_t x[t,m] dz[t,e]: partial sums over a range of tokens per block, then a reduction
+// over the ranges in a fixed order (no atomics: the result is reproducible).
+//
+// Block = 128 features x 32 ET experts x one range; wavefront = 32 features; v_mfma_f32_32x32x2_f32 with
+// k = tokens (x widened to fp32, so products are exact and the sums fp32).  Both operands are row-of-k:
+// stages of 32 tokens of x and dz travel global -> LDS directly, rows past the range or M read a zero
+// line.  (64 banks: chunk c of an odd row sits at c ^ 4 for 256-byte rows of bf16 x, c ^ 8 for longer
+// ones, so the two tokens of a step fall into different banks.)
+// Bound: one read of x.  32 768 tokens, M 1024, E 32: 56 us as a padded bf16 GEMM (three terms of dz in
+// 256 columns, 67 MB of partial sums) and its reduction -> 33 us; 3999 tokens, M 520, E 12: 59 us on
+// FMA -> 11 us.
+template <typename T, int ET>
 __global__ __launch_bounds__(256) void dwg_partial_kernel(
-    const T* __restrict__ x, const float* __restrict__ dz, float* __restrict__ partial,
-    int M, int E, long long tokens, long long tokens_per_split) {
-  __shared__ float xs[16][64];
-  __shared__ float zs[16][64];
-  const int m0 = blockIdx.x * 64, e0 = blockIdx.y * 64;
-  const long long t_begin = (long long)blockIdx.z * tokens_per_split;
-  const long long t_stop = t_begin + tokens_per_split < tokens ? t_begin + tokens_per_split : tokens;
-  const int tid = threadIdx.x, tm = tid & 15, te = tid >> 4;
-  const int lk = tid >> 4, lc = 4 * (tid & 15);
-  float acc[4][4] = {};
-  for (long long t0 = t_begin; t0 < t_stop; t0 += 16) {
-    const long long t = t0 + lk;
+    const T* __restrict__ x, const float* __restrict__ dz, float* __restrict__ partial, int M, int ez,
+    long long tokens, int tokens_per_split) {
+  constexpr int TK = 32, ST = 3;
+  constexpr int XP = 128 * sizeof(T), ZP = 128 * ET;             // row pitches in bytes
+  constexpr int kX = TK * XP, kStage = kX + TK * ZP;
+  constexpr int XC = XP / 16, ZC = ZP / 16;                      // 16-byte chunks per row
+  constexpr int XQ = kX / 4096, ZQ = ET;                         // copies per wavefront and stage
+  constexpr int XSW = sizeof(T) == 2 ? 4 : 8, ZSW = ET > 1 ? 8 : 0;
+  extern __shared__ __attribute__((aligned(16))) unsigned char dwg_smem[];
+  typedef unsigned char __attribute__((address_space(3))) * lds_ptr;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_ptr)dwg_smem);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, hf = lane >> 5;
+  const int m0 = blockIdx.x * 128, e0 = blockIdx.y * 32 * ET;
+  const long long t0 = (long long)blockIdx.z * tokens_per_split;
+  const long long left = tokens - t0;
+  const int cnt = left < 0 ? 0 : (left < tokens_per_split ? (int)left : tokens_per_split);
+  const int KT = (cnt + TK - 1) / TK;
+  const uint64_t zline = (uint64_t)(uintptr_t)&bwd_zero_line;
+  uint64_t xa[XQ], za[ZQ];
+  int xk[XQ], zk[ZQ];
+  bool xok[XQ];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = m0 + lc + i, e = e0 + lc + i;
-      xs[lk][lc + i] = (t < t_stop && m < M) ? Elt<T>::load(x + t * M + m) : 0.f;
-      zs[lk][lc + i] = (t < t_stop && e < E) ? dz[t * E + e] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = xs[k][4 * tm + i]; b[i] = zs[k][4 * te + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+  for (int q = 0; q < XQ; ++q) {
+    xk[q] = (64 / XC) * (wave * XQ + q) + lane / XC;
+    const int col = m0 + (16 / (int)sizeof(T)) * ((lane % XC) ^ (XSW * (xk[q] & 1)));
+    xok[q] = col < M;
+    xa[q] = (uint64_t)(uintptr_t)(x + (t0 + xk[q]) * M + (xok[q] ? col : 0));
   }
-  float* dst = partial + (size_t)blockIdx.z * M * E;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int q = 0; q < ZQ; ++q) {
+    zk[q] = (64 / ZC) * (wave * ZQ + q) + lane / ZC;
+    // columns past ez (a multiple of 32): only in the last of several expert tiles
+    const int col = e0 + 4 * ((lane % ZC) ^ (ZSW * (zk[q] & 1)));
+    za[q] = col < ez ? (uint64_t)(uintptr_t)(dz + (t0 + zk[q]) * ez + col) : 0;
+  }
+#define MOE_DWG_COPY(LDS_U32, ADDR_U64)                                                      \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"            \
+               :: "s"(LDS_U32), "v"(ADDR_U64) : "memory")
+  auto start_step = [&](int p, int stage) {
+    const uint32_t lx = lds0 + stage * kStage + wave * (XQ * 1024);
+    const uint32_t lz = lds0 + stage * kStage + kX + wave * (ZQ * 1024);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + 4 * tm + i, e = e0 + 4 * te + j;
-      if (m < M && e < E) dst[(size_t)m * E + e] = acc[i][j];
+    for (int q = 0; q < XQ; ++q) {
+      const uint64_t s = xok[q] && p * TK + xk[q] < cnt ? xa[q] + (uint64_t)p * TK * M * sizeof(T) : zline;
+      MOE_DWG_COPY(lx + q * 1024, s);
     }
+#pragma unroll
+    for (int q = 0; q < ZQ; ++q) {
+      const uint64_t s = za[q] != 0 && p * TK + zk[q] < cnt ? za[q] + (uint64_t)p * TK * ez * 4 : zline;
+      MOE_DWG_COPY(lz + q * 1024, s);
+    }
+  };
+  f32x16_t acc[ET];
+#pragma unroll
+  for (int j = 0; j < ET; ++j)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+  typedef const T __attribute__((address_space(3))) * lds_t_ptr;
+  typedef const float __attribute__((address_space(3))) * lds_f_ptr;
+  const int m = 32 * wave + l32;                                 // feature inside the tile
+  constexpr int XE = 16 / sizeof(T);
+  const uint32_t x_rd = hf * XP + (((m / XE) ^ (XSW * hf)) * 16) + (m % XE) * sizeof(T);
+  uint32_t z_rd[ET];
+#pragma unroll
+  for (int j = 0; j < ET; ++j) z_rd[j] = kX + hf * ZP + (((8 * j + l32 / 4) ^ (ZSW * hf)) * 16) + (l32 % 4) * 4;
+  int p = 0, pstage = 0, stage = 0;
+  for (; p < ST - 1 && p < KT; ++p) start_step(p, pstage++);
+  for (int s = 0; s < KT; ++s) {
+    if (s + 1 < KT) {
+      if (XQ + ZQ == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+      else if (XQ + ZQ == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+      else if (XQ + ZQ == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+      else if (XQ + ZQ == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    __syncthreads();
+    if (p < KT) {
+      start_step(p, pstage);
+      pstage = pstage + 1 == ST ? 0 : pstage + 1;
+      ++p;
+    }
+    const uint32_t sb = lds0 + stage * kStage;
+    stage = stage + 1 == ST ? 0 : stage + 1;
+#pragma unroll
+    for (int k = 0; k < TK / 2; ++k) {                           // tokens 2 k + hf
+      float a;
+      const T xv = *(lds_t_ptr)(uintptr_t)(sb + x_rd + k * 2 * XP);
+      if constexpr (sizeof(T) == 2) a = bf16_to_f32(xv);
+      else a = xv;
+#pragma unroll
+      for (int j = 0; j < ET; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, *(lds_f_ptr)(uintptr_t)(sb + z_rd[j] + k * 2 * ZP), acc[j], 0, 0, 0);
+    }
+  }
+#undef MOE_DWG_COPY
+  // acc[j][v]: feature 8 (v/4) + 4 hf + v%4 of the wavefront, expert 32 j + lane%32
+  float* dst = partial + (size_t)blockIdx.z * M * ez;
+#pragma unroll
+  for (int j = 0; j < ET; ++j)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int row = m0 + 32 * wave + 8 * (v >> 2) + 4 * hf + (v & 3), e = e0 + 32 * j + l32;
+      if (row < M && e < ez) dst[(size_t)row * ez + e] = acc[j][v];
+    }
+}
+
+// dwg[m,e] = sum over the token ranges: four threads per element add every fourth range, then their
+// four sums (a fixed order)
+__global__ __launch_bounds__(256) void dwg_sum_kernel(const float* __restrict__ partial,
+                                                      float* __restrict__ dwg, int M, int E, int ez,
+                                                      int splits) {
+  __shared__ float red[4][64];
+  const int c = threadIdx.x & 63, k = threadIdx.x >> 6;
+  const long long i = (long long)blockIdx.x * 64 + c;            // element of [M, ez]
+  const long long size = (long long)M * ez;
+  float acc = 0.f;
+  if (i < size) {
+#pragma unroll 8
+    for (int s = k; s < splits; s += 4) acc += partial[s * size + i];
+  }
+  red[k][c] = acc;
+  __syncthreads();
+  const int m = (int)(i / ez), e = (int)(i % ez);
+  if (k == 0 && i < size && e < E)
+    dwg[(size_t)m * E + e] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
 }
 
 // dwg[m,e] = sum over token ranges (in order) of the `terms` adjacent columns of e
@@ -227,67 +337,128 @@ __global__ __launch_bounds__(256) void dwg_reduce_kernel(
   dwg[i] = acc;
 }
 
-// dx tile of 64 tokens x 64 features: the gate projection dz . wg^T in fp32, then the
-// gradient rows of the token's kept choices are added (first, then second choice) and the
-// sum is rounded once.
+// dx tile of 64 tokens x 128 features: the gate projection dz . wg^T in fp32 on the matrix cores, then
+// the gradient rows of the token's kept choices are added (first, then second choice) and the sum is
+// rounded once.  Wavefront = 32 tokens x 64 features; 32 experts of both operands at a time in LDS; the
+// product (wg rows first, so a lane owns four consecutive features of a token) turns through LDS so that
+// the rows of dbuf and dx move in 16-byte pieces.
+// Bound: the two dbuf rows read and the dx row written per token.  32 768 tokens, M 1024, E 32: 102 us as
+// a bf16 GEMM with an fp32 result in memory and a pass that adds the rows -> 64 us; 3999 tokens, M 520,
+// E 12: 21.5 us on FMA -> 9.1 us.
 template <typename T>
 __global__ __launch_bounds__(256) void dx_kernel(
     const float* __restrict__ dz, const float* __restrict__ wg, const T* __restrict__ dbuf,
     const int32_t* __restrict__ expert_idx, const int32_t* __restrict__ slot,
-    T* __restrict__ dx, int S, int G, int C, int M, int E, long long tokens,
+    T* __restrict__ dx, int S, int G, int C, int M, int E, int ez, int mtiles, long long tokens,
     const int32_t* __restrict__ row_base) {
-  __shared__ float zs[16][65];
-  __shared__ float ws[16][65];
-  const long long n0 = (long long)blockIdx.x * 64;
-  const int m0 = blockIdx.y * 64;
-  const int tid = threadIdx.x, tt = tid & 15, tm = tid >> 4;
-  const int lr = tid >> 2, lc = 4 * (tid & 3);
-  float acc[4][4] = {};
-  for (int e0 = 0; e0 < E; e0 += 16) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = e0 + lc + i;
-      const long long n = n0 + lr;
-      const int m = m0 + lr;
-      zs[lc + i][lr] = (n < tokens && e < E) ? dz[n * E + e] : 0.f;
-      ws[lc + i][lr] = (m < M && e < E) ? wg[(size_t)m * E + e] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = zs[k][4 * tt + i]; b[i] = ws[k][4 * tm + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const long long n = n0 + 4 * tt + i;
-    if (n >= tokens) continue;
-    const int g = (int)(n / S);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int c = slot[2 * n + k];
-      if (c < 0) continue;
-      const size_t e = (size_t)expert_idx[2 * n + k];
-      const T* row = dbuf + (row_base != nullptr ? e * G * C + row_base[(size_t)g * E + e] + c
-                                                 : (e * G + g) * C + c) * M;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int m = m0 + 4 * tm + j;
-        if (m < M) acc[i][j] += Elt<T>::load(row + m);
+  constexpr int P = 36, OP = 68;                                 // pitches: 4 mod 32 floats
+  static_assert((128 + 64) * P <= 4 * 32 * OP, "the operands fit the space of the results");
+  __shared__ __attribute__((aligned(16))) float ops[4 * 32 * OP];      // wg rows, dz rows; then the results
+  __shared__ int rows_s[64][2];                                  // dbuf rows of the tokens' kept choices
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l32 = lane & 31, hf = lane >> 5;
+  const long long n0 = (long long)(blockIdx.x / mtiles) * 64;
+  const int m0 = (int)(blockIdx.x % mtiles) * 128;
+  const int wt = (wave >> 1) * 32, wm = (wave & 1) * 64;         // the wavefront's tokens, features
+  if (tid < 128) {
+    const long long n = n0 + (tid >> 1);
+    const int k = tid & 1;
+    int row = -1;
+    if (n < tokens) {
+      const int s = slot[2 * n + k];
+      if (s >= 0) {
+        // row of a kept choice: (e G + g) C + slot, or e G C + row_base[g,e] + slot when packed
+        const int e = expert_idx[2 * n + k], g = (int)(n / S);
+        row = row_base != nullptr ? e * G * C + row_base[(size_t)g * E + e] + s : (e * G + g) * C + s;
       }
     }
+    rows_s[tid >> 1][k] = row;
+  }
+  // the dbuf pieces this lane adds at the end, requested first: they come from HBM behind the product
+  constexpr int K = Vec16<T>::kElts, LPR = 64 / K, RPP = 64 / LPR;   // lanes per row, rows per pass
+  const int m = m0 + wm + K * (lane % LPR);                      // M is a multiple of K
+  uint4 drow[32 / RPP][2];
+  __syncthreads();
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + 4 * tm + j;
-      if (m < M) Elt<T>::store(dx + n * M + m, acc[i][j]);
+  for (int ps = 0; ps < 32 / RPP; ++ps)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int row = rows_s[wt + RPP * ps + lane / LPR][k];
+      drow[ps][k] = uint4{0u, 0u, 0u, 0u};
+      if (row >= 0 && m < M) drow[ps][k] = *reinterpret_cast<const uint4*>(dbuf + (size_t)row * M + m);
     }
+  f32x16_t acc[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+  float* zs = ops + 128 * P;
+  const bool quads = (E & 3) == 0;                               // rows of wg are whole 16-byte pieces
+  for (int e0 = 0; e0 < E; e0 += 32) {
+    if (e0 > 0) __syncthreads();                                 // the previous experts are multiplied
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = (tid >> 3) + 32 * i, c = 4 * (tid & 7), m = m0 + r;
+      f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+      if (m < M) {
+        const float* src = wg + (size_t)m * E + e0 + c;
+        if (quads) {
+          if (e0 + c < E) v = *reinterpret_cast<const f32x4_t*>(src);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (e0 + c + q < E) v[q] = src[q];
+        }
+      }
+      *reinterpret_cast<f32x4_t*>(&ops[r * P + c]) = v;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r = (tid >> 3) + 32 * i, c = 4 * (tid & 7);
+      const long long n = n0 + r;
+      f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+      if (n < tokens) v = *reinterpret_cast<const f32x4_t*>(dz + n * ez + e0 + c);
+      *reinterpret_cast<f32x4_t*>(&zs[r * P + c]) = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kg = 0; kg < 4; ++kg) {                             // experts 8 kg + 4 hf + q
+      const f32x4_t b = *reinterpret_cast<const f32x4_t*>(&zs[(wt + l32) * P + 8 * kg + 4 * hf]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const f32x4_t a = *reinterpret_cast<const f32x4_t*>(&ops[(wm + 32 * j + l32) * P + 8 * kg + 4 * hf]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], acc[j], 0, 0, 0);
+      }
+    }
+  }
+  // acc[j][v]: token lane%32, feature 32 j + 8 (v/4) + 4 hf + v%4 of the wavefront
+  __syncthreads();
+  float* o = ops + wave * 32 * OP;
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<f32x4_t*>(&o[l32 * OP + 32 * j + 8 * q + 4 * hf]) =
+          f32x4_t{acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+  __builtin_amdgcn_wave_barrier();
+  if (m >= M) return;
+#pragma unroll
+  for (int ps = 0; ps < 32 / RPP; ++ps) {
+    const int r = RPP * ps + lane / LPR;
+    const long long n = n0 + wt + r;
+    if (n >= tokens) continue;
+    float f[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) f[i] = o[r * OP + K * (lane % LPR) + i];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      float d[K];
+      Vec16<T>::unpack(drow[ps][k], d);
+#pragma unroll
+      for (int i = 0; i < K; ++i) f[i] += d[i];
+    }
+    *reinterpret_cast<uint4*>(dx + n * M + m) = Vec16<T>::pack(f);
   }
 }
 
@@ -317,7 +488,8 @@ GateBwdPlan gate_bwd_plan(const moe_config& c) {
   GateBwdPlan p{};
   const long long tokens = (long long)c.G * c.S;
   const long long cols = ((long long)3 * c.E + 255) / 256 * 256;
-  p.mfma = c.act_dtype == MOE_BF16 && tokens % 256 == 0 && tokens <= 0x7fffffffLL &&
+  // up to 128 experts the products are small enough for full fp32 (dwg_partial_kernel, dx_kernel)
+  p.mfma = c.act_dtype == MOE_BF16 && c.E > 128 && tokens % 256 == 0 && tokens <= 0x7fffffffLL &&
            cols <= 0x7fffffffLL && gemm_bf16_f32out_ok((int)tokens, c.M, (int)cols) &&
            gemm_bf16_f32out_ok(c.M, (int)cols, 128);
   if (p.mfma) {
@@ -334,10 +506,14 @@ GateBwdPlan gate_bwd_plan(const moe_config& c) {
     p.dxg_bytes = (size_t)tokens * c.M * 4;
     p.partial_bytes = (size_t)s * c.M * cols * 4;
   } else {
-    const long long s = (tokens + 511) / 512;
-    p.splits = (int)(s < 1 ? 1 : (s > 128 ? 128 : s));
-    p.dz_bytes = (size_t)tokens * c.E * 4;
-    p.partial_bytes = (size_t)p.splits * c.M * c.E * 4;
+    // token ranges of at least 128 tokens, about two blocks per compute unit
+    p.ez = (c.E + 31) / 32 * 32;
+    const long long tiles = (long long)((c.M + 127) / 128) * ((p.ez + 127) / 128);
+    long long s = (512 + tiles - 1) / tiles;
+    if (s > (tokens + 127) / 128) s = (tokens + 127) / 128;
+    p.splits = (int)s;
+    p.dz_bytes = (size_t)tokens * p.ez * 4;
+    p.partial_bytes = (size_t)p.splits * c.M * p.ez * 4;
   }
   return p;
 }
@@ -348,10 +524,14 @@ int launch_gate_bwd(const moe_config& c, const void* x, const float* wg, const f
                     hipStream_t st) {
   const GateBwdPlan p = gate_bwd_plan(c);
   const long long tokens = (long long)c.G * c.S;
-  const unsigned grid = (unsigned)((tokens + kRowsPerBlock - 1) / kRowsPerBlock);
-  hipLaunchKernelGGL(gate_bwd_kernel, dim3(grid), dim3(256), 0, st, gates, expert_idx, slot,
-                     dweight, c1, daux, p.mfma ? nullptr : w.dz, p.mfma ? w.dzp : nullptr, p.cols,
-                     c.S, c.E, tokens);
+#define MOE_GATE_BWD(LPT)                                                                              \
+  hipLaunchKernelGGL(gate_bwd_kernel<LPT>, dim3((unsigned)((tokens + 256 / LPT - 1) / (256 / LPT))),   \
+                     dim3(256), 0, st, gates, expert_idx, slot, dweight, c1, daux,                     \
+                     p.mfma ? nullptr : w.dz, p.ez, p.mfma ? w.dzp : nullptr, p.cols, c.S, c.E, tokens)
+  if (c.E <= 16) MOE_GATE_BWD(16);
+  else if (c.E <= 32) MOE_GATE_BWD(32);
+  else MOE_GATE_BWD(64);
+#undef MOE_GATE_BWD
   if (check_launch() != MOE_OK) return MOE_EHIP;
   const long long size = (long long)c.M * c.E;
   if (p.mfma) {
@@ -364,18 +544,28 @@ int launch_gate_bwd(const moe_config& c, const void* x, const float* wg, const f
                        w.partial, dwg, c.M, c.E, p.cols, 3, p.splits);
     return check_launch();
   }
-  long long tps = (tokens + p.splits - 1) / p.splits;
-  tps = (tps + 15) / 16 * 16;
-  const dim3 pgrid((unsigned)((c.M + 63) / 64), (unsigned)((c.E + 63) / 64), (unsigned)p.splits);
-  if (c.act_dtype == MOE_F32)
-    hipLaunchKernelGGL(dwg_partial_kernel<float>, pgrid, dim3(256), 0, st,
-                       static_cast<const float*>(x), w.dz, w.partial, c.M, c.E, tokens, tps);
-  else
-    hipLaunchKernelGGL(dwg_partial_kernel<bf16_t>, pgrid, dim3(256), 0, st,
-                       static_cast<const bf16_t*>(x), w.dz, w.partial, c.M, c.E, tokens, tps);
+  const long long tps = ((tokens + p.splits - 1) / p.splits + 31) / 32 * 32;
+  const int et = p.ez <= 32 ? 1 : p.ez <= 64 ? 2 : 4;
+  const dim3 pgrid((unsigned)((c.M + 127) / 128), (unsigned)((p.ez + 32 * et - 1) / (32 * et)), (unsigned)p.splits);
+#define MOE_DWG(T, ET)                                                                                 \
+  {                                                                                                    \
+    static LdsLimitOnce once;                                                                          \
+    constexpr int lds = 3 * 32 * 128 * ((int)sizeof(T) + ET);                                          \
+    if (ensure_lds_limit(once, reinterpret_cast<const void*>(dwg_partial_kernel<T, ET>), lds) != MOE_OK) \
+      return MOE_EHIP;                                                                                 \
+    hipLaunchKernelGGL((dwg_partial_kernel<T, ET>), pgrid, dim3(256), lds, st, static_cast<const T*>(x), \
+                       w.dz, w.partial, c.M, p.ez, tokens, (int)tps);                                  \
+  }
+  if (c.act_dtype == MOE_F32) {
+    if (et == 1) MOE_DWG(float, 1) else if (et == 2) MOE_DWG(float, 2) else MOE_DWG(float, 4)
+  } else {
+    if (et == 1) MOE_DWG(bf16_t, 1) else if (et == 2) MOE_DWG(bf16_t, 2) else MOE_DWG(bf16_t, 4)
+  }
+#undef MOE_DWG
   if (check_launch() != MOE_OK) return MOE_EHIP;
-  hipLaunchKernelGGL(dwg_reduce_kernel, dim3((unsigned)((size + 255) / 256)), dim3(256), 0, st,
-                     w.partial, dwg, c.M, c.E, c.E, 1, p.splits);
+  const long long padded = (long long)c.M * p.ez;
+  hipLaunchKernelGGL(dwg_sum_kernel, dim3((unsigned)((padded + 63) / 64)), dim3(256), 0, st, w.partial, dwg,
+                     c.M, c.E, p.ez, p.splits);
   return check_launch();
 }
 
@@ -400,16 +590,15 @@ int launch_dx(const moe_config& c, const float* wg, const void* dbuf, const int3
                        row_base);
     return check_launch();
   }
-  const dim3 grid((unsigned)((tokens + 63) / 64), (unsigned)((c.M + 63) / 64));
-  if (grid.y > 65535) return MOE_EUNSUPPORTED;
-  if (c.act_dtype == MOE_F32)
-    hipLaunchKernelGGL(dx_kernel<float>, grid, dim3(256), 0, st, w.dz, wg,
-                       static_cast<const float*>(dbuf), expert_idx, slot, static_cast<float*>(dx),
-                       c.S, c.G, c.C, c.M, c.E, tokens, row_base);
-  else
-    hipLaunchKernelGGL(dx_kernel<bf16_t>, grid, dim3(256), 0, st, w.dz, wg,
-                       static_cast<const bf16_t*>(dbuf), expert_idx, slot,
-                       static_cast<bf16_t*>(dx), c.S, c.G, c.C, c.M, c.E, tokens, row_base);
+  const int mtiles = (c.M + 127) / 128;
+  const long long blocks = (tokens + 63) / 64 * mtiles;
+  if (blocks > 0x7fffffffLL) return MOE_EUNSUPPORTED;
+#define MOE_DX(T)                                                                                      \
+  hipLaunchKernelGGL(dx_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, st, w.dz, wg,                 \
+                     static_cast<const T*>(dbuf), expert_idx, slot, static_cast<T*>(dx), c.S, c.G, c.C, \
+                     c.M, c.E, p.ez, mtiles, tokens, row_base)
+  if (c.act_dtype == MOE_F32) MOE_DX(float); else MOE_DX(bf16_t);
+#undef MOE_DX
   return check_launch();
 }
 

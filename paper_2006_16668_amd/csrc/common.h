@@ -175,21 +175,22 @@ size_t expert_signbits_bytes(const moe_config& c);
 int launch_combine_bwd(const moe_config& c, const void* dy, const void* out,
                        const int32_t* src_token, const int32_t* expert_idx, const float* weight,
                        void* dout, float* dweight, const int32_t* kept, hipStream_t st);
-// Gate gradients: on bf16 layers whose token count and M are multiples of 256 the two
-// projections (dwg = x^T dz, dz . wg^T) run on the matrix cores; otherwise fp32 FMA kernels.
+// Gate gradients: the two projections (dwg = x^T dz, dz . wg^T) in full fp32, or, for bf16 layers of more
+// than 128 experts whose token count and M are multiples of 256, as bf16 GEMMs over three terms of dz.
 struct GateBwdPlan {
-  bool mfma;
+  bool mfma;    // the bf16 GEMMs
   int cols;     // mfma: columns of the 3-term bf16 copy of dz, 3E rounded up to 256
+  int ez;       // else: columns of dz, E rounded up to 32
   int splits;   // token ranges of the dwg partial sums
   size_t dz_bytes, dzp_bytes, wgp_bytes, dxg_bytes, partial_bytes;
 };
 GateBwdPlan gate_bwd_plan(const moe_config& c);
 struct GateBwdWs {
-  float* dz;        // [N,E] fp32 (FMA path)
+  float* dz;        // [N,ez] fp32
   bf16_t* dzp;      // [N,cols] bf16 terms of dz (MFMA path)
   bf16_t* wgp;      // [M,cols] bf16 wg repeated per term (MFMA path)
   float* dxg;       // [N,M] fp32 gate part of dx (MFMA path)
-  float* partial;   // [splits,M,E or cols] fp32
+  float* partial;   // [splits,M,ez or cols] fp32
 };
 int launch_gate_bwd(const moe_config& c, const void* x, const float* wg, const float* gates,
                     const int32_t* expert_idx, const int32_t* slot, const float* dweight,
