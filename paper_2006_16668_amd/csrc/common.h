@@ -38,6 +38,15 @@ __device__ __forceinline__ uint32_t relu_bf16x2(uint32_t v) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2_t, v), zero));
 }
 
+// Wait until at most `younger` of the steps whose register-bypassing copies this wavefront has started
+// (PER copies each, issued in order) are still on their way, or at most MAX of them.
+template <int PER, int MAX>
+__device__ __forceinline__ void wait_copies(int younger) {
+  static_assert(PER * MAX < 64, "vmcnt has six bits");
+  if (MAX == 0 || younger >= MAX) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * MAX) : "memory");
+  else if constexpr (MAX > 0) wait_copies<PER, MAX - 1>(younger);
+}
+
 template <typename T> struct Elt;
 template <> struct Elt<float> {
   static __device__ __forceinline__ float load(const float* p) { return *p; }
@@ -282,11 +291,11 @@ inline int ensure_lds_limit(LdsLimitOnce& once, const void* kernel, int bytes) {
 int compute_units(int* cus);      // of the current device (cached per device)
 
 // Time the fullest compute unit needs for n equal tiles when `res` of them share a unit at a time:
-// rate[i] is what the unit delivers with i + 1 tiles on it (1 = one tile of `size` per time `size`).
-inline double tiles_time(long long n, int cus, int res, double size, const double* rate) {
+// t[i] is what i + 1 tiles sharing it take.
+inline double tiles_time(long long n, int cus, int res, const double* t) {
   const long long full = n / ((long long)res * cus), rem = n - full * res * cus;
   const int left = (int)((rem + cus - 1) / cus);
-  return full * res * size / rate[res - 1] + (left > 0 ? left * size / rate[left - 1] : 0.0);
+  return full * t[res - 1] + (left > 0 ? t[left - 1] : 0.0);
 }
 int prepare_expert_gemm();        // expert_gemm.hip
 int prepare_gate();               // gate.hip

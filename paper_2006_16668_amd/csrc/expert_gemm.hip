@@ -12,9 +12,9 @@
 //     tiles as one stream of K steps; operands travel global -> LDS without passing
 //     the registers; either operand in either layout; gathered rows, packed rows,
 //     scattered result rows and a per-expert k range as template options.
-//   expert_gemm_bf16_edge_kernel  every other shape: one block per 128 x 256 or 128 x 128
-//     tile, two or three blocks per CU, the same register-bypassing copies with per-lane
-//     source addresses (pieces past an edge come from a zero line).
+//   expert_gemm_bf16_edge_kernel  every other shape, and outputs of few tiles: one block per
+//     tile of 128 x 256 down to 64 x 64, two to four blocks per CU, the same register-bypassing
+//     copies with per-lane source addresses (pieces past an edge come from a zero line).
 //
 // In both, activation tiles (K contiguous) sit in LDS as [m][k] and are read with
 // 16-byte loads; weight tiles are [k][n] in memory (N contiguous), stay that way in
@@ -542,12 +542,12 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
 // Tiles of any shape: C [E,R,N] with R, N, K arbitrary (contiguous dimensions multiples of 8
 // elements), either operand in either layout (the products of the table above).
 //
-// One block of four wavefronts (2 x 2) per 128 x BN tile, wavefront tile 64 x BN/2, 32-wide K
-// steps in ST = 3 LDS stages.  The copies are those of the persistent kernel (1 KB per wavefront
+// One block of four wavefronts (2 x 2) per BM x BN tile, wavefront tile BM/2 x BN/2, 32-wide K
+// steps in ST LDS stages (three for BM = 128, four or five of the smaller ones).  The copies are those of the persistent kernel (1 KB per wavefront
 // instruction, the same source permutation against bank conflicts), but every lane carries its own
 // 64-bit source address: a row, column or k past an edge, an unoccupied packed row, reads a zero
 // line instead, so the inner loop knows no edges and nothing outside an operand is touched.
-// Two (BN = 256) or three (BN = 128) blocks share a compute unit: while one waits for its step or
+// Two (BN = 256) to four (64 x 64) blocks share a compute unit: while one waits for its step or
 // stores its tile the others multiply, and the dispatcher evens out tiles of different length,
 // which a persistent block cannot.
 //
@@ -565,34 +565,43 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
 // tiles) and the power they draw; 0.95 PFLOP/s on shapes of whole tiles where the persistent kernel
 // reaches 1.07.  Layer of 5 x 700 tokens, M 768, H 3072, 24 experts of 295 positions: 299 us with the
 // kernel it replaced (256 x 256 tiles through registers, one block per unit, every position
-// multiplied), 146 us with this one, 145 us over the occupied rows only.
+// multiplied), 146 us with this one, 145 us over the occupied rows only.  Few tiles: what a unit fetches,
+// about 50 bytes per ns (neither more stages nor fragment reads moved under the MFMAs changed the time),
+// hence the smaller tiles; sides measured at gemm_form.
 // ----------------------------------------------------------------------------
 static __device__ const u32x4_t edge_zero_line = {0u, 0u, 0u, 0u};
 
-template <int BN>
+template <int BM, int BN, int ST>
 struct EdgeSmem {
-  static constexpr int kStages = 3;
-  static constexpr int kAStage = 128 * 32 * 2, kBStage = BN * 32 * 2;
+  static constexpr int kAStage = BM * 32 * 2, kBStage = BN * 32 * 2;
   static constexpr int kStage = kAStage + kBStage;
-  static constexpr size_t kBytes = (size_t)kStages * kStage;
+  static constexpr size_t kBytes = (size_t)ST * kStage;
 };
 
-template <int BN, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
-__global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void expert_gemm_bf16_edge_kernel(
+// Position of the 16-byte chunks of row k of a row-of-k stage: chunk c sits at c ^ edge_swizzle(k).  The
+// transposing read of a half-wavefront takes 64 bytes of four consecutive rows; rows of 64 columns are half
+// the banks long, so two of them share a line of banks.
+template <int COLS>
+__device__ __forceinline__ constexpr int edge_swizzle(int k) {
+  return COLS == 64 ? 4 * ((k >> 1) & 1) : 4 * (k & 3);
+}
+
+template <int BM, int BN, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
+__global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert_gemm_bf16_edge_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ Cout,
     const bf16_t* __restrict__ mask, int R, int N, int K, int tiles_m, int tiles_n, int nblk,
     const int32_t* __restrict__ gather, const int32_t* __restrict__ kept,
     int row_pad, const int32_t* __restrict__ scatter) {
-  using SM = EdgeSmem<BN>;
-  constexpr int BM = 128, BK = 32, ST = SM::kStages, TM = 2, TN = BN / 64;
+  using SM = EdgeSmem<BM, BN, ST>;
+  constexpr int BK = 32, TM = BM / 64, TN = BN / 64;
   constexpr int WN = BN / 2;                                   // columns of a wavefront tile
-  constexpr int AC = 2, BC = BN / 64;                          // copies per wavefront and step
+  constexpr int AC = BM / 64, BC = BN / 64;                    // copies per wavefront and step
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   typedef unsigned char __attribute__((address_space(3))) * lds_ptr;
   const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_ptr)smem_raw);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * WN;
+  const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * WN;
 
   // Neighbouring tiles on one XCD; inside an expert bands of 8 row tiles, row tile fastest, so
   // that the tiles an XCD works on at a time share row and column panels in its L2.
@@ -620,13 +629,14 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void expert_gemm_bf16_edge_
   const uint64_t zline = (uint64_t)(uintptr_t)&edge_zero_line;
   uint64_t a_addr[AC], b_addr[BC];
   uint32_t a_inc[AC], b_inc[BC];
+  constexpr int ACH = BM / 8, ARPC = 64 / ACH, BCH = BN / 8, BRPC = 64 / BCH;   // row-of-k operands
 #pragma unroll
   for (int q = 0; q < AC; ++q) {
     const int c = wave * AC + q;
     bool ok;
     const bf16_t* src;
-    if (A_MNC) {                                               // 4 k rows of 16 chunks per copy
-      const int kr = 4 * c + (lane >> 4), col = m0 + 8 * ((lane & 15) ^ (4 * (kr & 3)));
+    if (A_MNC) {                                               // 512 / BM k rows of BM / 8 chunks per copy
+      const int kr = ARPC * c + lane / ACH, col = m0 + 8 * ((lane % ACH) ^ edge_swizzle<BM>(kr));
       ok = col < R && kr < KE;
       src = A + ((size_t)e * K + kr) * R + col;
     } else {                                                   // 16 rows of 4 chunks per copy
@@ -652,9 +662,8 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void expert_gemm_bf16_edge_
       const int row = 16 * c + (lane >> 2), ch = (lane & 3) ^ ((row >> 2) & 3);
       ok = n0 + row < N && 8 * ch < KE;
       src = B + ((size_t)e * N + n0 + row) * K + 8 * ch;
-    } else {                                                   // 1024 / (2 BN) k rows of BN / 8 chunks
-      constexpr int CH = BN / 8, RPC = 64 / CH;
-      const int kr = RPC * c + lane / CH, col = n0 + 8 * ((lane % CH) ^ (4 * (kr & 3)));
+    } else {
+      const int kr = BRPC * c + lane / BCH, col = n0 + 8 * ((lane % BCH) ^ edge_swizzle<BN>(kr));
       ok = col < N && kr < KE;
       src = B + ((size_t)e * K + kr) * N + col;
     }
@@ -677,15 +686,14 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void expert_gemm_bf16_edge_
 #pragma unroll
         for (int q = 0; q < AC; ++q) {
           const int c = wave * AC + q;
-          const int k = A_MNC ? 4 * c + (lane >> 4)
+          const int k = A_MNC ? ARPC * c + lane / ACH
                               : 8 * ((lane & 3) ^ (((16 * c + (lane >> 2)) >> 2) & 3));
           if (k >= kl) a_addr[q] = zline;
         }
 #pragma unroll
         for (int q = 0; q < BC; ++q) {
           const int c = wave * BC + q;
-          constexpr int CH = BN / 8, RPC = 64 / CH;
-          const int k = B_KC ? 8 * ((lane & 3) ^ (((16 * c + (lane >> 2)) >> 2) & 3)) : RPC * c + lane / CH;
+          const int k = B_KC ? 8 * ((lane & 3) ^ (((16 * c + (lane >> 2)) >> 2) & 3)) : BRPC * c + lane / BCH;
           if (k >= kl) b_addr[q] = zline;
         }
       }
@@ -702,20 +710,19 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void expert_gemm_bf16_edge_
   const int ar = lane & 31;
   const int p16 = lane & 15, bb = lane >> 4;
   const int bk = 8 * (bb >> 1) + (p16 >> 2);
-  const int bsw = 4 * (bk & 3);
   const int kcc0 = (lane >> 5) ^ ((ar >> 2) & 3), kcc1 = (2 + (lane >> 5)) ^ ((ar >> 2) & 3);
   uint32_t a_rd[2], b_rd[TN > 2 ? TN : 2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int ca = (wm0 >> 3) + 4 * j + 2 * (bb & 1) + ((p16 & 3) >> 1);
-    a_rd[j] = A_MNC ? (uint32_t)(bk * (BM * 2) + ((ca ^ bsw) * 16) + (p16 & 1) * 8)
+    a_rd[j] = A_MNC ? (uint32_t)(bk * (BM * 2) + ((ca ^ edge_swizzle<BM>(bk)) * 16) + (p16 & 1) * 8)
                     : (uint32_t)((wm0 + ar) * 64 + (j ? kcc1 : kcc0) * 16);
   }
 #pragma unroll
   for (int j = 0; j < (B_KC ? 2 : TN); ++j) {
     const int cb = (wn0 >> 3) + 4 * j + 2 * (bb & 1) + ((p16 & 3) >> 1);
     b_rd[j] = B_KC ? (uint32_t)(SM::kAStage + (wn0 + ar) * 64 + (j ? kcc1 : kcc0) * 16)
-                   : (uint32_t)(SM::kAStage + bk * (BN * 2) + ((cb ^ bsw) * 16) + (p16 & 1) * 8);
+                   : (uint32_t)(SM::kAStage + bk * (BN * 2) + ((cb ^ edge_swizzle<BN>(bk)) * 16) + (p16 & 1) * 8);
   }
   typedef s16x4_t __attribute__((address_space(3))) * lds_s16x4_ptr;
   typedef bf16x8_t __attribute__((address_space(3))) * lds_bf16x8_ptr;
@@ -738,20 +745,16 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void expert_gemm_bf16_edge_
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   int p = 0, pstage = 0;
+#pragma unroll 1
   for (; p < ST - 1 && p < KT; ++p) {
     start_step(p, pstage);
     ++pstage;
   }
   int stage = 0;
   for (int g = 0; g < KT; ++g) {
-    // own copies of step g landed (step g + 1 may still fly), then everybody's; the stage of step
-    // g - 1 is free after the barrier
-    if (g + 1 < KT) {
-      if (BC == 4) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    } else {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
+    // own copies of step g landed (the steps started after it may still fly), then everybody's; the
+    // stage of step g - 1 is free after the barrier
+    wait_copies<AC + BC, ST - 2>(KT - 1 - g);
     __syncthreads();
     if (p < KT) {
       start_step(p, pstage);
@@ -868,27 +871,34 @@ inline bool dma_shape_ok(int R, int N, int K) {
   return R % 256 == 0 && N % 256 == 0 && K % 32 == 0 && 256 * big * 2 < (1LL << 31);
 }
 
-// Which kernel multiplies C [E,R,N]: the persistent one on 256 x 256 tiles (shapes it takes), the
-// edge kernel on 128 x 256 or on 128 x 128 tiles.  All have the same k order, so the choice changes no
-// bit; it compares the time the fullest compute unit needs, counted in 128 x 128 tiles at the
-// persistent kernel's rate: that kernel's tile = 4 of them, one at a time; of 128 x 256 tiles two
-// share a unit at 0.9 of that rate, a lone one reaches 0.6; of 128 x 128 tiles three share it at 0.7,
-// two at 0.5, a lone one 0.4.  (h = relu(buf wi), out = h wo of E experts of R rows, in us,
-// persistent / 128 x 256 / 128 x 128, one form for both products:
-//   E 32 R 2048 M 1024 H 8192   2065 / 2304 / 2693      E 128 R 1024 M 1024 H 4096  2141 / 2345 / 2764
-//   E 24 R 512  M 768  H 3072    172 /  174 /  191      E 64  R 256  M 1024 H 2048   166 /  182 /  223
-//   E 32 R 256  M 1024 H 8192    373 /  348 /  432      E 16  R 512  M 512  H 2048  69.6 / 58.8 / 48.1)
-enum GemmForm { kPersistent, kEdge256, kEdge128 };
+// Which kernel multiplies C [E,R,N]: the persistent one on 256 x 256 tiles (shapes it takes), or the
+// edge kernel on tiles of 128 x 256, 128 x 128, 64 x 128 or 64 x 64.  All have the same k order, so the
+// choice changes no bit; it compares the time the fullest compute unit needs.  The tables hold what one
+// 32-wide k step of n tiles sharing a unit takes, in ns.  A large tile moves fewer bytes per product, but a
+// unit fetches no more than about 50 bytes per ns however many are asked for, so an output of a few large
+// tiles leaves the fetch rate of the idle units unused: a lone tile of 128 x 128 takes 330 ns a step, four
+// of 64 x 64 on four units 170.  (us of one product, 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64:
+//   E 5  R 136  N 1016 K 2080    33.4 / 21.5 / 18.7 / 14.0     E 23 R 24   N 624  K 2528   40.2 / 30.2 / 23.7 / 17.6
+//   E 32 R 4    N 1024 K 8192     146 /  112 / 81.1 /  106     E 13 R 31   N 1024 K 8192    123 /  100 / 73.5 / 57.2
+//   E 16 R 512  N 512  K 2048    37.2 / 26.0 / 29.0 / 37.4     E 24 R 295  N 768  K 3072   57.1 / 63.8 / 67.6 / 83.8
+//   E 1  R 768  N 256  K 4158    65.2 / 43.1 / 32.9 / 23.4     E 45 R 213  N 4096 K 1024    138 /  170 /  196 /  239)
+enum GemmForm { kPersistent, kEdge128x256, kEdge128x128, kEdge64x128, kEdge64x64 };
 GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int cus) {
-  auto tiles = [&](int bm, int bn) {
-    return (long long)E * ((R + bm - 1) / bm) * ((N + bn - 1) / bn);
+  static const double persistent[] = {950}, t128x256[] = {530, 1050}, t128x128[] = {330, 600, 900},
+                      t64x128[] = {250, 370, 600}, t64x64[] = {170, 260, 400, 460};
+  auto time = [&](int bm, int bn, int res, const double* t) {
+    return tiles_time((long long)E * ((R + bm - 1) / bm) * ((N + bn - 1) / bn), cus, res, t);
   };
-  static const double rate256[] = {0.6, 0.9}, rate128[] = {0.4, 0.5, 0.7};
-  const double t256 = tiles_time(tiles(128, 256), cus, 2, 2.0, rate256);
-  const double t128 = tiles_time(tiles(128, 128), cus, 3, 1.0, rate128);
-  if (persistent_ok && 4.0 * ((tiles(256, 256) + cus - 1) / cus) <= (t256 < t128 ? t256 : t128))
-    return kPersistent;
-  return t256 <= t128 ? kEdge256 : kEdge128;
+  GemmForm form = kEdge128x256;
+  double best = time(128, 256, 2, t128x256);
+  auto consider = [&](GemmForm f, double t) {
+    if (t < best) { best = t; form = f; }
+  };
+  if (persistent_ok) consider(kPersistent, time(256, 256, 1, persistent));
+  consider(kEdge128x128, time(128, 128, 3, t128x128));
+  consider(kEdge64x128, time(64, 128, 3, t64x128));
+  consider(kEdge64x64, time(64, 64, 4, t64x64));
+  return form;
 }
 // the form of this shape on the current device; k_kept: the sum over k runs over packed rows, of
 // which the persistent kernel takes whole 256-row tiles
@@ -899,22 +909,23 @@ int choose_form(int E, int R, int N, int K, GemmForm* form, bool k_kept = false)
   return MOE_OK;
 }
 
-template <int BN, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
+template <int BM, int BN, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
 int prepare_edge() {
   static LdsLimitOnce once;
   return ensure_lds_limit(
-      once, reinterpret_cast<const void*>(expert_gemm_bf16_edge_kernel<BN, EPI, A_MNC, B_KC, K_KEPT>),
-      (int)EdgeSmem<BN>::kBytes);
+      once, reinterpret_cast<const void*>(expert_gemm_bf16_edge_kernel<BM, BN, ST, EPI, A_MNC, B_KC, K_KEPT>),
+      (int)EdgeSmem<BM, BN, ST>::kBytes);
 }
 
-template <int BN, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
+template <int BM, int BN, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
 int launch_edge(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
-  if (prepare_edge<BN, EPI, A_MNC, B_KC, K_KEPT>() != MOE_OK) return MOE_EHIP;
-  const int tiles_m = (R + 127) / 128, tiles_n = (N + BN - 1) / BN;
+  if (prepare_edge<BM, BN, ST, EPI, A_MNC, B_KC, K_KEPT>() != MOE_OK) return MOE_EHIP;
+  constexpr size_t kLds = EdgeSmem<BM, BN, ST>::kBytes;
+  const int tiles_m = (R + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const long long nblk = (long long)E * tiles_m * tiles_n;
   if (nblk > 0x7fffffffLL || (K_KEPT && a.kept == nullptr)) return MOE_EUNSUPPORTED;
-  hipLaunchKernelGGL((expert_gemm_bf16_edge_kernel<BN, EPI, A_MNC, B_KC, K_KEPT>), dim3((unsigned)nblk),
-                     dim3(256), EdgeSmem<BN>::kBytes, st, static_cast<const bf16_t*>(a.A),
+  hipLaunchKernelGGL((expert_gemm_bf16_edge_kernel<BM, BN, ST, EPI, A_MNC, B_KC, K_KEPT>), dim3((unsigned)nblk),
+                     dim3(256), kLds, st, static_cast<const bf16_t*>(a.A),
                      static_cast<const bf16_t*>(a.B), static_cast<bf16_t*>(a.C),
                      static_cast<const bf16_t*>(a.mask), R, N, K, tiles_m, tiles_n, (int)nblk, a.gather,
                      a.kept, a.row_pad, a.scatter);
@@ -925,8 +936,12 @@ int launch_edge(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
 // (K for a K-contiguous operand, R / N for a row-of-k one)
 template <int EPI, bool A_MNC, bool B_KC, bool K_KEPT = false>
 int gemm_bf16_edge(GemmForm form, const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
-  return form == kEdge128 ? launch_edge<128, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st)
-                          : launch_edge<256, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+  switch (form) {
+    case kEdge64x64: return launch_edge<64, 64, 5, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+    case kEdge64x128: return launch_edge<64, 128, 4, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+    case kEdge128x128: return launch_edge<128, 128, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+    default: return launch_edge<128, 256, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+  }
 }
 
 template <bool RELU>
@@ -971,11 +986,13 @@ int prepare_expert_gemm() {
       prepare_dma<4, 5, false, false, true, true>(), prepare_dma<4, 0, false, false, true, true>(),
       prepare_dma<4, 0, false, true, false, false, false, true>(),
       // other shapes: forward (relu / plain), data gradients (plain / masked), weight gradients
-#define MOE_EDGE_BOTH(...) prepare_edge<256, __VA_ARGS__>(), prepare_edge<128, __VA_ARGS__>()
-      MOE_EDGE_BOTH(1, false, false, false), MOE_EDGE_BOTH(0, false, false, false),
-      MOE_EDGE_BOTH(0, false, true, false), MOE_EDGE_BOTH(2, false, true, false),
-      MOE_EDGE_BOTH(0, true, false, false), MOE_EDGE_BOTH(0, true, false, true)};
-#undef MOE_EDGE_BOTH
+#define MOE_EDGE_ALL(...)                                                                      \
+  prepare_edge<128, 256, 3, __VA_ARGS__>(), prepare_edge<128, 128, 3, __VA_ARGS__>(),        \
+      prepare_edge<64, 128, 4, __VA_ARGS__>(), prepare_edge<64, 64, 5, __VA_ARGS__>()
+      MOE_EDGE_ALL(1, false, false, false), MOE_EDGE_ALL(0, false, false, false),
+      MOE_EDGE_ALL(0, false, true, false), MOE_EDGE_ALL(2, false, true, false),
+      MOE_EDGE_ALL(0, true, false, false), MOE_EDGE_ALL(0, true, false, true)};
+#undef MOE_EDGE_ALL
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
   for (int rc : rcs)

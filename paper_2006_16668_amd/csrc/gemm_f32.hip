@@ -242,8 +242,9 @@ int launch_form(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
   auto tiles = [&](int edge) { return (long long)E * ((R + edge - 1) / edge) * ((N + edge - 1) / edge); };
-  static const double rate128[] = {0.74, 0.80, 0.84}, rate64[] = {0.5, 0.65, 0.7, 0.74, 0.74, 0.74};
-  const bool small = tiles_time(tiles(64), cus, 6, 1.0, rate64) < tiles_time(tiles(128), cus, 3, 4.0, rate128);
+  static const double t128[] = {4 / 0.74, 8 / 0.80, 12 / 0.84},
+                      t64[] = {1 / 0.5, 2 / 0.65, 3 / 0.7, 4 / 0.74, 5 / 0.74, 6 / 0.74};
+  const bool small = tiles_time(tiles(64), cus, 6, t64) < tiles_time(tiles(128), cus, 3, t128);
   return small ? launch_tiles<1, EPI, A_KC, B_KC, K_KEPT>(a, E, R, N, K, st)
                : launch_tiles<2, EPI, A_KC, B_KC, K_KEPT>(a, E, R, N, K, st);
 }
