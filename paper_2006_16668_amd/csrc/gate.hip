@@ -11,6 +11,8 @@
 //                       = position in the expert buffer; capacity test; combine
 //                       weights; inverse map slot -> token; l_aux
 //
+// Calls of few chunks run the last two as one (gate_route_kernel).
+//
 // bf16 activations take the MFMA form of the first kernel (gate_mfma_*): x is
 // exactly bf16, so with wg split into three bf16 terms (hi + mid + lo = all 24
 // mantissa bits) every product is exact in fp32 and only the accumulation order
@@ -1239,6 +1241,181 @@ __global__ __launch_bounds__(64) void gate_slots_kernel(
   }
 }
 
+// gate_scan_kernel and gate_slots_kernel in one launch, for calls of few chunks and up to 128 experts:
+// one block per chunk, which sums for itself the histograms of its group and, for the packed layout, of
+// the groups before it, instead of reading a prefix that another launch has written.  hist1 / hist2 stay
+// as the chunks wrote them.  The sums are integers; the gate sums (block of a group's first chunk) are
+// added in gate_scan_kernel's order, so every result has the same bits.
+//
+// Bound: launch and L2 latency, not bytes; both sides are measured at gate_route_form.
+//
+// Thread (e, k): expert e of EP = 16, 32, 64 or 128, slice k of 512 / EP.  Slice k sums every 512/EP-th chunk
+// of the block's own group and all chunks of every 512/EP-th earlier group.
+__global__ __launch_bounds__(512) void gate_route_kernel(
+    int S, int E, int C, int G, int nch, int ep_log2,
+    const int32_t* __restrict__ hist1, const int32_t* __restrict__ hist2, const float* __restrict__ msum,
+    const int32_t* __restrict__ expert_idx, int32_t* __restrict__ slot, float* __restrict__ weight,
+    int32_t* __restrict__ src_token, int32_t* __restrict__ c1, float* __restrict__ mean_gate,
+    int32_t* __restrict__ fill, float* __restrict__ aux, uint32_t* __restrict__ zero_fill, int zero_words,
+    RowPacking pk) {
+  constexpr int NT = 512, UN = 8;
+  __shared__ int sb1[NT], st1[NT], sb2[NT], st2[NT], srb[NT];   // [slices][EP]
+  __shared__ float tm[8 * 128];                                 // [8][EP]
+  __shared__ int base1[128], base2[128], row0[128], filled[128];
+  __shared__ float aux_term[128];
+  const int g = blockIdx.x / nch, ch = blockIdx.x % nch;
+  const int tid = threadIdx.x, EP = 1 << ep_log2, NS = NT >> ep_log2;
+  const int e = tid & (EP - 1), k = tid >> ep_log2;
+  const bool packing = pk.packed_src != nullptr, live = e < E;
+  if (blockIdx.x == 0)
+    for (int i = tid; i < zero_words; i += NT) zero_fill[i] = 0u;
+
+  // the token's record, requested before the counters
+  const int s = ch * kChunk + tid;
+  const bool token = tid < kChunk && s < S;
+  const size_t n = (size_t)g * S + (token ? s : 0);
+  int e1 = -1, e2 = -1;
+  if (token) {
+    e1 = expert_idx[2 * n];
+    if (slot[2 * n + 1] != MOE_SLOT_NOT_SAMPLED) e2 = expert_idx[2 * n + 1];
+  }
+
+  int b1 = 0, t1 = 0, b2 = 0, t2 = 0, rb = 0;
+  if (live) {
+    const size_t own = (size_t)g * nch * E + e;
+    for (int c0 = k; c0 < nch; c0 += UN * NS) {                 // loads of a batch are independent
+      int a1[UN], a2[UN];
+#pragma unroll
+      for (int j = 0; j < UN; ++j) {
+        const size_t i = own + (size_t)(c0 + j * NS < nch ? c0 + j * NS : k) * E;
+        a1[j] = hist1[i];
+        a2[j] = hist2[i];
+      }
+#pragma unroll
+      for (int j = 0; j < UN; ++j) {
+        const int c = c0 + j * NS;
+        b1 += c < ch ? a1[j] : 0;
+        b2 += c < ch ? a2[j] : 0;
+        t1 += c < nch ? a1[j] : 0;
+        t2 += c < nch ? a2[j] : 0;
+      }
+    }
+    if (packing)
+      for (int gg = k; gg < g; gg += NS) {
+        const size_t at = (size_t)gg * nch * E + e;
+        long long tot = 0;
+        for (int c0 = 0; c0 < nch; c0 += 2 * UN) {              // past the end: the last chunk again, not added
+          int a[2 * UN], b[2 * UN];
+#pragma unroll
+          for (int j = 0; j < 2 * UN; ++j) {
+            const size_t i = at + (size_t)(c0 + j < nch ? c0 + j : nch - 1) * E;
+            a[j] = hist1[i];
+            b[j] = hist2[i];
+          }
+#pragma unroll
+          for (int j = 0; j < 2 * UN; ++j)
+            if (c0 + j < nch) tot += a[j] + b[j];
+        }
+        rb += tot < C ? (int)tot : C;
+      }
+  }
+  sb1[tid] = b1;
+  st1[tid] = t1;
+  sb2[tid] = b2;
+  st2[tid] = t2;
+  srb[tid] = rb;
+  if (ch == 0 && live) {
+    const int seg = (nch + 7) / 8;
+    for (int kk = k; kk < 8; kk += NS) {
+      float ms = 0.f;
+      const int end = (kk + 1) * seg < nch ? (kk + 1) * seg : nch;
+      for (int c0 = kk * seg; c0 < end; c0 += UN) {
+        float a[UN];
+#pragma unroll
+        for (int j = 0; j < UN; ++j) a[j] = c0 + j < end ? msum[((size_t)g * nch + c0 + j) * E + e] : 0.f;
+#pragma unroll
+        for (int j = 0; j < UN; ++j)
+          if (c0 + j < end) ms += a[j];
+      }
+      tm[kk * EP + e] = ms;
+    }
+  }
+  __syncthreads();
+  if (tid < E) {
+    b1 = t1 = b2 = t2 = rb = 0;
+    for (int i = tid; i < NT; i += EP) {
+      b1 += sb1[i];
+      t1 += st1[i];
+      b2 += sb2[i];
+      t2 += st2[i];
+      rb += srb[i];
+    }
+    const long long tot = (long long)t1 + t2;
+    const int f = tot < C ? (int)tot : C;
+    base1[tid] = b1;
+    base2[tid] = t1 + b2;                                       // second choices queue behind all first ones
+    row0[tid] = rb;
+    filled[tid] = f;
+    if (ch == 0) {
+      float mtot = 0.f;
+      for (int kk = 0; kk < 8; ++kk) mtot += tm[kk * EP + tid];
+      const float mean = mtot / (float)S;
+      c1[(size_t)g * E + tid] = t1;
+      mean_gate[(size_t)g * E + tid] = mean;
+      fill[(size_t)g * E + tid] = f;
+      aux_term[tid] = ((float)t1 / (float)S) * mean;
+      if (packing) {
+        pk.row_base[(size_t)g * E + tid] = rb;
+        if (g == G - 1) pk.kept[tid] = rb + f;
+      }
+    }
+  }
+  __syncthreads();
+  if (tid >= kChunk) {
+    if (ch == 0 && tid < 2 * kChunk) {                          // l_aux[g], summed as in gate_slots_kernel
+      const int lane = tid & 63;
+      float part = 0.f;
+      for (int i = lane; i < E; i += 64) part += aux_term[i];
+      part = wave_sum(part);
+      if (lane == 0) aux[g] = part / (float)E;
+    }
+    // empty positions of every nch-th expert
+    for (int i = ch; i < E; i += nch) {
+      int32_t* st = src_token + ((size_t)i * G + g) * C;
+      for (int c = filled[i] + tid - kChunk; c < C; c += NT - kChunk) st[c] = -1;
+    }
+    return;
+  }
+  // ranks as in gate_slots_kernel
+  unsigned long long peers1 = __ballot(e1 >= 0), peers2 = __ballot(e2 >= 0);
+  for (int bit = 0; (E - 1) >> bit; ++bit) {
+    const bool x1 = (e1 >> bit) & 1, x2 = (e2 >> bit) & 1;
+    const unsigned long long m1 = __ballot(x1), m2 = __ballot(x2);
+    peers1 &= x1 ? m1 : ~m1;
+    peers2 &= x2 ? m2 : ~m2;
+  }
+  if (!token) return;
+  const unsigned long long earlier = (1ull << tid) - 1;
+  const int p1 = base1[e1] + __popcll(peers1 & earlier);
+  const int s1 = p1 < C ? p1 : MOE_SLOT_OVERFLOW;
+  int s2 = MOE_SLOT_NOT_SAMPLED;
+  if (e2 >= 0) {
+    const int p2 = base2[e2] + __popcll(peers2 & earlier);
+    s2 = p2 < C ? p2 : MOE_SLOT_OVERFLOW;
+  }
+  slot[2 * n] = s1;
+  slot[2 * n + 1] = s2;
+  if (s1 < 0) weight[2 * n] = 0.f;
+  if (s2 < 0) weight[2 * n + 1] = 0.f;
+  if (s1 >= 0) src_token[((size_t)e1 * G + g) * C + s1] = s;
+  if (s2 >= 0) src_token[((size_t)e2 * G + g) * C + s2] = s;
+  if (packing) {
+    const size_t R = (size_t)G * C;
+    if (s1 >= 0) pk.packed_src[(size_t)e1 * R + row0[e1] + s1] = (int32_t)n;
+    if (s2 >= 0) pk.packed_src[(size_t)e2 * R + row0[e2] + s2] = (int32_t)n;
+  }
+}
+
 // The packed row layout from fill alone, for expert buffers in the [E,G,C,M] order of the staged
 // entry points: row p of expert e comes from (and goes back to) row (e G + g) C + c of the buffer.
 __global__ __launch_bounds__(64) void row_maps_from_fill_kernel(
@@ -1422,6 +1599,17 @@ int prepare_gate() {
                           (int)kGateRowsLds2);
 }
 
+// One launch for positions and row maps (gate_route_kernel), or the scan and the slots kernel.  Every block
+// of the first reads up to all counters of the call, so its work grows with the square of the chunks; the
+// other two pay a launch, and slots a serial loop over the earlier groups.  Whole layer of M 128, H 8 (us,
+// two launches -> one; G x tokens, E): 5 x 700, 24: 28.8 -> 26.0; 4 x 1024, 16: 28.6 -> 26.2; 16 x 1024, 2:
+// 33.7 -> 30.6; 128 x 64, 16: 49.0 -> 28.4; 1 x 16 384, 32: 39.2 -> 31.7; 1 x 32 768, 16: 62.6 -> 47.5;
+// 8 x 1024, 128: 36.0 -> 32.5; at the line 8 x 4096, 32 (512 chunks, 16 384 counters): 47.5 -> 46.7; past
+// it 4 x 4096, 128: 40.0 -> 41.0.
+static bool gate_route_form(const moe_config& c, long long chunks) {
+  return c.E <= 128 && chunks <= 512 && chunks * c.E <= 16384;
+}
+
 int launch_gate(const moe_config& c, const void* x, const float* wg, const float* u,
                 int32_t* expert_idx, int32_t* slot, float* weight, int32_t* fill,
                 int32_t* src_token, int32_t* c1, float* mean_gate, float* aux,
@@ -1512,6 +1700,12 @@ int launch_gate(const moe_config& c, const void* x, const float* wg, const float
     rc = check_launch();
   }
   if (rc != MOE_OK) return rc;
+  if (gate_route_form(c, chunks)) {
+    hipLaunchKernelGGL(gate_route_kernel, dim3((unsigned)chunks), dim3(512), 0, st, c.S, c.E, c.C, c.G, nch,
+                       c.E <= 16 ? 4 : c.E <= 32 ? 5 : c.E <= 64 ? 6 : 7, hist1, hist2, msum, expert_idx, slot, weight,
+                       src_token, c1, mean_gate, fill, aux, static_cast<uint32_t*>(zero_row), zero_words, pk);
+    return check_launch();
+  }
   hipLaunchKernelGGL(gate_scan_kernel, dim3((unsigned)(c.G * ((c.E + 31) / 32))), dim3(256), 0, st,
                      c.S, c.E, c.C, c.G, nch, hist1, hist2, msum, c1, mean_gate, fill, src_token);
   if ((rc = check_launch()) != MOE_OK) return rc;

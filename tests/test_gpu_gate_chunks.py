@@ -1,7 +1,9 @@
 """The one-chunk-per-block gate kernel at the edges of its ranges (fp32: E <= 128, bf16: E <= 64): feature
 counts around its 32 / 64-feature blocks and their split over the wavefronts, expert counts around
 the 32-expert tiles, one token to several ragged chunks, and a single chunk in all (which skips the
-scan and the slots kernel), against the oracle: integers bit for bit, floats to 1e-5."""
+scan and the slots kernel), against the oracle: integers bit for bit, floats to 1e-5.  Likewise the kernel
+that counts positions in one launch, around its 512 chunks, its 16 384 counters and its expert widths, and
+the two kernels past them."""
 import pytest
 
 import test_gpu_random_shapes as shapes
@@ -27,6 +29,21 @@ def test_gate(G, S, M, E, C, dt):
     r = gpu_gate(cfg, inp.x, inp.wg, inp.u)
     assert_routing_equal(r, want)
     assert_gate_floats_close(r, want, gates=gates)
+
+
+ROUTE = [  # G, S, M, E, C: one launch up to 512 chunks, 128 experts, 16384 counters; two past that
+    (512, 1, 16, 5, 1), (513, 1, 16, 5, 1), (128, 2, 64, 128, 1), (129, 2, 64, 128, 1), (7, 70, 64, 129, 2),
+    (3, 1100, 32, 16, 150), (2, 2200, 32, 17, 200), (1, 4200, 32, 33, 260), (9, 130, 64, 65, 3), (70, 65, 16, 2, 40)]
+
+
+@pytest.mark.parametrize("G,S,M,E,C", ROUTE)
+def test_positions(G, S, M, E, C):
+    test_gate(G, S, M, E, C, "bf16")
+
+
+@pytest.mark.parametrize("G,S,E,C", [(512, 1, 5, 1), (513, 1, 5, 1), (37, 3, 17, 1), (3, 1100, 16, 150), (18, 66, 65, 2)])
+def test_row_maps(G, S, E, C):
+    shapes.test_random_shape(MoEConfig("route", G=G, S=S, M=136, H=72, E=E, C=C, act_dtype="bf16", seed=870 + S + E))
 
 
 @pytest.mark.parametrize("S,E,C", [(1, 2, 1), (37, 5, 9), (64, 32, 4), (64, 3, 64)])
