@@ -144,7 +144,7 @@ int forward_impl(const moe_config* cfg, const void* x, const float* wg, const fl
                         packed ? &pk : nullptr, wg_packed, st);
   if (rc != MOE_OK) return rc;
   if (!mark(1)) return MOE_EHIP;
-  if (!packed) rc = moe::launch_dispatch(*cfg, x, src_token, base + w.buf, nullptr, st);
+  if (!packed) rc = moe::launch_dispatch(*cfg, x, src_token, base + w.buf, st);
   if (rc != MOE_OK) return rc;
   if (!mark(2)) return MOE_EHIP;
   if (packed) {
@@ -474,7 +474,7 @@ int moe_dispatch(const moe_config* cfg, const void* x, const int32_t* src_token,
   const void* req[] = {x, src_token, buf};
   for (const void* p : req)
     if (p == nullptr || !aligned16(p)) return MOE_EINVAL;
-  return moe::launch_dispatch(*cfg, x, src_token, buf, nullptr, static_cast<hipStream_t>(stream));
+  return moe::launch_dispatch(*cfg, x, src_token, buf, static_cast<hipStream_t>(stream));
 }
 
 int moe_forward_packs_rows(const moe_config* cfg, int* packed) {
@@ -594,8 +594,8 @@ int moe_backward_events(const moe_config* cfg, const void* x, const float* wg, c
   const int32_t* kept = packed ? pk.kept : nullptr;
   const int32_t* rows_src = packed ? pk.packed_src : src_token;
   if (!mark(0)) return MOE_EHIP;
-  rc = moe::launch_combine_bwd(*cfg, dy, fb + f.out, rows_src, expert_idx, weight, base + b.dout,
-                               dweight, kept, st);
+  rc = moe::launch_combine_bwd(*cfg, dy, fb + f.out, x, rows_src, expert_idx, weight, base + b.dout,
+                               base + b.buf, dweight, kept, st);
   if (rc != MOE_OK) return rc;
   if (!mark(1)) return MOE_EHIP;
   rc = moe::launch_expert_dgrad2(*cfg, base + b.dout, wo, fb + f.h,
@@ -609,8 +609,6 @@ int moe_backward_events(const moe_config* cfg, const void* x, const float* wg, c
   rc = moe::launch_expert_dgrad1(*cfg, base + b.dh, wi, base + b.dbuf, kept, st);
   if (rc != MOE_OK) return rc;
   if (!mark(4)) return MOE_EHIP;
-  rc = moe::launch_dispatch(*cfg, x, rows_src, base + b.buf, kept, st);
-  if (rc != MOE_OK) return rc;
   rc = moe::launch_expert_wgrad1(*cfg, base + b.buf, base + b.dh, dwi, kept, st);
   if (rc != MOE_OK) return rc;
   if (!mark(5)) return MOE_EHIP;
@@ -619,7 +617,7 @@ int moe_backward_events(const moe_config* cfg, const void* x, const float* wg, c
                             dwg, st);
   if (rc != MOE_OK) return rc;
   if (!mark(6)) return MOE_EHIP;
-  rc = moe::launch_dx(*cfg, wg, base + b.dbuf, expert_idx, slot, gw, dx,
+  rc = moe::launch_dx(*cfg, wg, base + b.dbuf, expert_idx, slot, gw, dx, dwg,
                       packed ? pk.row_base : nullptr, st);
   if (rc != MOE_OK) return rc;
   return mark(7) ? MOE_OK : MOE_EHIP;

@@ -21,11 +21,18 @@ namespace {
 
 constexpr int kRowsPerBlock = 4;  // one wavefront per row / token
 
+// One wavefront per expert row: its gradient row dout, dweight of the choice that fills it, and its row of
+// the dispatched activations (buf, the first weight gradient's operand; the forward pass of packed layers
+// never writes one).  Bound: HBM, x, dy and out rows in, buf and dout rows out.  The copy into buf was a
+// launch of its own, as was the sum of dwg that dx_kernel's launch now makes: without the two, training
+// steps of 4 x 1024 tokens, M 512, E 16: 234.7 -> 228.5 us; 3 x 1333 tokens, M 520, E 12: 292.2 -> 286.9;
+// 32 768 tokens, M 1024, E 32: 6373 -> 6363.
 template <typename T>
 __global__ __launch_bounds__(256) void combine_bwd_kernel(
-    const uint4* __restrict__ dy, const uint4* __restrict__ out,
+    const uint4* __restrict__ dy, const uint4* __restrict__ out, const uint4* __restrict__ x,
     const int32_t* __restrict__ src_token, const int32_t* __restrict__ expert_idx,
-    const float* __restrict__ weight, uint4* __restrict__ dout, float* __restrict__ dweight,
+    const float* __restrict__ weight, uint4* __restrict__ dout, uint4* __restrict__ buf,
+    float* __restrict__ dweight,
     int S, int G, int C, int vec_per_row, long long rows, const int32_t* __restrict__ kept) {
   const long long r = (long long)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
   if (r >= rows) return;
@@ -43,9 +50,10 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
     if (p >= ke) t = -1;
   }
   uint4* dst = dout + r * vec_per_row;
+  uint4* bufr = buf + r * vec_per_row;
   if (t < 0) {
     const uint4 zero = {0u, 0u, 0u, 0u};
-    for (int v = lane; v < vec_per_row; v += 64) dst[v] = zero;
+    for (int v = lane; v < vec_per_row; v += 64) dst[v] = bufr[v] = zero;
     return;
   }
   const long long n = kept != nullptr ? (long long)t : (long long)g * S + t;
@@ -53,12 +61,14 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
   const float w = weight[2 * n + k];
   const uint4* dyr = dy + n * vec_per_row;
   const uint4* outr = out + r * vec_per_row;
+  const uint4* xr = x + n * vec_per_row;
   constexpr int K = Vec16<T>::kElts;
   float dot = 0.f;
   for (int v = lane; v < vec_per_row; v += 64) {
     float f[K], o[K];
     Vec16<T>::unpack(dyr[v], f);
     Vec16<T>::unpack(outr[v], o);
+    bufr[v] = xr[v];
 #pragma unroll
     for (int i = 0; i < K; ++i) {
       dot = fmaf(f[i], o[i], dot);
@@ -299,25 +309,23 @@ __global__ __launch_bounds__(256) void dwg_partial_kernel(
     }
 }
 
-// dwg[m,e] = sum over the token ranges: four threads per element add every fourth range, then their
-// four sums (a fixed order)
-__global__ __launch_bounds__(256) void dwg_sum_kernel(const float* __restrict__ partial,
-                                                      float* __restrict__ dwg, int M, int E, int ez,
-                                                      int splits) {
-  __shared__ float red[4][64];
+// dwg[m,e] = sum over the token ranges, 64 elements of [M, ez] per block: four threads per element add
+// every fourth range, then their four sums (a fixed order)
+__device__ __forceinline__ void dwg_sum(float* red, const float* __restrict__ partial, float* __restrict__ dwg,
+                                        int block, int M, int E, int ez, int splits) {
   const int c = threadIdx.x & 63, k = threadIdx.x >> 6;
-  const long long i = (long long)blockIdx.x * 64 + c;            // element of [M, ez]
+  const long long i = (long long)block * 64 + c;
   const long long size = (long long)M * ez;
   float acc = 0.f;
   if (i < size) {
 #pragma unroll 8
     for (int s = k; s < splits; s += 4) acc += partial[s * size + i];
   }
-  red[k][c] = acc;
+  red[64 * k + c] = acc;
   __syncthreads();
   const int m = (int)(i / ez), e = (int)(i % ez);
   if (k == 0 && i < size && e < E)
-    dwg[(size_t)m * E + e] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
+    dwg[(size_t)m * E + e] = (red[c] + red[64 + c]) + (red[128 + c] + red[192 + c]);
 }
 
 // dwg[m,e] = sum over token ranges (in order) of the `terms` adjacent columns of e
@@ -342,6 +350,7 @@ __global__ __launch_bounds__(256) void dwg_reduce_kernel(
 // rounded once.  Wavefront = 32 tokens x 64 features; 32 experts of both operands at a time in LDS; the
 // product (wg rows first, so a lane owns four consecutive features of a token) turns through LDS so that
 // the rows of dbuf and dx move in 16-byte pieces.
+// The first blocks add up dwg instead (dwg_sum): the same launch, since neither needs the other.
 // Bound: the two dbuf rows read and the dx row written per token.  32 768 tokens, M 1024, E 32: 102 us as
 // a bf16 GEMM with an fp32 result in memory and a pass that adds the rows -> 64 us; 3999 tokens, M 520,
 // E 12: 21.5 us on FMA -> 9.1 us.
@@ -350,15 +359,21 @@ __global__ __launch_bounds__(256) void dx_kernel(
     const float* __restrict__ dz, const float* __restrict__ wg, const T* __restrict__ dbuf,
     const int32_t* __restrict__ expert_idx, const int32_t* __restrict__ slot,
     T* __restrict__ dx, int S, int G, int C, int M, int E, int ez, int mtiles, long long tokens,
-    const int32_t* __restrict__ row_base) {
+    const int32_t* __restrict__ row_base, const float* __restrict__ partial, float* __restrict__ dwg,
+    int splits, int sum_blocks) {
   constexpr int P = 36, OP = 68;                                 // pitches: 4 mod 32 floats
   static_assert((128 + 64) * P <= 4 * 32 * OP, "the operands fit the space of the results");
   __shared__ __attribute__((aligned(16))) float ops[4 * 32 * OP];      // wg rows, dz rows; then the results
   __shared__ int rows_s[64][2];                                  // dbuf rows of the tokens' kept choices
+  if ((int)blockIdx.x < sum_blocks) {
+    dwg_sum(ops, partial, dwg, blockIdx.x, M, E, ez, splits);
+    return;
+  }
+  const int block = blockIdx.x - sum_blocks;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, hf = lane >> 5;
-  const long long n0 = (long long)(blockIdx.x / mtiles) * 64;
-  const int m0 = (int)(blockIdx.x % mtiles) * 128;
+  const long long n0 = (long long)(block / mtiles) * 64;
+  const int m0 = block % mtiles * 128;
   const int wt = (wave >> 1) * 32, wm = (wave & 1) * 64;         // the wavefront's tokens, features
   if (tid < 128) {
     const long long n = n0 + (tid >> 1);
@@ -464,22 +479,24 @@ __global__ __launch_bounds__(256) void dx_kernel(
 
 }  // namespace
 
-int launch_combine_bwd(const moe_config& c, const void* dy, const void* out,
+int launch_combine_bwd(const moe_config& c, const void* dy, const void* out, const void* x,
                        const int32_t* src_token, const int32_t* expert_idx, const float* weight,
-                       void* dout, float* dweight, const int32_t* kept, hipStream_t st) {
+                       void* dout, void* buf, float* dweight, const int32_t* kept, hipStream_t st) {
   const int elt = c.act_dtype == MOE_F32 ? 4 : 2;
   const int vec_per_row = c.M * elt / 16;
   const long long rows = (long long)c.E * c.G * c.C;
   const unsigned grid = (unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock);
   if (c.act_dtype == MOE_F32)
     hipLaunchKernelGGL(combine_bwd_kernel<float>, dim3(grid), dim3(256), 0, st,
-                       static_cast<const uint4*>(dy), static_cast<const uint4*>(out), src_token,
-                       expert_idx, weight, static_cast<uint4*>(dout), dweight, c.S, c.G, c.C,
+                       static_cast<const uint4*>(dy), static_cast<const uint4*>(out),
+                       static_cast<const uint4*>(x), src_token, expert_idx, weight,
+                       static_cast<uint4*>(dout), static_cast<uint4*>(buf), dweight, c.S, c.G, c.C,
                        vec_per_row, rows, kept);
   else
     hipLaunchKernelGGL(combine_bwd_kernel<bf16_t>, dim3(grid), dim3(256), 0, st,
-                       static_cast<const uint4*>(dy), static_cast<const uint4*>(out), src_token,
-                       expert_idx, weight, static_cast<uint4*>(dout), dweight, c.S, c.G, c.C,
+                       static_cast<const uint4*>(dy), static_cast<const uint4*>(out),
+                       static_cast<const uint4*>(x), src_token, expert_idx, weight,
+                       static_cast<uint4*>(dout), static_cast<uint4*>(buf), dweight, c.S, c.G, c.C,
                        vec_per_row, rows, kept);
   return check_launch();
 }
@@ -562,15 +579,11 @@ int launch_gate_bwd(const moe_config& c, const void* x, const float* wg, const f
     if (et == 1) MOE_DWG(bf16_t, 1) else if (et == 2) MOE_DWG(bf16_t, 2) else MOE_DWG(bf16_t, 4)
   }
 #undef MOE_DWG
-  if (check_launch() != MOE_OK) return MOE_EHIP;
-  const long long padded = (long long)c.M * p.ez;
-  hipLaunchKernelGGL(dwg_sum_kernel, dim3((unsigned)((padded + 63) / 64)), dim3(256), 0, st, w.partial, dwg,
-                     c.M, c.E, p.ez, p.splits);
-  return check_launch();
+  return check_launch();                                         // the dx launch adds the ranges up
 }
 
 int launch_dx(const moe_config& c, const float* wg, const void* dbuf, const int32_t* expert_idx,
-              const int32_t* slot, const GateBwdWs& w, void* dx, const int32_t* row_base,
+              const int32_t* slot, const GateBwdWs& w, void* dx, float* dwg, const int32_t* row_base,
               hipStream_t st) {
   const GateBwdPlan p = gate_bwd_plan(c);
   const long long tokens = (long long)c.G * c.S;
@@ -592,11 +605,12 @@ int launch_dx(const moe_config& c, const float* wg, const void* dbuf, const int3
   }
   const int mtiles = (c.M + 127) / 128;
   const long long blocks = (tokens + 63) / 64 * mtiles;
-  if (blocks > 0x7fffffffLL) return MOE_EUNSUPPORTED;
+  const long long sum_blocks = ((long long)c.M * p.ez + 63) / 64;
+  if (blocks + sum_blocks > 0x7fffffffLL) return MOE_EUNSUPPORTED;
 #define MOE_DX(T)                                                                                      \
-  hipLaunchKernelGGL(dx_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, st, w.dz, wg,                 \
+  hipLaunchKernelGGL(dx_kernel<T>, dim3((unsigned)(blocks + sum_blocks)), dim3(256), 0, st, w.dz, wg,  \
                      static_cast<const T*>(dbuf), expert_idx, slot, static_cast<T*>(dx), c.S, c.G, c.C, \
-                     c.M, c.E, p.ez, mtiles, tokens, row_base)
+                     c.M, c.E, p.ez, mtiles, tokens, row_base, w.partial, dwg, p.splits, (int)sum_blocks)
   if (c.act_dtype == MOE_F32) MOE_DX(float); else MOE_DX(bf16_t);
 #undef MOE_DX
   return check_launch();

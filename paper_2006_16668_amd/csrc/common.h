@@ -156,9 +156,8 @@ int launch_gate_pack(const moe_config& c, const float* wg, void* packed, hipStre
 int launch_row_maps_from_fill(const moe_config& c, const int32_t* fill, const RowPacking& pk,
                               void* zero_row, hipStream_t st);
 size_t gate_workspace_bytes(const moe_config& c);
-// kept: NULL, or the packed layout's row counts (src_token is then its packed_src)
 int launch_dispatch(const moe_config& c, const void* x, const int32_t* src_token, void* buf,
-                    const int32_t* kept, hipStream_t st);
+                    hipStream_t st);
 // row_base: NULL (out is [E,G,C,M]) or the [G,E] offsets of the packed row layout
 int launch_combine(const moe_config& c, const void* out, const int32_t* expert_idx,
                    const int32_t* slot, const float* weight, const int32_t* row_base, void* y,
@@ -181,9 +180,11 @@ int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPackin
 size_t expert_signbits_bytes(const moe_config& c);
 
 // backward pass (backward.hip)
-int launch_combine_bwd(const moe_config& c, const void* dy, const void* out,
+// dout, dweight and the dispatched rows of x (buf); kept: NULL, or the packed layout's row counts
+// (src_token is then its packed_src)
+int launch_combine_bwd(const moe_config& c, const void* dy, const void* out, const void* x,
                        const int32_t* src_token, const int32_t* expert_idx, const float* weight,
-                       void* dout, float* dweight, const int32_t* kept, hipStream_t st);
+                       void* dout, void* buf, float* dweight, const int32_t* kept, hipStream_t st);
 // Gate gradients: the two projections (dwg = x^T dz, dz . wg^T) in full fp32, or, for bf16 layers of more
 // than 128 experts whose token count and M are multiples of 256, as bf16 GEMMs over three terms of dz.
 struct GateBwdPlan {
@@ -205,8 +206,9 @@ int launch_gate_bwd(const moe_config& c, const void* x, const float* wg, const f
                     const int32_t* expert_idx, const int32_t* slot, const float* dweight,
                     const int32_t* c1, const float* daux, const GateBwdWs& w, float* dwg,
                     hipStream_t st);
+// dx, and the sum of launch_gate_bwd's partial dwg (without the bf16 GEMMs, which leave dwg finished)
 int launch_dx(const moe_config& c, const float* wg, const void* dbuf, const int32_t* expert_idx,
-              const int32_t* slot, const GateBwdWs& w, void* dx, const int32_t* row_base,
+              const int32_t* slot, const GateBwdWs& w, void* dx, float* dwg, const int32_t* row_base,
               hipStream_t st);
 // expert GEMMs of the backward pass (expert_gemm.hip), per expert with rows = G*C:
 //   dgrad2: dh   = (dout . wo^T) masked by h > 0     [rows,M] x [H,M]^T -> [rows,H]
