@@ -10,6 +10,7 @@
 // The attention core has two forms: a flash-style MFMA kernel (bf16, d = 64 or 128) and a plain
 // one-wavefront-per-query kernel for everything else.
 #include <math.h>
+#include <type_traits>
 #include "common.h"
 
 namespace moe {
@@ -154,7 +155,12 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
 //         [keys][d] with the key rows stored in the matching order (bits 2 and 3 of the key
 //         index swapped inside each 32-key tile).
 // The K and V blocks (64 keys x D each) are staged through LDS once per block and step, double
-// buffered, the next block waiting in registers while the current one is multiplied.
+// buffered, the next block waiting in registers while the current one is multiplied.  K runs one block
+// ahead of V: a step multiplies the scores of the next block between the exponentials of this one, and
+// requests fragments two products before their use.  Matrix pipes, vector ALU and LDS were each busy
+// 25 to 45 % of the time, so what bounds the kernel is how far they overlap; two wavefronts per SIMD
+// (registers allow no more) left them taking turns.  Same sums in the same order.  Self-attention sub-layer, 16 heads of 128: 16 x 1000 tokens 478 -> 467 us, 16 x 1024 462 -> 447;
+// 4 heads of 128, 2 x 1024 tokens (one block per compute unit) 50 -> 44.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
@@ -220,24 +226,33 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(
   constexpr int VV = 64 * D / 8 / 256;       // vectors per thread and operand
   constexpr int VPR = D / 8;                 // vectors per row
   u32x4_t kreg[VV], vreg[VV];
-#define MOE_ATT_LOAD_KV(kb)                                                                   \
+#define MOE_ATT_LOAD(reg, src, kb)                                                            \
   _Pragma("unroll") for (int i = 0; i < VV; ++i) {                                            \
     const int f = tid + 256 * i, c = f % VPR;                                                 \
     int key = (kb) * 64 + f / VPR;                                                            \
     if (RAGGED) key = key < L ? key : L - 1;                                                  \
-    kreg[i] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)key * ld + 8 * c);            \
-    vreg[i] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)key * ld + 8 * c);            \
+    reg[i] = *reinterpret_cast<const u32x4_t*>(src + (size_t)key * ld + 8 * c);               \
   }
-#define MOE_ATT_STORE_KV(stage)                                                               \
+#define MOE_ATT_STORE_K(stage)                                                                \
+  _Pragma("unroll") for (int i = 0; i < VV; ++i) {                                            \
+    const int f = tid + 256 * i, key = f / VPR, c = f % VPR;                                  \
+    *reinterpret_cast<u32x4_t*>(&kvs[stage][key * kKPitch + 16 * c]) = kreg[i];               \
+  }
+#define MOE_ATT_STORE_V(stage)                                                                \
   _Pragma("unroll") for (int i = 0; i < VV; ++i) {                                            \
     const int f = tid + 256 * i, key = f / VPR, c = f % VPR;                                  \
     const int pos = (key & ~12) | ((key & 4) << 1) | ((key & 8) >> 1); /* swap bits 2, 3 */   \
-    *reinterpret_cast<u32x4_t*>(&kvs[stage][key * kKPitch + 16 * c]) = kreg[i];               \
     *reinterpret_cast<u32x4_t*>(&kvs[stage][kKTile + pos * kVPitch + 16 * c]) = vreg[i];      \
   }
   const int nkb = RAGGED ? (L + 63) / 64 : L / 64;
-  MOE_ATT_LOAD_KV(0)
-  MOE_ATT_STORE_KV(0)
+  MOE_ATT_LOAD(kreg, kbase, 0)
+  MOE_ATT_LOAD(vreg, vbase, 0)
+  MOE_ATT_STORE_K(0)
+  MOE_ATT_STORE_V(0)
+  if (nkb > 1) {
+    MOE_ATT_LOAD(kreg, kbase, 1)
+    MOE_ATT_STORE_K(1)
+  }
   __syncthreads();
 
   typedef s16x4_t __attribute__((address_space(3))) * lds_s16x4_ptr;
@@ -246,25 +261,35 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(
   const uint32_t kvs0 = (uint32_t)(uintptr_t)((lds_ptr)&kvs[0][0]);
   const int p16 = lane & 15, bb = lane >> 4;
   const int krow0 = 8 * (bb >> 1) + (p16 >> 2);          // staged key row inside a 16-row step
-  for (int kb = 0; kb < nkb; ++kb) {
-    if (kb + 1 < nkb) MOE_ATT_LOAD_KV(kb + 1)
-    const uint32_t kst = kvs0 + (kb & 1) * kStage, vst = kst + kKTile;
-    if (live) {
-    // ---- scores S^T for 64 keys: two 32-key tiles; lane (r, hf) reads 16 bytes of key row r
-    f32x16_t sacc[2];
+  // scores S^T of the 64 keys staged at kst: two 32-key tiles; lane (r, hf) reads 16 bytes of key row r
+  f32x16_t sacc[2];
+  auto scores = [&](f32x16_t (&acc)[2], uint32_t kst) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sacc[t][i] = 0.f;
+      for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
         const u32x4_t kf = *(lds_u4_ptr)(uintptr_t)(kst + (32 * t + r) * kKPitch + 32 * s + 16 * hf);
-        sacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kf),
-                                                          __builtin_bit_cast(bf16x8_t, qf[s]),
-                                                          sacc[t], 0, 0, 0);
+        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kf),
+                                                         __builtin_bit_cast(bf16x8_t, qf[s]),
+                                                         acc[t], 0, 0, 0);
       }
     }
-    if (RAGGED && kb * 64 + 64 > L) {
+  };
+  if (live) scores(sacc, kvs0);
+  // One block of keys.  LAST: no block follows.
+  auto step = [&](int kb, auto last) __attribute__((always_inline)) {
+    constexpr bool LAST = decltype(last)::value;
+    if (!LAST) {
+      if (kb + 2 < nkb) MOE_ATT_LOAD(kreg, kbase, kb + 2)
+      MOE_ATT_LOAD(vreg, vbase, kb + 1)
+    }
+    const uint32_t vst = kvs0 + (kb & 1) * kStage + kKTile;
+    if (live) {
+    f32x16_t snext[2];
+    if (!LAST) scores(snext, kvs0 + ((kb + 1) & 1) * kStage);
+    if (RAGGED && LAST && kb * 64 + 64 > L) {
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -290,6 +315,17 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(
       for (int s = 0; s < 2; ++s)
         pf[t][s] = u32x4_t{pack_bf16x2(p[8 * s], p[8 * s + 1]), pack_bf16x2(p[8 * s + 2], p[8 * s + 3]),
                            pack_bf16x2(p[8 * s + 4], p[8 * s + 5]), pack_bf16x2(p[8 * s + 6], p[8 * s + 7])};
+    }
+    if (!LAST) {
+      // a product of the next block's scores every few vector instructions of this block's softmax,
+      // its fragment requested two products ahead
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+#pragma unroll
+      for (int i = 0; i < 2 * KS; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 112 / KS, 0);
+      }
     }
     psum += __shfl_xor(psum, 32, 64);
     // the running maximum rarely moves after the first blocks: rescale only when some query
@@ -322,13 +358,27 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(
           o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8_t, pf[t][s]),
                                                           o[dt], 0, 0, 0);
         }
+    // fragments of V two products ahead
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+    for (int i = 0; i < 4 * DT; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
     }
-    // the other stage was last read one iteration ago, before the previous barrier
-    if (kb + 1 < nkb) MOE_ATT_STORE_KV((kb + 1) & 1)
-    __syncthreads();
-  }
-#undef MOE_ATT_LOAD_KV
-#undef MOE_ATT_STORE_KV
+    if (!LAST) { sacc[0] = snext[0]; sacc[1] = snext[1]; }
+    }
+    // what the stores overwrite was last read one step ago, before the previous barrier
+    if (!LAST) {
+      if (kb + 2 < nkb) MOE_ATT_STORE_K(kb & 1)
+      MOE_ATT_STORE_V((kb + 1) & 1)
+      __syncthreads();
+    }
+  };
+  for (int kb = 0; kb + 1 < nkb; ++kb) step(kb, std::false_type{});
+  step(nkb - 1, std::true_type{});
+#undef MOE_ATT_LOAD
+#undef MOE_ATT_STORE_K
+#undef MOE_ATT_STORE_V
   // o[dt][i]: d = 32 dt + 8 (i/4) + 4 hf + i%4 of query r: four consecutive d per 8-byte store
   const float inv = 1.0f / l_run;
   // row statistic for the backward pass: log sum_k exp(score) in natural-log units

@@ -27,7 +27,7 @@ def test_pair_forward_and_backward(L, d):
     pair.test_encoder_pair_backward(_cfg(B, L, 600 + L), B, L, 2, d)
 
 
-@pytest.mark.parametrize("L,d", [(1, 64), (2, 128), (31, 128), (64, 64), (96, 128), (1000, 128)])
+@pytest.mark.parametrize("L,d", [(1, 64), (2, 128), (31, 128), (64, 64), (96, 128), (128, 64), (384, 128), (1000, 128)])
 def test_self_attention(L, d):
     B, heads = 3, 3
     cfg = _cfg(B, L, 700 + L)
