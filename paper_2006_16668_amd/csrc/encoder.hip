@@ -278,6 +278,7 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(
     }
   };
   if (live) scores(sacc, kvs0);
+  if (nkb > 2) __syncthreads();              // step 0 writes K block 2 where these scores read block 0
   // One block of keys.  LAST: no block follows.
   auto step = [&](int kb, auto last) __attribute__((always_inline)) {
     constexpr bool LAST = decltype(last)::value;
@@ -367,7 +368,8 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(
     }
     if (!LAST) { sacc[0] = snext[0]; sacc[1] = snext[1]; }
     }
-    // what the stores overwrite was last read one step ago, before the previous barrier
+    // What the stores overwrite was last read one step ago, before the previous barrier: V block kb - 1,
+    // and K block kb, whose scores step kb - 1 multiplied (the prologue before step 0, hence its barrier).
     if (!LAST) {
       if (kb + 2 < nkb) MOE_ATT_STORE_K(kb & 1)
       MOE_ATT_STORE_V((kb + 1) & 1)

@@ -48,3 +48,31 @@ def test_self_attention(L, d):
     assert rel_fro(f64(out), want) < 2e-2
     rows = np.linalg.norm(f64(out) - want, axis=-1) / np.linalg.norm(want, axis=-1)
     assert rows.max() < 6e-2, rows.max()
+
+
+@pytest.mark.parametrize("L,d", [(130, 64), (200, 128), (257, 128), (257, 64), (321, 128), (900, 64), (384, 128)])
+def test_self_attention_with_a_full_chip(L, d):
+    """Three and more key blocks with at least two workgroups on every compute unit, most lengths with
+    wavefronts that hold no query and so run ahead of the others: a stage must not be refilled before
+    all of them have read it.  Every row against the oracle, and the same bits on a second call."""
+    heads = 16
+    B = -(-512 // (heads * -(-L // 128)))
+    print(f"L={L} d={d} B={B}", flush=True)
+    cfg = _cfg(B, L, 800 + L)
+    dims = moe.EncoderDims(B, L, heads, d)
+    sh = shape_of(cfg)
+    inp = make_inputs(cfg, device=DEV, condition=False)
+    w = make_encoder_weights(cfg, heads, d, device=DEV)
+    wqkv = w["wqkv"][0].clone()
+    wqkv[:, :2 * heads * d] *= 2
+    ws = torch.empty(moe.moe_attention_workspace_bytes(sh, dims), dtype=torch.uint8, device=DEV)
+    outs = [torch.full_like(inp.x, float("nan")) for _ in range(2)]
+    for out in outs:
+        moe.moe_self_attention(sh, dims, inp.x, wqkv, w["wo_att"][0], out, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])
+    want = tro.self_attention(f64(inp.x), *_split_qkv(wqkv, heads * d), f64(w["wo_att"][0]), heads)
+    got = f64(outs[0])
+    assert rel_fro(got, want) < 2e-2                      # as above
+    rows = np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)
+    assert rows.max() < 6e-2, rows.max()
