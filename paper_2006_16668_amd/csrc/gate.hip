@@ -46,6 +46,14 @@ __device__ __forceinline__ void wave_argmax(float& bv, int& bi) {
   }
 }
 
+// A token with fewer than two logits above -inf (infinities or NaN in its row of x, or overflow): what is
+// missing of its two choices goes to the lowest other index, as a tie would.  Every later kernel addresses
+// memory with these indices, so they are valid whatever x holds.
+__device__ __forceinline__ void complete_choices(int& e1, int& e2) {
+  if (e1 == INT_MAX) e1 = 0;
+  if (e2 == INT_MAX) e2 = e1 == 0 ? 1 : 0;
+}
+
 // One block = one chunk of 64 tokens of one group; wave w takes tokens w, w+4, ...
 // Lane l owns experts l, l+64, ... (EPL of them).
 // PRE: the logits were computed beforehand on the matrix cores (very wide gates): zpre
@@ -117,6 +125,7 @@ __global__ __launch_bounds__(256) void gate_topk_kernel(
       if (e < E && e != e1) argmax_merge(v2, e2, z[j], e);
     }
     wave_argmax(v2, e2);
+    complete_choices(e1, e2);
 
     // softmax over all experts (needed for the mean gates m_E)
     float p[EPL], psum = 0.f;
@@ -274,6 +283,7 @@ __device__ __forceinline__ void gate_chunk_epilogue(
     other.v2 = __shfl_xor(t2.v2, o, 64); other.e2 = __shfl_xor(t2.e2, o, 64);
     t2 = top2_merge(t2, other);
   }
+  complete_choices(t2.e1, t2.e2);
   // softmax (bulk exponentials: the hardware exp2 path, relative error ~1e-6 at most over the
   // range a softmax tail can reach); rows past the end of the group count as zeros
   float psum = 0.f;
@@ -504,6 +514,7 @@ __global__ __launch_bounds__(256) void gate_mfma_rows_kernel(
     other.v2 = __shfl_xor(t2.v2, 16, 64); other.e2 = __shfl_xor(t2.e2, 16, 64);
     t2 = top2_merge(t2, other);
   }
+  complete_choices(t2.e1, t2.e2);
   // softmax numerators (bulk exponentials: the hardware exp2 path, relative error ~1e-6 at most
   // over the range a softmax tail can reach)
   float psum = 0.f;
@@ -960,6 +971,7 @@ __global__ __launch_bounds__(512) void gate_chunk_kernel(
   typedef float f32x4_t __attribute__((ext_vector_type(4)));
   // feature blocks: 64 bf16 (lane half h owns 32, in the packed operand's order) or 32 fp32 (half h
   // owns 16), 64 bytes of the token row per lane; features past M read the row start and meet zeros
+  // (fp32: are zeros themselves, so that an infinity at the row start stays one)
   constexpr int FB = F32 ? 32 : 64, PV = 16 / sizeof(T);
   const int KB = (M + FB - 1) / FB, per = (KB + KW - 1) / KW;
   const int kb0 = kw * per, kb1 = kb0 + per < KB ? kb0 + per : KB;
@@ -979,6 +991,7 @@ __global__ __launch_bounds__(512) void gate_chunk_kernel(
         for (int j = 0; j < 4; ++j) {
           const int col = cur * FB + FB / 2 * h + PV * j;
           a[n][rt][j] = *reinterpret_cast<const u32x4_t*>(xrow[rt] + (col < M ? col : 0));
+          if (F32 && col >= M) a[n][rt][j] = u32x4_t{0u, 0u, 0u, 0u};
         }
       if constexpr (F32) {
 #pragma unroll
