@@ -991,7 +991,6 @@ __global__ __launch_bounds__(512) void gate_chunk_kernel(
         for (int j = 0; j < 4; ++j) {
           const int col = cur * FB + FB / 2 * h + PV * j;
           a[n][rt][j] = *reinterpret_cast<const u32x4_t*>(xrow[rt] + (col < M ? col : 0));
-          if (F32 && col >= M) a[n][rt][j] = u32x4_t{0u, 0u, 0u, 0u};
         }
       if constexpr (F32) {
 #pragma unroll
@@ -1016,6 +1015,12 @@ __global__ __launch_bounds__(512) void gate_chunk_kernel(
     for (int n = 0; n < NB; ++n) {
       if (kb + n >= kb1) break;                         // wave-uniform
       if constexpr (F32) {
+        if ((kb + n + 1) * FB > M)                      // wave-uniform, last block only
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if ((kb + n) * FB + FB / 2 * h + PV * j >= M)
+#pragma unroll
+              for (int rt = 0; rt < 2; ++rt) a[n][rt][j] = u32x4_t{0u, 0u, 0u, 0u};
 #pragma unroll
         for (int q = 0; q < 16; ++q)
 #pragma unroll
