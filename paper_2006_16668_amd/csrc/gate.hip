@@ -1397,10 +1397,25 @@ __global__ __launch_bounds__(512) void gate_route_kernel(
       part = wave_sum(part);
       if (lane == 0) aux[g] = part / (float)E;
     }
-    // empty positions of every nch-th expert
-    for (int i = ch; i < E; i += nch) {
-      int32_t* st = src_token + ((size_t)i * G + g) * C;
-      for (int c = filled[i] + tid - kChunk; c < C; c += NT - kChunk) st[c] = -1;
+    // empty positions of every nch-th expert: one expert after another where each has work for all threads,
+    // else all of them as one sequence (one chunk, M 1024, E 128, whole gate: C 1 41.5 -> 30.6 us, C 64
+    // 42.9 -> 32.6; as one sequence the empty positions of 16 384 cost up to 4 us more)
+    constexpr int T = NT - kChunk;
+    const int t0 = tid - kChunk;
+    if (C >= T) {
+      for (int i = ch; i < E; i += nch) {
+        int32_t* st = src_token + ((size_t)i * G + g) * C;
+        for (int c = filled[i] + t0; c < C; c += T) st[c] = -1;
+      }
+      return;
+    }
+    const int dj = T / C, dc = T - dj * C;
+    int j = t0 / C, c = t0 - j * C;
+    for (int i = ch + nch * j; i < E; i = ch + nch * j) {
+      if (c >= filled[i]) src_token[((size_t)i * G + g) * C + c] = -1;
+      c += dc;
+      j += dj;
+      if (c >= C) { c -= C; ++j; }
     }
     return;
   }
