@@ -363,7 +363,9 @@ int moe_encoder_workspace_bytes(const moe_config* cfg, const moe_encoder_dims* d
 
 /* out = Attention(u) (no residual): u [B,L,M], wqkv [M,3A], wo_att [A,M] -> out [B,L,M].
  * The flash-style MFMA kernel serves bf16 with d in {64,128}, any L; other
- * shapes use a plain kernel that needs (L + d) * 16 bytes of LDS <= 64 KB. */
+ * shapes use a plain kernel that needs (L + d) * 16 bytes of LDS <= 64 KB.  Probabilities are rounded
+ * to bf16 before they multiply v when bf16, d in {64,128} and L % 128 == 0; every other call keeps
+ * them in fp32 (and so does the backward pass with them and their gradients). */
 int moe_self_attention(const moe_config* cfg, const moe_encoder_dims* dims, const void* u,
                        const void* wqkv, const void* wo_att, void* out,
                        void* ws, size_t ws_bytes, void* stream);

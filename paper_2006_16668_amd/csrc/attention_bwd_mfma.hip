@@ -20,8 +20,12 @@
 //
 // RAGGED (both): L is no multiple of 128.  Rows past the end are read from row L - 1 and their part of
 // P and dS is made 0 (dq kernel: keys >= L; dkv kernel: queries >= L, through lse = +inf and D = 0);
-// rows past the end of the block's own side are not stored.  L % 128 == 0 keeps the form without
-// these tests.
+// rows past the end of the block's own side are not stored.  P and dS stay fp32, as in the plain
+// kernels that served these lengths first: they enter the products as three bf16 terms (split_bf16x8),
+// which leaves dq, dk and dv with their own rounding and 2e-7 of the sum's magnitude against float64.
+// L % 128 == 0 keeps the form without these tests, whose P and dS are rounded to bf16 (2e-3 of it).  Training step of the
+// encoder pair, plain / one bf16 term / three: 16 x 1000 tokens, M 1024, 16 heads of 128 119 / 6.76 / 7.72 ms; 4 x 1000,
+// 16 of 64 17.3 / 1.59 / 1.71 ms; 16 x 200, M 512, 4 of 128 2.78 / 0.758 / 0.784 ms.
 //
 // MFMA register layout (v_mfma_f32_32x32x16_bf16): lane (r = lane % 32, hf = lane / 32) supplies
 // row r of the first operand and column r of the second, k = 8 hf .. 8 hf + 7 of the step; it
@@ -58,9 +62,10 @@ template <int D> struct AttBwdGeom {
   __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),                      \
                                           __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0)
 
-__device__ __forceinline__ u32x4_t pack8(const float* v) {
-  return u32x4_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]),
-                 pack_bf16x2(v[6], v[7])};
+template <typename V>
+__device__ __forceinline__ u32x4_t pack8(const V& v, int first) {
+  return u32x4_t{pack_bf16x2(v[first], v[first + 1]), pack_bf16x2(v[first + 2], v[first + 3]),
+                 pack_bf16x2(v[first + 4], v[first + 5]), pack_bf16x2(v[first + 6], v[first + 7])};
 }
 // Consecutive workgroups go to different XCDs (8, each with its own L2).  This gives every XCD
 // a contiguous range of work items instead, so the blocks of one (sequence, head), which read
@@ -93,6 +98,7 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
     int heads) {
   using GM = AttBwdGeom<D>;
   constexpr int KS = D / 16, DT = D / 32;
+  constexpr int TERMS = RAGGED ? 3 : 1;                               // bf16 terms of dS
   constexpr int kVRows = GM::kRowBlock, kKPerm = 2 * GM::kRowBlock;   // stage: K rows, V rows, K permuted
   constexpr int kStage = 2 * GM::kRowBlock + GM::kTrBlock;
   extern __shared__ __attribute__((aligned(16))) unsigned char att_bwd_lds[];
@@ -193,12 +199,15 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
       }
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        const u32x4_t dsf = pack8(ds + 8 * s);
+        u32x4_t dsf[3];
+        if (RAGGED) split_bf16x8(ds, 8 * s, dsf);
+        else dsf[0] = pack8(ds, 8 * s);
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-          dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              read_transposed<GM::kTrPitch>(kpst, 32 * t + 16 * s, dt, lane),
-              __builtin_bit_cast(bf16x8_t, dsf), dq[dt], 0, 0, 0);
+        for (int dt = 0; dt < DT; ++dt) {
+          const bf16x8_t kt = read_transposed<GM::kTrPitch>(kpst, 32 * t + 16 * s, dt, lane);
+#pragma unroll
+          for (int k = TERMS - 1; k >= 0; --k) dq[dt] = MOE_MFMA(kt, dsf[k], dq[dt]);
+        }
       }
     }
   }
@@ -224,6 +233,7 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
     const float* __restrict__ dvec, bf16_t* __restrict__ dqkv, int L, int heads) {
   using GM = AttBwdGeom<D>;
   constexpr int KS = D / 16, DT = D / 32;
+  constexpr int TERMS = RAGGED ? 3 : 1;      // bf16 terms of P and dS
   // stage: Q rows, dO rows, Q permuted, dO permuted, then 64 lse (log2 units) and 64 D
   constexpr int kGRows = GM::kRowBlock, kQPerm = 2 * GM::kRowBlock, kGPerm = kQPerm + GM::kTrBlock;
   constexpr int kStats = kGPerm + GM::kTrBlock;
@@ -328,33 +338,43 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
           l4[t][g4] = *(lds_f4_ptr)(uintptr_t)(sst + 4 * q0);
           d4[t][g4] = *(lds_f4_ptr)(uintptr_t)(sst + 256 + 4 * q0);
         }
-      auto probabilities = [&](int t) __attribute__((always_inline)) {
-        float p[16], ds[16];
+      auto probabilities = [&](int t) __attribute__((always_inline)) {      // p and ds in the products' place
+        f32x16_t &p = sacc[t], &ds = dpacc[t];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          p[i] = __builtin_amdgcn_exp2f(fmaf(sacc[t][i], sl2, -l4[t][i >> 2][i & 3]));
-          ds[i] = p[i] * (dpacc[t][i] - d4[t][i >> 2][i & 3]);
+          p[i] = __builtin_amdgcn_exp2f(fmaf(p[i], sl2, -l4[t][i >> 2][i & 3]));
+          ds[i] = p[i] * (ds[i] - d4[t][i >> 2][i & 3]);
         }
+        if (RAGGED) return;                                                 // (split where they are multiplied)
 #pragma unroll
-        for (int s = 0; s < 2; ++s) { pf[t][s] = pack8(p + 8 * s); dsf[t][s] = pack8(ds + 8 * s); }
+        for (int s = 0; s < 2; ++s) { pf[t][s] = pack8(p, 8 * s); dsf[t][s] = pack8(ds, 8 * s); }
       };
       auto gradients = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < 2; ++s) {
+          u32x4_t pt[3], dst[3];
+          if (RAGGED) {
+            split_bf16x8(sacc[t], 8 * s, pt);
+            split_bf16x8(dpacc[t], 8 * s, dst);
+          } else {
+            pt[0] = pf[t][s];
+            dst[0] = dsf[t][s];
+          }
 #pragma unroll
           for (int dt = 0; dt < DT; ++dt) {
-            dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                read_transposed<GM::kTrPitch>(gpst, 32 * t + 16 * s, dt, lane),
-                __builtin_bit_cast(bf16x8_t, pf[t][s]), dv[dt], 0, 0, 0);
-            dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                read_transposed<GM::kTrPitch>(qpst, 32 * t + 16 * s, dt, lane),
-                __builtin_bit_cast(bf16x8_t, dsf[t][s]), dk[dt], 0, 0, 0);
+            const bf16x8_t gt = read_transposed<GM::kTrPitch>(gpst, 32 * t + 16 * s, dt, lane);
+#pragma unroll
+            for (int k = TERMS - 1; k >= 0; --k) dv[dt] = MOE_MFMA(gt, pt[k], dv[dt]);
+            const bf16x8_t qt = read_transposed<GM::kTrPitch>(qpst, 32 * t + 16 * s, dt, lane);
+#pragma unroll
+            for (int k = TERMS - 1; k >= 0; --k) dk[dt] = MOE_MFMA(qt, dst[k], dk[dt]);
           }
+        }
       };
       // Four phases between fences; the probabilities of one half run between the products of the other,
       // and fragments are requested two products ahead.  With one wavefront per SIMD nothing else
-      // covers them.  Training step of the encoder pair, same bits: 4 x 1000 tokens, 8 heads of 128
-      // 918 -> 907 us; 8 x 512, 16 of 64 862 -> 857; 2 x 1024, 4 of 128 711 -> 704.
+      // covers them.  Training step of the encoder pair, same bits: 8 x 512 tokens, 16 heads of 64
+      // 862 -> 857 us; 2 x 1024, 4 of 128 711 -> 704.
       scores(0);
       __builtin_amdgcn_sched_barrier(0);
       scores(1);
@@ -372,17 +392,18 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
       __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
 #pragma unroll
       for (int i = 0; i < 4 * DT; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, TERMS, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 32 / DT, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, (RAGGED ? 80 : 32) / DT, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
       gradients(1);
       __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
 #pragma unroll
       for (int i = 0; i < 4 * DT; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, TERMS, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        if (RAGGED) __builtin_amdgcn_sched_group_barrier(0x002, 48 / DT, 0);
       }
     }
     if (qb + 1 < nqb) MOE_ATTB_STORE((qb + 1) & 1)

@@ -31,6 +31,24 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   const f32x2_t v = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
+// Eight fp32 as three bf16 operand fragments, v = t[0] + t[1] + t[2] exactly: each term is the leading 8
+// bits (truncated) of what the terms before it leave of the 24.  Products with bf16 are then exact in
+// fp32, and a matrix product over the terms is one with fp32 operands.
+typedef uint32_t bf16x8_bits_t __attribute__((ext_vector_type(4)));
+template <typename V>
+__device__ __forceinline__ void split_bf16x8(const V& v, int first, bf16x8_bits_t (&t)[3]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float a = v[first + 2 * i], b = v[first + 2 * i + 1];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+      t[k][i] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);        // the upper halves of a and b
+      a -= __uint_as_float(ua & 0xffff0000u);
+      b -= __uint_as_float(ub & 0xffff0000u);
+    }
+  }
+}
 // max(v, 0) on two packed bf16 in one op: a negative bf16 is a negative 16-bit integer
 __device__ __forceinline__ uint32_t relu_bf16x2(uint32_t v) {
   typedef short s16x2_t __attribute__((ext_vector_type(2)));

@@ -169,9 +169,13 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 //
 // RAGGED: L is no multiple of 128.  Query and key rows past the end are read from row L - 1, the
 // scores of such keys become -inf before the softmax (the last key block always holds a real key),
-// such queries are not stored, and a wavefront that has none but those only stages.  L % 128 == 0
-// keeps the form without these tests.  16 sequences of 1000 tokens, 16 heads of 128: 10.9 ms in the
-// plain kernel (which rereads K and V from L2 for every query), 0.2 ms here.
+// such queries are not stored, and a wavefront that has none but those only stages.  The
+// probabilities stay fp32, as in the plain kernel that served these lengths first: P^T enters the
+// product as three bf16 terms (split_bf16x8), so ctx differs from a float64 evaluation by its own
+// rounding and at most 2e-7 of the sum's magnitude.  L % 128 == 0 keeps the form without these tests, whose
+// probabilities are rounded to bf16 (1e-3 of that magnitude).  Self-attention sub-layer, M 1024, plain /
+// one bf16 term / three: 16 x 1000 tokens, 16 heads of 128 11.2 ms / 479 us / 564 us; 4 x 1000, 16 of 64
+// 1508 / 75.5 / 88.2 us; M 512, 16 x 200, 4 of 128 206 / 33.1 / 36.8 us.
 template <int D, bool RAGGED>
 __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(
     const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* __restrict__ lse, int L,
@@ -288,85 +292,95 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(
     }
     const uint32_t vst = kvs0 + (kb & 1) * kStage + kKTile;
     if (live) {
-    f32x16_t snext[2];
-    if (!LAST) scores(snext, kvs0 + ((kb + 1) & 1) * kStage);
-    if (RAGGED && LAST && kb * 64 + 64 > L) {
+      f32x16_t snext[2];
+      if (!LAST) scores(snext, kvs0 + ((kb + 1) & 1) * kStage);
+      if (RAGGED && LAST && kb * 64 + 64 > L) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (kb * 64 + 32 * t + 8 * (i >> 2) + 4 * hf + (i & 3) >= L) sacc[t][i] = -INFINITY;
+      }
+      // ---- online softmax for this lane's query (partner lane ^ 32 holds the other keys)
+      float mx = -INFINITY;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (kb * 64 + 32 * t + 8 * (i >> 2) + 4 * hf + (i & 3) >= L) sacc[t][i] = -INFINITY;
-    }
-    // ---- online softmax for this lane's query (partner lane ^ 32 holds the other keys)
-    float mx = -INFINITY;
+        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[t][i]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sl2;        // sl2 > 0: scaling commutes with max
+      const float m_new = fmaxf(m_run, mx);
+      float psum = 0.f;
+      u32x4_t pf[2][2];                                    // P^T fragments: tile t, MFMA step s
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < 2; ++t) {
+        f32x16_t& p = sacc[t];                             // probabilities in the scores' place
 #pragma unroll
-      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[t][i]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sl2;        // sl2 > 0: scaling commutes with max
-    const float m_new = fmaxf(m_run, mx);
-    float psum = 0.f;
-    u32x4_t pf[2][2];                                    // P^T fragments: tile t, MFMA step s
+        for (int i = 0; i < 16; ++i) { p[i] = __builtin_amdgcn_exp2f(fmaf(p[i], sl2, -m_new)); psum += p[i]; }
+        if (RAGGED) continue;                              // (split where they are multiplied)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      float p[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) { p[i] = __builtin_amdgcn_exp2f(fmaf(sacc[t][i], sl2, -m_new)); psum += p[i]; }
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-        pf[t][s] = u32x4_t{pack_bf16x2(p[8 * s], p[8 * s + 1]), pack_bf16x2(p[8 * s + 2], p[8 * s + 3]),
-                           pack_bf16x2(p[8 * s + 4], p[8 * s + 5]), pack_bf16x2(p[8 * s + 6], p[8 * s + 7])};
-    }
-    if (!LAST) {
-      // a product of the next block's scores every few vector instructions of this block's softmax,
-      // its fragment requested two products ahead
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-#pragma unroll
-      for (int i = 0; i < 2 * KS; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 112 / KS, 0);
+        for (int s = 0; s < 2; ++s)
+          pf[t][s] = u32x4_t{pack_bf16x2(p[8 * s], p[8 * s + 1]), pack_bf16x2(p[8 * s + 2], p[8 * s + 3]),
+                             pack_bf16x2(p[8 * s + 4], p[8 * s + 5]), pack_bf16x2(p[8 * s + 6], p[8 * s + 7])};
       }
-    }
-    psum += __shfl_xor(psum, 32, 64);
-    // the running maximum rarely moves after the first blocks: rescale only when some query
-    // of the wavefront needs it (alpha == 1 exactly otherwise)
-    if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first block (m_run = -inf)
-      l_run *= alpha;
+      if (!LAST) {
+        // a product of the next block's scores every few vector instructions of this block's softmax,
+        // its fragment requested two products ahead
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
-      for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[t][i] *= alpha;
-    }
-    l_run += psum;
-    m_run = m_new;
-    // ---- O^T += V^T . P^T: MFMA step (t, s) covers staged key rows 32 t + 16 s .. + 15
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          // lane needs V^T[d = 32 dt + lane%32][8 consecutive staged keys of its half]:
-          // 16-lane block bb reads rows krow0 (+4), columns 32 dt + 16 (bb&1) + 4 (p16&3) .. +3
-          const int col = 32 * dt + 16 * (bb & 1) + 4 * (p16 & 3);
-          const uint32_t pv = vst + (32 * t + 16 * s + krow0) * kVPitch + 2 * col;
-          const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)pv);
-          const s16x4_t hi =
-              __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(pv + 4 * kVPitch));
-          const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8_t, pf[t][s]),
-                                                          o[dt], 0, 0, 0);
+        for (int i = 0; i < 2 * KS; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 112 / KS, 0);
         }
-    // fragments of V two products ahead
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+      }
+      psum += __shfl_xor(psum, 32, 64);
+      // the running maximum rarely moves after the first blocks: rescale only when some query
+      // of the wavefront needs it (alpha == 1 exactly otherwise)
+      if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first block (m_run = -inf)
+        l_run *= alpha;
 #pragma unroll
-    for (int i = 0; i < 4 * DT; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-    }
-    if (!LAST) { sacc[0] = snext[0]; sacc[1] = snext[1]; }
+        for (int t = 0; t < DT; ++t)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[t][i] *= alpha;
+      }
+      l_run += psum;
+      m_run = m_new;
+      // ---- O^T += V^T . P^T: MFMA step (t, s) covers staged key rows 32 t + 16 s .. + 15
+      constexpr int TERMS = RAGGED ? 3 : 1;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          bf16x8_bits_t pt[3];
+          if (RAGGED) split_bf16x8(sacc[t], 8 * s, pt);
+          else pt[0] = pf[t][s];
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) {
+            // lane needs V^T[d = 32 dt + lane%32][8 consecutive staged keys of its half]:
+            // 16-lane block bb reads rows krow0 (+4), columns 32 dt + 16 (bb&1) + 4 (p16&3) .. +3
+            const int col = 32 * dt + 16 * (bb & 1) + 4 * (p16 & 3);
+            const uint32_t pv = vst + (32 * t + 16 * s + krow0) * kVPitch + 2 * col;
+            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)pv);
+            const s16x4_t hi =
+                __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(pv + 4 * kVPitch));
+            const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+            for (int k = TERMS - 1; k >= 0; --k)           // smallest term first
+              o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8_t, pt[k]),
+                                                              o[dt], 0, 0, 0);
+          }
+        }
+      if (!RAGGED) {
+        // fragments of V two products ahead (three products per fragment leave time enough without)
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+        for (int i = 0; i < 4 * DT; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+      }
+      if (!LAST) { sacc[0] = snext[0]; sacc[1] = snext[1]; }
     }
     // What the stores overwrite was last read one step ago, before the previous barrier: V block kb - 1,
     // and K block kb, whose scores step kb - 1 multiplied (the prologue before step 0, hence its barrier).
