@@ -9,6 +9,7 @@
 //
 // The attention core has two forms: a flash-style MFMA kernel (bf16, d = 64 or 128) and a plain
 // one-wavefront-per-query kernel for everything else.
+#include <float.h>
 #include <math.h>
 #include <type_traits>
 #include "common.h"
@@ -221,7 +222,9 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(
   for (int t = 0; t < DT; ++t)
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[t][i] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;       // running maximum (in log2 units) and sum
+  // running maximum (in log2 units) and sum; the maximum starts finite, so that a block of keys whose scores
+  // are all -inf adds nothing
+  float m_run = -FLT_MAX, l_run = 0.f;
   const float sl2 = 1.4426950408889634f / sqrtf((float)D);
 
   // cooperative staging of a block of 64 keys: K rows as they are, V rows in the order the
@@ -337,7 +340,7 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(
       // the running maximum rarely moves after the first blocks: rescale only when some query
       // of the wavefront needs it (alpha == 1 exactly otherwise)
       if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first block (m_run = -inf)
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first block
         l_run *= alpha;
 #pragma unroll
         for (int t = 0; t < DT; ++t)

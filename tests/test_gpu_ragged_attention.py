@@ -76,3 +76,28 @@ def test_self_attention_with_a_full_chip(L, d):
     assert rel_fro(got, want) < 2e-2                      # as above
     rows = np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)
     assert rows.max() < 6e-2, rows.max()
+
+
+@pytest.mark.parametrize("L,d,block", [(200, 64, 0), (200, 128, 64), (333, 128, 128), (256, 64, 0)])
+def test_a_block_of_keys_with_scores_of_minus_infinity(L, d, block):
+    """64 consecutive keys, the first ones among them, whose finite products overflow to -inf: they get
+    probability 0, whichever block they are in."""
+    M = max(3 * d, -(-L // 8) * 8)
+    cfg = MoEConfig("inf", G=1, S=L, M=M, H=64, E=2, C=L, act_dtype="bf16", seed=5)
+    dims, sh = moe.EncoderDims(1, L, 1, d), shape_of(cfg)
+    gen = torch.Generator(device=DEV).manual_seed(L + d)
+    x = torch.zeros((1, L, M), device=DEV, dtype=torch.bfloat16)
+    x[0, torch.arange(L), torch.arange(L)] = 1            # token t: q, k, v are row t of wqkv
+    w = torch.randn((M, 3 * d), generator=gen, device=DEV)
+    w[:, 0], w[:, d] = 2.0 ** 70, w[:, d] * 2.0 ** -70
+    w[block:block + 64, d] = -2.0 ** 70
+    wqkv = w.to(torch.bfloat16)
+    eye = torch.zeros((d, M), device=DEV, dtype=torch.bfloat16)
+    eye[torch.arange(d), torch.arange(d)] = 1
+    out = torch.full_like(x, float("nan"))
+    moe.moe_self_attention(sh, dims, x, wqkv, eye, out,
+                           torch.empty(moe.moe_attention_workspace_bytes(sh, dims), dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    want = tro.self_attention(f64(x), *_split_qkv(wqkv, d), f64(eye), 1)
+    rows = np.linalg.norm(f64(out) - want, axis=-1) / np.linalg.norm(want, axis=-1)
+    assert rows.max() < 1e-2, rows.max()                  # probabilities and ctx rounded to 8 bits
