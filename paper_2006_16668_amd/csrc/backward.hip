@@ -501,6 +501,23 @@ int launch_combine_bwd(const moe_config& c, const void* dy, const void* out, con
   return check_launch();
 }
 
+// three stages of 32 tokens: 128 features of x, 32 ET experts of dz
+template <typename T, int ET> constexpr int kDwgLds = 3 * 32 * 128 * ((int)sizeof(T) + ET);
+
+template <typename T, int ET>
+static int prepare_dwg() {
+  static LdsLimitOnce once;
+  return ensure_lds_limit(once, reinterpret_cast<const void*>(dwg_partial_kernel<T, ET>), kDwgLds<T, ET>);
+}
+
+int prepare_backward() {
+  const int rcs[] = {prepare_dwg<bf16_t, 1>(), prepare_dwg<bf16_t, 2>(), prepare_dwg<bf16_t, 4>(),
+                     prepare_dwg<float, 1>(), prepare_dwg<float, 2>(), prepare_dwg<float, 4>()};
+  for (int rc : rcs)
+    if (rc != MOE_OK) return rc;
+  return MOE_OK;
+}
+
 GateBwdPlan gate_bwd_plan(const moe_config& c) {
   GateBwdPlan p{};
   const long long tokens = (long long)c.G * c.S;
@@ -566,12 +583,9 @@ int launch_gate_bwd(const moe_config& c, const void* x, const float* wg, const f
   const dim3 pgrid((unsigned)((c.M + 127) / 128), (unsigned)((p.ez + 32 * et - 1) / (32 * et)), (unsigned)p.splits);
 #define MOE_DWG(T, ET)                                                                                 \
   {                                                                                                    \
-    static LdsLimitOnce once;                                                                          \
-    constexpr int lds = 3 * 32 * 128 * ((int)sizeof(T) + ET);                                          \
-    if (ensure_lds_limit(once, reinterpret_cast<const void*>(dwg_partial_kernel<T, ET>), lds) != MOE_OK) \
-      return MOE_EHIP;                                                                                 \
-    hipLaunchKernelGGL((dwg_partial_kernel<T, ET>), pgrid, dim3(256), lds, st, static_cast<const T*>(x), \
-                       w.dz, w.partial, c.M, p.ez, tokens, (int)tps);                                  \
+    if (prepare_dwg<T, ET>() != MOE_OK) return MOE_EHIP;                                               \
+    hipLaunchKernelGGL((dwg_partial_kernel<T, ET>), pgrid, dim3(256), (kDwgLds<T, ET>), st,            \
+                       static_cast<const T*>(x), w.dz, w.partial, c.M, p.ez, tokens, (int)tps);        \
   }
   if (c.act_dtype == MOE_F32) {
     if (et == 1) MOE_DWG(float, 1) else if (et == 2) MOE_DWG(float, 2) else MOE_DWG(float, 4)

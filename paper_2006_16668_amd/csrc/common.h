@@ -319,6 +319,7 @@ inline double tiles_time(long long n, int cus, int res, const double* t) {
 }
 int prepare_expert_gemm();        // expert_gemm.hip
 int prepare_gate();               // gate.hip
+int prepare_backward();           // backward.hip
 int prepare_attention_bwd();      // attention_bwd_mfma.hip
 
 }  // namespace moe
