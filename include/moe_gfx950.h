@@ -213,19 +213,21 @@ int moe_forward(const moe_config* cfg, const void* x, const float* wg, const flo
 /*
  * Whether moe_forward folds the dispatch into the first expert GEMM for this config
  * (Section 3.2's gather form: the GEMM's operand copies pick the rows of x through
- * row indices, and the [E,G,C,M] buffer is never written).  It does so for bf16 layers
- * with M >= 128 and E <= 2048; other shapes run the dispatch kernel.  The results are
- * bit-identical either way.
+ * row indices, and the [E,G,C,M] buffer is never written).  It does so for layers of either
+ * element type with M >= 128 and E <= 2048, whose GEMMs then multiply the occupied rows of each
+ * expert only (moe_forward_train does the same); other shapes run the dispatch kernel.  The
+ * results are bit-identical either way.
  * Pure host function: *fused = 1 or 0; returns MOE_OK or the config's error.
  */
 int moe_forward_fuses_dispatch(const moe_config* cfg, int* fused);
 
 /*
- * Whether moe_forward (and moe_expert_ffn with fill and ws) multiplies only the occupied
- * expert rows for this config (Section 2.2, "Expert capacity"): the kept rows of an expert
- * are packed to the front of its block of G*C rows and only the row tiles that hold them go
- * through the two GEMMs.  It does so for bf16 layers with M >= 128 and E <= 2048;
- * moe_forward_train does the same.
+ * Whether moe_expert_ffn with fill and ws multiplies only the occupied expert rows for this
+ * config and leaves the other slots of out unwritten (Section 2.2, "Expert capacity"): the kept
+ * rows of an expert are packed to the front of its block of G*C rows and only the row tiles that
+ * hold them go through the two GEMMs.  It does so for bf16 layers with G*C, M and H all multiples
+ * of 256 and E <= 2048.  moe_forward packs the rows of these layers, and of all others that
+ * moe_forward_fuses_dispatch names.
  * Pure host function: *packed = 1 or 0; returns MOE_OK or the config's error.
  */
 int moe_forward_packs_rows(const moe_config* cfg, int* packed);

@@ -482,7 +482,7 @@ int moe_forward_packs_rows(const moe_config* cfg, int* packed) {
   const int rc = check_config(cfg);
   if (rc != MOE_OK) return rc;
   if (packed == nullptr) return MOE_EINVAL;
-  *packed = moe::expert_ffn_can_pack(*cfg) ? 1 : 0;
+  *packed = moe::expert_ffn_whole_tiles(*cfg) ? 1 : 0;
   return MOE_OK;
 }
 
@@ -490,9 +490,8 @@ int moe_expert_ffn_workspace_bytes(const moe_config* cfg, size_t* bytes) {
   const int rc = check_config(cfg);
   if (rc != MOE_OK) return rc;
   if (bytes == nullptr) return MOE_EINVAL;
-  const size_t elt = cfg->act_dtype == MOE_F32 ? 4 : 2;
-  *bytes = moe::expert_ffn_can_pack(*cfg)
-               ? moe::row_packing_bytes(*cfg) + align_up((size_t)cfg->M * elt, 256) : 0;
+  *bytes = moe::expert_ffn_whole_tiles(*cfg)
+               ? moe::row_packing_bytes(*cfg) + align_up((size_t)cfg->M * 2, 256) : 0;
   return MOE_OK;
 }
 
@@ -505,12 +504,12 @@ int moe_expert_ffn(const moe_config* cfg, const void* buf, const int32_t* fill, 
     if (p == nullptr || !aligned16(p)) return MOE_EINVAL;
   if (fill != nullptr && !aligned16(fill)) return MOE_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (fill != nullptr && ws != nullptr && moe::expert_ffn_can_pack(*cfg)) {
+  if (fill != nullptr && ws != nullptr && moe::expert_ffn_whole_tiles(*cfg)) {
     // occupied rows only: row maps from fill, the first GEMM gathers the occupied rows of buf,
     // the second sends its rows back to their slots of out
     if ((reinterpret_cast<uintptr_t>(ws) & 255u) != 0) return MOE_EINVAL;
     const size_t maps = moe::row_packing_bytes(*cfg);
-    if (ws_bytes < maps + align_up((size_t)cfg->M * (cfg->act_dtype == MOE_F32 ? 4 : 2), 256)) return MOE_EWORKSPACE;
+    if (ws_bytes < maps + align_up((size_t)cfg->M * 2, 256)) return MOE_EWORKSPACE;
     const moe::RowPacking pk = moe::carve_row_packing(*cfg, ws);
     void* zero_row = static_cast<char*>(ws) + maps;
     int r = moe::launch_row_maps_from_fill(*cfg, fill, pk, zero_row, st);

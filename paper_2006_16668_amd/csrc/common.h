@@ -147,7 +147,7 @@ inline RowPacking carve_row_packing(const moe_config& c, void* base) {
 //   gather:  NULL, or row p of expert e of a K-contiguous A is the absolute row gather[e R + p]
 //   kept:    NULL, or the occupied rows of each expert (packed layout)
 //   row_pad: 255: zero rows follow the occupied ones in C up to the next multiple of 256 (bf16)
-//   scatter: NULL, or row p of expert e of C goes to the absolute row scatter[e R + p]
+//   scatter: NULL, or row p of expert e of C goes to the absolute row scatter[e R + p] (bf16)
 struct GemmArgs {
   const void *A, *B;
   void* C;
@@ -191,6 +191,8 @@ int launch_expert_gemm2(const moe_config& c, const void* h, const void* wo, void
 // signbits: NULL, or expert_signbits_bytes(c) bytes that may receive one bit per element of h (set
 // where h > 0) in the persistent kernel's private tile order, for launch_expert_dgrad2.
 bool expert_ffn_can_pack(const moe_config& c);
+// the layers whose expert calls do so too, given fill: the other slots of out then stay unwritten
+bool expert_ffn_whole_tiles(const moe_config& c);
 int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPacking& pk,
                              const void* zero_row, const void* wi, const void* wo, void* h,
                              void* out, bool scatter_out, bool train, void* signbits, hipStream_t st,

@@ -1041,8 +1041,14 @@ bool expert_ffn_can_pack(const moe_config& c) {
   return (long long)c.G * c.C <= 0x7fffffffLL && c.M >= 128 && c.E <= 2048;
 }
 
+bool expert_ffn_whole_tiles(const moe_config& c) {
+  return c.act_dtype == MOE_BF16 && expert_ffn_can_pack(c) && dma_shape_ok(c.G * c.C, c.H, c.M) &&
+         dma_shape_ok(c.G * c.C, c.M, c.H);
+}
+
 size_t expert_signbits_bytes(const moe_config& c) {
-  return c.act_dtype == MOE_BF16 && expert_ffn_can_pack(c) && dma_shape_ok(c.G * c.C, c.H, c.M) ? (size_t)c.E * c.G * c.C * c.H / 8 : 0;
+  const bool kept = c.act_dtype == MOE_BF16 && expert_ffn_can_pack(c) && dma_shape_ok(c.G * c.C, c.H, c.M);
+  return kept ? (size_t)c.E * c.G * c.C * c.H / 8 : 0;
 }
 
 // The weight gradients sum over whole 256-row tiles when the persistent kernel forms them: the rows of
@@ -1074,6 +1080,7 @@ int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPackin
   g2.scatter = scatter_out ? pk.packed_src : nullptr;
   int rc;
   if (c.act_dtype == MOE_F32) {
+    if (scatter_out) return MOE_EUNSUPPORTED;
     rc = launch_gemm_f32(kForwardRelu, g1, c.E, R, c.H, c.M, st);
     if (rc != MOE_OK) return rc;
     if (!between()) return MOE_EHIP;

@@ -35,13 +35,12 @@ constexpr int kF32Stages = 3, kBK = 16;
 
 // T: 64 T x 64 T tile, 32 T x 32 T per wavefront.  The other parameters are those of GemmArgs and of
 // the bf16 kernel: EPI 0 plain, 1 relu, 2 zero where mask[e,r,n] <= 0; gathered rows of A, kept rows
-// of an expert (or, K_KEPT, the length of its sum), scattered rows of C.
+// of an expert (or, K_KEPT, the length of its sum).
 template <int T, int EPI, bool A_KC, bool B_KC, bool K_KEPT>
 __global__ __launch_bounds__(256, T == 2 ? 3 : 4) void gemm_f32_mfma_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ Cout,
     const float* __restrict__ mask, int R, int N, int K, int tiles_r, int tiles_n,
-    const int32_t* __restrict__ gather, const int32_t* __restrict__ kept,
-    const int32_t* __restrict__ scatter) {
+    const int32_t* __restrict__ gather, const int32_t* __restrict__ kept) {
   constexpr int kTile = 64 * T, kAStage = kTile * kBK * 4, kStage = 2 * kAStage, ST = kF32Stages;
   __shared__ __attribute__((aligned(16))) unsigned char smem[ST * kStage];
   typedef unsigned char __attribute__((address_space(3))) * lds_ptr;
@@ -205,7 +204,6 @@ __global__ __launch_bounds__(256, T == 2 ? 3 : 4) void gemm_f32_mfma_kernel(
       const int r = r0 + wm0 + 32 * i + 8 * (v >> 2) + 4 * hf + (v & 3);
       if (r >= rows) continue;
       const size_t o = ((size_t)e * R + r) * N;
-      float* crow = Cout + (scatter != nullptr ? (size_t)scatter[(size_t)e * R + r] * N : o);
 #pragma unroll
       for (int j = 0; j < T; ++j) {
         const int n = n0 + wn0 + 32 * j + l32;
@@ -213,7 +211,7 @@ __global__ __launch_bounds__(256, T == 2 ? 3 : 4) void gemm_f32_mfma_kernel(
         float x = acc[i][j][v];
         if (EPI == 1) x = fmaxf(x, 0.f);
         if (EPI == 2) x = mask[o + n] > 0.f ? x : 0.f;
-        crow[n] = x;
+        Cout[o + n] = x;
       }
     }
 #undef MOE_F32_COPY
@@ -227,7 +225,7 @@ int launch_tiles(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) 
   hipLaunchKernelGGL((gemm_f32_mfma_kernel<T, EPI, A_KC, B_KC, K_KEPT>), dim3((unsigned)nblk), dim3(256), 0,
                      st, static_cast<const float*>(a.A), static_cast<const float*>(a.B),
                      static_cast<float*>(a.C), static_cast<const float*>(a.mask), R, N, K, tiles_r,
-                     tiles_n, a.gather, a.kept, a.scatter);
+                     tiles_n, a.gather, a.kept);
   return check_launch();
 }
 

@@ -36,9 +36,21 @@ def test_host_only_entry_points():
     extra = sh.G * sh.S * sh.E * 4 + rows * sh.H // 8
     assert got + extra <= moe.moe_train_workspace_bytes(sh) < got + extra + (1 << 20)
     assert 0 < moe.moe_gate_workspace_bytes(sh) < got
-    # the paper-size bf16 layer gathers inside the first GEMM; fp32 and short rows do not
+    # the paper-size bf16 layer gathers inside the first GEMM; short rows do not, of either type
     assert moe.moe_forward_fuses_dispatch(sh) is True
     assert moe.moe_forward_fuses_dispatch(moe.MoEShape(1, 64, 32, 64, 4, 32, "f32")) is False
     assert moe.moe_forward_fuses_dispatch(moe.MoEShape(1, 600, 32, 256, 4, 256, "bf16")) is False
     # the workspace of the fp32 layer is twice as wide in its activation buffers
     assert moe.moe_workspace_bytes(moe.MoEShape(1, 64, 32, 64, 4, 32, "f32")) > 128 * (64 + 64) * 4
+
+
+def test_which_calls_pack_occupied_rows():
+    whole = moe.MoEShape(8, 4096, 1024, 8192, 32, 256, "bf16")
+    others = [moe.MoEShape(8, 4096, 1024, 8192, 32, 256, "f32"), moe.MoEShape(3, 1333, 520, 2056, 12, 223, "bf16"),
+              moe.MoEShape(8, 4096, 1024, 8192, 32, 255, "bf16")]
+    assert moe.moe_forward_fuses_dispatch(whole) and moe.moe_forward_packs_rows(whole)
+    assert moe.moe_expert_ffn_workspace_bytes(whole) > 0
+    for sh in others:       # the layer gathers and packs; its expert call writes every slot and needs no workspace
+        assert moe.moe_forward_fuses_dispatch(sh)
+        assert not moe.moe_forward_packs_rows(sh)
+        assert moe.moe_expert_ffn_workspace_bytes(sh) == 0
