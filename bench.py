@@ -310,7 +310,7 @@ def time_f32_layer(moe, cfg, K, W):
     fwd_ms = (time.perf_counter() - t0) * 1e3 / K
     for i, n in enumerate(names):                  # stage times of the last call
         stage[n] = evs[i].elapsed_time(evs[i + 1])
-    padded = c32.E * c32.G * c32.C
+    kept = int(occupied_slots(moe, c32, sh, inp).sum().item())
     gemm_ms = stage["expert_gemm1"] + stage["expert_gemm2"]
     dy, daux = make_upstream(c32, device=dev)
     dx, dwg = torch.empty_like(inp.x), torch.empty_like(inp.wg)
@@ -327,25 +327,39 @@ def time_f32_layer(moe, cfg, K, W):
     bwd_ms = (time.perf_counter() - t0) * 1e3 / K
     return {"forward_ms_per_step": fwd_ms, "forward_tokens_per_s": c32.N / (fwd_ms * 1e-3),
             "stages_ms": stage, "backward_ms_per_step": bwd_ms,
-            # every slot is multiplied (no skipping of empty rows), so padded rows are the work
-            "ffn_mfma_f32_frac_padded_rows": 4.0 * c32.M * c32.H * padded / (gemm_ms * 1e-3) / 1e12 / PEAK_F32_TFLOPS,
+            # occupied rows are the work, as for the bf16 layer
+            "ffn_mfma_f32_frac": 4.0 * c32.M * c32.H * kept / (gemm_ms * 1e-3) / 1e12 / PEAK_F32_TFLOPS,
             "peak": PEAK_F32_TFLOPS, "unit": "TFLOP/s",
             "note": "same workload in fp32 (v_mfma_f32_32x32x2_f32); not part of value"}
 
 
+def occupied_slots(moe, cfg, sh, inp):
+    """fill [G,E] of the layer on these inputs, from one gate call."""
+    import torch
+    dev = inp.x.device
+    i32 = dict(dtype=torch.int32, device=dev)
+    f32 = dict(dtype=torch.float32, device=dev)
+    fill = torch.empty((cfg.G, cfg.E), **i32)
+    gws = torch.empty(moe.moe_gate_workspace_bytes(sh), dtype=torch.uint8, device=dev)
+    moe.moe_gate(sh, inp.x, inp.wg, inp.u, torch.empty((cfg.G, cfg.S, 2), **i32),
+                 torch.empty((cfg.G, cfg.S, 2), **i32), torch.empty((cfg.G, cfg.S, 2), **f32), fill,
+                 torch.empty((cfg.E, cfg.G, cfg.C), **i32), torch.empty((cfg.G, cfg.E), **i32),
+                 torch.empty((cfg.G, cfg.E), **f32), torch.empty((cfg.G,), **f32), None, gws)
+    torch.cuda.synchronize()
+    return fill
+
+
 def gemm_rows(moe, cfg, sh, fill):
     """Rows per GEMM launch: occupied slots (the algorithmic work), every slot of the buffer, and
-    the rows the launches really multiply (whole 256-row tiles of each expert's packed rows when
-    the layer packs them, else every slot)."""
-    import torch
+    the rows the launches really multiply: whole 256-row tiles of each expert's packed rows for layers
+    made of such tiles, every slot for layers that do not pack; None for the others, whose row tiles
+    (64 or 128 rows) the launch rule chooses."""
     kept = int(fill.sum().item())
     padded = cfg.E * cfg.G * cfg.C
-    multiplied = padded
-    if moe.moe_forward_fuses_dispatch(sh) and hasattr(moe, "moe_forward_packs_rows") \
-            and moe.moe_forward_packs_rows(sh):
+    if moe.moe_forward_packs_rows(sh):
         per_e = fill.sum(dim=0)
-        multiplied = int((((per_e + 255) // 256) * 256).sum().item())
-    return kept, padded, multiplied
+        return kept, padded, int((((per_e + 255) // 256) * 256).sum().item())
+    return kept, padded, None if moe.moe_forward_fuses_dispatch(sh) else padded
 
 
 def measure_forward(moe, cfg, inp, K, W, power=False):
@@ -358,18 +372,9 @@ def measure_forward(moe, cfg, inp, K, W, power=False):
     aux = torch.empty(cfg.G, dtype=torch.float32, device=dev)
     # (sized for the training forward, which the backward measurement runs in the same buffer)
     ws = torch.empty(moe.moe_train_workspace_bytes(sh), dtype=torch.uint8, device=dev)
-    # occupied expert rows (algorithmic work of the GEMMs counts kept rows only)
-    i32 = dict(dtype=torch.int32, device=dev)
-    f32 = dict(dtype=torch.float32, device=dev)
-    fill = torch.empty((cfg.G, cfg.E), **i32)
-    gws = torch.empty(moe.moe_gate_workspace_bytes(sh), dtype=torch.uint8, device=dev)
-    moe.moe_gate(sh, inp.x, inp.wg, inp.u, torch.empty((cfg.G, cfg.S, 2), **i32),
-                 torch.empty((cfg.G, cfg.S, 2), **i32), torch.empty((cfg.G, cfg.S, 2), **f32), fill,
-                 torch.empty((cfg.E, cfg.G, cfg.C), **i32), torch.empty((cfg.G, cfg.E), **i32),
-                 torch.empty((cfg.G, cfg.E), **f32), torch.empty((cfg.G,), **f32), None, gws)
-    torch.cuda.synchronize()
+    # (algorithmic work of the GEMMs counts kept rows only)
+    fill = occupied_slots(moe, cfg, sh, inp)
     kept_rows, padded_rows, multiplied_rows = gemm_rows(moe, cfg, sh, fill)
-    del gws
 
     events = [[torch.cuda.Event(enable_timing=True) for _ in range(moe.binding.FORWARD_EVENTS)]
               for _ in range(K)]
@@ -470,7 +475,8 @@ def headline_roofline(moe, cfg, m, roofs):
     out["traffic"] = traffic.get(dom)
     out["traffic_source"] = source
     out["achieved_padded_rows_TFLOPs"] = 2.0 * cfg.M * cfg.H * m["padded_rows"] / t / 1e12
-    out["achieved_multiplied_rows_TFLOPs"] = 2.0 * cfg.M * cfg.H * m["multiplied_rows"] / t / 1e12
+    if m["multiplied_rows"] is not None:
+        out["achieved_multiplied_rows_TFLOPs"] = 2.0 * cfg.M * cfg.H * m["multiplied_rows"] / t / 1e12
     return out
 
 
