@@ -1,6 +1,7 @@
-// Backward of the scaled dot-product attention core on the matrix cores (bf16, d = 64 or 128).  Section 2.1 of the paper names the self-attention sub-layer; the
-// derivative is the chain rule of ctx = softmax(q k^T / sqrt(d)) v, with the probabilities
-// recomputed from q, k and the stored row statistic lse = log sum_k exp(score):
+// Backward of the scaled dot-product attention core on the matrix cores (bf16, d = 64 or 128).
+// Section 2.1 of the paper names the self-attention sub-layer; the derivative is the chain rule of
+// ctx = softmax(q k^T / sqrt(d)) v, with the probabilities recomputed from q, k and the stored row
+// statistic lse = log sum_k exp(score):
 //
 //   p = exp(score - lse),  D = rowsum(dctx * ctx),  dv = p^T dctx,
 //   ds = p * (dctx v^T - D) / sqrt(d),  dq = ds k,  dk = ds^T q
@@ -23,9 +24,10 @@
 // rows past the end of the block's own side are not stored.  P and dS stay fp32, as in the plain
 // kernels that served these lengths first: they enter the products as three bf16 terms (split_bf16x8),
 // which leaves dq, dk and dv with their own rounding and 2e-7 of the sum's magnitude against float64.
-// L % 128 == 0 keeps the form without these tests, whose P and dS are rounded to bf16 (2e-3 of it).  Training step of the
-// encoder pair, plain / one bf16 term / three: 16 x 1000 tokens, M 1024, 16 heads of 128 119 / 6.76 / 7.72 ms; 4 x 1000,
-// 16 of 64 17.3 / 1.59 / 1.71 ms; 16 x 200, M 512, 4 of 128 2.78 / 0.758 / 0.784 ms.
+// L % 128 == 0 keeps the form without these tests, whose P and dS are rounded to bf16 (2e-3 of it).
+// Training step of the encoder pair, plain / one bf16 term / three: 16 x 1000 tokens, M 1024, 16
+// heads of 128 119 / 6.76 / 7.72 ms; 4 x 1000, 16 of 64 17.3 / 1.59 / 1.71 ms; 16 x 200, M 512, 4 of
+// 128 2.78 / 0.758 / 0.784 ms.
 //
 // MFMA register layout (v_mfma_f32_32x32x16_bf16): lane (r = lane % 32, hf = lane / 32) supplies
 // row r of the first operand and column r of the second, k = 8 hf .. 8 hf + 7 of the step; it

@@ -118,8 +118,9 @@ __device__ __forceinline__ float wave_sum(float v) {
 // Packed row layout of the expert GEMMs (Section 2.2, "Expert capacity": a buffer position holds
 // a token or nothing, and FFN_e(0) = 0, so positions that hold nothing need not be multiplied).
 // The kept rows of expert e (kept_e = sum over g of fill[g,e]), in (group, slot) order, occupy
-// rows 0 .. kept_e - 1 of its block of R = G*C rows; only the ceil(kept_e / 256) row tiles that
-// hold them are multiplied.  The GEMM kernels derive the tile counts from kept.
+// rows 0 .. kept_e - 1 of its block of R = G*C rows; only the row tiles that hold them (256 rows in
+// the persistent kernel, 64 or 128 in the edge and the fp32 kernel) are multiplied.  The GEMM kernels
+// derive the tile counts from kept.
 struct RowPacking {
   int32_t* row_base;     // [G,E]  kept rows of expert e in the groups before g
   int32_t* kept;         // [E]    kept_e
@@ -186,8 +187,8 @@ int launch_expert_gemm1(const moe_config& c, const void* buf, const void* wi, vo
 int launch_expert_gemm2(const moe_config& c, const void* h, const void* wo, void* out,
                         hipStream_t st);
 // Both GEMMs over the packed row layout: the first gathers its rows of `a` (x, or an expert buffer)
-// through pk.packed_src, so the dispatched buffer is never materialised (zero_row: M zeros of the
-// activation type).  train: the rows of h behind the occupied ones are what the backward pass expects.
+// through pk.packed_src, so the dispatched buffer is never materialised (zero_row: M bf16 zeros, read
+// by the persistent kernel).  train: the rows of h behind the occupied ones are what the backward pass expects.
 // signbits: NULL, or expert_signbits_bytes(c) bytes that may receive one bit per element of h (set
 // where h > 0) in the persistent kernel's private tile order, for launch_expert_dgrad2.
 bool expert_ffn_can_pack(const moe_config& c);

@@ -160,23 +160,23 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
 // ahead of V: a step multiplies the scores of the next block between the exponentials of this one, and
 // requests fragments two products before their use.  Matrix pipes, vector ALU and LDS were each busy
 // 25 to 45 % of the time, so what bounds the kernel is how far they overlap; two wavefronts per SIMD
-// (registers allow no more) left them taking turns.  Same sums in the same order.  Self-attention sub-layer, 16 heads of 128: 16 x 1000 tokens 478 -> 467 us, 16 x 1024 462 -> 447;
-// 4 heads of 128, 2 x 1024 tokens (one block per compute unit) 50 -> 44.
+// (registers allow no more) left them taking turns.  Same sums in the same order.  Self-attention
+// sub-layer, 16 heads of 128, 16 x 1024 tokens: 462 -> 447 us; 4 heads of 128, 2 x 1024 tokens (one
+// block per compute unit): 50 -> 44.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-//
 // RAGGED: L is no multiple of 128.  Query and key rows past the end are read from row L - 1, the
 // scores of such keys become -inf before the softmax (the last key block always holds a real key),
 // such queries are not stored, and a wavefront that has none but those only stages.  The
 // probabilities stay fp32, as in the plain kernel that served these lengths first: P^T enters the
 // product as three bf16 terms (split_bf16x8), so ctx differs from a float64 evaluation by its own
-// rounding and at most 2e-7 of the sum's magnitude.  L % 128 == 0 keeps the form without these tests, whose
-// probabilities are rounded to bf16 (1e-3 of that magnitude).  Self-attention sub-layer, M 1024, plain /
-// one bf16 term / three: 16 x 1000 tokens, 16 heads of 128 11.2 ms / 479 us / 564 us; 4 x 1000, 16 of 64
-// 1508 / 75.5 / 88.2 us; M 512, 16 x 200, 4 of 128 206 / 33.1 / 36.8 us.
+// rounding and at most 2e-7 of the sum's magnitude.  L % 128 == 0 keeps the form without these tests,
+// whose probabilities are rounded to bf16 (1e-3 of that magnitude).  Self-attention sub-layer, M 1024,
+// plain / one bf16 term / three: 16 x 1000 tokens, 16 heads of 128 11.2 ms / 479 us / 564 us; 4 x 1000,
+// 16 of 64 1508 / 75.5 / 88.2 us; M 512, 16 x 200, 4 of 128 206 / 33.1 / 36.8 us.
 template <int D, bool RAGGED>
 __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(
     const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* __restrict__ lse, int L,

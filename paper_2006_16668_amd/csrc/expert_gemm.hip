@@ -543,10 +543,11 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
 // elements), either operand in either layout (the products of the table above).
 //
 // One block of four wavefronts (2 x 2) per BM x BN tile, wavefront tile BM/2 x BN/2, 32-wide K
-// steps in ST LDS stages (three for BM = 128, four or five of the smaller ones).  The copies are those of the persistent kernel (1 KB per wavefront
-// instruction, the same source permutation against bank conflicts), but every lane carries its own
-// 64-bit source address: a row, column or k past an edge, an unoccupied packed row, reads a zero
-// line instead, so the inner loop knows no edges and nothing outside an operand is touched.
+// steps in ST LDS stages (three for BM = 128, four or five of the smaller ones).  The copies are those
+// of the persistent kernel (1 KB per wavefront instruction, the same source permutation against bank
+// conflicts), but every lane carries its own 64-bit source address: a row, column or k past an edge,
+// an unoccupied packed row, reads a zero line instead, so the inner loop knows no edges and nothing
+// outside an operand is touched.
 // Two (BN = 256) to four (64 x 64) blocks share a compute unit: while one waits for its step or
 // stores its tile the others multiply, and the dispatcher evens out tiles of different length,
 // which a persistent block cannot.
