@@ -933,7 +933,8 @@ __device__ __forceinline__ void gate_single_chunk_finish(
 //     split into bf16 terms, a logit GEMM and a softmax pass -> 45 us.
 // A call with a single chunk in all (a server's step) finishes here, no scan and no slots kernel: 64
 // tokens, M 1024, E 32: 16.9 -> 10.6 us.
-template <typename T, int ETW, int KW>
+// TAIL: fp32 and M % 32 != 0.
+template <typename T, int ETW, int KW, bool TAIL>
 __global__ __launch_bounds__(512) void gate_chunk_kernel(
     const T* __restrict__ x, const uint4* __restrict__ wgP, const float* __restrict__ wg,
     const float* __restrict__ u, int S, int M, int E, int C, int nch, int32_t* expert_idx, int32_t* slot,
@@ -970,8 +971,8 @@ __global__ __launch_bounds__(512) void gate_chunk_kernel(
   typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
   typedef float f32x4_t __attribute__((ext_vector_type(4)));
   // feature blocks: 64 bf16 (lane half h owns 32, in the packed operand's order) or 32 fp32 (half h
-  // owns 16), 64 bytes of the token row per lane; features past M read the row start and meet zeros
-  // (fp32: are zeros themselves, so that an infinity at the row start stays one)
+  // owns 16), 64 bytes of the token row per lane; features past M read the row start and meet zeros (TAIL:
+  // are made zeros themselves, so that an infinity at the row start stays one)
   constexpr int FB = F32 ? 32 : 64, PV = 16 / sizeof(T);
   const int KB = (M + FB - 1) / FB, per = (KB + KW - 1) / KW;
   const int kb0 = kw * per, kb1 = kb0 + per < KB ? kb0 + per : KB;
@@ -1015,12 +1016,10 @@ __global__ __launch_bounds__(512) void gate_chunk_kernel(
     for (int n = 0; n < NB; ++n) {
       if (kb + n >= kb1) break;                         // wave-uniform
       if constexpr (F32) {
-        if ((kb + n + 1) * FB > M)                      // wave-uniform, last block only
+        if (TAIL)
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            if ((kb + n) * FB + FB / 2 * h + PV * j >= M)
-#pragma unroll
-              for (int rt = 0; rt < 2; ++rt) a[n][rt][j] = u32x4_t{0u, 0u, 0u, 0u};
+            if ((kb + n) * FB + FB / 2 * h + PV * j >= M) a[n][0][j] = a[n][1][j] = u32x4_t{0u, 0u, 0u, 0u};
 #pragma unroll
         for (int q = 0; q < 16; ++q)
 #pragma unroll
@@ -1398,24 +1397,15 @@ __global__ __launch_bounds__(512) void gate_route_kernel(
       if (lane == 0) aux[g] = part / (float)E;
     }
     // empty positions of every nch-th expert: one expert after another where each has work for all threads,
-    // else all of them as one sequence (one chunk, M 1024, E 128, whole gate: C 1 41.5 -> 30.6 us, C 64
-    // 42.9 -> 32.6; as one sequence the empty positions of 16 384 cost up to 4 us more)
+    // else one per wavefront at a time (one chunk, M 1024, E 128, whole gate: C 1 39.3 -> 31.7 us, C 64
+    // 42.0 -> 32.1; by wavefronts the empty positions of 16 384 cost up to 5 us more)
     constexpr int T = NT - kChunk;
     const int t0 = tid - kChunk;
-    if (C >= T) {
-      for (int i = ch; i < E; i += nch) {
-        int32_t* st = src_token + ((size_t)i * G + g) * C;
-        for (int c = filled[i] + t0; c < C; c += T) st[c] = -1;
-      }
-      return;
-    }
-    const int dj = T / C, dc = T - dj * C;
-    int j = t0 / C, c = t0 - j * C;
-    for (int i = ch + nch * j; i < E; i = ch + nch * j) {
-      if (c >= filled[i]) src_token[((size_t)i * G + g) * C + c] = -1;
-      c += dc;
-      j += dj;
-      if (c >= C) { c -= C; ++j; }
+    const bool all = C >= T;
+    const int first = all ? 0 : t0 >> 6, experts = all ? 1 : T / 64, lane = all ? t0 : t0 & 63, step = all ? T : 64;
+    for (int i = ch + nch * first; i < E; i += nch * experts) {
+      int32_t* st = src_token + ((size_t)i * G + g) * C;
+      for (int c = filled[i] + lane; c < C; c += step) st[c] = -1;
     }
     return;
   }
@@ -1611,25 +1601,29 @@ constexpr size_t kGateRowsLds1 = (4 * 128 * 36 + 8 * 32) * 4, kGateRowsLds2 = (4
 // partial logits [KW][64][Epad + 8] and two histograms [Epad]
 template <int ETW, int KW> constexpr int kGateChunkLds = (KW * 64 * (32 * ETW * 8 / KW + 8) + 2 * 32 * ETW * 8 / KW) * 4;
 
-template <typename T, int ETW, int KW>
+template <typename T, int ETW, int KW, bool TAIL>
 static int prepare_gate_chunk() {
   static LdsLimitOnce once;
-  return ensure_lds_limit(once, reinterpret_cast<const void*>(gate_chunk_kernel<T, ETW, KW>),
+  return ensure_lds_limit(once, reinterpret_cast<const void*>(gate_chunk_kernel<T, ETW, KW, TAIL>),
                           kGateChunkLds<ETW, KW>);
 }
 
+template <int ET>
+static int prepare_gate_rows() {
+  static LdsLimitOnce once;
+  return ensure_lds_limit(once, reinterpret_cast<const void*>(gate_mfma_rows_kernel<ET>),
+                          (int)(ET == 1 ? kGateRowsLds1 : kGateRowsLds2));
+}
+
 int prepare_gate() {
-  static LdsLimitOnce once1, once2;
-  int rc = ensure_lds_limit(once1, reinterpret_cast<const void*>(gate_mfma_rows_kernel<1>),
-                            (int)kGateRowsLds1);
-  if (rc == MOE_OK) rc = prepare_gate_chunk<bf16_t, 1, 8>();
-  if (rc == MOE_OK) rc = prepare_gate_chunk<bf16_t, 2, 8>();
-  if (rc == MOE_OK) rc = prepare_gate_chunk<float, 1, 8>();
-  if (rc == MOE_OK) rc = prepare_gate_chunk<float, 2, 8>();
-  if (rc == MOE_OK) rc = prepare_gate_chunk<float, 2, 4>();
-  if (rc != MOE_OK) return rc;
-  return ensure_lds_limit(once2, reinterpret_cast<const void*>(gate_mfma_rows_kernel<2>),
-                          (int)kGateRowsLds2);
+  const int rcs[] = {prepare_gate_rows<1>(), prepare_gate_rows<2>(),
+                     prepare_gate_chunk<bf16_t, 1, 8, false>(), prepare_gate_chunk<bf16_t, 2, 8, false>(),
+                     prepare_gate_chunk<float, 1, 8, false>(), prepare_gate_chunk<float, 1, 8, true>(),
+                     prepare_gate_chunk<float, 2, 8, false>(), prepare_gate_chunk<float, 2, 8, true>(),
+                     prepare_gate_chunk<float, 2, 4, false>(), prepare_gate_chunk<float, 2, 4, true>()};
+  for (int rc : rcs)
+    if (rc != MOE_OK) return rc;
+  return MOE_OK;
 }
 
 // One launch for positions and row maps (gate_route_kernel), or the scan and the slots kernel.  Every block
@@ -1667,17 +1661,26 @@ int launch_gate(const moe_config& c, const void* x, const float* wg, const float
   const RowPacking pk = packing != nullptr ? *packing : RowPacking{nullptr, nullptr, nullptr};
   if (wg_prepacked == nullptr && (rc = launch_gate_pack(c, wg, own, st)) != MOE_OK) return rc;
   if (chunk_form) {
-    if (prepare_gate() != MOE_OK) return MOE_EHIP;
-#define MOE_GATE_CHUNK(T, ETW, KW)                                                                      \
-  hipLaunchKernelGGL((gate_chunk_kernel<T, ETW, KW>), dim3((unsigned)chunks), dim3(512),                \
-                     (kGateChunkLds<ETW, KW>), st, static_cast<const T*>(x), wgP, wg, u, c.S, c.M, c.E, c.C, \
-                     nch, expert_idx, slot, weight, gates_opt, hist1, hist2, msum, src_token, c1,       \
-                     mean_gate, fill, aux, static_cast<uint32_t*>(zero_row), zero_words, pk, single)
+#define MOE_GATE_CHUNK(T, ETW, KW, TAIL)                                                                \
+  {                                                                                                     \
+    if (prepare_gate_chunk<T, ETW, KW, TAIL>() != MOE_OK) return MOE_EHIP;                              \
+    hipLaunchKernelGGL((gate_chunk_kernel<T, ETW, KW, TAIL>), dim3((unsigned)chunks), dim3(512),        \
+                       (kGateChunkLds<ETW, KW>), st, static_cast<const T*>(x), wgP, wg, u, c.S, c.M, c.E, c.C, \
+                       nch, expert_idx, slot, weight, gates_opt, hist1, hist2, msum, src_token, c1,     \
+                       mean_gate, fill, aux, static_cast<uint32_t*>(zero_row), zero_words, pk, single); \
+  }
+#define MOE_GATE_CHUNK_F32(ETW, KW)                                                                     \
+  if (c.M % 32 != 0) MOE_GATE_CHUNK(float, ETW, KW, true) else MOE_GATE_CHUNK(float, ETW, KW, false)
     if (c.act_dtype == MOE_BF16) {
-      if (c.E <= 32) MOE_GATE_CHUNK(bf16_t, 1, 8); else MOE_GATE_CHUNK(bf16_t, 2, 8);
-    } else if (c.E <= 32) MOE_GATE_CHUNK(float, 1, 8);
-    else if (c.E <= 64) MOE_GATE_CHUNK(float, 2, 8);
-    else MOE_GATE_CHUNK(float, 2, 4);
+      if (c.E <= 32) MOE_GATE_CHUNK(bf16_t, 1, 8, false) else MOE_GATE_CHUNK(bf16_t, 2, 8, false)
+    } else if (c.E <= 32) {
+      MOE_GATE_CHUNK_F32(1, 8)
+    } else if (c.E <= 64) {
+      MOE_GATE_CHUNK_F32(2, 8)
+    } else {
+      MOE_GATE_CHUNK_F32(2, 4)
+    }
+#undef MOE_GATE_CHUNK_F32
 #undef MOE_GATE_CHUNK
     if ((rc = check_launch()) != MOE_OK || single) return rc;
   } else if (wide_geom(c).cols != 0) {
@@ -1715,7 +1718,7 @@ int launch_gate(const moe_config& c, const void* x, const float* wg, const float
 #define MOE_GATE_ARGS xb, wgP, u, c.S, c.M, c.E, nch, expert_idx, slot, weight, gates_opt, hist1, hist2, msum
     if (c.E <= 64) {
       const size_t lds1 = kGateRowsLds1, lds2 = kGateRowsLds2;
-      if (prepare_gate() != MOE_OK) return MOE_EHIP;
+      if ((c.E <= 32 ? prepare_gate_rows<1>() : prepare_gate_rows<2>()) != MOE_OK) return MOE_EHIP;
       if (c.E <= 32) hipLaunchKernelGGL(gate_mfma_rows_kernel<1>, grid, block, lds1, st, MOE_GATE_ARGS);
       else hipLaunchKernelGGL(gate_mfma_rows_kernel<2>, grid, block, lds2, st, MOE_GATE_ARGS);
     }
