@@ -1157,8 +1157,49 @@ __global__ __launch_bounds__(256) void gate_scan_kernel(
   for (int c = f + k; c < C; c += 8) st[c] = -1;
 }
 
+// row_base[g,e] = sum of fill over the groups before g, kept[e] = over all, for layers of many groups: block = 32
+// experts, thread (e, k) walks the k-th of 32 segments of the groups, twice (sum, then prefix), loads in
+// batches of eight.
+__global__ __launch_bounds__(1024) void gate_row_base_kernel(int G, int E, const int32_t* __restrict__ fill,
+                                                             int32_t* __restrict__ row_base,
+                                                             int32_t* __restrict__ kept) {
+  __shared__ int part[32][33];
+  constexpr int UN = 8;
+  const int c = threadIdx.x & 31, k = threadIdx.x >> 5, e = 32 * blockIdx.x + c;
+  const int seg = (G + 31) / 32, g0 = k * seg < G ? k * seg : G, g1 = g0 + seg < G ? g0 + seg : G;
+  const bool live = e < E;
+  int sum = 0;
+  if (live)
+    for (int gg = g0; gg < g1; gg += UN) {
+      int f[UN];
+#pragma unroll
+      for (int j = 0; j < UN; ++j) f[j] = gg + j < g1 ? fill[(size_t)(gg + j) * E + e] : 0;
+#pragma unroll
+      for (int j = 0; j < UN; ++j) sum += f[j];
+    }
+  part[k][c] = sum;
+  __syncthreads();
+  if (!live) return;
+  int run = 0;
+  for (int i = 0; i < k; ++i) run += part[i][c];
+  for (int gg = g0; gg < g1; gg += UN) {
+    int f[UN];
+#pragma unroll
+    for (int j = 0; j < UN; ++j) f[j] = gg + j < g1 ? fill[(size_t)(gg + j) * E + e] : 0;
+#pragma unroll
+    for (int j = 0; j < UN; ++j)
+      if (gg + j < g1) {
+        row_base[(size_t)(gg + j) * E + e] = run;
+        run += f[j];
+      }
+  }
+  if (k == 31) kept[e] = run;
+}
+
 // One wavefront per chunk.  pk.packed_src != NULL: also builds the packed row layout of the
-// expert GEMMs (row of a kept choice = kept rows of the same expert in earlier groups + slot).
+// expert GEMMs (row of a kept choice = kept rows of the same expert in earlier groups + slot);
+// BASED: gate_row_base_kernel has summed the groups, else every block does so for itself.
+template <bool BASED>
 __global__ __launch_bounds__(64) void gate_slots_kernel(
     int S, int E, int C, int G, int nch,
     const int32_t* __restrict__ base1, const int32_t* __restrict__ base2,
@@ -1168,7 +1209,7 @@ __global__ __launch_bounds__(64) void gate_slots_kernel(
     uint32_t* __restrict__ zero_fill, int zero_words, const int32_t* __restrict__ fill, RowPacking pk) {
   const int g = blockIdx.x / nch, ch = blockIdx.x % nch;
   const int lane = threadIdx.x;
-  const bool packing = pk.packed_src != nullptr;
+  const bool packing = pk.packed_src != nullptr, summing = packing && !BASED;
   // optional: clear the all-zero activation row that stands in for empty expert slots when
   // the first expert GEMM gathers its rows from x
   if (blockIdx.x == 0)
@@ -1183,7 +1224,7 @@ __global__ __launch_bounds__(64) void gate_slots_kernel(
   }
   // packed layout: row_base[:, e] = running sum of fill[:, e] over the groups, 64 experts per
   // block (coalesced rows of fill, G loads per lane)
-  if (packing)
+  if (summing)
     for (int e = 64 * blockIdx.x + lane; e < E; e += 64 * gridDim.x) {   // no wave-level ops inside
       int run = 0;
       for (int gg = 0; gg < G; ++gg) {
@@ -1210,7 +1251,11 @@ __global__ __launch_bounds__(64) void gate_slots_kernel(
   __shared__ int rb_s[128];
   const bool rb_shared = E <= 128;
   int rb1 = 0, rb2 = 0;
-  if (packing) {
+  if (packing && BASED) {
+    if (e1 >= 0) rb1 = pk.row_base[(size_t)g * E + e1];
+    if (e2 >= 0) rb2 = pk.row_base[(size_t)g * E + e2];
+  }
+  if (summing) {
     const int ca = rb_shared ? (lane < E ? lane : -1) : e1;
     const int cb = rb_shared ? (lane + 64 < E ? lane + 64 : -1) : e2;
     for (int gg = 0; gg < g; ++gg) {
@@ -1229,7 +1274,7 @@ __global__ __launch_bounds__(64) void gate_slots_kernel(
   }
   const unsigned long long earlier = (1ull << lane) - 1;
   const int r1 = __popcll(peers1 & earlier), r2 = __popcll(peers2 & earlier);
-  if (packing && rb_shared) {
+  if (summing && rb_shared) {
     rb_s[lane] = rb1;
     rb_s[lane + 64] = rb2;
     __syncthreads();                                  // the block is this one wavefront
@@ -1258,6 +1303,40 @@ __global__ __launch_bounds__(64) void gate_slots_kernel(
   }
 }
 
+// Kept rows of expert e in the groups k, k + stride, ... before g, from the chunk histograms.  The loads of GB
+// groups x CB chunks go out together; past the last group or chunk the last one is read again, not added.
+template <int GB, int CB>
+__device__ __forceinline__ int kept_before(const int32_t* __restrict__ hist1, const int32_t* __restrict__ hist2,
+                                           int e, int k, int g, int stride, int nch, int E, int C) {
+  int rb = 0;
+  for (int g0 = k; g0 < g; g0 += GB * stride) {
+    long long tot[GB];
+#pragma unroll
+    for (int i = 0; i < GB; ++i) tot[i] = 0;
+    for (int c0 = 0; c0 < nch; c0 += CB) {
+      int a[GB][CB], b[GB][CB];
+#pragma unroll
+      for (int i = 0; i < GB; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+          const int gg = g0 + i * stride < g ? g0 + i * stride : g0;
+          const size_t at = ((size_t)gg * nch + (c0 + j < nch ? c0 + j : nch - 1)) * E + e;
+          a[i][j] = hist1[at];
+          b[i][j] = hist2[at];
+        }
+#pragma unroll
+      for (int i = 0; i < GB; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j)
+          if (c0 + j < nch) tot[i] += a[i][j] + b[i][j];
+    }
+#pragma unroll
+    for (int i = 0; i < GB; ++i)
+      if (g0 + i * stride < g) rb += tot[i] < C ? (int)tot[i] : C;
+  }
+  return rb;
+}
+
 // gate_scan_kernel and gate_slots_kernel in one launch, for calls of few chunks and up to 128 experts:
 // one block per chunk, which sums for itself the histograms of its group and, for the packed layout, of
 // the groups before it, instead of reading a prefix that another launch has written.  hist1 / hist2 stay
@@ -1268,6 +1347,7 @@ __global__ __launch_bounds__(64) void gate_slots_kernel(
 //
 // Thread (e, k): expert e of EP = 16, 32, 64 or 128, slice k of 512 / EP.  Slice k sums every 512/EP-th chunk
 // of the block's own group and all chunks of every 512/EP-th earlier group.
+template <int GB, int CB>
 __global__ __launch_bounds__(512) void gate_route_kernel(
     int S, int E, int C, int G, int nch, int ep_log2,
     const int32_t* __restrict__ hist1, const int32_t* __restrict__ hist2, const float* __restrict__ msum,
@@ -1317,24 +1397,7 @@ __global__ __launch_bounds__(512) void gate_route_kernel(
         t2 += c < nch ? a2[j] : 0;
       }
     }
-    if (packing)
-      for (int gg = k; gg < g; gg += NS) {
-        const size_t at = (size_t)gg * nch * E + e;
-        long long tot = 0;
-        for (int c0 = 0; c0 < nch; c0 += 2 * UN) {              // past the end: the last chunk again, not added
-          int a[2 * UN], b[2 * UN];
-#pragma unroll
-          for (int j = 0; j < 2 * UN; ++j) {
-            const size_t i = at + (size_t)(c0 + j < nch ? c0 + j : nch - 1) * E;
-            a[j] = hist1[i];
-            b[j] = hist2[i];
-          }
-#pragma unroll
-          for (int j = 0; j < 2 * UN; ++j)
-            if (c0 + j < nch) tot += a[j] + b[j];
-        }
-        rb += tot < C ? (int)tot : C;
-      }
+    if (packing) rb = kept_before<GB, CB>(hist1, hist2, e, k, g, NS, nch, E, C);
   }
   sb1[tid] = b1;
   st1[tid] = t1;
@@ -1637,6 +1700,13 @@ static bool gate_route_form(const moe_config& c, long long chunks) {
   return c.E <= 128 && chunks <= 512 && chunks * c.E <= 16384;
 }
 
+// Packed layers of more groups than this sum them in a launch of their own (gate_row_base_kernel) before
+// gate_slots_kernel, whose blocks otherwise each walk the groups before theirs, up to 0.4 us a group.  Whole
+// layer of M 256, H 64 (us, walked / summed; G x tokens, E): 12 x 2816, 4 74.5 / 76.3, 512 137.7 / 138.9;
+// 16 x 2112, 4 74.6 / 75.7, 130 103.5 / 100.7; 24 x 1408, 4 75.1 / 75.9, 32 80.3 / 76.2; 48 x 704, 32 86.9 /
+// 75.6; 1000 x 20, 32 318 / 76.
+constexpr int kSumGroups = 16;
+
 int launch_gate(const moe_config& c, const void* x, const float* wg, const float* u,
                 int32_t* expert_idx, int32_t* slot, float* weight, int32_t* fill,
                 int32_t* src_token, int32_t* c1, float* mean_gate, float* aux,
@@ -1737,7 +1807,9 @@ int launch_gate(const moe_config& c, const void* x, const float* wg, const float
   }
   if (rc != MOE_OK) return rc;
   if (gate_route_form(c, chunks)) {
-    hipLaunchKernelGGL(gate_route_kernel, dim3((unsigned)chunks), dim3(512), 0, st, c.S, c.E, c.C, c.G, nch,
+    // groups of one or two chunks are added up eight at a time
+    auto route = pk.packed_src != nullptr && nch <= 2 ? gate_route_kernel<8, 2> : gate_route_kernel<1, 16>;
+    hipLaunchKernelGGL(route, dim3((unsigned)chunks), dim3(512), 0, st, c.S, c.E, c.C, c.G, nch,
                        c.E <= 16 ? 4 : c.E <= 32 ? 5 : c.E <= 64 ? 6 : 7, hist1, hist2, msum, expert_idx, slot, weight,
                        src_token, c1, mean_gate, fill, aux, static_cast<uint32_t*>(zero_row), zero_words, pk);
     return check_launch();
@@ -1745,9 +1817,15 @@ int launch_gate(const moe_config& c, const void* x, const float* wg, const float
   hipLaunchKernelGGL(gate_scan_kernel, dim3((unsigned)(c.G * ((c.E + 31) / 32))), dim3(256), 0, st,
                      c.S, c.E, c.C, c.G, nch, hist1, hist2, msum, c1, mean_gate, fill, src_token);
   if ((rc = check_launch()) != MOE_OK) return rc;
-  hipLaunchKernelGGL(gate_slots_kernel, dim3((unsigned)(c.G * nch)), dim3(64), 0, st, c.S, c.E,
-                     c.C, c.G, nch, hist1, hist2, expert_idx, slot, weight, src_token, c1,
-                     mean_gate, aux, static_cast<uint32_t*>(zero_row), zero_words, fill, pk);
+  const bool based = pk.packed_src != nullptr && c.G > kSumGroups;
+  if (based) {
+    hipLaunchKernelGGL(gate_row_base_kernel, dim3((unsigned)((c.E + 31) / 32)), dim3(1024), 0, st, c.G, c.E,
+                       fill, pk.row_base, pk.kept);
+    if ((rc = check_launch()) != MOE_OK) return rc;
+  }
+  hipLaunchKernelGGL(based ? gate_slots_kernel<true> : gate_slots_kernel<false>, dim3((unsigned)(c.G * nch)),
+                     dim3(64), 0, st, c.S, c.E, c.C, c.G, nch, hist1, hist2, expert_idx, slot, weight,
+                     src_token, c1, mean_gate, aux, static_cast<uint32_t*>(zero_row), zero_words, fill, pk);
   return check_launch();
 }
 

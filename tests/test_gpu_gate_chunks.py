@@ -49,3 +49,12 @@ def test_row_maps(G, S, E, C):
 @pytest.mark.parametrize("S,E,C", [(1, 2, 1), (37, 5, 9), (64, 32, 4), (64, 3, 64)])
 def test_layer_of_a_single_chunk_packs_its_rows(S, E, C):
     shapes.test_random_shape(MoEConfig("chunk", G=1, S=S, M=136, H=72, E=E, C=C, act_dtype="bf16", seed=850 + S + E))
+
+
+@pytest.mark.parametrize("G,S,E,C", [
+    # counted in one launch: groups of one, two and three chunks, eight or one of them summed at a time
+    (100, 5, 6, 2), (60, 70, 20, 8), (9, 128, 100, 3), (40, 150, 3, 60),
+    # sums by a launch of its own from 17 groups on, around its 32 segments and their batches of eight
+    (16, 2060, 5, 500), (17, 1990, 5, 500), (31, 3, 130, 1), (33, 3, 130, 1), (257, 2, 140, 1), (600, 3, 9, 1), (1030, 2, 4, 1)])
+def test_row_maps_of_many_groups(G, S, E, C):
+    shapes.test_random_shape(MoEConfig("groups", G=G, S=S, M=136, H=72, E=E, C=C, act_dtype="bf16", seed=880 + G + S + E))
