@@ -94,6 +94,8 @@ int moe_train_workspace_bytes(const moe_config* cfg, size_t* bytes);
  *
  *   g[g,s,:]   = softmax_e( sum_m x[g,s,m] wg[m,e] )
  *   (e1,e2)    = indices of the largest and second largest gate (ties: lowest index)
+ *                (a logit that is NaN or -inf is never chosen before another; two different
+ *                indices below E whatever x holds)
  *   pass 1     : token s takes position #{s'<s : e1[s']=e1[s]} of expert e1,
  *                kept when the position is < C; weight g1/(g1+g2)
  *   l_aux[g]   = (1/E) sum_e (c1[g,e]/S) mean_gate[g,e],  c1 = first-choice counts
