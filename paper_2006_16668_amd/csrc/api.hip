@@ -337,6 +337,7 @@ const char* moe_status_string(int status) {
 
 int moe_prepare(void) {
   int rc = moe::prepare_expert_gemm();
+  if (rc == MOE_OK) rc = moe::prepare_gemm_f32();
   if (rc == MOE_OK) rc = moe::prepare_gate();
   if (rc == MOE_OK) rc = moe::prepare_backward();
   if (rc == MOE_OK) rc = moe::prepare_attention_bwd();

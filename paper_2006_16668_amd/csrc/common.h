@@ -321,6 +321,7 @@ inline double tiles_time(long long n, int cus, int res, const double* t) {
   return full * t[res - 1] + (left > 0 ? t[left - 1] : 0.0);
 }
 int prepare_expert_gemm();        // expert_gemm.hip
+int prepare_gemm_f32();           // gemm_f32.hip
 int prepare_gate();               // gate.hip
 int prepare_backward();           // backward.hip
 int prepare_attention_bwd();      // attention_bwd_mfma.hip

@@ -1,52 +1,92 @@
-// fp32 expert GEMMs on the matrix cores (v_mfma_f32_32x32x2_f32: full fp32 products, fp32
-// accumulation).  The paper trained its experts in fp32 (Section 4, "Model Details"); bf16 is
-// this library's fast path, this kernel is the fp32 one for all six expert GEMMs of the forward
-// and backward pass and the dense layers around them.
+// fp32 expert GEMMs on the matrix cores.  The paper trained its experts in fp32 (Section 4, "Model
+// Details"); bf16 is this library's fast path, this kernel is the fp32 one for all six expert GEMMs of
+// the forward and backward pass and the dense layers around them.
 //
-// Built like the bf16 kernel of expert_gemm.hip that takes any shape: one block of four wavefronts
-// (2 x 2) per tile, operands travel global -> LDS without passing the registers
-// (global_load_lds_dwordx4, 1 KB per wavefront instruction, three stages of 16 k), every lane with its
-// own source address, and a row, column or k past an edge, or an unoccupied packed row, reads a zero
-// line.  Unit strides run along dimensions that are multiples of 4 elements.
+// The bf16 pipes multiply sixteen times as fast as the fp32 ones, so every operand enters as the three
+// bf16 terms that hold its 24 bits (a = hi + mid + lo, each the leading 8 bits of what is left) and a
+// product of two numbers as the six products of terms that reach 2^-16 of it (hi hi, hi mid, mid hi, mid
+// mid, hi lo, lo hi), exact in fp32 and summed in fp32.  What is left out (mid lo, lo mid, lo lo) is at most
+// 2^-21 of a product, 2^-24 on average.  The five smaller products have sums of their own, so the sum that
+// carries the result is rounded twice per 16 k where v_mfma_f32_32x32x2_f32 rounds it 16 times; all six in
+// one sum were worse than that instruction where the operand is half zeros.  Error against float64, relative
+// (2-norm), v_mfma_f32 / this kernel: K 512 4.1e-7 / 1.4e-7, K 1024 5.7e-7 / 1.9e-7, K 4096 with a ReLU'd
+// operand 8.1e-7 / 3.3e-7.
+// Terms of an operand that is not finite (or of a sum that overflows) make NaN where the fp32 product may
+// be an infinity, so a wavefront whose result holds anything but finite numbers multiplies its tile again
+// with v_mfma_f32_32x32x2_f32, operands straight from memory.
 //
-//   K-contiguous operand [rows][K]: stage [rows][4 chunks of 4 k], chunk c of row r at position
-//     c ^ ((r>>2)&3); a lane reads 16 bytes = the 4 k of four MFMA steps.
-//   row-of-k operand [K][rows]: stage [16 k][rows / 4 chunks], chunk c of row k at c ^ (8 ((k>>2)&1));
-//     one 4-byte read per step.  (64 banks: both reads touch every bank once)
-// Lane half h of step j of an 8-wide group of k takes k = 4 h + j in both operands.
+// One block of four wavefronts (2 x 2) per tile, or KG groups of four that take the steps of 16 k in turn and
+// meet at the end.  A thread fetches its pieces of a step PD steps ahead into registers, from an address of
+// its own: a row, column or k past an edge, or an unoccupied packed row, reads a zero line.  Their terms go
+// to one of two LDS buffers, once for all wavefronts (split by every wavefront that reads an element,
+// straight from fp32 stages, the same products took 8 % longer).  Unit strides run along dimensions that
+// are multiples of 4 elements.
 //
-// Bound: the matrix pipes (one instruction occupies its pipe for 64 cycles, so LDS and issue rates
-// are far from binding); what the kernel has to do is keep them fed across the barrier and the tile's
-// ends, which takes several blocks per compute unit.  The 128 x 128 kernel before this one staged
-// through registers and waited for each load where it was issued.
-// Forward products of 8 experts of 2048 rows, M 1024, H 4096: 111 TFLOP/s with that kernel, 132 with
-// this one (0.84 of the fp32 matrix peak); 16 experts of 512 rows, M 1024, H 2048: 97 -> 129.
+// Bound: six matrix instructions of 32 cycles per product of two fragments; per 128 x 128 tile and step 768
+// matrix cycles, about 560 of LDS and 450 of vector instructions on each SIMD, which overlap in part.
+// Large shapes run at 175 to 190 TFLOP/s (the fp32 instruction: 120 to 130, peak 157); few tiles are bound by
+// a step's chain of barrier, reads, products, split and writes, about 900 cycles, hence the groups.  Both expert
+// products, start of this design (fp32 instruction) / now, us:
+//   E 2  R 8192 M 1024 H 4096  2094 / 1436    E 16 R 512 M 1024 H 2048  632 / 426
+//   E 66 R 12   M 848  H 3424   472 /  341    E 24 R 295 M 768  H 3072  671 / 458
+//   E 19 R 24   M 608  H 2504    96 /   75    E 16 R 128 M 512  H 1024   49 /  44
 #include "common.h"
 
 namespace moe {
 namespace {
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 static __device__ const f32x4_t f32_zero_line = {0.f, 0.f, 0.f, 0.f};
 
-constexpr int kF32Stages = 3, kBK = 16;
+constexpr int kBK = 16;
 
-// T: 64 T x 64 T tile, 32 T x 32 T per wavefront.  The other parameters are those of GemmArgs and of
-// the bf16 kernel: EPI 0 plain, 1 relu, 2 zero where mask[e,r,n] <= 0; gathered rows of A, kept rows
+// LDS of a block: two buffers of the three bf16 planes of a step's operands.
+//   K-contiguous operand: plane [2 halves of 8 k][rows][16 bytes], the halves 128 bytes apart beyond their
+//     size (a half-wavefront's 8-byte writes then meet every bank once); a fragment is one 16-byte read
+//   row-of-k operand: plane [16 k][rows], 16-byte chunk c of row k at c ^ swizzle(k), read transposing
+template <int T, bool KC>
+struct F32Plane {
+  static constexpr int kRows = 64 * T, kHalf = kRows * 16 + 128;
+  static constexpr int kBytes = KC ? 2 * kHalf : 16 * kRows * 2;
+  static __device__ __forceinline__ int swizzle(int k) { return T == 1 ? 4 * ((k >> 1) & 1) : 4 * (k & 3); }
+  // where 4 consecutive k (KC) or rows of operand row `row` at `k` go
+  static __device__ __forceinline__ uint32_t offset(int row, int k) {
+    return KC ? (k >> 3) * kHalf + row * 16 + 2 * (k & 7)
+              : k * (kRows * 2) + (((row >> 3) ^ swizzle(k)) * 16) + 2 * (row & 7);
+  }
+};
+
+template <int TM, int TN, int KG, bool A_KC, bool B_KC>
+struct F32Smem {
+  static constexpr int kBOff = 3 * F32Plane<TM, A_KC>::kBytes, kBuf = kBOff + 3 * F32Plane<TN, B_KC>::kBytes;
+  static constexpr int kBytes = KG * 2 * kBuf;
+  static_assert((KG - 1) * TM * TN * 64 * 64 * 4 <= kBytes, "the groups' sums meet in the planes' place");
+};
+
+// TM x TN tiles of 32 x 32 per wavefront, PD steps of 16 k on their way in registers; KG groups of four
+// wavefronts share a tile, group g taking steps g, g + KG, ...  The other parameters are those of GemmArgs
+// and of the bf16 kernel: EPI 0 plain, 1 relu, 2 zero where mask[e,r,n] <= 0; gathered rows of A, kept rows
 // of an expert (or, K_KEPT, the length of its sum).
-template <int T, int EPI, bool A_KC, bool B_KC, bool K_KEPT>
-__global__ __launch_bounds__(256, T == 2 ? 3 : 4) void gemm_f32_mfma_kernel(
+template <int TM, int TN, int PD, int KG, int EPI, bool A_KC, bool B_KC, bool K_KEPT>
+__global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) void gemm_f32_mfma_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ Cout,
     const float* __restrict__ mask, int R, int N, int K, int tiles_r, int tiles_n,
     const int32_t* __restrict__ gather, const int32_t* __restrict__ kept) {
-  constexpr int kTile = 64 * T, kAStage = kTile * kBK * 4, kStage = 2 * kAStage, ST = kF32Stages;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[ST * kStage];
+  using PA = F32Plane<TM, A_KC>;
+  using PB = F32Plane<TN, B_KC>;
+  static_assert(PD % 2 == 0, "a buffer per parity of the step");
+  using SM = F32Smem<TM, TN, KG, A_KC, B_KC>;
+  constexpr int BM = 64 * TM, BN = 64 * TN, kBOff = SM::kBOff, kBuf = SM::kBuf;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   typedef unsigned char __attribute__((address_space(3))) * lds_ptr;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_ptr)smem);
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x & 255, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const uint32_t smem0 = (uint32_t)(uintptr_t)((lds_ptr)smem), lds0 = smem0 + group * 2 * kBuf;
   // Consecutive workgroups go to different XCDs (8, each with its own L2).  Give every XCD a
   // contiguous range of tiles, in bands of 8 row tiles with the row tile fastest, so that the tiles
   // that share panels run next to each other under one L2.
@@ -58,196 +98,347 @@ __global__ __launch_bounds__(256, T == 2 ? 3 : 4) void gemm_f32_mfma_kernel(
   const int band = t / (8 * tiles_n), rem = t - band * 8 * tiles_n;
   const int left = tiles_r - 8 * band, brows = left < 8 ? left : 8;
   const int ct = rem / brows, rt = 8 * band + (rem - ct * brows);
-  const int r0 = rt * kTile, n0 = ct * kTile;
+  const int r0 = rt * BM, n0 = ct * BN;
   const int rows = kept != nullptr && !K_KEPT ? kept[e] : R;
   if (r0 >= rows) return;                                      // block-uniform
   const int KE = K_KEPT ? kept[e] : K;
-  const int KT = (KE + kBK - 1) / kBK;
-  const int wm0 = (wave >> 1) * 32 * T, wn0 = (wave & 1) * 32 * T;
+  const int KT = (KE + KG * kBK - 1) / (KG * kBK);             // steps of a group
+  const int wm0 = (wave >> 1) * 32 * TM, wn0 = (wave & 1) * 32 * TN;
   const int l32 = lane & 31, hf = lane >> 5;
 
-  // per-lane sources: T copies of each operand per wavefront and step.  A copy fills 16 rows of 4
-  // chunks (K-contiguous) or 4 / T k rows of 16 T chunks (row-of-k)
-  constexpr int CH = 16 * T, RPC = 64 / CH;
+  // The 16-byte pieces a thread fetches of a step: 4 k of a row (K-contiguous) or 4 rows of a k
+  // (row-of-k); where they come from, how far that moves per step (0 on the zero line), where their
+  // terms go
   const uint64_t zline = (uint64_t)(uintptr_t)&f32_zero_line;
-  uint64_t a_addr[T], b_addr[T];
-  uint32_t a_inc[T], b_inc[T];
-  int a_k[T], b_k[T];                                          // the lane's first k inside a step
+  uint64_t a_addr[TM], b_addr[TN];
+  uint32_t a_inc[TM], b_inc[TN], a_put[TM], b_put[TN];
+  auto piece_row = [&](bool kc, int q, int T) { return kc ? 64 * q + (tid >> 2) : 4 * ((tid + 256 * q) % (16 * T)); };
+  auto piece_k = [&](bool kc, int q, int T) { return kc ? 4 * (tid & 3) : (tid + 256 * q) / (16 * T); };
+  const int kg = group * kBK;                                  // the group's first k
 #pragma unroll
-  for (int q = 0; q < T; ++q) {
-    const int c = wave * T + q;
-    const int krow = RPC * c + lane / CH, kcol = 4 * ((lane % CH) ^ (8 * ((krow >> 2) & 1)));
-    const int row = 16 * c + (lane >> 2), kch = 4 * ((lane & 3) ^ ((row >> 2) & 3));
+  for (int q = 0; q < TM; ++q) {
+    const int row = piece_row(A_KC, q, TM), k = piece_k(A_KC, q, TM);
     bool ok;
     const float* src;
     if (A_KC) {
-      a_k[q] = kch;
-      ok = r0 + row < rows && kch < KE;
+      ok = r0 + row < rows && kg + k < KE;
       long long arow = (long long)e * R + r0 + row;
       if (gather != nullptr) {
         const int tok = ok ? gather[arow] : -1;
         ok = tok >= 0;
         arow = tok;
       }
-      src = A + arow * K + kch;
+      src = A + arow * K + kg + k;
     } else {
-      a_k[q] = krow;
-      ok = r0 + kcol < R && krow < KE;
-      src = A + ((size_t)e * K + krow) * R + r0 + kcol;
+      ok = r0 + row < R && kg + k < KE;
+      src = A + ((size_t)e * K + kg + k) * R + r0 + row;
     }
     a_addr[q] = ok ? (uint64_t)(uintptr_t)src : zline;
-    a_inc[q] = ok ? (A_KC ? kBK * 4 : (uint32_t)R * kBK * 4) : 0u;
-    if (B_KC) {
-      b_k[q] = kch;
-      ok = n0 + row < N && kch < KE;
-      src = B + ((size_t)e * N + n0 + row) * K + kch;
-    } else {
-      b_k[q] = krow;
-      ok = n0 + kcol < N && krow < KE;
-      src = B + ((size_t)e * K + krow) * N + n0 + kcol;
-    }
-    b_addr[q] = ok ? (uint64_t)(uintptr_t)src : zline;
-    b_inc[q] = ok ? (B_KC ? kBK * 4 : (uint32_t)N * kBK * 4) : 0u;
+    a_inc[q] = ok ? (A_KC ? 1u : (uint32_t)R) * (KG * kBK * 4) : 0u;
+    a_put[q] = PA::offset(row, k);
   }
-#define MOE_F32_COPY(LDS_U32, ADDR_U64)                                                      \
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"            \
-               :: "s"(LDS_U32), "v"(ADDR_U64) : "memory")
-  auto start_step = [&](int p, int stage) {                    // the next step in order
+#pragma unroll
+  for (int q = 0; q < TN; ++q) {
+    const int row = piece_row(B_KC, q, TN), k = piece_k(B_KC, q, TN);
+    const bool ok = n0 + row < N && kg + k < KE;
+    const float* src = B_KC ? B + ((size_t)e * N + n0 + row) * K + kg + k : B + ((size_t)e * K + kg + k) * N + n0 + row;
+    b_addr[q] = ok ? (uint64_t)(uintptr_t)src : zline;
+    b_inc[q] = ok ? (B_KC ? 1u : (uint32_t)N) * (KG * kBK * 4) : 0u;
+    b_put[q] = kBOff + PB::offset(row, k);
+  }
+  f32x4_t raw[PD][TM + TN];
+  auto fetch = [&](int p, f32x4_t (&r)[TM + TN]) __attribute__((always_inline)) {      // step p, the next in order
     if (p > 0) {
 #pragma unroll
-      for (int q = 0; q < T; ++q) { a_addr[q] += a_inc[q]; b_addr[q] += b_inc[q]; }
-      const int kl = KE - p * kBK;                             // k left, this step's included
-      if (kl < kBK) {                                          // block-uniform, last step only
+      for (int q = 0; q < TM; ++q) a_addr[q] += a_inc[q];
 #pragma unroll
-        for (int q = 0; q < T; ++q) {
-          if (a_k[q] >= kl) a_addr[q] = zline;
-          if (b_k[q] >= kl) b_addr[q] = zline;
-        }
+      for (int q = 0; q < TN; ++q) b_addr[q] += b_inc[q];
+      const int kl = KE - p * (KG * kBK) - kg;                             // k left, this step's included
+      if (kl < kBK) {                                          // block-uniform, from the last step on
+#pragma unroll
+        for (int q = 0; q < TM; ++q)
+          if (piece_k(A_KC, q, TM) >= kl) a_addr[q] = zline;
+#pragma unroll
+        for (int q = 0; q < TN; ++q)
+          if (piece_k(B_KC, q, TN) >= kl) b_addr[q] = zline;
       }
     }
-    const uint32_t la = lds0 + stage * kStage + wave * (T * 1024);
+    typedef const f32x4_t __attribute__((address_space(1))) * glb_f4_ptr;
 #pragma unroll
-    for (int q = 0; q < T; ++q) {
-      MOE_F32_COPY(la + q * 1024, a_addr[q]);
-      MOE_F32_COPY(la + kAStage + q * 1024, b_addr[q]);
+    for (int q = 0; q < TM; ++q) r[q] = *(glb_f4_ptr)(uintptr_t)a_addr[q];
+#pragma unroll
+    for (int q = 0; q < TN; ++q) r[TM + q] = *(glb_f4_ptr)(uintptr_t)b_addr[q];
+  };
+  // the terms of the fetched pieces into the planes of a buffer
+  typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+  typedef u32x2_t __attribute__((address_space(3))) * lds_u2_ptr;
+  auto put = [&](const f32x4_t& v, uint32_t at, int plane_bytes) __attribute__((always_inline)) {
+    float x[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      u32x2_t w;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const uint32_t ua = __float_as_uint(x[2 * i]), ub = __float_as_uint(x[2 * i + 1]);
+        w[i] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);     // the upper halves of both
+        x[2 * i] -= __uint_as_float(ua & 0xffff0000u);
+        x[2 * i + 1] -= __uint_as_float(ub & 0xffff0000u);
+      }
+      *(lds_u2_ptr)(uintptr_t)(at + k * plane_bytes) = w;
     }
   };
-
-  // fragment reads of k group kg (8 k): value j is step j's operand
-  typedef f32x4_t __attribute__((address_space(3))) * lds_f4_ptr;
-  typedef float __attribute__((address_space(3))) * lds_f_ptr;
-  auto read_frag = [&](bool kc, uint32_t base, int w0, int i, int kg) {
-    const int row = w0 + 32 * i + l32;
-    if (kc)
-      return *(lds_f4_ptr)(uintptr_t)(base + row * 64 + (((2 * kg + hf) ^ ((row >> 2) & 3)) * 16));
-    f32x4_t v;
-    const uint32_t p = base + (8 * kg + 4 * hf) * (kTile * 4) + (((row >> 2) ^ (8 * hf)) * 16) + 4 * (row & 3);
+  auto split = [&](const f32x4_t (&r)[TM + TN], int buf) __attribute__((always_inline)) {
+    const uint32_t base = lds0 + buf * kBuf;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = *(lds_f_ptr)(uintptr_t)(p + j * (kTile * 4));
-    return v;
+    for (int q = 0; q < TM; ++q) put(r[q], base + a_put[q], PA::kBytes);
+#pragma unroll
+    for (int q = 0; q < TN; ++q) put(r[TM + q], base + b_put[q], PB::kBytes);
   };
 
-  f32x16_t acc[T][T];
+  // fragment reads: 8 k (8 hf ..) of row l32 of 32-row tile i
+  typedef short s16x4_t __attribute__((ext_vector_type(4)));
+  typedef s16x4_t __attribute__((address_space(3))) * lds_s16x4_ptr;
+  typedef bf16x8_t __attribute__((address_space(3))) * lds_bf16x8_ptr;
+  const int p16 = lane & 15, bb = lane >> 4, bk = 8 * (bb >> 1) + (p16 >> 2);
+  uint32_t a_rd[TM], b_rd[TN];
 #pragma unroll
-  for (int i = 0; i < T; ++i)
+  for (int i = 0; i < TM; ++i)
+    a_rd[i] = A_KC ? PA::offset(wm0 + 32 * i + l32, 8 * hf)
+                   : PA::offset(wm0 + 32 * i + 16 * (bb & 1) + 4 * (p16 & 3), bk);
 #pragma unroll
-    for (int j = 0; j < T; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  for (int j = 0; j < TN; ++j)
+    b_rd[j] = kBOff + (B_KC ? PB::offset(wn0 + 32 * j + l32, 8 * hf)
+                            : PB::offset(wn0 + 32 * j + 16 * (bb & 1) + 4 * (p16 & 3), bk));
+  auto read_frag = [&](bool kc, uint32_t at, int pitch) __attribute__((always_inline)) {
+    if (kc) return *(lds_bf16x8_ptr)(uintptr_t)at;
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)at);
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(at + 4 * pitch));
+    return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
 
-  int p = 0, pstage = 0;
-  for (; p < ST - 1 && p < KT; ++p) {
-    start_step(p, pstage);
-    ++pstage;
+  // main: the products of the leading terms; rest: all others
+  f32x16_t main[TM][TN], rest[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) main[i][j][v] = rest[i][j][v] = 0.f;
+
+#pragma unroll
+  for (int u = 0; u < PD; ++u)
+    fetch(u, raw[u]);
+  split(raw[0], 0);
+  __syncthreads();
+  // step s, whose pieces were in raw[u]
+  auto step = [&](int s, int u) __attribute__((always_inline)) {
+    // unconditional (past the end: zeros, never multiplied): a wait for the older fetches would
+    // otherwise have to be one for all.  What raw[u] held went to the planes a step ago.
+    fetch(s + PD, raw[u]);
+    __builtin_amdgcn_sched_barrier(0);                         // (the compiler sinks them behind the split)
+    const uint32_t sb = lds0 + (u & 1) * kBuf;
+    bf16x8_t a[TM][3];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) a[i][k] = read_frag(A_KC, sb + a_rd[i] + k * PA::kBytes, BM * 2);
+    // terms of A and B in a product, smallest first
+    constexpr int ta[6] = {2, 0, 1, 1, 0, 0}, tb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      bf16x8_t b[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) b[k] = read_frag(B_KC, sb + b_rd[j] + k * PB::kBytes, BN * 2);
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          f32x16_t& c = q == 5 ? main[i][j] : rest[i][j];
+          c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][ta[q]], b[tb[q]], c, 0, 0, 0);
+        }
+    }
+    // the next step's planes: last read in step s - 1, before the previous barrier
+    split(raw[(u + 1) % PD], (u + 1) & 1);
+    __syncthreads();
+  };
+  int s = 0;
+  for (; s + PD <= KT; s += PD) {
+#pragma unroll
+    for (int u = 0; u < PD; ++u) step(s + u, u);
   }
-  int stage = 0;
-  for (int s = 0; s < KT; ++s) {
-    // own copies of step s landed (step s + 1 may still fly), then everybody's; the stage of step
-    // s - 1 is free after the barrier
-    if (s + 1 < KT) {
-      if (T == 2) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-    } else {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int u = 0; u < PD - 1; ++u)
+    if (s + u < KT) step(s + u, u);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) main[i][j][v] += rest[i][j][v];
+  if (KG > 1) {                                                // the groups' sums, in order
+    float* const sums = reinterpret_cast<float*>(smem) + wave * (TM * TN * 1024) + lane;
+    if (group > 0) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            sums[(group - 1) * (TM * TN * 4096) + ((i * TN + j) * 16 + v) * 64] = main[i][j][v];
     }
     __syncthreads();
-    if (p < KT) {
-      start_step(p, pstage);
-      pstage = pstage + 1 == ST ? 0 : pstage + 1;
-      ++p;
-    }
-    const uint32_t sb = lds0 + stage * kStage;
-    stage = stage + 1 == ST ? 0 : stage + 1;
+    if (group > 0) return;
 #pragma unroll
-    for (int kg = 0; kg < 2; ++kg) {
-      f32x4_t a[T], b[T];
+    for (int g = 0; g < KG - 1; ++g)
 #pragma unroll
-      for (int i = 0; i < T; ++i) {
-        a[i] = read_frag(A_KC, sb, wm0, i, kg);
-        b[i] = read_frag(B_KC, sb + kAStage, wn0, i, kg);
-      }
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int i = 0; i < T; ++i)
-#pragma unroll
-          for (int j = 0; j < T; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][q], b[j][q], acc[i][j], 0, 0, 0);
-    }
+          for (int v = 0; v < 16; ++v) main[i][j][v] += sums[g * (TM * TN * 4096) + ((i * TN + j) * 16 + v) * 64];
   }
-  // acc[i][j][v]: row 32 i + 8 (v/4) + 4 hf + v%4, column 32 j + lane%32 of the wavefront tile: a store
-  // covers whole 128-byte pieces of two rows
+
+  // c[v] of the wavefront's 32 x 32 tile (i, j): row 32 i + 8 (v/4) + 4 hf + v%4, column 32 j + lane%32: a
+  // store covers whole 128-byte pieces of two rows
+  auto store_tile = [&](int i, int j, const f32x16_t& c) {
+    const int n = n0 + wn0 + 32 * j + l32, rb = r0 + wm0 + 32 * i + 4 * hf;
+    if (n >= N) return;
+    const size_t o = ((size_t)e * R + rb) * N + n;
+    float m[16];
+    if (EPI == 2) {
 #pragma unroll
-  for (int i = 0; i < T; ++i)
+      for (int v = 0; v < 16; ++v) {
+        const int dr = 8 * (v >> 2) + (v & 3);
+        m[v] = rb + dr < rows ? mask[o + (size_t)dr * N] : 0.f;
+      }
+    }
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int r = r0 + wm0 + 32 * i + 8 * (v >> 2) + 4 * hf + (v & 3);
-      if (r >= rows) continue;
-      const size_t o = ((size_t)e * R + r) * N;
-#pragma unroll
-      for (int j = 0; j < T; ++j) {
-        const int n = n0 + wn0 + 32 * j + l32;
-        if (n >= N) continue;
-        float x = acc[i][j][v];
-        if (EPI == 1) x = fmaxf(x, 0.f);
-        if (EPI == 2) x = mask[o + n] > 0.f ? x : 0.f;
-        Cout[o + n] = x;
-      }
+      const int dr = 8 * (v >> 2) + (v & 3);
+      float x = c[v];
+      if (EPI == 1) x = fmaxf(x, 0.f);
+      if (EPI == 2) x = m[v] > 0.f ? x : 0.f;
+      if (rb + dr < rows) Cout[o + (size_t)dr * N] = x;
     }
-#undef MOE_F32_COPY
+  };
+
+  // anything but finite numbers (0 x number is 0 else): this wavefront's tiles again, in fp32 products
+  float zero = 0.f;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) zero = fmaf(main[i][j][v], 0.f, zero);
+  if (__builtin_amdgcn_ballot_w64(!(zero == 0.f)) != 0) {
+#pragma unroll 1
+    for (int ij = 0; ij < TM * TN; ++ij) {
+      const int i = ij / TN, j = ij % TN;
+      const int row = r0 + wm0 + 32 * i + l32, col = n0 + wn0 + 32 * j + l32;
+      const bool row_ok = row < (A_KC ? rows : R), col_ok = col < N;
+      long long arow = (long long)e * R + row;
+      if (A_KC && gather != nullptr && row_ok) arow = gather[arow];
+      const bool a_ok = row_ok && arow >= 0;
+      f32x16_t c;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) c[v] = 0.f;
+#pragma unroll 1
+      for (int k0 = 0; k0 < KE; k0 += 2) {                     // lane half hf takes k0 + hf
+        const int k = k0 + hf;
+        float x = 0.f, y = 0.f;
+        if (k < KE && a_ok) x = A_KC ? A[arow * K + k] : A[((size_t)e * K + k) * R + row];
+        if (k < KE && col_ok) y = B_KC ? B[((size_t)e * N + col) * K + k] : B[((size_t)e * K + k) * N + col];
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, c, 0, 0, 0);
+      }
+      store_tile(i, j, c);
+    }
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) store_tile(i, j, main[i][j]);
 }
 
-template <int T, int EPI, bool A_KC, bool B_KC, bool K_KEPT>
+template <int TM, int TN, int PD, int KG, int EPI, bool A_KC, bool B_KC, bool K_KEPT>
+int prepare_tiles() {
+  static LdsLimitOnce once;
+  return ensure_lds_limit(
+      once, reinterpret_cast<const void*>(gemm_f32_mfma_kernel<TM, TN, PD, KG, EPI, A_KC, B_KC, K_KEPT>),
+      F32Smem<TM, TN, KG, A_KC, B_KC>::kBytes);
+}
+
+template <int TM, int TN, int PD, int KG, int EPI, bool A_KC, bool B_KC, bool K_KEPT>
 int launch_tiles(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
-  const int tiles_r = (R + 64 * T - 1) / (64 * T), tiles_n = (N + 64 * T - 1) / (64 * T);
+  if (prepare_tiles<TM, TN, PD, KG, EPI, A_KC, B_KC, K_KEPT>() != MOE_OK) return MOE_EHIP;
+  constexpr size_t kLds = F32Smem<TM, TN, KG, A_KC, B_KC>::kBytes;
+  const int tiles_r = (R + 64 * TM - 1) / (64 * TM), tiles_n = (N + 64 * TN - 1) / (64 * TN);
   const long long nblk = (long long)E * tiles_r * tiles_n;
   if (nblk > 0x7fffffffLL) return MOE_EUNSUPPORTED;
-  hipLaunchKernelGGL((gemm_f32_mfma_kernel<T, EPI, A_KC, B_KC, K_KEPT>), dim3((unsigned)nblk), dim3(256), 0,
-                     st, static_cast<const float*>(a.A), static_cast<const float*>(a.B),
+  hipLaunchKernelGGL((gemm_f32_mfma_kernel<TM, TN, PD, KG, EPI, A_KC, B_KC, K_KEPT>), dim3((unsigned)nblk),
+                     dim3(256 * KG), kLds, st, static_cast<const float*>(a.A), static_cast<const float*>(a.B),
                      static_cast<float*>(a.C), static_cast<const float*>(a.mask), R, N, K, tiles_r,
                      tiles_n, a.gather, a.kept);
   return check_launch();
 }
 
-// 128 x 128 or 64 x 64 tiles: whichever keeps the fullest compute unit busy for a shorter time.  Of the
-// larger three share a unit, one alone reaches 0.74 of the fp32 matrix rate, three 0.84; of the smaller
-// six share it, 0.5 for one, 0.74 from four on.  (h = relu(buf wi), out = h wo, 128 / 64, us:
-//   E 16 R 512 M 1024 H 2048  533 / 604    E 8  R 2048 M 1024 H 4096  2090 / 2365
-//   E 24 R 295 M 768  H 3072  732 / 663    E 16 R 128  M 512  H 1024   114 / 48.7
-//   E 4  R 512 M 512  H 2048  183 / 90.3   E 32 R 64   M 1024 H 2048   278 / 174)
+// Tile and groups: the shape's time on the fullest compute unit.  The tables hold what 16 k of n tiles that
+// share a unit take, in ns, n up to what fits a unit (mean of shapes whose blocks share operands and shapes
+// that stream weights, K 1024); a tile's ends take about 2.5 us more.  A lone tile's step is a chain that no
+// form shortens much, so more groups help until the tiles fill the units.
+//   us, tiles 64 x 64 with 1 / 2 / 4 groups, 64 x 128, 128 x 128 (both expert products):
+//   E 3  R 64  M 1024 H 4096  112 / 89 / 77 / 136 / 206    E 16 R 128 M 512 H 1024    47 / 44 / 45 / 51 / 73
+//   E 66 R 12  M 848  H 3424  393 / 403 / 438 / 341 / 523  E 40 R 100 M 600 H 1500  169 / 184 / 224 / 148 / 142
+//   E 16 R 512 M 1024 H 2048  543 / 567 / 628 / 469 / 426  E 2  R 300 M 512 H 2048    67 / 56 / 56 / 75 / 109
+enum F32Form { k64x64, k64x64x2, k64x64x4, k64x128, k128x128 };
+F32Form f32_form(int E, int R, int N, int K, int cus) {
+  static const double t64[] = {425, 635, 915, 1230}, t64x2[] = {375, 615}, t64x4[] = {345}, t64x128[] = {590, 990, 1550},
+                      t128[] = {890, 1700};
+  F32Form form = k64x64;
+  double best = 0;
+  auto consider = [&](F32Form f, int bm, int bn, int groups, int res, const double* t) {
+    const long long n = (long long)E * ((R + bm - 1) / bm) * ((N + bn - 1) / bn), full = n / ((long long)res * cus);
+    const int left = (int)((n - full * res * cus + cus - 1) / cus);
+    const double steps = (double)((K + 16 * groups - 1) / (16 * groups)) * groups;
+    const double us = steps * (full * t[res - 1] + (left > 0 ? t[left - 1] : 0.0)) + 2500.0 * (double)(full + (left > 0));
+    if (f == k64x64 || us < best) { best = us; form = f; }
+  };
+  consider(k64x64, 64, 64, 1, 4, t64);
+  consider(k64x64x2, 64, 64, 2, 2, t64x2);
+  consider(k64x64x4, 64, 64, 4, 1, t64x4);
+  consider(k64x128, 64, 128, 1, 3, t64x128);
+  consider(k128x128, 128, 128, 1, 2, t128);
+  return form;
+}
+
 template <int EPI, bool A_KC, bool B_KC, bool K_KEPT = false>
 int launch_form(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
-  auto tiles = [&](int edge) { return (long long)E * ((R + edge - 1) / edge) * ((N + edge - 1) / edge); };
-  static const double t128[] = {4 / 0.74, 8 / 0.80, 12 / 0.84},
-                      t64[] = {1 / 0.5, 2 / 0.65, 3 / 0.7, 4 / 0.74, 5 / 0.74, 6 / 0.74};
-  const bool small = tiles_time(tiles(64), cus, 6, t64) < tiles_time(tiles(128), cus, 3, t128);
-  return small ? launch_tiles<1, EPI, A_KC, B_KC, K_KEPT>(a, E, R, N, K, st)
-               : launch_tiles<2, EPI, A_KC, B_KC, K_KEPT>(a, E, R, N, K, st);
+  switch (f32_form(E, R, N, K, cus)) {
+    case k64x64: return launch_tiles<1, 1, 4, 1, EPI, A_KC, B_KC, K_KEPT>(a, E, R, N, K, st);
+    case k64x64x2: return launch_tiles<1, 1, 2, 2, EPI, A_KC, B_KC, K_KEPT>(a, E, R, N, K, st);
+    case k64x64x4: return launch_tiles<1, 1, 2, 4, EPI, A_KC, B_KC, K_KEPT>(a, E, R, N, K, st);
+    case k64x128: return launch_tiles<1, 2, 2, 1, EPI, A_KC, B_KC, K_KEPT>(a, E, R, N, K, st);
+    default: return launch_tiles<2, 2, 2, 1, EPI, A_KC, B_KC, K_KEPT>(a, E, R, N, K, st);
+  }
 }
 
 }  // namespace
+
+int prepare_gemm_f32() {
+  const int rcs[] = {
+#define MOE_F32_ALL(...)                                                                              \
+  prepare_tiles<1, 1, 4, 1, __VA_ARGS__>(), prepare_tiles<1, 1, 2, 2, __VA_ARGS__>(),                \
+      prepare_tiles<1, 1, 2, 4, __VA_ARGS__>(), prepare_tiles<1, 2, 2, 1, __VA_ARGS__>(),            \
+      prepare_tiles<2, 2, 2, 1, __VA_ARGS__>()
+      MOE_F32_ALL(0, true, false, false), MOE_F32_ALL(1, true, false, false), MOE_F32_ALL(0, true, true, false),
+      MOE_F32_ALL(2, true, true, false), MOE_F32_ALL(0, false, false, true), MOE_F32_ALL(0, false, false, false)};
+#undef MOE_F32_ALL
+  for (int rc : rcs)
+    if (rc != MOE_OK) return rc;
+  return MOE_OK;
+}
 
 int launch_gemm_f32(GemmKind kind, const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
   // unit strides along K (kForward: A; kDataGrad: A and B), N and R in whole 16-byte pieces

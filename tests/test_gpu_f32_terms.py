@@ -1,0 +1,66 @@
+"""The fp32 products as products of bf16 terms: every tile form and group count, operands that are not finite
+or overflow, and the error against float64 (less than the fp32 matrix instruction's on the same operands:
+4.1e-7 at K 512, 5.7e-7 at K 1024)."""
+import pytest
+import torch
+
+import paper_2006_16668_amd as moe
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _ffn(E, R, M, H, edit=None):
+    g = torch.Generator(device=DEV).manual_seed(E * R + M + H)
+    buf = torch.randn(E, 1, R, M, device=DEV, generator=g)
+    wi = torch.randn(E, M, H, device=DEV, generator=g) / M ** 0.5
+    wo = torch.randn(E, H, M, device=DEV, generator=g) / H ** 0.5
+    if edit:
+        edit(buf, wi)
+    h = torch.full((E, 1, R, H), float("nan"), device=DEV)
+    out = torch.full((E, 1, R, M), float("nan"), device=DEV)
+    moe.moe_expert_ffn(moe.MoEShape(1, R, M, H, E, R, "f32"), buf, wi, wo, h, out)
+    torch.cuda.synchronize()
+    return buf[:, 0], wi, wo, h[:, 0], out[:, 0]
+
+
+def _error(got, want):
+    return float((got.double() - want).norm() / want.norm())
+
+
+# the shapes take 64 x 64 tiles with four, two and one groups, 64 x 128 and 128 x 128 tiles (256 units)
+@pytest.mark.parametrize("E,R,M,H", [(2, 70, 516, 260), (3, 190, 1024, 1028), (16, 128, 512, 1024), (66, 12, 848, 3424),
+                                     (2, 3000, 1024, 1536)])
+def test_error_against_float64(E, R, M, H):
+    buf, wi, wo, h, out = _ffn(E, R, M, H)
+    # the leading products' sum is rounded twice per 16 k: about 0.1 x 2^-24 sqrt(K) on these operands, allowed twice
+    # that; plus a last place
+    bound = lambda K: 2.0 ** -24 * (1 + 0.2 * K ** 0.5)
+    assert _error(h, torch.relu(buf.double() @ wi.double())) < bound(M)
+    assert _error(out, h.double() @ wo.double()) < bound(H)
+
+
+@pytest.mark.parametrize("E,R,M,H", [(2, 70, 132, 260), (3, 300, 160, 1028), (40, 200, 128, 1024), (2, 3000, 144, 1536)])
+def test_infinities_nan_and_overflow(E, R, M, H):
+    inf, nan = float("inf"), float("nan")
+
+    def edit(buf, wi):
+        buf[0, 0, 3, 5], buf[1, 0, R - 1, M - 1], buf[1, 0, 7, 0] = inf, -inf, nan
+        buf[0, 0, 40] = 0                                      # finite, near the largest: some products overflow
+        buf[0, 0, 40, 5] = 3e38
+        wi[0, 5, ::7] = 2
+        wi[E - 1, 2, H - 2] = inf
+        wi[0, M // 2, 9] = 3.4e38
+
+    buf, wi, _, h, _ = _ffn(E, R, M, H, edit)
+    want = torch.bmm(buf, wi)                                  # fp32 (no order of the sums changes what overflows)
+    ok = torch.isfinite(want)
+    assert 0 < int((~ok).sum()) < ok.numel() // 4
+    assert torch.equal(torch.isfinite(h) | ~ok, torch.ones_like(ok))        # a finite sum stays one
+    pos, neg, und = want == inf, want == -inf, torch.isnan(want)
+    assert bool((h[pos] == inf).all()) and bool((h[neg] == 0).all())
+    assert bool((h[und] == 0).all())                           # relu of NaN, as maxnum gives it
+    exact = torch.relu(buf.double() @ wi.double())
+    scale = exact[ok].abs() + 1e-3 * torch.linalg.vector_norm(buf.double(), dim=-1, keepdim=True).expand_as(exact)[ok]
+    fin = torch.isfinite(scale)
+    assert float(((h[ok].double() - exact[ok]).abs() / scale)[fin].max()) < 1e-3
