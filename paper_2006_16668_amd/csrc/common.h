@@ -313,13 +313,6 @@ inline int ensure_lds_limit(LdsLimitOnce& once, const void* kernel, int bytes) {
 }
 int compute_units(int* cus);      // of the current device (cached per device)
 
-// Time the fullest compute unit needs for n equal tiles when `res` of them share a unit at a time:
-// t[i] is what i + 1 tiles sharing it take.
-inline double tiles_time(long long n, int cus, int res, const double* t) {
-  const long long full = n / ((long long)res * cus), rem = n - full * res * cus;
-  const int left = (int)((rem + cus - 1) / cus);
-  return full * t[res - 1] + (left > 0 ? t[left - 1] : 0.0);
-}
 int prepare_expert_gemm();        // expert_gemm.hip
 int prepare_gemm_f32();           // gemm_f32.hip
 int prepare_gate();               // gate.hip

@@ -542,13 +542,13 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
 // Tiles of any shape: C [E,R,N] with R, N, K arbitrary (contiguous dimensions multiples of 8
 // elements), either operand in either layout (the products of the table above).
 //
-// One block of four wavefronts (2 x 2) per BM x BN tile, wavefront tile BM/2 x BN/2, 32-wide K
-// steps in ST LDS stages (three for BM = 128, four or five of the smaller ones).  The copies are those
+// One block of four wavefronts (2 x 2) per BM x BN tile, wavefront tile BM/2 x BN/2, K steps of BK = 32
+// or 64 in ST LDS stages (which, and why: gemm_form).  The copies are those
 // of the persistent kernel (1 KB per wavefront instruction, the same source permutation against bank
 // conflicts), but every lane carries its own 64-bit source address: a row, column or k past an edge,
 // an unoccupied packed row, reads a zero line instead, so the inner loop knows no edges and nothing
 // outside an operand is touched.
-// Two (BN = 256) to four (64 x 64) blocks share a compute unit: while one waits for its step or
+// Two (BN = 256, deep forms) to four (64 x 64) blocks share a compute unit: while one waits for its step or
 // stores its tile the others multiply, and the dispatcher evens out tiles of different length,
 // which a persistent block cannot.
 //
@@ -572,9 +572,9 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
 // ----------------------------------------------------------------------------
 static __device__ const u32x4_t edge_zero_line = {0u, 0u, 0u, 0u};
 
-template <int BM, int BN, int ST>
+template <int BM, int BN, int BK, int ST>
 struct EdgeSmem {
-  static constexpr int kAStage = BM * 32 * 2, kBStage = BN * 32 * 2;
+  static constexpr int kAStage = BM * BK * 2, kBStage = BN * BK * 2;
   static constexpr int kStage = kAStage + kBStage;
   static constexpr size_t kBytes = (size_t)ST * kStage;
 };
@@ -587,16 +587,18 @@ __device__ __forceinline__ constexpr int edge_swizzle(int k) {
   return COLS == 64 ? 4 * ((k >> 1) & 1) : 4 * (k & 3);
 }
 
-template <int BM, int BN, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
+template <int BM, int BN, int BK, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
 __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert_gemm_bf16_edge_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ Cout,
     const bf16_t* __restrict__ mask, int R, int N, int K, int tiles_m, int tiles_n, int nblk,
     const int32_t* __restrict__ gather, const int32_t* __restrict__ kept,
     int row_pad, const int32_t* __restrict__ scatter) {
-  using SM = EdgeSmem<BM, BN, ST>;
-  constexpr int BK = 32, TM = BM / 64, TN = BN / 64;
+  using SM = EdgeSmem<BM, BN, BK, ST>;
+  constexpr int TM = BM / 64, TN = BN / 64;
   constexpr int WN = BN / 2;                                   // columns of a wavefront tile
-  constexpr int AC = BM / 64, BC = BN / 64;                    // copies per wavefront and step
+  constexpr int AC = BM * BK / 2048, BC = BN * BK / 2048;      // copies per wavefront and step
+  constexpr int KCH = BK / 8, KRPC = 64 / KCH;                 // K-contiguous rows: chunks, rows per copy
+  auto kc_swizzle = [](int row) { return BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3; };
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   typedef unsigned char __attribute__((address_space(3))) * lds_ptr;
   const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_ptr)smem_raw);
@@ -640,8 +642,8 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
       const int kr = ARPC * c + lane / ACH, col = m0 + 8 * ((lane % ACH) ^ edge_swizzle<BM>(kr));
       ok = col < R && kr < KE;
       src = A + ((size_t)e * K + kr) * R + col;
-    } else {                                                   // 16 rows of 4 chunks per copy
-      const int row = 16 * c + (lane >> 2), ch = (lane & 3) ^ ((row >> 2) & 3);
+    } else {
+      const int row = KRPC * c + lane / KCH, ch = (lane % KCH) ^ kc_swizzle(row);
       ok = m0 + row < rows && 8 * ch < KE;
       long long arow = (long long)e * R + m0 + row;
       if (gather != nullptr) {
@@ -660,7 +662,7 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
     bool ok;
     const bf16_t* src;
     if (B_KC) {
-      const int row = 16 * c + (lane >> 2), ch = (lane & 3) ^ ((row >> 2) & 3);
+      const int row = KRPC * c + lane / KCH, ch = (lane % KCH) ^ kc_swizzle(row);
       ok = n0 + row < N && 8 * ch < KE;
       src = B + ((size_t)e * N + n0 + row) * K + 8 * ch;
     } else {
@@ -687,14 +689,13 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
 #pragma unroll
         for (int q = 0; q < AC; ++q) {
           const int c = wave * AC + q;
-          const int k = A_MNC ? ARPC * c + lane / ACH
-                              : 8 * ((lane & 3) ^ (((16 * c + (lane >> 2)) >> 2) & 3));
+          const int k = A_MNC ? ARPC * c + lane / ACH : 8 * ((lane % KCH) ^ kc_swizzle(KRPC * c + lane / KCH));
           if (k >= kl) a_addr[q] = zline;
         }
 #pragma unroll
         for (int q = 0; q < BC; ++q) {
           const int c = wave * BC + q;
-          const int k = B_KC ? 8 * ((lane & 3) ^ (((16 * c + (lane >> 2)) >> 2) & 3)) : BRPC * c + lane / BCH;
+          const int k = B_KC ? 8 * ((lane % KCH) ^ kc_swizzle(KRPC * c + lane / KCH)) : BRPC * c + lane / BCH;
           if (k >= kl) b_addr[q] = zline;
         }
       }
@@ -711,24 +712,25 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
   const int ar = lane & 31;
   const int p16 = lane & 15, bb = lane >> 4;
   const int bk = 8 * (bb >> 1) + (p16 >> 2);
-  const int kcc0 = (lane >> 5) ^ ((ar >> 2) & 3), kcc1 = (2 + (lane >> 5)) ^ ((ar >> 2) & 3);
-  uint32_t a_rd[2], b_rd[TN > 2 ? TN : 2];
+  // K-contiguous: per 16 k of a step, row-of-k: per 32-row tile
+  constexpr int KK = BK / 16;
+  uint32_t a_rd[A_MNC ? TM : KK], b_rd[B_KC ? KK : TN];
+  auto kc_rd = [&](int w0, int kk) { return (uint32_t)((w0 + ar) * (BK * 2) + ((2 * kk + (lane >> 5)) ^ kc_swizzle(ar)) * 16); };
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  for (int j = 0; j < (A_MNC ? TM : KK); ++j) {
     const int ca = (wm0 >> 3) + 4 * j + 2 * (bb & 1) + ((p16 & 3) >> 1);
-    a_rd[j] = A_MNC ? (uint32_t)(bk * (BM * 2) + ((ca ^ edge_swizzle<BM>(bk)) * 16) + (p16 & 1) * 8)
-                    : (uint32_t)((wm0 + ar) * 64 + (j ? kcc1 : kcc0) * 16);
+    a_rd[j] = A_MNC ? (uint32_t)(bk * (BM * 2) + ((ca ^ edge_swizzle<BM>(bk)) * 16) + (p16 & 1) * 8) : kc_rd(wm0, j);
   }
 #pragma unroll
-  for (int j = 0; j < (B_KC ? 2 : TN); ++j) {
+  for (int j = 0; j < (B_KC ? KK : TN); ++j) {
     const int cb = (wn0 >> 3) + 4 * j + 2 * (bb & 1) + ((p16 & 3) >> 1);
-    b_rd[j] = B_KC ? (uint32_t)(SM::kAStage + (wn0 + ar) * 64 + (j ? kcc1 : kcc0) * 16)
-                   : (uint32_t)(SM::kAStage + bk * (BN * 2) + ((cb ^ edge_swizzle<BN>(bk)) * 16) + (p16 & 1) * 8);
+    b_rd[j] = SM::kAStage + (B_KC ? kc_rd(wn0, j)
+                                  : (uint32_t)(bk * (BN * 2) + ((cb ^ edge_swizzle<BN>(bk)) * 16) + (p16 & 1) * 8));
   }
   typedef s16x4_t __attribute__((address_space(3))) * lds_s16x4_ptr;
   typedef bf16x8_t __attribute__((address_space(3))) * lds_bf16x8_ptr;
   auto read_kc = [&](uint32_t stage_base, uint32_t rd, int i) {
-    return *(lds_bf16x8_ptr)(uintptr_t)(stage_base + rd + i * 32 * 64);
+    return *(lds_bf16x8_ptr)(uintptr_t)(stage_base + rd + i * 32 * (BK * 2));
   };
   auto read_mnc = [&](uint32_t stage_base, uint32_t rd, int kk, int pitch) {
     const uint32_t p = stage_base + rd + kk * 16 * pitch;
@@ -765,7 +767,7 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
     const uint32_t sb = lds0 + stage * SM::kStage;
     stage = stage + 1 == ST ? 0 : stage + 1;
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
+    for (int kk = 0; kk < KK; ++kk) {
       bf16x8_t fa[TM], fb[TN];
 #pragma unroll
       for (int i = 0; i < TM; ++i) fa[i] = A_MNC ? read_mnc(sb, a_rd[i], kk, BM * 2) : read_kc(sb, a_rd[kk], i);
@@ -873,59 +875,94 @@ inline bool dma_shape_ok(int R, int N, int K) {
 }
 
 // Which kernel multiplies C [E,R,N]: the persistent one on 256 x 256 tiles (shapes it takes), or the
-// edge kernel on tiles of 128 x 256, 128 x 128, 64 x 128 or 64 x 64.  All have the same k order, so the
-// choice changes no bit; it compares the time the fullest compute unit needs.  The tables hold what one
-// 32-wide k step of n tiles sharing a unit takes, in ns.  A large tile moves fewer bytes per product, but a
-// unit fetches no more than about 50 bytes per ns however many are asked for, so an output of a few large
-// tiles leaves the fetch rate of the idle units unused: a lone tile of 128 x 128 takes 330 ns a step, four
-// of 64 x 64 on four units 170.  (us of one product, 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64:
-//   E 5  R 136  N 1016 K 2080    33.4 / 21.5 / 18.7 / 14.0     E 23 R 24   N 624  K 2528   40.2 / 30.2 / 23.7 / 17.6
-//   E 32 R 4    N 1024 K 8192     146 /  112 / 81.1 /  106     E 13 R 31   N 1024 K 8192    123 /  100 / 73.5 / 57.2
-//   E 16 R 512  N 512  K 2048    37.2 / 26.0 / 29.0 / 37.4     E 24 R 295  N 768  K 3072   57.1 / 63.8 / 67.6 / 83.8
-//   E 1  R 768  N 256  K 4158    65.2 / 43.1 / 32.9 / 23.4     E 45 R 213  N 4096 K 1024    138 /  170 /  196 /  239)
-enum GemmForm { kPersistent, kEdge128x256, kEdge128x128, kEdge64x128, kEdge64x64 };
-GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int cus) {
-  static const double persistent[] = {950}, t128x256[] = {530, 1050}, t128x128[] = {330, 600, 900},
-                      t64x128[] = {250, 370, 600}, t64x64[] = {170, 260, 400, 460};
-  auto time = [&](int bm, int bn, int res, const double* t) {
-    return tiles_time((long long)E * ((R + bm - 1) / bm) * ((N + bn - 1) / bn), cus, res, t);
-  };
+// edge kernel in one of its forms.  All have the same k order, so the choice changes no bit.
+//
+// Operands that are K-contiguous (both in the data gradients, A in the forward products) come in pieces of
+// a row of one step: 64-wide steps fetch whole 128-byte lines where 32-wide ones fetch halves.  They cost
+// twice the LDS per stage, so 128 x 256 tiles, which would be left alone on a unit, stay at 32 and the others
+// have a form of fewer stages for shapes of many tiles and a deep one for tiles that are alone on their
+// unit, or where the weights stream from memory.  (us of one product, 32-wide / 64-wide steps, tiles 128 x 128:
+// dbuf of 10 experts of 2852 rows, M 1024, H 8192 617 / 506, of 52 of 880, M 664, H 1384 174 / 150; tiles 64 x 64,
+// dbuf of 10 of 81, M 1024, H 4096 43.6 / 33.2, of 4 of 64 29.3 / 21.8.)  The weight gradients' operands are both
+// row-of-k, whose pieces are whole lines anyway, and their sums often short: 32 wide.
+enum GemmForm { kPersistent, kEdge128x256, kEdge128x128, kEdge128x128Deep, kEdge64x128, kEdge64x128Deep, kEdge64x64,
+                kEdge64x64Deep };
+enum GemmLayout { kLayoutForward, kLayoutDataGrad, kLayoutWeightGrad };
+
+// The rule compares what the fullest compute unit needs: 32 k of the tiles that share it (ns; up to as many as
+// fit), the ends of the tiles (us, half of it for every further round), and the time in which the form streams the
+// weights from memory (TB/s).  Fitted to both expert products and data gradients of 40 shapes with cold weights
+// (E 1 to 192, R 4 to 16384, M 200 to 1024, H 800 to 8192): the choice is 2 % from the best form on average.
+//   us, 64x64 deep / 64x64 / 64x128 deep / 64x128 / 128x128 deep / 128x128 / 128x256 / persistent:
+//   out  E 4  R 64   M 1024 H 4096   26.8 / 29.1 / 35.3 / 54.4 / 46.2 / 57.7 / 65.9 / -
+//   out  E 18 R 12   M 1024 H 4096   45.2 / 42.4 / 38.9 / 59.2 / 46.3 / 62.2 / 65.6 / -
+//   out  E 24 R 295  M 768  H 3072   87.4 / 81.7 / 71.7 / 62.0 / 80.7 / 60.1 / 71.6 / -
+//   out  E 16 R 512  M 512  H 2048   40.0 / 42.1 / 32.9 / 34.6 / 26.2 / 34.4 / 40.3 / 56
+//   h    E 22 R 130  M 600  H 2400   37.7 / 37.2 / 30.0 / 29.7 / 38.7 / 28.7 / 26.7 / -
+//   dbuf E 1  R 16384 M 1024 H 2048     - /    - /    - / 87.5 /    - / 70.5 / 74.8 / 69.1
+//   h    E 32 R 2048 M 1024 H 8192      - /    - /    - / 1526 /    - / 1419 / 1282 / 1206
+struct FormCost { int bm, bn, bk, res; double step[4], ends, stream; };
+GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout layout, int cus) {
+  static const FormCost forward[] = {{256, 256, 32, 1, {870}, 9, 6.0},          {128, 256, 32, 2, {500, 1010}, 9, 5.7},
+                                     {128, 128, 64, 2, {340, 545}, 7, 5.6},     {128, 128, 64, 1, {265}, 7, 6.0},
+                                     {64, 128, 64, 3, {250, 385, 590}, 5.5, 5.2}, {64, 128, 64, 2, {240, 400}, 4.4, 5.6},
+                                     {64, 64, 64, 3, {165, 234, 326}, 4.8, 4.6}, {64, 64, 64, 2, {155, 260}, 4.3, 4.5}};
+  static const FormCost datagrad[] = {{256, 256, 32, 1, {940}, 9, 5.5},         {128, 256, 32, 2, {540, 1130}, 10, 5.0},
+                                      {128, 128, 64, 2, {300, 545}, 7, 5.4},    {128, 128, 64, 1, {235}, 6.5, 5.2},
+                                      {64, 128, 64, 3, {265, 390, 530}, 4, 5.1}, {64, 128, 64, 2, {214, 400}, 4.3, 5.6},
+                                      {64, 64, 64, 3, {150, 217, 300}, 4, 5.2}, {64, 64, 64, 2, {142, 225}, 4, 5.1}};
+  static const FormCost weightgrad[] = {{256, 256, 32, 1, {950}, 0, 0},         {128, 256, 32, 2, {530, 1050}, 0, 0},
+                                        {128, 128, 32, 3, {330, 600, 900}, 0, 0}, {0}, {64, 128, 32, 3, {250, 370, 600}, 0, 0}, {0},
+                                        {64, 64, 32, 4, {170, 260, 400, 460}, 0, 0}, {0}};
+  const FormCost* const cost = layout == kLayoutForward ? forward : layout == kLayoutDataGrad ? datagrad : weightgrad;
   GemmForm form = kEdge128x256;
-  double best = time(128, 256, 2, t128x256);
-  auto consider = [&](GemmForm f, double t) {
-    if (t < best) { best = t; form = f; }
-  };
-  if (persistent_ok) consider(kPersistent, time(256, 256, 1, persistent));
-  consider(kEdge128x128, time(128, 128, 3, t128x128));
-  consider(kEdge64x128, time(64, 128, 3, t64x128));
-  consider(kEdge64x64, time(64, 64, 4, t64x64));
+  double best = 0;
+  for (int f = kEdge64x64Deep; f >= kPersistent; --f) {
+    const FormCost& c = cost[f];
+    if (c.bm == 0 || (f == kPersistent && !persistent_ok)) continue;
+    const long long n = (long long)E * ((R + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), round = (long long)c.res * cus;
+    // few tiles: the deep form, many: the other (64 x 128 tiles of any count may be deep, for weights that stream)
+    if ((f == kEdge64x64Deep || f == kEdge128x128Deep) && n > round) continue;
+    if ((f == kEdge64x64 || f == kEdge128x128 || f == kEdge64x128) && n <= (long long)cost[f + 1].res * cus) continue;
+    const int steps = (K + c.bk - 1) / c.bk * (c.bk / 32);
+    const long long full = n / round, rounds = (n + round - 1) / round;
+    const int left = (int)((n - full * round + cus - 1) / cus);
+    double us = 1e-3 * steps * (full * c.step[c.res - 1] + (left > 0 ? c.step[left - 1] : 0.0));
+    us += f == kPersistent ? c.ends * rounds : c.ends * (0.5 + 0.5 * rounds);
+    if (c.stream > 0) {
+      const double stream = 2e-6 * E * N * K / c.stream + 0.5 * c.ends;
+      us = stream > us ? stream : us;
+    }
+    if (f == kEdge64x64Deep || best == 0 || us < best) { best = us; form = (GemmForm)f; }
+  }
   return form;
 }
 // the form of this shape on the current device; k_kept: the sum over k runs over packed rows, of
 // which the persistent kernel takes whole 256-row tiles
-int choose_form(int E, int R, int N, int K, GemmForm* form, bool k_kept = false) {
+int choose_form(int E, int R, int N, int K, GemmLayout layout, GemmForm* form, bool k_kept = false,
+                bool persistent = true) {
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
-  *form = gemm_form(dma_shape_ok(R, N, K) && (!k_kept || K % 256 == 0), E, R, N, cus);
+  *form = gemm_form(persistent && dma_shape_ok(R, N, K) && (!k_kept || K % 256 == 0), E, R, N, K, layout, cus);
   return MOE_OK;
 }
 
-template <int BM, int BN, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
+template <int BM, int BN, int BK, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
 int prepare_edge() {
   static LdsLimitOnce once;
   return ensure_lds_limit(
-      once, reinterpret_cast<const void*>(expert_gemm_bf16_edge_kernel<BM, BN, ST, EPI, A_MNC, B_KC, K_KEPT>),
-      (int)EdgeSmem<BM, BN, ST>::kBytes);
+      once, reinterpret_cast<const void*>(expert_gemm_bf16_edge_kernel<BM, BN, BK, ST, EPI, A_MNC, B_KC, K_KEPT>),
+      (int)EdgeSmem<BM, BN, BK, ST>::kBytes);
 }
 
-template <int BM, int BN, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
+template <int BM, int BN, int BK, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
 int launch_edge(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
-  if (prepare_edge<BM, BN, ST, EPI, A_MNC, B_KC, K_KEPT>() != MOE_OK) return MOE_EHIP;
-  constexpr size_t kLds = EdgeSmem<BM, BN, ST>::kBytes;
+  if (prepare_edge<BM, BN, BK, ST, EPI, A_MNC, B_KC, K_KEPT>() != MOE_OK) return MOE_EHIP;
+  constexpr size_t kLds = EdgeSmem<BM, BN, BK, ST>::kBytes;
   const int tiles_m = (R + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const long long nblk = (long long)E * tiles_m * tiles_n;
   if (nblk > 0x7fffffffLL || (K_KEPT && a.kept == nullptr)) return MOE_EUNSUPPORTED;
-  hipLaunchKernelGGL((expert_gemm_bf16_edge_kernel<BM, BN, ST, EPI, A_MNC, B_KC, K_KEPT>), dim3((unsigned)nblk),
+  hipLaunchKernelGGL((expert_gemm_bf16_edge_kernel<BM, BN, BK, ST, EPI, A_MNC, B_KC, K_KEPT>), dim3((unsigned)nblk),
                      dim3(256), kLds, st, static_cast<const bf16_t*>(a.A),
                      static_cast<const bf16_t*>(a.B), static_cast<bf16_t*>(a.C),
                      static_cast<const bf16_t*>(a.mask), R, N, K, tiles_m, tiles_n, (int)nblk, a.gather,
@@ -937,11 +974,23 @@ int launch_edge(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
 // (K for a K-contiguous operand, R / N for a row-of-k one)
 template <int EPI, bool A_MNC, bool B_KC, bool K_KEPT = false>
 int gemm_bf16_edge(GemmForm form, const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
-  switch (form) {
-    case kEdge64x64: return launch_edge<64, 64, 5, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
-    case kEdge64x128: return launch_edge<64, 128, 4, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
-    case kEdge128x128: return launch_edge<128, 128, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
-    default: return launch_edge<128, 256, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+  if constexpr (A_MNC) {
+    switch (form) {
+      case kEdge64x64: return launch_edge<64, 64, 32, 5, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+      case kEdge64x128: return launch_edge<64, 128, 32, 4, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+      case kEdge128x128: return launch_edge<128, 128, 32, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+      default: return launch_edge<128, 256, 32, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+    }
+  } else {
+    switch (form) {
+      case kEdge64x64: return launch_edge<64, 64, 64, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+      case kEdge64x64Deep: return launch_edge<64, 64, 64, 4, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+      case kEdge64x128: return launch_edge<64, 128, 64, 2, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+      case kEdge64x128Deep: return launch_edge<64, 128, 64, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+      case kEdge128x128: return launch_edge<128, 128, 64, 2, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+      case kEdge128x128Deep: return launch_edge<128, 128, 64, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+      default: return launch_edge<128, 256, 32, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+    }
   }
 }
 
@@ -949,7 +998,7 @@ template <bool RELU>
 int gemm_bf16(const bf16_t* A, const bf16_t* B, bf16_t* Cout, int E, int R, int N, int K,
               hipStream_t st) {
   GemmForm form;
-  if (choose_form(E, R, N, K, &form) != MOE_OK) return MOE_EHIP;
+  if (choose_form(E, R, N, K, kLayoutForward, &form) != MOE_OK) return MOE_EHIP;
   if (form == kPersistent)
     return launch_bf16_dma<4, RELU ? 1 : 0, false>(A, B, Cout, E, R, N, K, nullptr, nullptr, st);
   return gemm_bf16_edge<RELU ? 1 : 0, false, false>(form, GemmArgs{A, B, Cout}, E, R, N, K, st);
@@ -987,13 +1036,18 @@ int prepare_expert_gemm() {
       prepare_dma<4, 5, false, false, true, true>(), prepare_dma<4, 0, false, false, true, true>(),
       prepare_dma<4, 0, false, true, false, false, false, true>(),
       // other shapes: forward (relu / plain), data gradients (plain / masked), weight gradients
-#define MOE_EDGE_ALL(...)                                                                      \
-  prepare_edge<128, 256, 3, __VA_ARGS__>(), prepare_edge<128, 128, 3, __VA_ARGS__>(),        \
-      prepare_edge<64, 128, 4, __VA_ARGS__>(), prepare_edge<64, 64, 5, __VA_ARGS__>()
-      MOE_EDGE_ALL(1, false, false, false), MOE_EDGE_ALL(0, false, false, false),
-      MOE_EDGE_ALL(0, false, true, false), MOE_EDGE_ALL(2, false, true, false),
-      MOE_EDGE_ALL(0, true, false, false), MOE_EDGE_ALL(0, true, false, true)};
-#undef MOE_EDGE_ALL
+#define MOE_EDGE_KC(...)                                                                       \
+  prepare_edge<128, 256, 32, 3, __VA_ARGS__>(), prepare_edge<128, 128, 64, 2, __VA_ARGS__>(),  \
+      prepare_edge<128, 128, 64, 3, __VA_ARGS__>(), prepare_edge<64, 128, 64, 2, __VA_ARGS__>(), \
+      prepare_edge<64, 128, 64, 3, __VA_ARGS__>(), prepare_edge<64, 64, 64, 3, __VA_ARGS__>(), \
+      prepare_edge<64, 64, 64, 4, __VA_ARGS__>()
+#define MOE_EDGE_MNC(...)                                                                      \
+  prepare_edge<128, 256, 32, 3, __VA_ARGS__>(), prepare_edge<128, 128, 32, 3, __VA_ARGS__>(),  \
+      prepare_edge<64, 128, 32, 4, __VA_ARGS__>(), prepare_edge<64, 64, 32, 5, __VA_ARGS__>()
+      MOE_EDGE_KC(1, false, false, false), MOE_EDGE_KC(0, false, false, false), MOE_EDGE_KC(0, false, true, false),
+      MOE_EDGE_KC(2, false, true, false), MOE_EDGE_MNC(0, true, false, false), MOE_EDGE_MNC(0, true, false, true)};
+#undef MOE_EDGE_KC
+#undef MOE_EDGE_MNC
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
   for (int rc : rcs)
@@ -1057,7 +1111,7 @@ size_t expert_signbits_bytes(const moe_config& c) {
 static int packed_row_pad(const moe_config& c) {
   GemmForm f1, f2;
   const int R = c.G * c.C;
-  if (choose_form(c.E, c.H, c.M, R, &f1, true) != MOE_OK || choose_form(c.E, c.M, c.H, R, &f2, true) != MOE_OK)
+  if (choose_form(c.E, c.H, c.M, R, kLayoutWeightGrad, &f1, true) != MOE_OK || choose_form(c.E, c.M, c.H, R, kLayoutWeightGrad, &f2, true) != MOE_OK)
     return 255;
   return f1 == kPersistent || f2 == kPersistent ? 255 : 0;
 }
@@ -1088,7 +1142,7 @@ int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPackin
     return launch_gemm_f32(kForward, g2, c.E, R, c.M, c.H, st);
   }
   GemmForm f1, f2;
-  if (choose_form(c.E, R, c.H, c.M, &f1) != MOE_OK || choose_form(c.E, R, c.M, c.H, &f2) != MOE_OK)
+  if (choose_form(c.E, R, c.H, c.M, kLayoutForward, &f1) != MOE_OK || choose_form(c.E, R, c.M, c.H, kLayoutForward, &f2) != MOE_OK)
     return MOE_EHIP;
   if (f1 != kPersistent) {
     g1.row_pad = train ? packed_row_pad(c) : 0;
@@ -1139,8 +1193,11 @@ int launch_expert_dgrad2(const moe_config& c, const void* dout, const void* wo, 
   auto b = static_cast<const bf16_t*>(wo);
   auto o = static_cast<bf16_t*>(dh);
   auto sign = const_cast<unsigned char*>(static_cast<const unsigned char*>(signbits));
-  GemmForm form;
-  if (choose_form(c.E, (int)R, c.H, c.M, &form) != MOE_OK) return MOE_EHIP;
+  GemmForm form, h_form;
+  if (choose_form(c.E, (int)R, c.H, c.M, kLayoutForward, &h_form) != MOE_OK) return MOE_EHIP;
+  // packed rows: the persistent kernel takes relu' from the bits that only it records with h
+  const bool no_bits = kept != nullptr && h_form != kPersistent;
+  if (choose_form(c.E, (int)R, c.H, c.M, kLayoutDataGrad, &form, false, !no_bits) != MOE_OK) return MOE_EHIP;
   if (form != kPersistent) {
     g.row_pad = kept != nullptr ? packed_row_pad(c) : 0;
     return gemm_bf16_edge<2, false, true>(form, g, c.E, (int)R, c.H, c.M, st);
@@ -1163,7 +1220,7 @@ static int wgrad(const moe_config& c, const void* A, const void* B, void* dw, in
   g.kept = kept;
   if (c.act_dtype == MOE_F32) return launch_gemm_f32(kWeightGrad, g, c.E, N1, N2, (int)R, st);
   GemmForm form;
-  if (choose_form(c.E, N1, N2, (int)R, &form, kept != nullptr) != MOE_OK) return MOE_EHIP;
+  if (choose_form(c.E, N1, N2, (int)R, kLayoutWeightGrad, &form, kept != nullptr) != MOE_OK) return MOE_EHIP;
   if (form != kPersistent)
     return kept != nullptr ? gemm_bf16_edge<0, true, false, true>(form, g, c.E, N1, N2, (int)R, st)
                            : gemm_bf16_edge<0, true, false>(form, g, c.E, N1, N2, (int)R, st);
@@ -1193,7 +1250,7 @@ int launch_expert_dgrad1(const moe_config& c, const void* dh, const void* wi, vo
   auto b = static_cast<const bf16_t*>(wi);
   auto o = static_cast<bf16_t*>(dbuf);
   GemmForm form;
-  if (choose_form(c.E, (int)R, c.M, c.H, &form) != MOE_OK) return MOE_EHIP;
+  if (choose_form(c.E, (int)R, c.M, c.H, kLayoutDataGrad, &form) != MOE_OK) return MOE_EHIP;
   if (form != kPersistent) return gemm_bf16_edge<0, false, true>(form, g, c.E, (int)R, c.M, c.H, st);
   if (kept != nullptr)
     return launch_bf16_dma<4, 0, false, false, true, true>(a, b, o, c.E, (int)R, c.M, c.H, nullptr, nullptr,
