@@ -280,7 +280,10 @@ int launch_layer_norm_bwd(int act_dtype, const void* s, const void* dn, const fl
 //   dqkv [B*L, 3*heads*d] from qkv, ctx, dctx [B*L, heads*d] and lse; dvec: [B*heads*L] scratch
 // dW [in,out] = X^T dY over rows tokens (X [rows,in], dY [rows,out]); partial: scratch of
 // dense_wgrad_partial_bytes() for the token ranges of the split (may be NULL: no split)
-int dense_wgrad_splits(int act_dtype, long long rows, int in, int out);
+struct DenseWgradPlan { int splits, k; };      // ranges, tokens of each (the last may be shorter)
+DenseWgradPlan dense_wgrad_plan(long long rows, int in, int out);     // expert_gemm.hip
+int launch_dense_wgrad_ranges(const DenseWgradPlan& p, long long rows, int in, int out, const void* X, const void* dY,
+                              float* partial, hipStream_t st);
 size_t dense_wgrad_partial_bytes(int act_dtype, long long rows, int in, int out);
 int launch_dense_wgrad(const moe_config& c, long long rows, int in, int out, const void* X,
                        const void* dY, void* dW, float* partial, hipStream_t st);

@@ -36,11 +36,12 @@ __global__ __launch_bounds__(256) void layer_norm_bwd_kernel(
 #pragma unroll
   for (int j = 0; j < VPL; ++j)
 #pragma unroll
-    for (int i = 0; i < K; ++i) {
-      ag[j][i] = 0.f;
-      ab[j][i] = 0.f;
-      const int col = (lane + 64 * j) * K + i;
-      gam[j][i] = col < M ? gamma[col] : 0.f;
+    for (int i = 0; i < K; i += 4) {
+      const int col = (lane + 64 * j) * K + i;                 // (M is a multiple of K)
+      const float4 g4 = col < M ? *reinterpret_cast<const float4*>(gamma + col) : float4{0.f, 0.f, 0.f, 0.f};
+      gam[j][i] = g4.x; gam[j][i + 1] = g4.y; gam[j][i + 2] = g4.z; gam[j][i + 3] = g4.w;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) ag[j][i + k] = ab[j][i + k] = 0.f;
     }
   const float inv_m = 1.0f / (float)M;
   for (long long row = wave_id; row < rows; row += waves) {
@@ -107,35 +108,54 @@ __global__ __launch_bounds__(256) void layer_norm_bwd_kernel(
 #pragma unroll
     for (int j = 0; j < VPL; ++j)
 #pragma unroll
-      for (int i = 0; i < K; ++i) {
+      for (int i = 0; i < K; i += 4) {
         const int col = (lane + 64 * j) * K + i;
-        if (col < M) mine[col] = which == 0 ? ag[j][i] : ab[j][i];
+        const float* a = which == 0 ? &ag[j][i] : &ab[j][i];
+        if (col < M) *reinterpret_cast<float4*>(mine + col) = float4{a[0], a[1], a[2], a[3]};
       }
     __syncthreads();
-    for (int i = threadIdx.x; i < M; i += 256)
-      pg[which * M + i] = ((ln_bwd_smem[i] + ln_bwd_smem[M + i]) + ln_bwd_smem[2 * M + i]) + ln_bwd_smem[3 * M + i];
+    for (int i = threadIdx.x * 4; i < M; i += 1024) {
+      float4 t = *reinterpret_cast<const float4*>(ln_bwd_smem + i);
+#pragma unroll
+      for (int w = 1; w < 4; ++w) {
+        const float4 o = *reinterpret_cast<const float4*>(ln_bwd_smem + w * M + i);
+        t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
+      }
+      *reinterpret_cast<float4*>(pg + which * M + i) = t;
+    }
     __syncthreads();
   }
 }
 
 // dgamma[m] = sum_p partial[p][0][m], dbeta[m] = sum_p partial[p][1][m]: a block owns 16 of the
-// 2 M columns, its 16 groups of 16 threads each sum every 16th partial row, LDS adds the groups
-// in a fixed order (bit-reproducible)
-__global__ __launch_bounds__(256) void layer_norm_param_reduce_kernel(
+// 2 M columns, its 64 groups of 16 threads each sum every 64th partial row, LDS adds the groups
+// in a fixed order (bit-reproducible).  Bound by the latency of a thread's dependent loads, so many short
+// chains with the loads of eight rows in flight: 1024 partial rows, M 1024 20.6 -> 5.2 us (16 groups before).
+constexpr int kReduceGroups = 64;
+__global__ __launch_bounds__(16 * kReduceGroups) void layer_norm_param_reduce_kernel(
     const float* __restrict__ partial, int parts, int M, float* __restrict__ dgamma,
     float* __restrict__ dbeta) {
-  __shared__ float red[16][17];
+  __shared__ float red[kReduceGroups][17];
   const int c = threadIdx.x & 15, pl = threadIdx.x >> 4;
   const int i = blockIdx.x * 16 + c;
   float acc = 0.f;
-  if (i < 2 * M)
-    for (int p = pl; p < parts; p += 16) acc += partial[(size_t)p * 2 * M + i];
+  if (i < 2 * M) {
+#pragma unroll 8
+    for (int p = pl; p < parts; p += kReduceGroups) acc += partial[(size_t)p * 2 * M + i];
+  }
   red[pl][c] = acc;
+  __syncthreads();
+  if (pl < 8) {
+    float t = 0.f;
+#pragma unroll
+    for (int k = 0; k < kReduceGroups / 8; ++k) t += red[pl * (kReduceGroups / 8) + k][c];
+    red[pl * (kReduceGroups / 8)][c] = t;                      // (its own rows only)
+  }
   __syncthreads();
   if (pl == 0 && i < 2 * M) {
     float t = 0.f;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) t += red[k][c];
+    for (int k = 0; k < 8; ++k) t += red[k * (kReduceGroups / 8)][c];
     if (i < M) dgamma[i] = t; else dbeta[i - M] = t;
   }
 }
@@ -273,45 +293,29 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 
 }  // namespace
 
-// Weight gradient of a dense layer, dW [in,out] = X^T dY over `rows` tokens.  Its output has
-// few 256 x 256 tiles (in/256 * out/256) but a very long K (the tokens), so the persistent GEMM
-// alone would leave most compute units idle: the tokens are cut into `splits` ranges that run
-// as a batch with fp32 results, and one pass adds the ranges in order and rounds once.
-// The plan picks the number of ranges that fills the 256 compute units best.
-int dense_wgrad_splits(int act_dtype, long long rows, int in, int out) {
-  if (act_dtype != MOE_BF16 || in % 256 != 0 || out % 256 != 0) return 1;
-  const long long tiles = (long long)(in / 256) * (out / 256);
-  int best = 1;
-  double best_fill = 0.0;
-  for (int sp = 1; sp <= 16; sp *= 2) {
-    if (rows % sp != 0 || (rows / sp) % 32 != 0 || rows / sp < 512) break;
-    if (!gemm_bf16_f32out_ok(in, out, (int)(rows / sp))) continue;
-    const long long t = tiles * sp;
-    const double fill = (double)t / (double)((t + 255) / 256 * 256);
-    if (fill > best_fill + 1e-9) { best_fill = fill; best = sp; }
-  }
-  return best;
-}
-
+// Weight gradient of a dense layer, dW [in,out] = X^T dY over `rows` tokens.  Its output has few tiles but a very
+// long K (the tokens), so one product alone would leave most compute units idle: the tokens are cut into ranges
+// (dense_wgrad_plan) that run as a batch with fp32 results, and one pass adds the ranges in order and rounds once.
 size_t dense_wgrad_partial_bytes(int act_dtype, long long rows, int in, int out) {
-  const int sp = dense_wgrad_splits(act_dtype, rows, in, out);
+  if (act_dtype != MOE_BF16 || rows > 0x7fffffffLL) return 0;
+  const int sp = dense_wgrad_plan(rows, in, out).splits;
   return sp > 1 ? (size_t)sp * in * out * sizeof(float) : 0;
 }
 
 int launch_dense_wgrad(const moe_config& c, long long rows, int in, int out, const void* X,
                        const void* dY, void* dW, float* partial, hipStream_t st) {
   if (rows > 0x7fffffffLL) return MOE_EUNSUPPORTED;
-  const int sp = dense_wgrad_splits(c.act_dtype, rows, in, out);
-  if (sp <= 1 || partial == nullptr) {
+  const DenseWgradPlan plan = c.act_dtype == MOE_BF16 ? dense_wgrad_plan(rows, in, out) : DenseWgradPlan{1, (int)rows};
+  if (plan.splits <= 1 || partial == nullptr) {
     moe_config g = c;
     g.E = 1; g.G = 1; g.C = (int)rows; g.M = in; g.H = out;
     return launch_expert_wgrad1(g, X, dY, dW, nullptr, st);
   }
-  const int rc = launch_gemm_bf16_f32out(true, X, dY, partial, sp, in, out, (int)(rows / sp), st);
+  const int rc = launch_dense_wgrad_ranges(plan, rows, in, out, X, dY, partial, st);
   if (rc != MOE_OK) return rc;
   const long long elems = (long long)in * out;
   hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((elems / 8 + 255) / 256)), dim3(256), 0, st,
-                     partial, sp, elems, static_cast<uint4*>(dW));
+                     partial, plan.splits, elems, static_cast<uint4*>(dW));
   return check_launch();
 }
 
@@ -346,7 +350,7 @@ int launch_layer_norm_bwd(int act_dtype, const void* s, const void* dn, const fl
 #undef MOE_LNB_CASE
   int rc = check_launch();
   if (rc != MOE_OK) return rc;
-  hipLaunchKernelGGL(layer_norm_param_reduce_kernel, dim3((unsigned)((2 * M + 15) / 16)), dim3(256),
+  hipLaunchKernelGGL(layer_norm_param_reduce_kernel, dim3((unsigned)((2 * M + 15) / 16)), dim3(16 * kReduceGroups),
                      0, st, partial, parts, M, dgamma, dbeta);
   return check_launch();
 }

@@ -558,7 +558,8 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
 //         the persistent kernel's DYNK sums run over.  K_KEPT: kept[e] limits the sum over k instead
 //         (weight gradients).
 // scatter: NULL, or row p of expert e goes to the absolute row scatter[e R + p] of C.
-// EPI: 0 plain, 1 relu, 2 zero every element whose `mask` element (same index as C) is <= 0.
+// EPI: 0 plain, 1 relu, 2 zero every element whose `mask` element (same index as C) is <= 0, 3 plain with an
+// fp32 result, "expert" e summing the k from e K on, up to k_total in all (row-of-k operands).
 //
 // The k order of a sum is the persistent kernel's, so a layer gets the same bits from either.
 //
@@ -592,7 +593,8 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ Cout,
     const bf16_t* __restrict__ mask, int R, int N, int K, int tiles_m, int tiles_n, int nblk,
     const int32_t* __restrict__ gather, const int32_t* __restrict__ kept,
-    int row_pad, const int32_t* __restrict__ scatter) {
+    int row_pad, const int32_t* __restrict__ scatter, int k_total) {
+  static_assert(EPI != 3 || (A_MNC && !B_KC && !K_KEPT), "ranges of k: of row-of-k operands");
   using SM = EdgeSmem<BM, BN, BK, ST>;
   constexpr int TM = BM / 64, TN = BN / 64;
   constexpr int WN = BN / 2;                                   // columns of a wavefront tile
@@ -624,7 +626,8 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
     rows_out = rows_out < R ? rows_out : R;
   }
   if (m0 >= rows_out) return;                                  // block-uniform
-  const int KE = K_KEPT ? kept[e] : K;                         // length of the sum
+  int KE = K_KEPT ? kept[e] : K;                               // length of the sum
+  if (EPI == 3) KE = k_total - e * K < K ? k_total - e * K : K;
   const int KT = (KE + BK - 1) / BK;
 
   // Per-lane source addresses of the copies and their advance per K step (0 for a lane that reads
@@ -780,6 +783,25 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
     }
   }
+  if (EPI == 3) {                                              // a lane owns four consecutive columns of a row
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    float* const Cf = reinterpret_cast<float*>(Cout) + (size_t)e * R * N;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int row = m0 + wm0 + 32 * i + (lane & 31);
+      if (row >= R) continue;
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int col = n0 + wn0 + 32 * j + 8 * q + 4 * (lane >> 5);
+          if (col < N)
+            *reinterpret_cast<f32x4_t*>(Cf + (size_t)row * N + col) =
+                f32x4_t{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+        }
+    }
+    return;
+  }
   __syncthreads();                                             // the stages are free
 
   // acc[i][j][4 q + r] = C[32 i + r32][32 j + 8 q + 4 h + r] of the wavefront tile: 32 rows at a time
@@ -891,8 +913,8 @@ enum GemmLayout { kLayoutForward, kLayoutDataGrad, kLayoutWeightGrad };
 
 // The rule compares what the fullest compute unit needs: 32 k of the tiles that share it (ns; up to as many as
 // fit), the ends of the tiles (us, half of it for every further round), and the time in which the form streams the
-// weights from memory (TB/s).  Fitted to both expert products and data gradients of 40 shapes with cold weights
-// (E 1 to 192, R 4 to 16384, M 200 to 1024, H 800 to 8192): the choice is 2 % from the best form on average.
+// weights from memory (TB/s).  Fitted to the six products of 40 shapes with cold weights
+// (E 1 to 192, R 4 to 16384, M 200 to 1024, H 800 to 8192): the choice is 1 to 2 % from the best form on average.
 //   us, 64x64 deep / 64x64 / 64x128 deep / 64x128 / 128x128 deep / 128x128 / 128x256 / persistent:
 //   out  E 4  R 64   M 1024 H 4096   26.8 / 29.1 / 35.3 / 54.4 / 46.2 / 57.7 / 65.9 / -
 //   out  E 18 R 12   M 1024 H 4096   45.2 / 42.4 / 38.9 / 59.2 / 46.3 / 62.2 / 65.6 / -
@@ -902,7 +924,7 @@ enum GemmLayout { kLayoutForward, kLayoutDataGrad, kLayoutWeightGrad };
 //   dbuf E 1  R 16384 M 1024 H 2048     - /    - /    - / 87.5 /    - / 70.5 / 74.8 / 69.1
 //   h    E 32 R 2048 M 1024 H 8192      - /    - /    - / 1526 /    - / 1419 / 1282 / 1206
 struct FormCost { int bm, bn, bk, res; double step[4], ends, stream; };
-GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout layout, int cus) {
+GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout layout, int cus, double* time = nullptr) {
   static const FormCost forward[] = {{256, 256, 32, 1, {870}, 9, 6.0},          {128, 256, 32, 2, {500, 1010}, 9, 5.7},
                                      {128, 128, 64, 2, {340, 545}, 7, 5.6},     {128, 128, 64, 1, {265}, 7, 6.0},
                                      {64, 128, 64, 3, {250, 385, 590}, 5.5, 5.2}, {64, 128, 64, 2, {240, 400}, 4.4, 5.6},
@@ -911,9 +933,10 @@ GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout la
                                       {128, 128, 64, 2, {300, 545}, 7, 5.4},    {128, 128, 64, 1, {235}, 6.5, 5.2},
                                       {64, 128, 64, 3, {265, 390, 530}, 4, 5.1}, {64, 128, 64, 2, {214, 400}, 4.3, 5.6},
                                       {64, 64, 64, 3, {150, 217, 300}, 4, 5.2}, {64, 64, 64, 2, {142, 225}, 4, 5.1}};
-  static const FormCost weightgrad[] = {{256, 256, 32, 1, {950}, 0, 0},         {128, 256, 32, 2, {530, 1050}, 0, 0},
-                                        {128, 128, 32, 3, {330, 600, 900}, 0, 0}, {0}, {64, 128, 32, 3, {250, 370, 600}, 0, 0}, {0},
-                                        {64, 64, 32, 4, {170, 260, 400, 460}, 0, 0}, {0}};
+  static const FormCost weightgrad[] = {{256, 256, 32, 1, {870}, 12, 0},        {128, 256, 32, 2, {500, 1060}, 10, 0},
+                                        {128, 128, 32, 3, {290, 550, 810}, 5, 0}, {0},
+                                        {64, 128, 32, 3, {230, 350, 530}, 4.5, 0}, {0},
+                                        {64, 64, 32, 4, {170, 230, 330, 400}, 4, 0}, {0}};
   const FormCost* const cost = layout == kLayoutForward ? forward : layout == kLayoutDataGrad ? datagrad : weightgrad;
   GemmForm form = kEdge128x256;
   double best = 0;
@@ -928,13 +951,14 @@ GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout la
     const long long full = n / round, rounds = (n + round - 1) / round;
     const int left = (int)((n - full * round + cus - 1) / cus);
     double us = 1e-3 * steps * (full * c.step[c.res - 1] + (left > 0 ? c.step[left - 1] : 0.0));
-    us += f == kPersistent ? c.ends * rounds : c.ends * (0.5 + 0.5 * rounds);
+    us += c.ends * (f != kPersistent ? 0.5 + 0.5 * rounds : layout == kLayoutWeightGrad ? 0.625 + 0.375 * rounds : 1.0 * rounds);
     if (c.stream > 0) {
       const double stream = 2e-6 * E * N * K / c.stream + 0.5 * c.ends;
       us = stream > us ? stream : us;
     }
     if (f == kEdge64x64Deep || best == 0 || us < best) { best = us; form = (GemmForm)f; }
   }
+  if (time != nullptr) *time = best;
   return form;
 }
 // the form of this shape on the current device; k_kept: the sum over k runs over packed rows, of
@@ -956,7 +980,7 @@ int prepare_edge() {
 }
 
 template <int BM, int BN, int BK, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
-int launch_edge(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
+int launch_edge(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st, int k_total = 0) {
   if (prepare_edge<BM, BN, BK, ST, EPI, A_MNC, B_KC, K_KEPT>() != MOE_OK) return MOE_EHIP;
   constexpr size_t kLds = EdgeSmem<BM, BN, BK, ST>::kBytes;
   const int tiles_m = (R + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -966,20 +990,20 @@ int launch_edge(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
                      dim3(256), kLds, st, static_cast<const bf16_t*>(a.A),
                      static_cast<const bf16_t*>(a.B), static_cast<bf16_t*>(a.C),
                      static_cast<const bf16_t*>(a.mask), R, N, K, tiles_m, tiles_n, (int)nblk, a.gather,
-                     a.kept, a.row_pad, a.scatter);
+                     a.kept, a.row_pad, a.scatter, k_total);
   return check_launch();
 }
 
 // C [E,R,N] for any R, N, K with N % 8 == 0 and the operands' contiguous dimensions % 8 == 0
 // (K for a K-contiguous operand, R / N for a row-of-k one)
 template <int EPI, bool A_MNC, bool B_KC, bool K_KEPT = false>
-int gemm_bf16_edge(GemmForm form, const GemmArgs& a, int E, int R, int N, int K, hipStream_t st) {
+int gemm_bf16_edge(GemmForm form, const GemmArgs& a, int E, int R, int N, int K, hipStream_t st, int k_total = 0) {
   if constexpr (A_MNC) {
     switch (form) {
-      case kEdge64x64: return launch_edge<64, 64, 32, 5, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
-      case kEdge64x128: return launch_edge<64, 128, 32, 4, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
-      case kEdge128x128: return launch_edge<128, 128, 32, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
-      default: return launch_edge<128, 256, 32, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
+      case kEdge64x64: return launch_edge<64, 64, 32, 5, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st, k_total);
+      case kEdge64x128: return launch_edge<64, 128, 32, 4, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st, k_total);
+      case kEdge128x128: return launch_edge<128, 128, 32, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st, k_total);
+      default: return launch_edge<128, 256, 32, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st, k_total);
     }
   } else {
     switch (form) {
@@ -1045,7 +1069,8 @@ int prepare_expert_gemm() {
   prepare_edge<128, 256, 32, 3, __VA_ARGS__>(), prepare_edge<128, 128, 32, 3, __VA_ARGS__>(),  \
       prepare_edge<64, 128, 32, 4, __VA_ARGS__>(), prepare_edge<64, 64, 32, 5, __VA_ARGS__>()
       MOE_EDGE_KC(1, false, false, false), MOE_EDGE_KC(0, false, false, false), MOE_EDGE_KC(0, false, true, false),
-      MOE_EDGE_KC(2, false, true, false), MOE_EDGE_MNC(0, true, false, false), MOE_EDGE_MNC(0, true, false, true)};
+      MOE_EDGE_KC(2, false, true, false), MOE_EDGE_MNC(0, true, false, false), MOE_EDGE_MNC(0, true, false, true),
+      MOE_EDGE_MNC(3, true, false, false)};
 #undef MOE_EDGE_KC
 #undef MOE_EDGE_MNC
   int cus = 0;
@@ -1168,6 +1193,33 @@ int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPackin
   return launch_bf16_dma<4, 0, false, false, false, true, false>(
       static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(wo), static_cast<bf16_t*>(out), c.E, R,
       c.M, c.H, nullptr, nullptr, st, nullptr, nullptr, pk.kept);
+}
+
+// dW [in,out] = X^T dY over rows tokens: few tiles and a long sum.  The ranges run as a batch with fp32 results,
+// at the rule's time for that batch, and adding them up costs a launch and their bytes at about 6 TB/s (they
+// are in the last-level cache).
+DenseWgradPlan dense_wgrad_plan(long long rows, int in, int out) {
+  DenseWgradPlan best{1, (int)rows};
+  double best_us = 0;
+  for (int want = 1; want <= 16; want += want < 4 ? 1 : want < 8 ? 2 : 4) {
+    const int k = (int)(((rows + want - 1) / want + 31) / 32 * 32), sp = (int)((rows + k - 1) / k);
+    if (want > 1 && (k < 128 || sp < want)) continue;
+    const bool persistent = dma_shape_ok(in, out, k) && (long long)sp * k == rows;
+    double us = 0;
+    gemm_form(persistent, sp, in, out, sp == 1 ? (int)rows : k, kLayoutWeightGrad, 256, &us);
+    if (sp > 1) us += 3.0 + 4e-6 * sp * in * out / 6.0;
+    if (want == 1 || us < best_us) { best_us = us; best = DenseWgradPlan{sp, sp == 1 ? (int)rows : k}; }
+  }
+  return best;
+}
+
+// the batch of the plan: partial [splits, in, out]
+int launch_dense_wgrad_ranges(const DenseWgradPlan& p, long long rows, int in, int out, const void* X, const void* dY,
+                              float* partial, hipStream_t st) {
+  const bool persistent = dma_shape_ok(in, out, p.k) && (long long)p.splits * p.k == rows;
+  const GemmForm form = gemm_form(persistent, p.splits, in, out, p.k, kLayoutWeightGrad, 256);
+  if (form == kPersistent) return launch_gemm_bf16_f32out(true, X, dY, partial, p.splits, in, out, p.k, st);
+  return gemm_bf16_edge<3, true, false>(form, GemmArgs{X, dY, partial}, p.splits, in, out, p.k, st, (int)rows);
 }
 
 int launch_expert_gemm2(const moe_config& c, const void* h, const void* wo, void* out,
