@@ -7,8 +7,8 @@
 //
 // bf16, v_mfma_f32_32x32x16_bf16 with fp32 accumulation, in two kernels:
 //
-//   expert_gemm_bf16_dma_kernel   shapes made of whole 256x256 tiles with K % 32 == 0
-//     (the large layers): persistent, one block per CU walks its share of the
+//   expert_gemm_bf16_dma_kernel   column counts of whole 256-wide tiles with K % 32 == 0, any
+//     number of rows of a K-contiguous operand (the large layers): persistent, one block per CU walks its share of the
 //     tiles as one stream of K steps; operands travel global -> LDS without passing
 //     the registers; either operand in either layout; gathered rows, packed rows,
 //     scattered result rows and a per-expert k range as template options.
@@ -43,7 +43,7 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblk) {
 }
 
 // ----------------------------------------------------------------------------
-// Exact 256x256 tiles: a persistent kernel (one block per CU) that walks its share
+// 256x256 tiles: a persistent kernel (one block per CU) that walks its share
 // of the tiles as ONE stream of 32-wide K steps.
 //
 // Global -> LDS copies bypass the registers (global_load_lds_dwordx4), ST stages of
@@ -104,9 +104,13 @@ struct DmaSmem {
 // block's tile numbers only grow it finds a tile's expert by stepping a cursor forward.  Rows
 // from kept[e] to the end of the last tile are multiplied as zero rows.  SCATTER (with PACKED):
 // the rows of C go to the absolute rows src_token[e * R + p] of Cout ([rows, N]), -1 = not stored.
+// ROWS: R is no multiple of 256.  The last row tile of an expert reads its last row in place of those past it and
+// does not store them.  Before, such layers ran 128 x 256 tiles of the edge kernel (us, before / after): 16 000 rows,
+// 1024 x 6144 264 / 240, 2048 x 1024 81 / 66; out and dbuf of 10 experts of 2852 rows, M 1024, H 8192 540 / 482
+// and 591 / 518, dh 671 / 584.
 // DYNK: the sum over k of expert e stops at 256 ceil(kept[e] / 256) instead of K (the weight
 // gradients, whose k runs over an expert's packed rows); an expert with no rows gets zeros.
-template <int ST, int EPI, bool GATHER, bool A_MNC, bool B_KC, bool PACKED, bool SCATTER, bool DYNK>
+template <int ST, int EPI, bool GATHER, bool A_MNC, bool B_KC, bool PACKED, bool SCATTER, bool DYNK, bool ROWS>
 __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ Cout,
     int R, int N, int K, int tiles_m, int tiles_n, int ntiles_static,
@@ -116,6 +120,7 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
   static_assert(!GATHER || PACKED, "gathered rows are packed rows");
   static_assert(!SCATTER || (PACKED && EPI == 0), "scattered rows: plain bf16 result of a packed launch");
   static_assert(!(DYNK && (PACKED || GATHER)), "a shortened k range comes with the full list of output tiles");
+  static_assert(!ROWS || !(A_MNC || SCATTER || DYNK || EPI == 3), "rows of a K-contiguous A and of C");
   constexpr bool RELU = EPI == 1 || EPI == 4;
   using SM = DmaSmem<ST>;
   constexpr int BM = 256, BN = 256, BK = 32, TM = 4, TN = 4;
@@ -210,7 +215,7 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
 #define MOE_DMA_STEPS(e_) (DYNK ? ((kept_s[e_] + 255) >> 8) * (256 / BK) : KT)
 
   // per-lane source byte offsets of the 4 + 4 copy instructions of this wavefront
-  uint32_t a_voff[4], b_voff[4];
+  uint32_t a_voff[4], b_voff[4], a_last[4];                    // a_last: of the tile being copied (ROWS)
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int row = 16 * (wave * 4 + q) + (lane >> 2);
@@ -238,8 +243,9 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
   {                                                                                          \
     MOE_DMA_TILE(TILE, pcur, e_, rt_, ct_)                                                   \
     (void)ct_;                                                                               \
-    const uint64_t ta_ = (uint64_t)(uintptr_t)(                                              \
-        src_token + (size_t)e_ * R + (size_t)rt_ * BM + 64 * wave + lane);                   \
+    int p_ = rt_ * BM + 64 * wave + lane;                                                    \
+    if (ROWS) p_ = p_ < R ? p_ : R - 1;                                                      \
+    const uint64_t ta_ = (uint64_t)(uintptr_t)(src_token + (size_t)e_ * R + p_);             \
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"            \
                  :: "s"(lds_tok), "v"(ta_) : "memory");                                      \
   }
@@ -258,7 +264,8 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"            \
                :: "s"(LDS_U32), "v"(ADDR_U64) : "memory")
 #define MOE_DMA_COPY_A(LDS_U32, q)                                                           \
-  if (GATHER) { MOE_DMA16_ADDR(LDS_U32, a_addr[q]); } else { MOE_DMA16(LDS_U32, a_voff[q], p_a); }
+  if (GATHER) { MOE_DMA16_ADDR(LDS_U32, a_addr[q]); }                                         \
+  else { MOE_DMA16(LDS_U32, (ROWS ? a_last[q] : a_voff[q]), p_a); }
 #define MOE_DMA_SET_SOURCES()                                                                \
   {                                                                                          \
     if (DYNK) {                                 /* pass over tiles without a single k step */ \
@@ -270,7 +277,15 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
       p_steps = __builtin_amdgcn_readfirstlane(MOE_DMA_STEPS(e_));                           \
       if (GATHER) MOE_DMA_GATHER_ROWS(e_, rt_ * BM)                                          \
       else if (A_MNC) p_a = A + (size_t)e_ * K * R + (size_t)rt_ * BM;                       \
-      else p_a = A + ((size_t)e_ * R + (size_t)rt_ * BM) * K;                                \
+      else {                                                                                 \
+        p_a = A + ((size_t)e_ * R + (size_t)rt_ * BM) * K;                                   \
+        if (ROWS) {                                                                          \
+          _Pragma("unroll") for (int q = 0; q < 4; ++q) {                                    \
+            const int row_ = 16 * (wave * 4 + q) + (lane >> 2), past_ = row_ - (R - 1 - rt_ * BM); \
+            a_last[q] = a_voff[q] - (past_ > 0 ? (uint32_t)(past_ * K * 2) : 0u);            \
+          }                                                                                  \
+        }                                                                                    \
+      }                                                                                      \
       if (B_KC) p_b = B + ((size_t)e_ * N + (size_t)ct_ * BN) * K;                           \
       else p_b = B + (size_t)e_ * K * N + (size_t)ct_ * BN;                                  \
     }                                                                                        \
@@ -431,6 +446,12 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
     const int m0 = rt * BM, n0 = ct * BN;
     const size_t c_off = ((size_t)e * R + m0 + wm0) * N + n0 + wn0;
     bf16_t* Ce = Cout + c_off;
+    // ROWS: stores past the wavefront's last row are past the end of this buffer, and dropped there (branches
+    // around them cost registers that the K loop does not have)
+    const int rows_left = R - m0 - wm0 < 128 ? R - m0 - wm0 : 128;
+    __amdgpu_buffer_rsrc_t c_rsrc;
+    if (ROWS)
+      c_rsrc = __builtin_amdgcn_make_buffer_rsrc(Ce, 0, rows_left > 0 ? ((rows_left - 1) * N + 128) * 2 : 0, 0x00027000);
     const uint32_t st_base = lds0 + (stage == 0 ? ST - 1 : stage - 1) * SM::kStage + wave * 8192;
     const int r32 = lane & 31, hh = lane >> 5;
     const uint32_t st_wr = st_base + r32 * 256 + 8 * (hh ^ (r32 >> 4));
@@ -471,9 +492,12 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
       u32x4_t mk[8];
       if (EPI == 2) {
 #pragma unroll
-        for (int ps = 0; ps < 8; ++ps)
+        for (int ps = 0; ps < 8; ++ps) {
+          int mrow = m0 + wm0 + 32 * i + 4 * ps + (lane >> 4);
+          if (ROWS) mrow = mrow < R ? mrow : R - 1;            // (the result of such a row is not stored)
           mk[ps] = *reinterpret_cast<const u32x4_t*>(
-              mask + c_off + (size_t)(32 * i + 4 * ps + (lane >> 4)) * N + 8 * (lane & 15));
+              mask + ((size_t)e * R + mrow) * N + n0 + wn0 + 8 * (lane & 15));
+        }
       }
 #pragma unroll
       for (int j = 0; j < TN; ++j)
@@ -510,6 +534,8 @@ __global__ __launch_bounds__(256) void expert_gemm_bf16_dma_kernel(
         if (SCATTER) {
           if (drow[ps] >= 0)
             *reinterpret_cast<u32x4_t*>(Cout + (size_t)drow[ps] * N + n0 + wn0 + 8 * c) = d;
+        } else if (ROWS) {
+          __builtin_amdgcn_raw_buffer_store_b128(d, c_rsrc, ((32 * i + rr) * N + 8 * c) * 2, 0, 0);
         } else {
           *reinterpret_cast<u32x4_t*>(Ce + (size_t)(32 * i + rr) * N + 8 * c) = d;
         }
@@ -852,22 +878,20 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
 // LDS limit of one instantiation of the persistent kernel on the current device (all of the
 // 160 KB when the size depends on the number of experts)
 template <int ST, int EPI, bool GATHER, bool A_MNC = false, bool B_KC = false, bool PACKED = false,
-          bool SCATTER = false, bool DYNK = false>
+          bool SCATTER = false, bool DYNK = false, bool ROWS = false>
 int prepare_dma() {
   static LdsLimitOnce once;
   constexpr int kFixed = (int)DmaSmem<ST>::kBytes + (GATHER ? 1024 : 0) + (EPI == 5 ? 8192 : 0);
   return ensure_lds_limit(
       once, reinterpret_cast<const void*>(
-                expert_gemm_bf16_dma_kernel<ST, EPI, GATHER, A_MNC, B_KC, PACKED, SCATTER, DYNK>),
+                expert_gemm_bf16_dma_kernel<ST, EPI, GATHER, A_MNC, B_KC, PACKED, SCATTER, DYNK, ROWS>),
       PACKED || DYNK ? 160 * 1024 : kFixed);
 }
 
-template <int ST, int EPI, bool GATHER, bool A_MNC = false, bool B_KC = false, bool PACKED = false,
-          bool SCATTER = false, bool DYNK = false>
-int launch_bf16_dma(const bf16_t* A, const bf16_t* B, bf16_t* Cout, int E, int R, int N, int K,
-                    const int32_t* src_token, const bf16_t* zero_row, hipStream_t st,
-                    const bf16_t* mask = nullptr, unsigned char* signbits = nullptr,
-                    const int32_t* kept = nullptr) {
+template <int ST, int EPI, bool GATHER, bool A_MNC, bool B_KC, bool PACKED, bool SCATTER, bool DYNK, bool ROWS>
+int launch_bf16_dma_rows(const bf16_t* A, const bf16_t* B, bf16_t* Cout, int E, int R, int N, int K,
+                         const int32_t* src_token, const bf16_t* zero_row, hipStream_t st,
+                         const bf16_t* mask, unsigned char* signbits, const int32_t* kept) {
   using SM = DmaSmem<ST>;
   static_assert(!(GATHER && EPI == 5), "the two users of the spare LDS exclude each other");
   // PACKED / DYNK: 2 E + 1 more integers of LDS (row counts and running tile counts of the experts)
@@ -875,12 +899,12 @@ int launch_bf16_dma(const bf16_t* A, const bf16_t* B, bf16_t* Cout, int E, int R
                       (PACKED || DYNK ? align_up(((size_t)2 * E + 1) * sizeof(int32_t), 16) : 0);
   if (kLds > 160 * 1024) return MOE_EUNSUPPORTED;
   if ((PACKED || DYNK) && kept == nullptr) return MOE_EINVAL;
-  auto kern = expert_gemm_bf16_dma_kernel<ST, EPI, GATHER, A_MNC, B_KC, PACKED, SCATTER, DYNK>;
+  auto kern = expert_gemm_bf16_dma_kernel<ST, EPI, GATHER, A_MNC, B_KC, PACKED, SCATTER, DYNK, ROWS>;
   int cus = 0;
-  if (prepare_dma<ST, EPI, GATHER, A_MNC, B_KC, PACKED, SCATTER, DYNK>() != MOE_OK ||
+  if (prepare_dma<ST, EPI, GATHER, A_MNC, B_KC, PACKED, SCATTER, DYNK, ROWS>() != MOE_OK ||
       compute_units(&cus) != MOE_OK)
     return MOE_EHIP;
-  const int tiles_m = R / 256, tiles_n = N / 256;
+  const int tiles_m = (R + 255) / 256, tiles_n = N / 256;
   const long long ntiles = (long long)E * tiles_m * tiles_n;
   if (ntiles > 0x7fffffffLL) return MOE_EUNSUPPORTED;
   const unsigned grid = (unsigned)(ntiles < cus ? ntiles : cus);   // one block per CU (LDS-bound)
@@ -890,7 +914,28 @@ int launch_bf16_dma(const bf16_t* A, const bf16_t* B, bf16_t* Cout, int E, int R
   return check_launch();
 }
 
-// shapes the persistent 256x256 kernel takes (its per-lane byte offsets are 32-bit)
+template <int ST, int EPI, bool GATHER, bool A_MNC = false, bool B_KC = false, bool PACKED = false,
+          bool SCATTER = false, bool DYNK = false>
+int launch_bf16_dma(const bf16_t* A, const bf16_t* B, bf16_t* Cout, int E, int R, int N, int K,
+                    const int32_t* src_token, const bf16_t* zero_row, hipStream_t st,
+                    const bf16_t* mask = nullptr, unsigned char* signbits = nullptr,
+                    const int32_t* kept = nullptr) {
+  if (R % 256 != 0) {
+    if constexpr (!A_MNC && !SCATTER && !DYNK && EPI != 3)
+      return launch_bf16_dma_rows<ST, EPI, GATHER, A_MNC, B_KC, PACKED, SCATTER, DYNK, true>(
+          A, B, Cout, E, R, N, K, src_token, zero_row, st, mask, signbits, kept);
+    return MOE_EUNSUPPORTED;
+  }
+  return launch_bf16_dma_rows<ST, EPI, GATHER, A_MNC, B_KC, PACKED, SCATTER, DYNK, false>(
+      A, B, Cout, E, R, N, K, src_token, zero_row, st, mask, signbits, kept);
+}
+
+// shapes the persistent 256x256 kernel takes (its per-lane byte offsets are 32-bit); rows of a K-contiguous A
+// may be any number
+inline bool dma_columns_ok(int R, int N, int K) {
+  const long long big = R > N ? (R > K ? R : K) : (N > K ? N : K);
+  return N % 256 == 0 && K % 32 == 0 && K >= 128 && 256 * big * 2 < (1LL << 31);
+}
 inline bool dma_shape_ok(int R, int N, int K) {
   const long long big = R > N ? (R > K ? R : K) : (N > K ? N : K);
   return R % 256 == 0 && N % 256 == 0 && K % 32 == 0 && 256 * big * 2 < (1LL << 31);
@@ -933,8 +978,8 @@ GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout la
                                       {128, 128, 64, 2, {300, 545}, 7, 5.4},    {128, 128, 64, 1, {235}, 6.5, 5.2},
                                       {64, 128, 64, 3, {265, 390, 530}, 4, 5.1}, {64, 128, 64, 2, {214, 400}, 4.3, 5.6},
                                       {64, 64, 64, 3, {150, 217, 300}, 4, 5.2}, {64, 64, 64, 2, {142, 225}, 4, 5.1}};
-  static const FormCost weightgrad[] = {{256, 256, 32, 1, {870}, 12, 0},        {128, 256, 32, 2, {500, 1060}, 10, 0},
-                                        {128, 128, 32, 3, {290, 550, 810}, 5, 0}, {0},
+  static const FormCost weightgrad[] = {{256, 256, 32, 1, {870}, 12, 0},        {128, 256, 32, 2, {470, 930}, 11, 0},
+                                        {128, 128, 32, 3, {290, 550, 820}, 5, 0}, {0},
                                         {64, 128, 32, 3, {230, 350, 530}, 4.5, 0}, {0},
                                         {64, 64, 32, 4, {170, 230, 330, 400}, 4, 0}, {0}};
   const FormCost* const cost = layout == kLayoutForward ? forward : layout == kLayoutDataGrad ? datagrad : weightgrad;
@@ -950,7 +995,11 @@ GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout la
     const int steps = (K + c.bk - 1) / c.bk * (c.bk / 32);
     const long long full = n / round, rounds = (n + round - 1) / round;
     const int left = (int)((n - full * round + cus - 1) / cus);
-    double us = 1e-3 * steps * (full * c.step[c.res - 1] + (left > 0 ? c.step[left - 1] : 0.0));
+    double part = left > 0 ? c.step[left - 1] : 0.0;
+    // (the weight gradients' last round starts while the one before it ends)
+    if (layout == kLayoutWeightGrad && full > 0 && left > 0)
+      part = 0.5 * (part + (double)(n - full * round) / round * c.step[c.res - 1]);
+    double us = 1e-3 * steps * (full * c.step[c.res - 1] + part);
     us += c.ends * (f != kPersistent ? 0.5 + 0.5 * rounds : layout == kLayoutWeightGrad ? 0.625 + 0.375 * rounds : 1.0 * rounds);
     if (c.stream > 0) {
       const double stream = 2e-6 * E * N * K / c.stream + 0.5 * c.ends;
@@ -967,7 +1016,8 @@ int choose_form(int E, int R, int N, int K, GemmLayout layout, GemmForm* form, b
                 bool persistent = true) {
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
-  *form = gemm_form(persistent && dma_shape_ok(R, N, K) && (!k_kept || K % 256 == 0), E, R, N, K, layout, cus);
+  persistent = persistent && (dma_shape_ok(R, N, K) || (layout != kLayoutWeightGrad && dma_columns_ok(R, N, K)));
+  *form = gemm_form(persistent && (!k_kept || K % 256 == 0), E, R, N, K, layout, cus);
   return MOE_OK;
 }
 
@@ -1049,16 +1099,19 @@ int compute_units(int* cus) {
 int prepare_expert_gemm() {
   const int rcs[] = {
       // forward
-      prepare_dma<4, 1, false>(), prepare_dma<4, 0, false>(),
-      prepare_dma<4, 1, true, false, false, true>(), prepare_dma<4, 4, true, false, false, true>(),
-      prepare_dma<4, 0, false, false, false, true, false>(), prepare_dma<4, 0, false, false, false, true, true>(),
+      prepare_dma<4, 0, false, false, false, true, true>(),
       // fp32 results (gate logits and gate gradients)
       prepare_dma<4, 3, false, true, false>(), prepare_dma<4, 3, false, false, true>(),
-      // backward
-      prepare_dma<4, 2, false, false, true>(),
-      prepare_dma<4, 0, false, true, false>(), prepare_dma<4, 0, false, false, true>(),
-      prepare_dma<4, 5, false, false, true, true>(), prepare_dma<4, 0, false, false, true, true>(),
-      prepare_dma<4, 0, false, true, false, false, false, true>(),
+      // weight gradients
+      prepare_dma<4, 0, false, true, false>(), prepare_dma<4, 0, false, true, false, false, false, true>(),
+      // whole 256-row tiles and any number of rows: forward, data gradients
+#define MOE_DMA_BOTH(...) prepare_dma<__VA_ARGS__, false>(), prepare_dma<__VA_ARGS__, true>()
+      MOE_DMA_BOTH(4, 1, false, false, false, false, false, false), MOE_DMA_BOTH(4, 0, false, false, false, false, false, false),
+      MOE_DMA_BOTH(4, 1, true, false, false, true, false, false), MOE_DMA_BOTH(4, 4, true, false, false, true, false, false),
+      MOE_DMA_BOTH(4, 0, false, false, false, true, false, false), MOE_DMA_BOTH(4, 2, false, false, true, false, false, false),
+      MOE_DMA_BOTH(4, 0, false, false, true, false, false, false), MOE_DMA_BOTH(4, 5, false, false, true, true, false, false),
+      MOE_DMA_BOTH(4, 0, false, false, true, true, false, false),
+#undef MOE_DMA_BOTH
       // other shapes: forward (relu / plain), data gradients (plain / masked), weight gradients
 #define MOE_EDGE_KC(...)                                                                       \
   prepare_edge<128, 256, 32, 3, __VA_ARGS__>(), prepare_edge<128, 128, 64, 2, __VA_ARGS__>(),  \
@@ -1127,8 +1180,8 @@ bool expert_ffn_whole_tiles(const moe_config& c) {
 }
 
 size_t expert_signbits_bytes(const moe_config& c) {
-  const bool kept = c.act_dtype == MOE_BF16 && expert_ffn_can_pack(c) && dma_shape_ok(c.G * c.C, c.H, c.M);
-  return kept ? (size_t)c.E * c.G * c.C * c.H / 8 : 0;
+  const bool kept = c.act_dtype == MOE_BF16 && expert_ffn_can_pack(c) && dma_columns_ok(c.G * c.C, c.H, c.M);
+  return kept ? (size_t)c.E * align_up((size_t)c.G * c.C, 256) * c.H / 8 : 0;      // of whole 256-row tiles
 }
 
 // The weight gradients sum over whole 256-row tiles when the persistent kernel forms them: the rows of
