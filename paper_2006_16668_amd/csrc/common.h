@@ -292,6 +292,12 @@ bool attention_bwd_mfma_ok(int act_dtype, int d);
 int launch_attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, const float* lse,
                               void* dqkv, float* dvec, long long B, int L, int heads, int d,
                               hipStream_t st);
+// fp32 form on the matrix cores (attention_f32.hip): d = 64 or 128, not for a handful of queries
+bool attention_f32_ok(int act_dtype, int d, long long queries);
+int launch_attention_f32(const void* qkv, void* ctx, float* lse, long long B, int L, int heads, int d,
+                         hipStream_t st);
+int launch_attention_f32_bwd(const void* qkv, const void* ctx, const void* dctx, const float* lse, void* dqkv,
+                             float* dvec, long long B, int L, int heads, int d, hipStream_t st);
 int launch_attention_core_bwd(int act_dtype, const void* qkv, const void* ctx, const void* dctx,
                               const float* lse, void* dqkv, float* dvec, long long B, int L,
                               int heads, int d, hipStream_t st);

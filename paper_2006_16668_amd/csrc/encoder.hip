@@ -7,8 +7,8 @@
 //   attention core   ctx[b,l,h,:] = softmax_l'( q[b,l,h,:] . k[b,l',h,:] / sqrt(d) ) v[b,l',h,:]
 //                    on the output of the fused Q|K|V projection, qkv [tokens, 3*heads*d]
 //
-// The attention core has two forms: a flash-style MFMA kernel (bf16, d = 64 or 128) and a plain
-// one-wavefront-per-query kernel for everything else.
+// The attention core has two forms here: a flash-style MFMA kernel (bf16, d = 64 or 128) and a plain
+// one-wavefront-per-query kernel for other d; the fp32 one on the matrix cores is in attention_f32.hip.
 #include <float.h>
 #include <math.h>
 #include <type_traits>
@@ -477,6 +477,7 @@ int launch_attention_core(int act_dtype, const void* qkv, void* ctx, float* lse,
   }
   const size_t shm = (size_t)4 * (L + d) * sizeof(float);
   if (shm > 64 * 1024) return MOE_EUNSUPPORTED;          // sequences of more than ~4000 tokens
+  if (attention_f32_ok(act_dtype, d, B * heads * L)) return launch_attention_f32(qkv, ctx, lse, B, L, heads, d, st);
   const long long queries = B * heads * L;
   const long long blocks = (queries + 3) / 4;
   if (blocks > 0x7fffffffLL) return MOE_EUNSUPPORTED;

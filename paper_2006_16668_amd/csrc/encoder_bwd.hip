@@ -364,6 +364,8 @@ int launch_attention_core_bwd(int act_dtype, const void* qkv, const void* ctx, c
   const long long rows = B * heads * L;
   const size_t lds = (size_t)4 * (2 * L + 2 * d) * sizeof(float);
   if (lds > 64 * 1024 || (rows + 3) / 4 > 0x7fffffffLL) return MOE_EUNSUPPORTED;
+  if (attention_f32_ok(act_dtype, d, B * heads * L))
+    return launch_attention_f32_bwd(qkv, ctx, dctx, lse, dqkv, dvec, B, L, heads, d, st);
   const size_t lds_q = (size_t)4 * (L + 2 * d) * sizeof(float);
   const unsigned grid = (unsigned)((rows + 3) / 4);
   if (act_dtype == MOE_F32) {
