@@ -22,7 +22,7 @@
 // k of its column that the MFMA operand wants.  Blocks of one XCD (own L2) take
 // neighbouring tiles so that they share operand panels.
 //
-// fp32 layers run the fp32 MFMA kernel of gemm_f32.hip.
+// fp32 layers run the kernel of gemm_f32.hip.
 #include "common.h"
 
 namespace moe {
@@ -957,9 +957,10 @@ enum GemmForm { kPersistent, kEdge128x256, kEdge128x128, kEdge128x128Deep, kEdge
 enum GemmLayout { kLayoutForward, kLayoutDataGrad, kLayoutWeightGrad };
 
 // The rule compares what the fullest compute unit needs: 32 k of the tiles that share it (ns; up to as many as
-// fit), the ends of the tiles (us, half of it for every further round), and the time in which the form streams the
-// weights from memory (TB/s).  Fitted to the six products of 40 shapes with cold weights
-// (E 1 to 192, R 4 to 16384, M 200 to 1024, H 800 to 8192): the choice is 1 to 2 % from the best form on average.
+// fit), the ends of the tiles (us; `more` of it for every further round), and the time in which the form streams the
+// weights from memory (TB/s).  Fitted to the six products of 185 shapes with cold weights (E 1 to 192, R 1 to 16384,
+// M 130 to 1024, H 260 to 8192).  On 49 shapes that an earlier fit had not seen, its choice was 0.9, 2.3 and 0.9 %
+// from the best form on average (forward, data gradients, weight gradients).
 //   us, 64x64 deep / 64x64 / 64x128 deep / 64x128 / 128x128 deep / 128x128 / 128x256 / persistent:
 //   out  E 4  R 64   M 1024 H 4096   26.8 / 29.1 / 35.3 / 54.4 / 46.2 / 57.7 / 65.9 / -
 //   out  E 18 R 12   M 1024 H 4096   45.2 / 42.4 / 38.9 / 59.2 / 46.3 / 62.2 / 65.6 / -
@@ -968,20 +969,20 @@ enum GemmLayout { kLayoutForward, kLayoutDataGrad, kLayoutWeightGrad };
 //   h    E 22 R 130  M 600  H 2400   37.7 / 37.2 / 30.0 / 29.7 / 38.7 / 28.7 / 26.7 / -
 //   dbuf E 1  R 16384 M 1024 H 2048     - /    - /    - / 87.5 /    - / 70.5 / 74.8 / 69.1
 //   h    E 32 R 2048 M 1024 H 8192      - /    - /    - / 1526 /    - / 1419 / 1282 / 1206
-struct FormCost { int bm, bn, bk, res; double step[4], ends, stream; };
+struct FormCost { int bm, bn, bk, res; double step[4], ends, more, stream; };
 GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout layout, int cus, double* time = nullptr) {
-  static const FormCost forward[] = {{256, 256, 32, 1, {870}, 9, 6.0},          {128, 256, 32, 2, {500, 1010}, 9, 5.7},
-                                     {128, 128, 64, 2, {340, 545}, 7, 5.6},     {128, 128, 64, 1, {265}, 7, 6.0},
-                                     {64, 128, 64, 3, {250, 385, 590}, 5.5, 5.2}, {64, 128, 64, 2, {240, 400}, 4.4, 5.6},
-                                     {64, 64, 64, 3, {165, 234, 326}, 4.8, 4.6}, {64, 64, 64, 2, {155, 260}, 4.3, 4.5}};
-  static const FormCost datagrad[] = {{256, 256, 32, 1, {940}, 9, 5.5},         {128, 256, 32, 2, {540, 1130}, 10, 5.0},
-                                      {128, 128, 64, 2, {300, 545}, 7, 5.4},    {128, 128, 64, 1, {235}, 6.5, 5.2},
-                                      {64, 128, 64, 3, {265, 390, 530}, 4, 5.1}, {64, 128, 64, 2, {214, 400}, 4.3, 5.6},
-                                      {64, 64, 64, 3, {150, 217, 300}, 4, 5.2}, {64, 64, 64, 2, {142, 225}, 4, 5.1}};
-  static const FormCost weightgrad[] = {{256, 256, 32, 1, {870}, 12, 0},        {128, 256, 32, 2, {470, 930}, 11, 0},
-                                        {128, 128, 32, 3, {290, 550, 820}, 5, 0}, {0},
-                                        {64, 128, 32, 3, {230, 350, 530}, 4.5, 0}, {0},
-                                        {64, 64, 32, 4, {170, 230, 330, 400}, 4, 0}, {0}};
+  static const FormCost forward[] = {{256, 256, 32, 1, {840}, 7, 1, 6.0},             {128, 256, 32, 2, {500, 1010}, 9, 0.5, 6.0},
+                                     {128, 128, 64, 2, {340, 640}, 7, 0.5, 5.6},      {128, 128, 64, 1, {265}, 7, 0.5, 5.7},
+                                     {64, 128, 64, 3, {250, 385, 590}, 7, 0.5, 5.2},  {64, 128, 64, 2, {240, 575}, 4.4, 0.5, 5.5},
+                                     {64, 64, 64, 3, {168, 242, 340}, 4.8, 0.5, 4.6}, {64, 64, 64, 2, {155, 260}, 4.3, 0.5, 4.5}};
+  static const FormCost datagrad[] = {{256, 256, 32, 1, {870}, 6.5, 1, 5.5},          {128, 256, 32, 2, {610, 1240}, 8.6, 0.5, 5.0},
+                                      {128, 128, 64, 2, {283, 605}, 6.2, 0.5, 5.4},   {128, 128, 64, 1, {235}, 6.5, 0.5, 5.2},
+                                      {64, 128, 64, 3, {265, 375, 575}, 4, 0.5, 4.7}, {64, 128, 64, 2, {213, 445}, 4.3, 0.5, 5.6},
+                                      {64, 64, 64, 3, {152, 242, 328}, 4, 0.5, 5.2},  {64, 64, 64, 2, {142, 242}, 4, 0.5, 5.6}};
+  static const FormCost weightgrad[] = {{256, 256, 32, 1, {840}, 12, 0.38, 0},            {128, 256, 32, 2, {480, 950}, 11, 0.3, 0},
+                                        {128, 128, 32, 3, {272, 505, 760}, 5.6, 0.5, 0},  {0},
+                                        {64, 128, 32, 3, {230, 350, 530}, 4.1, 0.6, 0},   {0},
+                                        {64, 64, 32, 4, {162, 220, 320, 395}, 4, 0.5, 0}, {0}};
   const FormCost* const cost = layout == kLayoutForward ? forward : layout == kLayoutDataGrad ? datagrad : weightgrad;
   GemmForm form = kEdge128x256;
   double best = 0;
@@ -1000,7 +1001,7 @@ GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout la
     if (layout == kLayoutWeightGrad && full > 0 && left > 0)
       part = 0.5 * (part + (double)(n - full * round) / round * c.step[c.res - 1]);
     double us = 1e-3 * steps * (full * c.step[c.res - 1] + part);
-    us += c.ends * (f != kPersistent ? 0.5 + 0.5 * rounds : layout == kLayoutWeightGrad ? 0.625 + 0.375 * rounds : 1.0 * rounds);
+    us += c.ends * (1 + c.more * (double)(rounds - 1));
     if (c.stream > 0) {
       const double stream = 2e-6 * E * N * K / c.stream + 0.5 * c.ends;
       us = stream > us ? stream : us;

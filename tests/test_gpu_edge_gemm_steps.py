@@ -23,7 +23,9 @@ CASES = [
     _cfg("128x128", 3, 1000, 136, 2104, 12, 67, bias=0.5),
     _cfg("128x128_forward", 4, 2000, 136, 264, 12, 375),
     _cfg("128x128_deep", 1, 900, 520, 2056, 6, 200),
-    _cfg("persistent_h_tiled_dh", 2, 1200, 256, 1536, 12, 256),
+    _cfg("persistent_h_persistent_dh", 2, 1200, 256, 1536, 12, 256),
+    _cfg("persistent_h_tiled_dh", 1, 2500, 256, 1024, 13, 515),
+    _cfg("tiled_h_dh_without_bits", 2, 2500, 512, 2304, 20, 256),
 ]
 
 

@@ -13,8 +13,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# products the persistent kernel forms: h and out; h and dh (with bits); out and dbuf; out, where dh may not have it
-# because h was formed without bits
+# products the persistent kernel forms: all four; h and dh (with bits); out and dbuf; all four, a tile's last rows only
 @pytest.mark.parametrize("G,S,M,H,E,C", [(2, 8200, 256, 256, 4, 4100), (1, 3700, 256, 2048, 8, 903), (2, 4100, 768, 256, 2, 4100),
                                          (1, 20400, 256, 768, 20, 2040)])
 def test_forward_and_backward(G, S, M, H, E, C):
