@@ -300,18 +300,10 @@ __global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) 
 
   // c[v] of the wavefront's 32 x 32 tile (i, j): row 32 i + 8 (v/4) + 4 hf + v%4, column 32 j + lane%32: a
   // store covers whole 128-byte pieces of two rows
-  auto store_tile = [&](int i, int j, const f32x16_t& c) {
+  auto store_tile = [&](int i, int j, const f32x16_t& c, const f32x16_t& m) {
     const int n = n0 + wn0 + 32 * j + l32, rb = r0 + wm0 + 32 * i + 4 * hf;
     if (n >= N) return;
     const size_t o = ((size_t)e * R + rb) * N + n;
-    float m[16];
-    if (EPI == 2) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int dr = 8 * (v >> 2) + (v & 3);
-        m[v] = rb + dr < rows ? mask[o + (size_t)dr * N] : 0.f;
-      }
-    }
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int dr = 8 * (v >> 2) + (v & 3);
@@ -321,6 +313,28 @@ __global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) 
       if (rb + dr < rows) Cout[o + (size_t)dr * N] = x;
     }
   };
+
+  // Its mask, past an edge the last row or column.  All tiles' are asked for at once, without branches, as the sums
+  // are over: a block waits for memory once instead of once per tile (training step of 4096 tokens, M 1024, H 2048,
+  // 16 experts 1125 -> 1090 us).
+  auto load_mask = [&](int i, int j) {
+    f32x16_t m;
+    if (EPI == 2) {
+      const int n = n0 + wn0 + 32 * j + l32, rb = r0 + wm0 + 32 * i + 4 * hf;
+      const float* const mc = mask + (size_t)e * R * N + (n < N ? n : N - 1);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = rb + 8 * (v >> 2) + (v & 3);
+        m[v] = mc[(size_t)(row < rows ? row : rows - 1) * N];
+      }
+    }
+    return m;
+  };
+  f32x16_t masks[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) masks[i][j] = load_mask(i, j);
 
   // anything but finite numbers (0 x number is 0 else): this wavefront's tiles again, in fp32 products
   float zero = 0.f;
@@ -350,14 +364,14 @@ __global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) 
         if (k < KE && col_ok) y = B_KC ? B[((size_t)e * N + col) * K + k] : B[((size_t)e * K + k) * N + col];
         c = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, c, 0, 0, 0);
       }
-      store_tile(i, j, c);
+      store_tile(i, j, c, load_mask(i, j));
     }
     return;
   }
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) store_tile(i, j, main[i][j]);
+    for (int j = 0; j < TN; ++j) store_tile(i, j, main[i][j], masks[i][j]);
 }
 
 template <int TM, int TN, int PD, int KG, int EPI, bool A_KC, bool B_KC, bool K_KEPT>
