@@ -330,7 +330,8 @@ def time_f32_layer(moe, cfg, K, W):
             # occupied rows are the work, as for the bf16 layer
             "ffn_mfma_f32_frac": 4.0 * c32.M * c32.H * kept / (gemm_ms * 1e-3) / 1e12 / PEAK_F32_TFLOPS,
             "peak": PEAK_F32_TFLOPS, "unit": "TFLOP/s",
-            "note": "same workload in fp32 (v_mfma_f32_32x32x2_f32); not part of value"}
+            "note": "same workload in fp32 (six products of bf16 terms, so the share of the fp32 instruction's peak "
+                    "may pass 1); not part of value"}
 
 
 def occupied_slots(moe, cfg, sh, inp):

@@ -367,7 +367,8 @@ int moe_encoder_workspace_bytes(const moe_config* cfg, const moe_encoder_dims* d
 
 /* out = Attention(u) (no residual): u [B,L,M], wqkv [M,3A], wo_att [A,M] -> out [B,L,M].
  * The flash-style MFMA kernel serves bf16 with d in {64,128}, any L; other
- * shapes use a plain kernel that needs (L + d) * 16 bytes of LDS <= 64 KB.  Probabilities are rounded
+ * shapes need (L + d) * 16 bytes <= 64 KB (the LDS of the plain kernel; fp32 with d in {64,128}
+ * and B L heads >= 128 has MFMA kernels of its own, under the same limit).  Probabilities are rounded
  * to bf16 before they multiply v when bf16, d in {64,128} and L % 128 == 0; every other call keeps
  * them in fp32 (and so does the backward pass with them and their gradients). */
 int moe_self_attention(const moe_config* cfg, const moe_encoder_dims* dims, const void* u,
@@ -420,8 +421,8 @@ int moe_encoder_pair_forward_train(const moe_config* cfg, const moe_encoder_dims
  * moe_encoder_pair_forward_train.  out: dx [B,L,M]; every member of g (fully overwritten).
  * ws >= moe_encoder_backward_workspace_bytes, 256-byte aligned.  Errors as the other calls;
  * MOE_EUNSUPPORTED also when the attention shape is served by neither form of the core's
- * derivative: the MFMA kernels take bf16 with d in {64,128}, the plain kernels
- * need (2 L + 2 d) * 16 bytes of LDS <= 64 KB; and when M * 16 bytes > 64 KB (layer-norm
+ * derivative: the MFMA kernels take bf16 with d in {64,128}, other calls (fp32 ones
+ * of MFMA kernels included) need (2 L + 2 d) * 16 bytes of LDS <= 64 KB; and when M * 16 bytes > 64 KB (layer-norm
  * parameter sums).  Results are bit-reproducible (no atomics). */
 int moe_encoder_pair_backward(const moe_config* cfg, const moe_encoder_dims* dims, const void* x,
                               const moe_encoder_weights* w, const void* dy, const float* daux,
