@@ -3,14 +3,15 @@
 // the forward and backward pass and the dense layers around them.
 //
 // The bf16 pipes multiply sixteen times as fast as the fp32 ones, so every operand enters as the three
-// bf16 terms that hold its 24 bits (a = hi + mid + lo, each the leading 8 bits of what is left) and a
-// product of two numbers as the six products of terms that reach 2^-16 of it (hi hi, hi mid, mid hi, mid
-// mid, hi lo, lo hi), exact in fp32 and summed in fp32.  What is left out (mid lo, lo mid, lo lo) is at most
-// 2^-21 of a product, 2^-24 on average.  The five smaller products have sums of their own, so the sum that
+// bf16 terms that hold its 24 bits (a = hi + mid + lo, each what is left rounded to nearest) and a product of two
+// numbers as six products of terms (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi), exact in fp32 and summed in
+// fp32.  What is left out (mid lo, lo mid, lo lo) is at most 2^-24 of a product, as much as one fp32 rounding of it,
+// 2^-27 in the mean, and of either sign; terms cut off instead of rounded left out up to 2^-21, always with the
+// product's sign.  The five smaller products have sums of their own, so the sum that
 // carries the result is rounded twice per 16 k where v_mfma_f32_32x32x2_f32 rounds it 16 times; all six in
 // one sum were worse than that instruction where the operand is half zeros.  Error against float64, relative
-// (2-norm), v_mfma_f32 / this kernel: K 512 4.1e-7 / 1.4e-7, K 1024 5.7e-7 / 1.9e-7, K 4096 with a ReLU'd
-// operand 8.1e-7 / 3.3e-7.
+// (2-norm), v_mfma_f32 / this kernel, normal operands: K 4 4.1e-8 / 2.8e-8, K 16 7.3e-8 / 3.2e-8, K 64 1.4e-7 / 5.1e-8,
+// K 1024 5.7e-7 / 1.9e-7, K 3424 with a ReLU'd operand 7.4e-7 / 2.9e-7; all operands 1.2345678, K 1024 6.6e-6 / 2.2e-8.
 // Terms of an operand that is not finite (or of a sum that overflows) make NaN where the fp32 product may
 // be an infinity, so a wavefront whose result holds anything but finite numbers multiplies its tile again
 // with v_mfma_f32_32x32x2_f32, operands straight from memory.
@@ -179,10 +180,10 @@ __global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) 
       u32x2_t w;
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const uint32_t ua = __float_as_uint(x[2 * i]), ub = __float_as_uint(x[2 * i + 1]);
-        w[i] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);     // the upper halves of both
-        x[2 * i] -= __uint_as_float(ua & 0xffff0000u);
-        x[2 * i + 1] -= __uint_as_float(ub & 0xffff0000u);
+        w[i] = pack_bf16x2(x[2 * i], x[2 * i + 1]);
+        if (k == 2) continue;                                  // (nothing is left)
+        x[2 * i] -= __uint_as_float(w[i] << 16);
+        x[2 * i + 1] -= __uint_as_float(w[i] & 0xffff0000u);
       }
       *(lds_u2_ptr)(uintptr_t)(at + k * plane_bytes) = w;
     }

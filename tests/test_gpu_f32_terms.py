@@ -1,6 +1,6 @@
 """The fp32 products as products of bf16 terms: every tile form and group count, operands that are not finite
 or overflow, and the error against float64 (less than the fp32 matrix instruction's on the same operands:
-4.1e-7 at K 512, 5.7e-7 at K 1024)."""
+4.1e-7 at K 512, 5.7e-7 at K 1024), also of short sums and of operands whose terms are all long."""
 import pytest
 import torch
 
@@ -64,3 +64,32 @@ def test_infinities_nan_and_overflow(E, R, M, H):
     scale = exact[ok].abs() + 1e-3 * torch.linalg.vector_norm(buf.double(), dim=-1, keepdim=True).expand_as(exact)[ok]
     fin = torch.isfinite(scale)
     assert float(((h[ok].double() - exact[ok]).abs() / scale)[fin].max()) < 1e-3
+
+
+def _chain(a, b):
+    """a [E,R,K] b [E,K,N] summed k by k, one fp32 rounding per product and sum: the fp32 instruction's way."""
+    s = torch.zeros(a.shape[0], a.shape[1], b.shape[2], device=DEV)
+    for k in range(a.shape[2]):
+        s = (s.double() + a[:, :, k, None].double() * b[:, None, k].double()).float()
+    return s
+
+
+@pytest.mark.parametrize("K", [4, 8, 12, 16, 32])
+def test_short_sums(K):
+    buf, wi, _, h, _ = _ffn(2, 70, K, 260)
+    want = torch.relu(buf.double() @ wi.double())
+    assert _error(h, want) <= _error(torch.relu(_chain(buf, wi)), want)
+
+
+@pytest.mark.parametrize("E,R,M,H", [(2, 70, 4, 260), (2, 70, 512, 260), (64, 130, 132, 132)])
+def test_long_mantissas(E, R, M, H):
+    # truncated terms left 2^-21 of these products out, of every product the same
+    c = 1 + 2.0 ** -7 - 2.0 ** -23
+
+    def edit(buf, wi):
+        buf.fill_(c), wi.fill_(c)
+
+    h = _ffn(E, R, M, H, edit)[3]
+    want = M * c * c
+    # their three terms are exact in two, so are the products: the sums' own roundings, half a last place each
+    assert float((h.double() - want).abs().max()) < want * 2.0 ** -24 * (1 + 2.0 ** -6)
