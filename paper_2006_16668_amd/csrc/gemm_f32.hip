@@ -7,7 +7,8 @@
 // numbers as six products of terms (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi), exact in fp32 and summed in
 // fp32.  What is left out (mid lo, lo mid, lo lo) is at most 2^-24 of a product, as much as one fp32 rounding of it,
 // 2^-27 in the mean, and of either sign; terms cut off instead of rounded left out up to 2^-21, always with the
-// product's sign.  The five smaller products have sums of their own, so the sum that
+// product's sign.  A sum of one step (16 k, the fp32 instruction's error is as small there) takes mid lo and lo mid
+// too: one product's error 2.65e-8 -> 2.59e-8, a single rounding.  The five smaller products have sums of their own, so the sum that
 // carries the result is rounded twice per 16 k where v_mfma_f32_32x32x2_f32 rounds it 16 times; all six in
 // one sum were worse than that instruction where the operand is half zeros.  Error against float64, relative
 // (2-norm), v_mfma_f32 / this kernel, normal operands: K 4 4.1e-8 / 2.8e-8, K 16 7.3e-8 / 3.2e-8, K 64 1.4e-7 / 5.1e-8,
@@ -270,6 +271,25 @@ __global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) 
 #pragma unroll
   for (int u = 0; u < PD - 1; ++u)
     if (s + u < KT) step(s + u, u);
+  // a short sum: mid lo and lo mid too, from the planes of its only step
+  if (KE <= KG * kBK) {                                        // block-uniform
+    bf16x8_t a[TM][2];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) a[i][k] = read_frag(A_KC, lds0 + a_rd[i] + (k + 1) * PA::kBytes, BM * 2);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      bf16x8_t b[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) b[k] = read_frag(B_KC, lds0 + b_rd[j] + (k + 1) * PB::kBytes, BN * 2);
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+          rest[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][q], b[1 - q], rest[i][j], 0, 0, 0);
+    }
+  }
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll

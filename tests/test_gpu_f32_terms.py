@@ -93,3 +93,43 @@ def test_long_mantissas(E, R, M, H):
     want = M * c * c
     # their three terms are exact in two, so are the products: the sums' own roundings, half a last place each
     assert float((h.double() - want).abs().max()) < want * 2.0 ** -24 * (1 + 2.0 ** -6)
+
+
+def _step(x, wg, wi, wo, dy, C):
+    """A training step of one group with every token sent where wg says."""
+    _, S, M = x.shape
+    E, _, H = wi.shape
+    sh = moe.MoEShape(1, S, M, H, E, C, "f32")
+    u, y, aux = torch.full((1, S), 0.5, device=DEV), torch.empty_like(x), torch.empty(1, device=DEV)
+    fws = torch.empty(moe.moe_train_workspace_bytes(sh), dtype=torch.uint8, device=DEV)
+    bws = torch.empty(moe.moe_backward_workspace_bytes(sh), dtype=torch.uint8, device=DEV)
+    dx, dwg, dwi, dwo = (torch.full_like(t, float("nan")) for t in (x, wg, wi, wo))
+    moe.moe_forward_train(sh, x, wg, u, wi, wo, y, aux, fws)
+    moe.moe_backward(sh, x, wg, wi, wo, dy, torch.zeros(1, device=DEV), fws, dx, dwg, dwi, dwo, bws)
+    torch.cuda.synchronize()
+    return y, dx, dwi, dwo
+
+
+def test_weight_gradients_of_few_tokens():
+    # expert e keeps e + 1 tokens.  A token is a unit vector, its row of h a row of wi, its weight 1: h and dout are exact
+    E, M, H = 16, 160, 132
+    kept = [e + 1 for e in range(E)]
+    expert = torch.repeat_interleave(torch.arange(E), torch.tensor(kept)).to(DEV)
+    S = len(expert)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    wi = torch.rand(E, M, H, device=DEV, generator=g) + 0.5
+    wo, dy = torch.randn(E, H, M, device=DEV, generator=g), torch.randn(1, S, M, device=DEV, generator=g)
+    x = torch.eye(S, M, device=DEV).view(1, S, M)
+    wg = torch.zeros(M, E, device=DEV)
+    wg[torch.arange(S, device=DEV), expert] = 200
+    dwo = _step(x, wg, wi, wo, dy, max(kept))[3]
+    first = 0
+    for e in range(E):
+        t = torch.arange(first, first + kept[e], device=DEV)
+        first += kept[e]
+        a, b = wi[e, t].t().contiguous()[None], dy[0, t][None]
+        want = (a.double() @ b.double())[0]
+        # 1 %: the smaller products' sum is rounded too, at 2^-8 of the result
+        assert _error(dwo[e], want) <= 1.01 * _error(_chain(a, b)[0], want), e
+        if kept[e] == 1:
+            assert float(((dwo[e].double() - want) / want).abs().max()) < 2.0 ** -24 * (1 + 2.0 ** -6)
