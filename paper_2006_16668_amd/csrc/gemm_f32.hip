@@ -13,6 +13,9 @@
 // one sum were worse than that instruction where the operand is half zeros.  Error against float64, relative
 // (2-norm), v_mfma_f32 / this kernel, normal operands: K 4 4.1e-8 / 2.8e-8, K 16 7.3e-8 / 3.2e-8, K 64 1.4e-7 / 5.1e-8,
 // K 1024 5.7e-7 / 1.9e-7, K 3424 with a ReLU'd operand 7.4e-7 / 2.9e-7; all operands 1.2345678, K 1024 6.6e-6 / 2.2e-8.
+// Operands are scaled by 2^24, results by 2^-48: the smallest fp32 number's terms are normal bf16 numbers then, and
+// products keep all their bits (operands of 2^-124: 1e-3 and 3e-2 without, 8e-8 with; a multiplication per element
+// fetched, 2 % of the time of large shapes).  Sums past 2^80 and operands past 2^104 overflow and are multiplied again:
 // Terms of an operand that is not finite (or of a sum that overflows) make NaN where the fp32 product may
 // be an infinity, so a wavefront whose result holds anything but finite numbers multiplies its tile again
 // with v_mfma_f32_32x32x2_f32, operands straight from memory.
@@ -45,6 +48,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 static __device__ const f32x4_t f32_zero_line = {0.f, 0.f, 0.f, 0.f};
 
 constexpr int kBK = 16;
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;               // of an operand, of a sum
 
 // LDS of a block: two buffers of the three bf16 planes of a step's operands.
 //   K-contiguous operand: plane [2 halves of 8 k][rows][16 bytes], the halves 128 bytes apart beyond their
@@ -175,7 +179,7 @@ __global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) 
   typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
   typedef u32x2_t __attribute__((address_space(3))) * lds_u2_ptr;
   auto put = [&](const f32x4_t& v, uint32_t at, int plane_bytes) __attribute__((always_inline)) {
-    float x[4] = {v[0], v[1], v[2], v[3]};
+    float x[4] = {v[0] * kUp, v[1] * kUp, v[2] * kUp, v[3] * kUp};
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       u32x2_t w;
@@ -392,7 +396,11 @@ __global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) 
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) store_tile(i, j, main[i][j], masks[i][j]);
+    for (int j = 0; j < TN; ++j) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) main[i][j][v] *= kDown;
+      store_tile(i, j, main[i][j], masks[i][j]);
+    }
 }
 
 template <int TM, int TN, int PD, int KG, int EPI, bool A_KC, bool B_KC, bool K_KEPT>

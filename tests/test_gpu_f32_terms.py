@@ -133,3 +133,16 @@ def test_weight_gradients_of_few_tokens():
         assert _error(dwo[e], want) <= 1.01 * _error(_chain(a, b)[0], want), e
         if kept[e] == 1:
             assert float(((dwo[e].double() - want) / want).abs().max()) < 2.0 ** -24 * (1 + 2.0 ** -6)
+
+
+@pytest.mark.parametrize("E,R,M,H", [(2, 70, 516, 132), (64, 130, 132, 132)])
+@pytest.mark.parametrize("small", ["a", "b"])
+def test_operands_near_the_smallest(E, R, M, H, small):
+    # of these the smallest terms (2^-16 of an operand and less) are below bf16's range, some below fp32's normal one
+    def edit(buf, wi):
+        a, b = (2.0 ** -124, 2.0 ** 60) if small == "a" else (2.0 ** 60, 2.0 ** -124)
+        buf.mul_(a), wi.mul_(b)
+
+    buf, wi, _, h, _ = _ffn(E, R, M, H, edit)
+    want = torch.relu(buf.double() @ wi.double())
+    assert _error(h, want) <= _error(torch.relu(_chain(buf, wi)), want)
