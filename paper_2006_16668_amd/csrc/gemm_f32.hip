@@ -7,18 +7,21 @@
 // numbers as six products of terms (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi), exact in fp32 and summed in
 // fp32.  What is left out (mid lo, lo mid, lo lo) is at most 2^-24 of a product, as much as one fp32 rounding of it,
 // 2^-27 in the mean, and of either sign; terms cut off instead of rounded left out up to 2^-21, always with the
-// product's sign.  A sum of one step (16 k, the fp32 instruction's error is as small there) takes mid lo and lo mid
-// too: one product's error 2.65e-8 -> 2.59e-8, a single rounding.  The five smaller products have sums of their own, so the sum that
-// carries the result is rounded twice per 16 k where v_mfma_f32_32x32x2_f32 rounds it 16 times; all six in
-// one sum were worse than that instruction where the operand is half zeros.  Error against float64, relative
-// (2-norm), v_mfma_f32 / this kernel, normal operands: K 4 4.1e-8 / 2.8e-8, K 16 7.3e-8 / 3.2e-8, K 64 1.4e-7 / 5.1e-8,
-// K 1024 5.7e-7 / 1.9e-7, K 3424 with a ReLU'd operand 7.4e-7 / 2.9e-7; all operands 1.2345678, K 1024 6.6e-6 / 2.2e-8.
+// product's sign.  A sum of one step (16 k), which the fp32 instruction rounds seldom too, takes mid lo and lo mid
+// as well: one product's error 2.65e-8 -> 2.59e-8, a single rounding.
+// The five smaller products have sums of their own, so the sum that carries the result is rounded twice per 16 k
+// where v_mfma_f32_32x32x2_f32 rounds it 16 times; all six in one sum were worse than that instruction where the
+// operand is half zeros.  Error against float64, relative (2-norm), v_mfma_f32 / this kernel, normal operands:
+// K 4 4.1e-8 / 2.7e-8, K 16 7.3e-8 / 3.2e-8, K 64 1.4e-7 / 5.1e-8, K 1024 5.7e-7 / 1.9e-7, K 3424 with a ReLU'd
+// operand 7.4e-7 / 2.9e-7; all operands 1.2345678, K 1024 6.6e-6 / 2.2e-8.
 // Operands are scaled by 2^24, results by 2^-48: the smallest fp32 number's terms are normal bf16 numbers then, and
-// products keep all their bits (operands of 2^-124: 1e-3 and 3e-2 without, 8e-8 with; a multiplication per element
-// fetched, 2 % of the time of large shapes).  Sums past 2^80 and operands past 2^104 overflow and are multiplied again:
-// Terms of an operand that is not finite (or of a sum that overflows) make NaN where the fp32 product may
-// be an infinity, so a wavefront whose result holds anything but finite numbers multiplies its tile again
-// with v_mfma_f32_32x32x2_f32, operands straight from memory.
+// products keep all their bits (error with operands of 2^-124: 1e-3 and 3e-2 without, 8e-8 with; a multiplication per
+// element fetched, 2 % of the time of large shapes).
+// Terms of an operand that is not finite make NaN where the fp32 product may be an infinity, and sums past 2^80 or
+// operands past 2^104 overflow by the scale, so a wavefront whose result holds anything but finite numbers multiplies
+// its tiles again with v_mfma_f32_32x32x2_f32, operands straight from memory.  16 experts of 512 rows, M 1024, H 2048, us,
+// all finite / every row NaN / an infinity in every 64th row: 350 / 620 / 997 (with two k at a time and nothing in
+// flight 348 / 1740 / 3230; the fp32 instruction from LDS stages 535).
 //
 // One block of four wavefronts (2 x 2) per tile, or KG groups of four that take the steps of 16 k in turn and
 // meet at the end.  A thread fetches its pieces of a step PD steps ahead into registers, from an address of
@@ -29,12 +32,12 @@
 //
 // Bound: six matrix instructions of 32 cycles per product of two fragments; per 128 x 128 tile and step 768
 // matrix cycles, about 560 of LDS and 450 of vector instructions on each SIMD, which overlap in part.
-// Large shapes run at 175 to 190 TFLOP/s (the fp32 instruction: 120 to 130, peak 157); few tiles are bound by
+// Large shapes run at 195 to 205 TFLOP/s (the fp32 instruction: 130, peak 157); few tiles are bound by
 // a step's chain of barrier, reads, products, split and writes, about 900 cycles, hence the groups.  Both expert
-// products, start of this design (fp32 instruction) / now, us:
-//   E 2  R 8192 M 1024 H 4096  2094 / 1436    E 16 R 512 M 1024 H 2048  632 / 426
-//   E 66 R 12   M 848  H 3424   472 /  341    E 24 R 295 M 768  H 3072  671 / 458
-//   E 19 R 24   M 608  H 2504    96 /   75    E 16 R 128 M 512  H 1024   49 /  44
+// products, start of this design (fp32 instruction) / now, us, two sets of operands in turn:
+//   E 2  R 8192 M 1024 H 4096  2100 / 1326    E 16 R 512 M 1024 H 2048  535 / 350
+//   E 66 R 12   M 848  H 3424   470 /  328    E 24 R 295 M 768  H 3072  664 / 437
+//   E 19 R 24   M 608  H 2504    96 /   71    E 16 R 128 M 512  H 1024   50 /  39
 #include "common.h"
 
 namespace moe {
@@ -340,8 +343,8 @@ __global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) 
   };
 
   // Its mask, past an edge the last row or column.  All tiles' are asked for at once, without branches, as the sums
-  // are over: a block waits for memory once instead of once per tile (training step of 4096 tokens, M 1024, H 2048,
-  // 16 experts 1125 -> 1090 us).
+  // are over: a block waits for memory once instead of once per tile (128 x 128 tiles, training step of 4096 tokens,
+  // M 1024, H 2048, 16 experts 1125 -> 1090 us).
   auto load_mask = [&](int i, int j) {
     f32x16_t m;
     if (EPI == 2) {
@@ -361,6 +364,67 @@ __global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) 
 #pragma unroll
     for (int j = 0; j < TN; ++j) masks[i][j] = load_mask(i, j);
 
+  // The wavefront's tiles with v_mfma_f32_32x32x2_f32, operands straight from memory, eight k ahead: lane half
+  // hf takes k = 4 hf + q of eight in step q.
+  auto fp32_products = [&](f32x16_t (&c)[TM][TN]) __attribute__((always_inline)) {
+    uint64_t ap[TM], bp[TN];                                   // where a lane's k starts, 0: a row or column past an edge
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int row = r0 + wm0 + 32 * i + l32;
+      bool ok = row < (A_KC ? rows : R);
+      long long arow = (long long)e * R + row;
+      if (A_KC && gather != nullptr) {
+        arow = ok ? gather[arow] : -1;
+        ok = arow >= 0;
+      }
+      const float* src = A_KC ? A + arow * K + 4 * hf : A + ((size_t)e * K + 4 * hf) * R + row;
+      ap[i] = ok ? (uint64_t)(uintptr_t)src : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int col = n0 + wn0 + 32 * j + l32;
+      const float* src = B_KC ? B + ((size_t)e * N + col) * K + 4 * hf : B + ((size_t)e * K + 4 * hf) * N + col;
+      bp[j] = col < N ? (uint64_t)(uintptr_t)src : 0;
+    }
+    auto load = [&](bool kc, uint64_t p, int k0, int ld) __attribute__((always_inline)) {
+      const int k = k0 + 4 * hf;
+      if (kc) return *reinterpret_cast<const f32x4_t*>((uintptr_t)(p != 0 && k < KE ? p + (uint64_t)k0 * 4 : zline));
+      f32x4_t v;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        v[q] = *reinterpret_cast<const float*>((uintptr_t)(p != 0 && k + q < KE ? p + (uint64_t)(k0 + q) * ld * 4 : zline));
+      return v;
+    };
+    f32x4_t x[2][TM], y[2][TN];
+    auto fetch8 = [&](int k0, int u) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) x[u][i] = load(A_KC, ap[i], k0, R);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) y[u][j] = load(B_KC, bp[j], k0, N);
+    };
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) c[i][j][v] = 0.f;
+    fetch8(0, 0);
+#pragma unroll 1
+    for (int k0 = 0; k0 < KE; k0 += 16) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        fetch8(k0 + 8 * (u + 1), 1 - u);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+              c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u][i][q], y[u][j][q], c[i][j], 0, 0, 0);
+      }
+    }
+  };
+
   // anything but finite numbers (0 x number is 0 else): this wavefront's tiles again, in fp32 products
   float zero = 0.f;
 #pragma unroll
@@ -368,39 +432,15 @@ __global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) 
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) zero = fmaf(main[i][j][v], 0.f, zero);
-  if (__builtin_amdgcn_ballot_w64(!(zero == 0.f)) != 0) {
-#pragma unroll 1
-    for (int ij = 0; ij < TM * TN; ++ij) {
-      const int i = ij / TN, j = ij % TN;
-      const int row = r0 + wm0 + 32 * i + l32, col = n0 + wn0 + 32 * j + l32;
-      const bool row_ok = row < (A_KC ? rows : R), col_ok = col < N;
-      long long arow = (long long)e * R + row;
-      if (A_KC && gather != nullptr && row_ok) arow = gather[arow];
-      const bool a_ok = row_ok && arow >= 0;
-      f32x16_t c;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) c[v] = 0.f;
-#pragma unroll 1
-      for (int k0 = 0; k0 < KE; k0 += 2) {                     // lane half hf takes k0 + hf
-        const int k = k0 + hf;
-        float x = 0.f, y = 0.f;
-        if (k < KE && a_ok) x = A_KC ? A[arow * K + k] : A[((size_t)e * K + k) * R + row];
-        if (k < KE && col_ok) y = B_KC ? B[((size_t)e * N + col) * K + k] : B[((size_t)e * K + k) * N + col];
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, c, 0, 0, 0);
+      for (int v = 0; v < 16; ++v) {
+        zero = fmaf(main[i][j][v], 0.f, zero);
+        main[i][j][v] *= kDown;
       }
-      store_tile(i, j, c, load_mask(i, j));
-    }
-    return;
-  }
+  if (__builtin_amdgcn_ballot_w64(!(zero == 0.f)) != 0) fp32_products(main);
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) main[i][j][v] *= kDown;
-      store_tile(i, j, main[i][j], masks[i][j]);
-    }
+    for (int j = 0; j < TN; ++j) store_tile(i, j, main[i][j], masks[i][j]);
 }
 
 template <int TM, int TN, int PD, int KG, int EPI, bool A_KC, bool B_KC, bool K_KEPT>

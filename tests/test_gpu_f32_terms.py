@@ -146,3 +146,52 @@ def test_operands_near_the_smallest(E, R, M, H, small):
     buf, wi, _, h, _ = _ffn(E, R, M, H, edit)
     want = torch.relu(buf.double() @ wi.double())
     assert _error(h, want) <= _error(torch.relu(_chain(buf, wi)), want)
+
+
+def _same(got, want, tol):
+    """Infinities and NaN where float64 has them, every other element within tol of the norm of its kind."""
+    want = want.float()
+    for v in (torch.isnan, torch.isposinf, torch.isneginf):
+        assert torch.equal(v(got), v(want)), v.__name__
+    big = want.abs() > 1e30                                    # (sums that a single huge term decides)
+    ok = torch.isfinite(want) & ~big
+    assert not ok.any() or _error(got[ok], want[ok].double()) < tol
+    big &= torch.isfinite(want)
+    assert not big.any() or _error(got[big], want[big].double()) < tol
+
+
+# tiles 128 x 128 throughout; 64 x 128 (weight gradients 128 x 128); 64 x 64 with groups and without
+@pytest.mark.parametrize("E,C,M,H", [(16, 512, 1024, 2048), (66, 12, 848, 3424), (3, 70, 132, 260)])
+def test_training_step_with_infinities(E, C, M, H):
+    """Masked and plain data gradients and weight gradients over kept rows with operands that are not finite."""
+    inf, nan = float("inf"), float("nan")
+    S = E * C - 5 if E > 3 else E * C - 1                      # (one expert with empty positions)
+    g = torch.Generator(device=DEV).manual_seed(E + C)
+    expert = torch.arange(S, device=DEV) % E
+    x = torch.randn(1, S, M, device=DEV, generator=g)
+    x[0, :, M - E:] = 0
+    x[0, torch.arange(S, device=DEV), M - E + expert] = 1
+    wg = torch.zeros(M, E, device=DEV)
+    wg[M - E + torch.arange(E), torch.arange(E)] = 200
+    wi = torch.randn(E, M, H, device=DEV, generator=g) / M ** 0.5
+    wo = torch.randn(E, H, M, device=DEV, generator=g) / H ** 0.5
+    dy = torch.randn(1, S, M, device=DEV, generator=g)
+    wi[0, 5, 3], wi[0, 2, 1] = inf, nan
+    dy[0, 1, 7], dy[0, 1 + E, 9] = inf, nan                    # of expert 1
+    dy[0, 2, 11] = 3e38                                        # of expert 2: some products overflow
+    y, dx, dwi, dwo = _step(x, wg, wi, wo, dy, C)
+    for e in range(min(E, 4)):
+        t = torch.nonzero(expert == e).flatten()
+        xe, de = x[0, t].double(), dy[0, t].double()
+        h = (xe @ wi[e].double()).float().double()
+        h = torch.where(h > 0, h, 0.0)                         # relu of NaN, as maxnum gives it
+        dh = torch.where(h > 0, (de @ wo[e].double().t()).float().double(), 0.0)
+        # a few of up to 2 million h may be on the other side of 0: a share p of them shows as sqrt(p)
+        tol = 2e-3
+        _same(y[0, t], h @ wo[e].double(), tol)
+        _same(dwo[e], h.t() @ de, tol)
+        _same(dwi[e], xe.t() @ dh, tol)
+        want = dh @ wi[e].double().t()
+        # tokens whose gate gradient is finite too
+        ok = torch.isfinite((y[0, t].double() * de).sum(-1).float()) & torch.isfinite(want).all(-1)
+        _same(dx[0, t][ok], want[ok], tol)
