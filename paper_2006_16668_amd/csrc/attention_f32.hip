@@ -1,6 +1,6 @@
 // Scaled dot-product attention core and its backward pass in fp32 on the matrix cores (d = 64 or 128),
-// v_mfma_f32_32x32x2_f32: full fp32 products and sums, exponentials with expf.  Other d run the plain kernels
-// of encoder.hip and encoder_bwd.hip, which took every fp32 call before.
+// v_mfma_f32_32x32x2_f32: full fp32 products and sums, exponentials with expf.  Other d, and calls of fewer
+// than 128 queries, run the plain kernels of encoder.hip and encoder_bwd.hip, which took every fp32 call before.
 //
 // The transposed arrangement of the bf16 kernels: a lane owns one column (a query; a key in the dk/dv kernel).
 // The instruction takes one k per lane half: lane (r = lane % 32, hf = lane / 32) supplies row r of the first
@@ -43,7 +43,9 @@ template <int D> struct Pieces {
   }
   __device__ __forceinline__ f32x4_t piece(int g) const { return v[g]; }
 };
-// the floats of a block's 32 rows that the sums over rows take; rows past the end: the last one
+// The floats of a block's 32 rows that the sums over rows take.  Rows past the end are copies of the last one, with a
+// factor of 0.  An infinity in that row of v or dctx must not become 0 x inf there, so they are cleared before use (q and
+// k need not be: their infinities make the head's scores, so all results, NaN anyway).
 template <int D> struct Rows {
   float v[16][D / 32];
   __device__ __forceinline__ void load(const float* base, size_t ld, int row0, int L, int r, int hf) {
@@ -54,6 +56,12 @@ template <int D> struct Rows {
 #pragma unroll
       for (int t = 0; t < D / 32; ++t) v[i][t] = base[(size_t)row * ld + 32 * t + r];
     }
+  }
+  __device__ __forceinline__ void clear_past(int row0, int L, int hf) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+      for (int t = 0; t < D / 32; ++t) v[i][t] = row0 + 8 * (i >> 2) + 4 * hf + (i & 3) < L ? v[i][t] : 0.f;
   }
   __device__ __forceinline__ float at(int i, int t) const { return v[i][t]; }
 };
@@ -69,7 +77,7 @@ template <int D> struct Staged {
     return rows[(8 * (i >> 2) + 4 * hf + (i & 3)) * kPitch + 32 * t + r];
   }
 };
-// the rows 32 blk .. + 31 (past the end: the last one) of two operands on their way to LDS
+// the rows 32 blk .. + 31 of two operands on their way to LDS (past the end: the last one on the way, zeros in LDS)
 template <int D> struct Transit {
   static constexpr int kPer = 32 * D / 4 / 256, kVecs = D / 4;
   f32x4_t a[kPer], b[kPer];
@@ -83,7 +91,18 @@ template <int D> struct Transit {
       b[i] = *reinterpret_cast<const f32x4_t*>(pb + (size_t)row * ldb + c);
     }
   }
-  __device__ __forceinline__ void put(float* la, float* lb) const {
+  __device__ __forceinline__ void put(float* la, float* lb, int blk, int L) {
+    if (32 * blk + 32 > L) {                                   // block-uniform
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        const bool past = 32 * blk + (int)(threadIdx.x + 256 * i) / kVecs >= L;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          a[i][k] = past ? 0.f : a[i][k];
+          b[i][k] = past ? 0.f : b[i][k];
+        }
+      }
+    }
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       const int f = threadIdx.x + 256 * i, at = f / kVecs * Staged<D>::kPitch + 4 * (f % kVecs);
@@ -240,6 +259,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 2 : 1) void attention_f32_ke
       f32x16_t p = over_d<D>(kf, qf);
       load_keys(kb + w.step);
       softmax_block(kb, p);
+      if (32 * kb + 32 > L) vf.clear_past(32 * kb, L, hf);     // wavefront-uniform
       over_rows<D>(o, vf, p);
     }
   } else {
@@ -248,7 +268,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 2 : 1) void attention_f32_ke
     next.fetch(base + A, ld, base + 2 * A, ld, 0, L);
     for (int kb = 0; kb < nkb; ++kb) {
       __syncthreads();                                         // the block before has been read by everyone
-      next.put(ks, vs);
+      next.put(ks, vs, kb, L);
       __syncthreads();
       if (kb + 1 < nkb) next.fetch(base + A, ld, base + 2 * A, ld, kb + 1, L);
       f32x16_t p = over_d<D>(Staged<D>{ks, r, hf}, qf);
@@ -341,7 +361,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attention_f32_bwd_dq_kernel(
     next.fetch(base + A, ld, base + 2 * A, ld, 0, L);
     for (int kb = 0; kb < nkb; ++kb) {
       __syncthreads();
-      next.put(ks, vs);
+      next.put(ks, vs, kb, L);
       __syncthreads();
       if (kb + 1 < nkb) next.fetch(base + A, ld, base + 2 * A, ld, kb + 1, L);
       const f32x16_t s = over_d<D>(Staged<D>{ks, r, hf}, qf);
@@ -359,7 +379,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attention_f32_bwd_dq_kernel(
   store_column<D>(dqkv + ((size_t)w.b * L + q) * ld + (size_t)w.h * D, dq, 1.0f, hf);
 }
 
-// dk and dv; needs lse and D of every query of the head
+// dk and dv; needs lse and D of every query of the head.  (d = 128: 12 values more than vector registers, 26 where
+// wavefronts share columns; the compiler keeps them in accumulation registers, none in memory.)
 template <int D, bool SPLIT>
 __global__ __launch_bounds__(64 * kWaves, 1) void attention_f32_bwd_dkv_kernel(
     const float* __restrict__ qkv, const float* __restrict__ dctx, const float* __restrict__ lse,
@@ -386,12 +407,13 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attention_f32_bwd_dkv_kernel(
   clear<D>(dk);
   clear<D>(dv);
   const int nqb = (L + 31) / 32;
-  // scores to p, dctx v^T to ds; ls, dd: lse and D of the queries.  A query past the end has lse = inf, D = 0: p = ds = 0
+  // scores to p, dctx v^T to ds; ls, dd: lse and D of the queries.  A query past the end has lse = inf: p = ds = 0
   auto probabilities = [&](f32x16_t& p, f32x16_t& ds, const float (&ls)[16], const float (&dd)[16]) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       p[i] = expf(p[i] * scale - ls[i]);
       ds[i] = p[i] * (ds[i] - dd[i]) * scale;
+      if (ls[i] == INFINITY) p[i] = ds[i] = 0.f;               // (also where a copied row's products are not finite)
     }
   };
   float ls[16], dd[16];
@@ -413,6 +435,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attention_f32_bwd_dkv_kernel(
       if (kAhead) load_queries(qb + w.step);
       else rows.load(gbase, (size_t)A, 32 * qb, L, r, hf);
       probabilities(p, ds, ls, dd);
+      rows.clear_past(32 * qb, L, hf);
       over_rows<D>(dv, rows, p);
       rows.load(base, ld, 32 * qb, L, r, hf);
       over_rows<D>(dk, rows, ds);
@@ -430,7 +453,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attention_f32_bwd_dkv_kernel(
     fetch(0);
     for (int qb = 0; qb < nqb; ++qb) {
       __syncthreads();
-      next.put(qs, gs);
+      next.put(qs, gs, qb, L);
       if (threadIdx.x < 64) stats[threadIdx.x >> 5][threadIdx.x & 31] = next_stat;
       __syncthreads();
       if (qb + 1 < nqb) fetch(qb + 1);

@@ -8,7 +8,8 @@
 //                    on the output of the fused Q|K|V projection, qkv [tokens, 3*heads*d]
 //
 // The attention core has two forms here: a flash-style MFMA kernel (bf16, d = 64 or 128) and a plain
-// one-wavefront-per-query kernel for other d; the fp32 one on the matrix cores is in attention_f32.hip.
+// one-wavefront-per-query kernel for other d and for fp32 calls of fewer than 128 queries; the fp32 one on the matrix
+// cores is in attention_f32.hip.
 #include <float.h>
 #include <math.h>
 #include <type_traits>

@@ -58,3 +58,23 @@ def test_scores_of_minus_infinity_add_nothing(B, L, heads, d):
 def test_backward(B, L, heads, d):
     enc.test_encoder_pair_backward(MoEConfig("f32", G=B, S=L, M=64, H=72, E=2, C=L, act_dtype="f32", seed=9600 + L,
                                              logit_bias_std=0.0), B, L, heads, d)
+
+
+@pytest.mark.parametrize("B,L,heads,d,last", [(2, 200, 2, 64, True), (40, 70, 16, 64, True), (1, 97, 2, 128, True), (34, 95, 4, 128, True),
+                                              (1, 96, 2, 64, True), (2, 200, 2, 64, False)])
+def test_infinite_value(B, L, heads, d, last):
+    """One infinite element of v makes its column of the context infinite, wherever its row stands: blocks of 32 rows
+    are filled up with others than copies of it."""
+    g = torch.Generator(device=DEV).manual_seed(L + d)
+    A = heads * d
+    u = torch.randn(B, L, 3 * A, device=DEV, generator=g)
+    w = torch.eye(3 * A, device=DEV)
+    col = 2 * A + 5                                            # element 5 of v of the first head
+    w[col, col] = 2
+    u[:, L - 1 if last else 3, col] = 3e38
+    out = torch.zeros_like(u)
+    sh, dims = moe.MoEShape(B, L, 3 * A, 8, 2, L, "f32"), moe.EncoderDims(B, L, heads, d)
+    ws = torch.empty(moe.moe_attention_workspace_bytes(sh, dims), dtype=torch.uint8, device=DEV)
+    moe.moe_self_attention(sh, dims, u, w, torch.eye(A, 3 * A, device=DEV), out, ws)
+    torch.cuda.synchronize()
+    assert bool((out[..., 5] == float("inf")).all())
