@@ -54,7 +54,10 @@ def test_scores_of_minus_infinity_add_nothing(B, L, heads, d):
     assert float((got - want).norm() / want.norm()) < 1e-6
 
 
-@pytest.mark.parametrize("B,L,heads,d", [(3, 33, 2, 64), (2, 95, 1, 128), (1, 257, 2, 64), (36, 40, 16, 64)])
+# columns of their own: 3 x 33, 36 x 40, 3 x 40 and 2 x 31; shared: 2 x 95, 1 x 257, and 1 x 170 (two blocks of rows to a
+# wavefront at d = 128)
+@pytest.mark.parametrize("B,L,heads,d", [(3, 33, 2, 64), (2, 95, 1, 128), (1, 257, 2, 64), (36, 40, 16, 64), (3, 40, 2, 128),
+                                         (2, 31, 3, 128), (1, 170, 2, 128)])
 def test_backward(B, L, heads, d):
     enc.test_encoder_pair_backward(MoEConfig("f32", G=B, S=L, M=64, H=72, E=2, C=L, act_dtype="f32", seed=9600 + L,
                                              logit_bias_std=0.0), B, L, heads, d)

@@ -21,8 +21,11 @@ CASES = [
     _cfg("rows_129", 3, 140, 128, 132, 3, 43),
     _cfg("columns_252", 2, 90, 252, 260, 5, 40),
     _cfg("skewed", 4, 333, 192, 328, 9, 75, bias=1.0),
-    # enough tiles for the 128 x 128 form, more row tiles than a band of eight
+    # more row tiles than a band of eight: 64 x 128 and 64 x 64 tiles; 128 x 128 tiles, weight gradients in four groups
     _cfg("many_tiles", 2, 1400, 384, 520, 2, 700),
+    _cfg("many_tiles_128", 2, 2600, 132, 132, 9, 577),
+    # 128 x 128 tiles throughout
+    _cfg("tiles_128", 2, 2100, 132, 132, 64, 65),
 ]
 
 

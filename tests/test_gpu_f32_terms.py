@@ -28,9 +28,10 @@ def _error(got, want):
     return float((got.double() - want).norm() / want.norm())
 
 
-# the shapes take 64 x 64 tiles with four, two and one groups, 64 x 128 and 128 x 128 tiles (256 units)
+# tiles of h and out on 256 units: 64 x 64 with four groups and with two; with four both; 64 x 128, 64 x 64 with four;
+# 64 x 128 both, twice; 64 x 64 without groups both; 128 x 128 both
 @pytest.mark.parametrize("E,R,M,H", [(2, 70, 516, 260), (3, 190, 1024, 1028), (16, 128, 512, 1024), (66, 12, 848, 3424),
-                                     (2, 3000, 1024, 1536)])
+                                     (2, 3000, 1024, 1536), (64, 257, 64, 132), (64, 130, 132, 132)])
 def test_error_against_float64(E, R, M, H):
     buf, wi, wo, h, out = _ffn(E, R, M, H)
     # the leading products' sum is rounded twice per 16 k: about 0.1 x 2^-24 sqrt(K) on these operands, allowed twice
@@ -40,7 +41,9 @@ def test_error_against_float64(E, R, M, H):
     assert _error(out, h.double() @ wo.double()) < bound(H)
 
 
-@pytest.mark.parametrize("E,R,M,H", [(2, 70, 132, 260), (3, 300, 160, 1028), (40, 200, 128, 1024), (2, 3000, 144, 1536)])
+# tiles of h: 64 x 64 with two groups, twice; 64 x 128, twice; 64 x 64 without groups; 128 x 128
+@pytest.mark.parametrize("E,R,M,H", [(2, 70, 132, 260), (3, 300, 160, 1028), (40, 200, 128, 1024), (2, 3000, 144, 1536),
+                                     (64, 257, 64, 132), (64, 130, 132, 132)])
 def test_infinities_nan_and_overflow(E, R, M, H):
     inf, nan = float("inf"), float("nan")
 
@@ -160,7 +163,7 @@ def _same(got, want, tol):
     assert not big.any() or _error(got[big], want[big].double()) < tol
 
 
-# tiles 128 x 128 throughout; 64 x 128 (weight gradients 128 x 128); 64 x 64 with groups and without
+# tiles of 128 x 128 throughout; 64 x 128 (weight gradients 128 x 128); 64 x 64 with two groups (weight gradients without)
 @pytest.mark.parametrize("E,C,M,H", [(16, 512, 1024, 2048), (66, 12, 848, 3424), (3, 70, 132, 260)])
 def test_training_step_with_infinities(E, C, M, H):
     """Masked and plain data gradients and weight gradients over kept rows with operands that are not finite."""
