@@ -33,7 +33,10 @@
  *   - Activations / expert weights / buffers have the element type
  *     cfg->act_dtype (fp32 or bf16).  The gate path (wg, u, gates, weights,
  *     auxiliary loss) is always fp32.  bf16 expert GEMMs accumulate in fp32; the
- *     hidden activation h is rounded to bf16 once.
+ *     hidden activation h is rounded to bf16 once.  fp32 GEMMs multiply operands as
+ *     three bf16 terms each: of a product of two numbers at most 2^-24 is left out, as
+ *     much as one fp32 rounding of it, over the whole range of fp32; sums are fp32.
+ *     Infinities, NaN and sums past 2^80 are formed in fp32 products (slower).
  *
  * Slot codes in `slot[G,S,2]`:  >= 0  position c in the expert's buffer;
  *   MOE_SLOT_OVERFLOW (-1) expert already full (Section 2.2, "Expert capacity");

@@ -33,7 +33,9 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 }
 // Eight fp32 as three bf16 operand fragments, v = t[0] + t[1] + t[2] exactly: each term is the leading 8
 // bits (truncated) of what the terms before it leave of the 24.  Products with bf16 are then exact in
-// fp32, and a matrix product over the terms is one with fp32 operands.
+// fp32, and a matrix product over the terms is one with fp32 operands.  (All three products are formed, so cut
+// off or rounded makes no difference to them; where products of small terms are left out, gemm_f32.hip, the terms are
+// rounded and scaled.)
 typedef uint32_t bf16x8_bits_t __attribute__((ext_vector_type(4)));
 template <typename V>
 __device__ __forceinline__ void split_bf16x8(const V& v, int first, bf16x8_bits_t (&t)[3]) {

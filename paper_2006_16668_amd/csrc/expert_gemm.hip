@@ -954,71 +954,122 @@ inline bool dma_shape_ok(int R, int N, int K) {
 // row-of-k, whose pieces are whole lines anyway, and their sums often short: 32 wide.
 enum GemmForm { kPersistent, kEdge128x256, kEdge128x128, kEdge128x128Deep, kEdge64x128, kEdge64x128Deep, kEdge64x64,
                 kEdge64x64Deep };
-enum GemmLayout { kLayoutForward, kLayoutDataGrad, kLayoutWeightGrad };
+enum GemmLayout { kLayoutForward, kLayoutDataGrad, kLayoutWeightGrad, kLayoutMaskedDataGrad };
 
 // The rule compares what the fullest compute unit needs: 32 k of the tiles that share it (ns; up to as many as
 // fit), the ends of the tiles (us; `more` of it for every further round), and the time in which the form streams the
-// weights from memory (TB/s).  Fitted to the six products of 185 shapes with cold weights (E 1 to 192, R 1 to 16384,
-// M 130 to 1024, H 260 to 8192).  On 49 shapes that an earlier fit had not seen, its choice was 0.9, 2.3 and 0.9 %
-// from the best form on average (forward, data gradients, weight gradients).
+// weights from memory (TB/s).  dh, whose sums are short and whose results are long, is often bound by its rows and
+// masks instead, so all its bytes count there (positions are 0.85 full in the mean; the persistent kernel reads the masks
+// as bits).
+// Fitted to the choices among the forms for the products of 430 shapes (E 1 to 192, R 1 to 16384, M 130 to 1024, H 260 to
+// 8192; two states of operands in turn).  On 110 others its choice was 3.0 % from the best form in the mean; with the
+// constants before, which took the persistent kernel too often where N or K is a few hundred and 128 x 256 tiles for long
+// sums of few tiles, 3.9 %.
 //   us, 64x64 deep / 64x64 / 64x128 deep / 64x128 / 128x128 deep / 128x128 / 128x256 / persistent:
-//   out  E 4  R 64   M 1024 H 4096   26.8 / 29.1 / 35.3 / 54.4 / 46.2 / 57.7 / 65.9 / -
-//   out  E 18 R 12   M 1024 H 4096   45.2 / 42.4 / 38.9 / 59.2 / 46.3 / 62.2 / 65.6 / -
-//   out  E 24 R 295  M 768  H 3072   87.4 / 81.7 / 71.7 / 62.0 / 80.7 / 60.1 / 71.6 / -
-//   out  E 16 R 512  M 512  H 2048   40.0 / 42.1 / 32.9 / 34.6 / 26.2 / 34.4 / 40.3 / 56
-//   h    E 22 R 130  M 600  H 2400   37.7 / 37.2 / 30.0 / 29.7 / 38.7 / 28.7 / 26.7 / -
-//   dbuf E 1  R 16384 M 1024 H 2048     - /    - /    - / 87.5 /    - / 70.5 / 74.8 / 69.1
-//   h    E 32 R 2048 M 1024 H 8192      - /    - /    - / 1526 /    - / 1419 / 1282 / 1206
+//   out  E 16  R 15   M 1024 H 4096    54 /   47 /   55 /   66 /   57 /   71 /   74 /   88
+//   out  E 24  R 295  M 768  H 3072    79 /   77 /   70 /   61 /   70 /   58 /   69 /  100
+//   out  E 100 R 290  M 256  H 512     24 /   22 /   21 /   24 /   25 /   24 /   23 /   36
+//   h    E 81  R 456  M 512  H 1024   112 /   96 /   87 /   82 /   94 /   75 /   64 /   78
+//   h    E 32  R 2048 M 1024 H 8192  2096 / 1740 / 1607 / 1402 / 1804 / 1335 / 1160 / 1147
+//   dbuf E 81  R 456  M 512  H 1024    96 /   90 /   79 /   77 /   81 /   69 /   69 /   88
+//   dh   E 5   R 612  M 512  H 1024    13 /   14 /   11 /   11 /   14 /   14 /   20 /   21
+//   dh   E 51  R 862  M 512  H 4096   545 /  454 /  455 /  402 /  537 /  392 /  370 /  291
 struct FormCost { int bm, bn, bk, res; double step[4], ends, more, stream; };
-GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout layout, int cus, double* time = nullptr) {
-  static const FormCost forward[] = {{256, 256, 32, 1, {840}, 7, 1, 6.0},             {128, 256, 32, 2, {500, 1010}, 9, 0.5, 6.0},
-                                     {128, 128, 64, 2, {340, 640}, 7, 0.5, 5.6},      {128, 128, 64, 1, {265}, 7, 0.5, 5.7},
-                                     {64, 128, 64, 3, {250, 385, 590}, 7, 0.5, 5.2},  {64, 128, 64, 2, {240, 575}, 4.4, 0.5, 5.5},
-                                     {64, 64, 64, 3, {168, 242, 340}, 4.8, 0.5, 4.6}, {64, 64, 64, 2, {155, 260}, 4.3, 0.5, 4.5}};
-  static const FormCost datagrad[] = {{256, 256, 32, 1, {870}, 6.5, 1, 5.5},          {128, 256, 32, 2, {610, 1240}, 8.6, 0.5, 5.0},
-                                      {128, 128, 64, 2, {283, 605}, 6.2, 0.5, 5.4},   {128, 128, 64, 1, {235}, 6.5, 0.5, 5.2},
-                                      {64, 128, 64, 3, {265, 375, 575}, 4, 0.5, 4.7}, {64, 128, 64, 2, {213, 445}, 4.3, 0.5, 5.6},
-                                      {64, 64, 64, 3, {152, 242, 328}, 4, 0.5, 5.2},  {64, 64, 64, 2, {142, 242}, 4, 0.5, 5.6}};
+const FormCost* form_costs(GemmLayout layout) {
+  static const FormCost forward[] = {{256, 256, 32, 1, {840}, 7.5, 1, 6.0},             {128, 256, 32, 2, {595, 980}, 8.3, 0.5, 6.0},
+                                     {128, 128, 64, 2, {360, 605}, 7, 0.5, 5.6},        {128, 128, 64, 1, {280}, 6.1, 0.5, 5.7},
+                                     {64, 128, 64, 3, {250, 288, 555}, 4.9, 0.47, 4.6}, {64, 128, 64, 2, {227, 405}, 4.1, 0.48, 4.6},
+                                     {64, 64, 64, 3, {168, 242, 340}, 4.6, 0.37, 4.8},  {64, 64, 64, 2, {119, 230}, 4, 0.5, 4.3}};
+  static const FormCost datagrad[] = {{256, 256, 32, 1, {930}, 6.5, 1, 5.5},          {128, 256, 32, 2, {640, 1110}, 8.6, 0.5, 5.0},
+                                      {128, 128, 64, 2, {283, 500}, 6.2, 0.5, 4.1},   {128, 128, 64, 1, {280}, 5.8, 0.5, 5.2},
+                                      {64, 128, 64, 3, {265, 322, 565}, 4, 0.5, 3.9}, {64, 128, 64, 2, {190, 393}, 3.7, 0.5, 5.1},
+                                      {64, 64, 64, 3, {152, 242, 330}, 3.4, 0.5, 5.1}, {64, 64, 64, 2, {123, 268}, 3.6, 0.5, 5.15}};
+  static const FormCost masked[] = {{256, 256, 32, 1, {767}, 6.9, 0.82, 5.5},          {128, 256, 32, 2, {580, 1245}, 10.7, 0.5, 5.2},
+                                    {128, 128, 64, 2, {289, 590}, 6.7, 0.5, 6.7},      {128, 128, 64, 1, {235}, 7.1, 0.5, 5.2},
+                                    {64, 128, 64, 3, {265, 268, 543}, 4.1, 0.44, 6.3}, {64, 128, 64, 2, {213, 390}, 4.6, 0.5, 6.5},
+                                    {64, 64, 64, 3, {152, 242, 300}, 3.5, 0.43, 6.5},  {64, 64, 64, 2, {142, 242}, 3.9, 0.5, 6.0}};
   static const FormCost weightgrad[] = {{256, 256, 32, 1, {840}, 12, 0.38, 0},            {128, 256, 32, 2, {480, 950}, 11, 0.3, 0},
                                         {128, 128, 32, 3, {272, 505, 760}, 5.6, 0.5, 0},  {0},
                                         {64, 128, 32, 3, {230, 350, 530}, 4.1, 0.6, 0},   {0},
                                         {64, 64, 32, 4, {162, 220, 320, 395}, 4, 0.5, 0}, {0}};
-  const FormCost* const cost = layout == kLayoutForward ? forward : layout == kLayoutDataGrad ? datagrad : weightgrad;
+  switch (layout) {
+    case kLayoutForward: return forward;
+    case kLayoutDataGrad: return datagrad;
+    case kLayoutMaskedDataGrad: return masked;
+    default: return weightgrad;
+  }
+}
+// us of a form, 0: not one for this shape (the persistent kernel's shapes are the caller's to check)
+double form_time(GemmForm f, int E, int R, int N, int K, GemmLayout layout, int cus) {
+  const FormCost* const cost = form_costs(layout);
+  const FormCost& c = cost[f];
+  if (c.bm == 0) return 0;
+  const long long n = (long long)E * ((R + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), round = (long long)c.res * cus;
+  // few tiles: the deep form, many: the other (64 x 128 tiles of any count may be deep, for weights that stream)
+  if ((f == kEdge64x64Deep || f == kEdge128x128Deep) && n > round) return 0;
+  if ((f == kEdge64x64 || f == kEdge128x128 || f == kEdge64x128) && n <= (long long)cost[f + 1].res * cus) return 0;
+  const int steps = (K + c.bk - 1) / c.bk * (c.bk / 32);
+  const long long full = n / round, rounds = (n + round - 1) / round;
+  const int left = (int)((n - full * round + cus - 1) / cus);
+  double part = left > 0 ? c.step[left - 1] : 0.0;
+  // (the weight gradients' last round starts while the one before it ends)
+  if (layout == kLayoutWeightGrad && full > 0 && left > 0)
+    part = 0.5 * (part + (double)(n - full * round) / round * c.step[c.res - 1]);
+  double us = 1e-3 * steps * (full * c.step[c.res - 1] + part);
+  us += c.ends * (1 + c.more * (double)(rounds - 1));
+  if (c.stream > 0) {
+    double elems = (double)N * K;
+    if (layout == kLayoutMaskedDataGrad) elems += 0.85 * R * ((double)K + (f == kPersistent ? 1.0 : 2.0) * N);
+    const double stream = 2e-6 * E * elems / c.stream + 0.5 * c.ends;
+    us = stream > us ? stream : us;
+  }
+  return us;
+}
+GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout layout, int cus, double* time = nullptr) {
   GemmForm form = kEdge128x256;
   double best = 0;
-  for (int f = kEdge64x64Deep; f >= kPersistent; --f) {
-    const FormCost& c = cost[f];
-    if (c.bm == 0 || (f == kPersistent && !persistent_ok)) continue;
-    const long long n = (long long)E * ((R + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), round = (long long)c.res * cus;
-    // few tiles: the deep form, many: the other (64 x 128 tiles of any count may be deep, for weights that stream)
-    if ((f == kEdge64x64Deep || f == kEdge128x128Deep) && n > round) continue;
-    if ((f == kEdge64x64 || f == kEdge128x128 || f == kEdge64x128) && n <= (long long)cost[f + 1].res * cus) continue;
-    const int steps = (K + c.bk - 1) / c.bk * (c.bk / 32);
-    const long long full = n / round, rounds = (n + round - 1) / round;
-    const int left = (int)((n - full * round + cus - 1) / cus);
-    double part = left > 0 ? c.step[left - 1] : 0.0;
-    // (the weight gradients' last round starts while the one before it ends)
-    if (layout == kLayoutWeightGrad && full > 0 && left > 0)
-      part = 0.5 * (part + (double)(n - full * round) / round * c.step[c.res - 1]);
-    double us = 1e-3 * steps * (full * c.step[c.res - 1] + part);
-    us += c.ends * (1 + c.more * (double)(rounds - 1));
-    if (c.stream > 0) {
-      const double stream = 2e-6 * E * N * K / c.stream + 0.5 * c.ends;
-      us = stream > us ? stream : us;
-    }
-    if (f == kEdge64x64Deep || best == 0 || us < best) { best = us; form = (GemmForm)f; }
+  for (int f = kEdge64x64Deep; f >= (persistent_ok ? kPersistent : kEdge128x256); --f) {
+    const double us = form_time((GemmForm)f, E, R, N, K, layout, cus);
+    if (us > 0 && (best == 0 || us < best)) { best = us; form = (GemmForm)f; }
   }
   if (time != nullptr) *time = best;
   return form;
 }
+// h of a training pass over packed rows: the persistent kernel takes relu' of dh from the bits that only it records
+// with h, so the two products are chosen together.  A dh that reads h leaves it in the last-level cache for dwo, unless it
+// is too large to stay there: an h that is slower persistent has to be that large, and gain 4 % of both.  us of h / dh / dwo,
+// each by its own best form, then h and dh persistent (MB of h at 0.85 full):
+//   E 12 R 4352 M 256  H 2048 (182)   80 / 162 /  83    97 /  93 /  91
+//   E 51 R 862  M 512  H 4096 (306)  234 / 346 / 198   259 / 265 / 205
+//   E 4  R 3376 M 512  H 4096  (94)   72 /  94 /  63    70 /  67 /  66
+//   E 10 R 602  M 768  H 6144  (63)   78 /  88 /  64    90 /  85 /  76
+//   E 5  R 1048 M 1024 H 4096  (36)   58 /  63 /  45    68 /  66 /  46
+bool persistent_h(int E, int R, int H, int M, int cus) {
+  double h = 0, dh = 0;
+  gemm_form(false, E, R, H, M, kLayoutForward, cus, &h);
+  gemm_form(false, E, R, H, M, kLayoutMaskedDataGrad, cus, &dh);
+  const double hp = form_time(kPersistent, E, R, H, M, kLayoutForward, cus);
+  const double dhp = form_time(kPersistent, E, R, H, M, kLayoutMaskedDataGrad, cus);
+  const double both = hp + (dhp < dh ? dhp : dh);
+  return hp < h ? both < h + dh : both < 0.96 * (h + dh) && 0.85 * 2 * E * R * H > 80e6;
+}
 // the form of this shape on the current device; k_kept: the sum over k runs over packed rows, of
 // which the persistent kernel takes whole 256-row tiles
-int choose_form(int E, int R, int N, int K, GemmLayout layout, GemmForm* form, bool k_kept = false,
-                bool persistent = true) {
+int choose_form(int E, int R, int N, int K, GemmLayout layout, GemmForm* form, bool k_kept = false) {
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
-  persistent = persistent && (dma_shape_ok(R, N, K) || (layout != kLayoutWeightGrad && dma_columns_ok(R, N, K)));
+  const bool persistent = dma_shape_ok(R, N, K) || (layout != kLayoutWeightGrad && dma_columns_ok(R, N, K));
   *form = gemm_form(persistent && (!k_kept || K % 256 == 0), E, R, N, K, layout, cus);
+  return MOE_OK;
+}
+// h and dh of a training pass over packed rows
+int choose_train_forms(const moe_config& c, GemmForm* h, GemmForm* dh) {
+  int cus = 0;
+  if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
+  const int R = c.G * c.C;
+  const bool bits = (dma_shape_ok(R, c.H, c.M) || dma_columns_ok(R, c.H, c.M)) && persistent_h(c.E, R, c.H, c.M, cus);
+  *h = bits ? kPersistent : gemm_form(false, c.E, R, c.H, c.M, kLayoutForward, cus);
+  *dh = gemm_form(bits, c.E, R, c.H, c.M, kLayoutMaskedDataGrad, cus);
   return MOE_OK;
 }
 
@@ -1220,8 +1271,9 @@ int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPackin
     if (!between()) return MOE_EHIP;
     return launch_gemm_f32(kForward, g2, c.E, R, c.M, c.H, st);
   }
-  GemmForm f1, f2;
-  if (choose_form(c.E, R, c.H, c.M, kLayoutForward, &f1) != MOE_OK || choose_form(c.E, R, c.M, c.H, kLayoutForward, &f2) != MOE_OK)
+  GemmForm f1, f2, dh;
+  if ((train ? choose_train_forms(c, &f1, &dh) : choose_form(c.E, R, c.H, c.M, kLayoutForward, &f1)) != MOE_OK ||
+      choose_form(c.E, R, c.M, c.H, kLayoutForward, &f2) != MOE_OK)
     return MOE_EHIP;
   if (f1 != kPersistent) {
     g1.row_pad = train ? packed_row_pad(c) : 0;
@@ -1300,10 +1352,9 @@ int launch_expert_dgrad2(const moe_config& c, const void* dout, const void* wo, 
   auto o = static_cast<bf16_t*>(dh);
   auto sign = const_cast<unsigned char*>(static_cast<const unsigned char*>(signbits));
   GemmForm form, h_form;
-  if (choose_form(c.E, (int)R, c.H, c.M, kLayoutForward, &h_form) != MOE_OK) return MOE_EHIP;
-  // packed rows: the persistent kernel takes relu' from the bits that only it records with h
-  const bool no_bits = kept != nullptr && h_form != kPersistent;
-  if (choose_form(c.E, (int)R, c.H, c.M, kLayoutDataGrad, &form, false, !no_bits) != MOE_OK) return MOE_EHIP;
+  if ((kept != nullptr ? choose_train_forms(c, &h_form, &form)
+                       : choose_form(c.E, (int)R, c.H, c.M, kLayoutMaskedDataGrad, &form)) != MOE_OK)
+    return MOE_EHIP;
   if (form != kPersistent) {
     g.row_pad = kept != nullptr ? packed_row_pad(c) : 0;
     return gemm_bf16_edge<2, false, true>(form, g, c.E, (int)R, c.H, c.M, st);

@@ -13,14 +13,16 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# products the persistent kernel forms: all four; h and dh (with bits); out and dbuf; all four, a tile's last rows only
-@pytest.mark.parametrize("G,S,M,H,E,C", [(2, 8200, 256, 256, 4, 4100), (1, 3700, 256, 2048, 8, 903), (2, 4100, 768, 256, 2, 4100),
-                                         (1, 20400, 256, 768, 20, 2040)])
+# products the persistent kernel forms: all four; h and dh (with bits); out and dbuf; h and dh, a tile's last rows only;
+# none (tiles of 64 x 128)
+@pytest.mark.parametrize("G,S,M,H,E,C", [(1, 20500, 256, 256, 10, 4100), (1, 3700, 256, 2048, 8, 903), (2, 4100, 768, 256, 2, 4100),
+                                         (1, 20400, 256, 768, 20, 2040), (2, 8200, 256, 256, 4, 4100)])
 def test_forward_and_backward(G, S, M, H, E, C):
     shapes.test_random_shape(MoEConfig("rows", G=G, S=S, M=M, H=H, E=E, C=C, act_dtype="bf16", seed=9800 + C, logit_bias_std=0.0))
 
 
-@pytest.mark.parametrize("rows,M,H", [(16000, 1024, 1024), (8209, 1024, 1024)])
+# persistent, persistent with one row in the last tile, tiles of 64 x 128
+@pytest.mark.parametrize("rows,M,H", [(16000, 1024, 1024), (15873, 1024, 1024), (8209, 1024, 1024)])
 def test_dense_rows(rows, M, H):
     g = torch.Generator(device=DEV).manual_seed(rows)
     u = torch.randn(rows, M, device=DEV, generator=g).bfloat16()
