@@ -296,6 +296,7 @@ __global__ __launch_bounds__(256 * KG, TM * TN >= 4 ? 2 : TM * TN >= 2 ? 3 : 4) 
         for (int i = 0; i < TM; ++i)
           rest[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][q], b[1 - q], rest[i][j], 0, 0, 0);
     }
+    if (KG > 1) __syncthreads();                               // the groups' sums will overwrite the planes
   }
 #pragma unroll
   for (int i = 0; i < TM; ++i)

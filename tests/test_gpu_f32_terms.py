@@ -77,7 +77,8 @@ def _chain(a, b):
     return s
 
 
-@pytest.mark.parametrize("K", [4, 8, 12, 16, 32])
+# one step of 16 k; of two groups (32) and of four (64), which meet in LDS after it
+@pytest.mark.parametrize("K", [4, 8, 12, 16, 32, 64])
 def test_short_sums(K):
     buf, wi, _, h, _ = _ffn(2, 70, K, 260)
     want = torch.relu(buf.double() @ wi.double())
