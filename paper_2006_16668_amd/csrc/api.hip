@@ -340,7 +340,7 @@ int moe_prepare(void) {
   if (rc == MOE_OK) rc = moe::prepare_gemm_f32();
   if (rc == MOE_OK) rc = moe::prepare_gate();
   if (rc == MOE_OK) rc = moe::prepare_backward();
-  if (rc == MOE_OK) rc = moe::prepare_attention_bwd();
+  if (rc == MOE_OK) rc = moe::prepare_attention_mfma();
   void* p = nullptr;
   if (rc == MOE_OK) rc = gate_scratch_ptr(&p);
   return rc;

@@ -289,8 +289,9 @@ int launch_dense_wgrad_ranges(const DenseWgradPlan& p, long long rows, int in, i
 size_t dense_wgrad_partial_bytes(int act_dtype, long long rows, int in, int out);
 int launch_dense_wgrad(const moe_config& c, long long rows, int in, int out, const void* X,
                        const void* dY, void* dW, float* partial, hipStream_t st);
-// MFMA form (attention_bwd_mfma.hip): bf16, d = 64 or 128
-bool attention_bwd_mfma_ok(int act_dtype, int d);
+// MFMA form (attention_mfma.hip): bf16, d = 64 or 128
+bool attention_mfma_ok(int act_dtype, int L, int heads, int d);
+int launch_attention_mfma(const void* qkv, void* ctx, float* lse, long long B, int L, int heads, int d, hipStream_t st);
 int launch_attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, const float* lse,
                               void* dqkv, float* dvec, long long B, int L, int heads, int d,
                               hipStream_t st);
@@ -328,6 +329,6 @@ int prepare_expert_gemm();        // expert_gemm.hip
 int prepare_gemm_f32();           // gemm_f32.hip
 int prepare_gate();               // gate.hip
 int prepare_backward();           // backward.hip
-int prepare_attention_bwd();      // attention_bwd_mfma.hip
+int prepare_attention_mfma();     // attention_mfma.hip
 
 }  // namespace moe

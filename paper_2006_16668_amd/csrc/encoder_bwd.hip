@@ -12,7 +12,7 @@
 //
 // The attention core has a plain form here (one wavefront per query row for dq, one per key row
 // for dk and dv, any dtype and shape whose rows fit in LDS); the MFMA form lives in
-// attention_bwd_mfma.hip.
+// attention_mfma.hip.
 #include <math.h>
 #include "common.h"
 
@@ -359,7 +359,7 @@ int launch_layer_norm_bwd(int act_dtype, const void* s, const void* dn, const fl
 int launch_attention_core_bwd(int act_dtype, const void* qkv, const void* ctx, const void* dctx,
                               const float* lse, void* dqkv, float* dvec, long long B, int L,
                               int heads, int d, hipStream_t st) {
-  if (attention_bwd_mfma_ok(act_dtype, d))
+  if (attention_mfma_ok(act_dtype, L, heads, d))
     return launch_attention_bwd_mfma(qkv, ctx, dctx, lse, dqkv, dvec, B, L, heads, d, st);
   const long long rows = B * heads * L;
   const size_t lds = (size_t)4 * (2 * L + 2 * d) * sizeof(float);
