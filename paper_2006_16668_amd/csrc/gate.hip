@@ -933,8 +933,10 @@ __device__ __forceinline__ void gate_single_chunk_finish(
 //     split into bf16 terms, a logit GEMM and a softmax pass -> 45 us.
 // A call with a single chunk in all (a server's step) finishes here, no scan and no slots kernel: 64
 // tokens, M 1024, E 32: 16.9 -> 10.6 us.
-// TAIL: fp32 and M % 32 != 0.
-template <typename T, int ETW, int KW, bool TAIL>
+// TAIL: fp32 and M % 32 != 0.  RAW: bf16 and wg as it is, split into its three terms on the way to the products: a
+// chunk's wavefronts together read each weight once, so packing them first (a launch of 4 to 5 us) does not
+// pay for one call.  Training step of 4 x 1024 tokens, M 512, H 2048, E 16 211.0 -> 203.3 us.
+template <typename T, int ETW, int KW, bool TAIL, bool RAW>
 __global__ __launch_bounds__(512) void gate_chunk_kernel(
     const T* __restrict__ x, const uint4* __restrict__ wgP, const float* __restrict__ wg,
     const float* __restrict__ u, int S, int M, int E, int C, int nch, int32_t* expert_idx, int32_t* slot,
@@ -981,7 +983,7 @@ __global__ __launch_bounds__(512) void gate_chunk_kernel(
   constexpr int NB = !F32 && ETW == 2 ? 1 : 2;
   for (int kb = kb0; kb < kb1; kb += NB) {
     u32x4_t a[NB][2][4];
-    float bf[NB][16][ETW];
+    float bf[NB][F32 ? 16 : 32][ETW];
     u32x4_t bp[NB][4][ETW * 3];
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
@@ -999,6 +1001,14 @@ __global__ __launch_bounds__(512) void gate_chunk_kernel(
 #pragma unroll
           for (int t = 0; t < ETW; ++t) {
             const int m = cur * FB + 16 * h + q, e = 32 * (cw * ETW + t) + r;
+            bf[n][q][t] = wg[m < M && e < E ? (size_t)m * E + e : 0];
+          }
+      } else if constexpr (RAW) {
+#pragma unroll
+        for (int q = 0; q < 32; ++q)
+#pragma unroll
+          for (int t = 0; t < ETW; ++t) {
+            const int m = cur * FB + 32 * h + q, e = 32 * (cw * ETW + t) + r;
             bf[n][q][t] = wg[m < M && e < E ? (size_t)m * E + e : 0];
           }
       } else {
@@ -1031,6 +1041,25 @@ __global__ __launch_bounds__(512) void gate_chunk_kernel(
                                                                 acc[rt][t], 0, 0, 0);
           }
       } else {
+        if constexpr (RAW) {                            // the terms of gate_pack_wg_kernel
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int t = 0; t < ETW; ++t)
+#pragma unroll
+              for (int i = 0; i < 8; i += 2) {
+                const bool col = 32 * (cw * ETW + t) + r < E;
+                const int m = (kb + n) * FB + 32 * h + 8 * j + i;
+                float v0 = col && m < M ? bf[n][8 * j + i][t] : 0.f, v1 = col && m + 1 < M ? bf[n][8 * j + i + 1][t] : 0.f;
+#pragma unroll
+                for (int sp = 0; sp < 3; ++sp) {
+                  const uint32_t w = pack_bf16x2(v0, v1);
+                  bp[n][j][t * 3 + sp][i / 2] = w;
+                  v0 -= __uint_as_float(w << 16);       // exact
+                  v1 -= __uint_as_float(w & 0xffff0000u);
+                }
+              }
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -1664,10 +1693,10 @@ constexpr size_t kGateRowsLds1 = (4 * 128 * 36 + 8 * 32) * 4, kGateRowsLds2 = (4
 // partial logits [KW][64][Epad + 8] and two histograms [Epad]
 template <int ETW, int KW> constexpr int kGateChunkLds = (KW * 64 * (32 * ETW * 8 / KW + 8) + 2 * 32 * ETW * 8 / KW) * 4;
 
-template <typename T, int ETW, int KW, bool TAIL>
+template <typename T, int ETW, int KW, bool TAIL, bool RAW = false>
 static int prepare_gate_chunk() {
   static LdsLimitOnce once;
-  return ensure_lds_limit(once, reinterpret_cast<const void*>(gate_chunk_kernel<T, ETW, KW, TAIL>),
+  return ensure_lds_limit(once, reinterpret_cast<const void*>(gate_chunk_kernel<T, ETW, KW, TAIL, RAW>),
                           kGateChunkLds<ETW, KW>);
 }
 
@@ -1681,6 +1710,7 @@ static int prepare_gate_rows() {
 int prepare_gate() {
   const int rcs[] = {prepare_gate_rows<1>(), prepare_gate_rows<2>(),
                      prepare_gate_chunk<bf16_t, 1, 8, false>(), prepare_gate_chunk<bf16_t, 2, 8, false>(),
+                     prepare_gate_chunk<bf16_t, 1, 8, false, true>(), prepare_gate_chunk<bf16_t, 2, 8, false, true>(),
                      prepare_gate_chunk<float, 1, 8, false>(), prepare_gate_chunk<float, 1, 8, true>(),
                      prepare_gate_chunk<float, 2, 8, false>(), prepare_gate_chunk<float, 2, 8, true>(),
                      prepare_gate_chunk<float, 2, 4, false>(), prepare_gate_chunk<float, 2, 4, true>()};
@@ -1729,20 +1759,27 @@ int launch_gate(const moe_config& c, const void* x, const float* wg, const float
   const bool single = chunk_form && chunks == 1;
   const int zero_words = zero_row != nullptr ? c.M / 2 : 0;
   const RowPacking pk = packing != nullptr ? *packing : RowPacking{nullptr, nullptr, nullptr};
-  if (wg_prepacked == nullptr && (rc = launch_gate_pack(c, wg, own, st)) != MOE_OK) return rc;
+  const bool raw = chunk_form && c.act_dtype == MOE_BF16 && wg_prepacked == nullptr;
+  if (wg_prepacked == nullptr && !raw && (rc = launch_gate_pack(c, wg, own, st)) != MOE_OK) return rc;
   if (chunk_form) {
-#define MOE_GATE_CHUNK(T, ETW, KW, TAIL)                                                                \
+#define MOE_GATE_CHUNK(T, ETW, KW, TAIL, RAW)                                                           \
   {                                                                                                     \
-    if (prepare_gate_chunk<T, ETW, KW, TAIL>() != MOE_OK) return MOE_EHIP;                              \
-    hipLaunchKernelGGL((gate_chunk_kernel<T, ETW, KW, TAIL>), dim3((unsigned)chunks), dim3(512),        \
+    if (prepare_gate_chunk<T, ETW, KW, TAIL, RAW>() != MOE_OK) return MOE_EHIP;                         \
+    hipLaunchKernelGGL((gate_chunk_kernel<T, ETW, KW, TAIL, RAW>), dim3((unsigned)chunks), dim3(512),   \
                        (kGateChunkLds<ETW, KW>), st, static_cast<const T*>(x), wgP, wg, u, c.S, c.M, c.E, c.C, \
                        nch, expert_idx, slot, weight, gates_opt, hist1, hist2, msum, src_token, c1,     \
                        mean_gate, fill, aux, static_cast<uint32_t*>(zero_row), zero_words, pk, single); \
   }
 #define MOE_GATE_CHUNK_F32(ETW, KW)                                                                     \
-  if (c.M % 32 != 0) MOE_GATE_CHUNK(float, ETW, KW, true) else MOE_GATE_CHUNK(float, ETW, KW, false)
+  if (c.M % 32 != 0) MOE_GATE_CHUNK(float, ETW, KW, true, false) else MOE_GATE_CHUNK(float, ETW, KW, false, false)
     if (c.act_dtype == MOE_BF16) {
-      if (c.E <= 32) MOE_GATE_CHUNK(bf16_t, 1, 8, false) else MOE_GATE_CHUNK(bf16_t, 2, 8, false)
+      if (c.E <= 32) {
+        if (raw) MOE_GATE_CHUNK(bf16_t, 1, 8, false, true) else MOE_GATE_CHUNK(bf16_t, 1, 8, false, false)
+      } else if (raw) {
+        MOE_GATE_CHUNK(bf16_t, 2, 8, false, true)
+      } else {
+        MOE_GATE_CHUNK(bf16_t, 2, 8, false, false)
+      }
     } else if (c.E <= 32) {
       MOE_GATE_CHUNK_F32(1, 8)
     } else if (c.E <= 64) {
