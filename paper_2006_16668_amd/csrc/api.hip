@@ -288,17 +288,6 @@ EncoderBwdWs carve_enc_bwd(const moe_config& c, const moe_encoder_dims& d) {
   return w;
 }
 
-// one-expert configuration for the dense layers' gradient GEMMs: rows tokens, widths in -> out
-moe_config dense_cfg(const moe_config& c, long long rows, int in, int out) {
-  moe_config g = c;
-  g.E = 1;
-  g.G = 1;
-  g.C = (int)rows;
-  g.M = in;
-  g.H = out;
-  return g;
-}
-
 // gradients of out = Attention(u): dout [N,M] -> du [N,M], dwqkv [M,3A], dwo_att [A,M]
 int attention_bwd_impl(const moe_config& c, const moe_encoder_dims& d, const void* u,
                        const void* wqkv, const void* wo_att, const void* qkv, const void* ctx,
@@ -307,17 +296,13 @@ int attention_bwd_impl(const moe_config& c, const moe_encoder_dims& d, const voi
   const long long N = (long long)c.G * c.S;
   const int A = d.heads * d.d;
   // out = ctx . wo_att
-  int rc = moe::launch_dense_wgrad(c, N, A, c.M, ctx, dout, dwo_att, wpart, st);
-  if (rc != MOE_OK) return rc;
-  rc = moe::launch_expert_dgrad1(dense_cfg(c, N, A, c.M), dout, wo_att, dctx, nullptr, st);
+  int rc = moe::launch_dense_grads(c, N, A, c.M, ctx, dout, wo_att, nullptr, dctx, dwo_att, wpart, st);
   if (rc != MOE_OK) return rc;
   rc = moe::launch_attention_core_bwd(c.act_dtype, qkv, ctx, dctx, lse, dqkv, dvec, d.B, d.L, d.heads,
                                       d.d, st);
   if (rc != MOE_OK) return rc;
   // qkv = u . wqkv
-  rc = moe::launch_dense_wgrad(c, N, c.M, 3 * A, u, dqkv, dwqkv, wpart, st);
-  if (rc != MOE_OK) return rc;
-  return moe::launch_expert_dgrad1(dense_cfg(c, N, c.M, 3 * A), dqkv, wqkv, du, nullptr, st);
+  return moe::launch_dense_grads(c, N, c.M, 3 * A, u, dqkv, wqkv, nullptr, du, dwqkv, wpart, st);
 }
 
 }  // namespace
@@ -599,20 +584,26 @@ int moe_backward_events(const moe_config* cfg, const void* x, const float* wg, c
                                base + b.buf, dweight, kept, st);
   if (rc != MOE_OK) return rc;
   if (!mark(1)) return MOE_EHIP;
-  rc = moe::launch_expert_dgrad2(*cfg, base + b.dout, wo, fb + f.h,
-                                 packed ? fb + f.signbits : nullptr,
-                                 base + b.dh, kept, st);
-  if (rc != MOE_OK) return rc;
-  if (!mark(2)) return MOE_EHIP;
-  rc = moe::launch_expert_wgrad2(*cfg, fb + f.h, base + b.dout, dwo, kept, st);
-  if (rc != MOE_OK) return rc;
-  if (!mark(3)) return MOE_EHIP;
-  rc = moe::launch_expert_dgrad1(*cfg, base + b.dh, wi, base + b.dbuf, kept, st);
-  if (rc != MOE_OK) return rc;
-  if (!mark(4)) return MOE_EHIP;
-  rc = moe::launch_expert_wgrad1(*cfg, base + b.buf, base + b.dh, dwi, kept, st);
-  if (rc != MOE_OK) return rc;
-  if (!mark(5)) return MOE_EHIP;
+  const void* const signbits = packed ? fb + f.signbits : nullptr;
+  if (events == nullptr) {
+    rc = moe::launch_expert_grads2(*cfg, base + b.dout, wo, fb + f.h, signbits, base + b.dh, dwo, kept, st);
+    if (rc != MOE_OK) return rc;
+    rc = moe::launch_expert_grads1(*cfg, base + b.dh, wi, base + b.dbuf, base + b.buf, dwi, kept, st);
+    if (rc != MOE_OK) return rc;
+  } else {                                  // a mark behind each product: one launch each
+    rc = moe::launch_expert_dgrad2(*cfg, base + b.dout, wo, fb + f.h, signbits, base + b.dh, kept, st);
+    if (rc != MOE_OK) return rc;
+    if (!mark(2)) return MOE_EHIP;
+    rc = moe::launch_expert_wgrad2(*cfg, fb + f.h, base + b.dout, dwo, kept, st);
+    if (rc != MOE_OK) return rc;
+    if (!mark(3)) return MOE_EHIP;
+    rc = moe::launch_expert_dgrad1(*cfg, base + b.dh, wi, base + b.dbuf, kept, st);
+    if (rc != MOE_OK) return rc;
+    if (!mark(4)) return MOE_EHIP;
+    rc = moe::launch_expert_wgrad1(*cfg, base + b.buf, base + b.dh, dwi, kept, st);
+    if (rc != MOE_OK) return rc;
+    if (!mark(5)) return MOE_EHIP;
+  }
   rc = moe::launch_gate_bwd(*cfg, x, wg, reinterpret_cast<const float*>(fb + f.gates), expert_idx,
                             slot, dweight, reinterpret_cast<const int32_t*>(fb + f.c1), daux, gw,
                             dwg, st);
@@ -860,17 +851,10 @@ int moe_encoder_pair_backward(const moe_config* cfg, const moe_encoder_dims* dim
                                   g->ln_beta[2], N, cfg->M, st);
   if (rc != MOE_OK) return rc;
   // b = a + relu(n2 w1) w2
-  {
-    const moe_config fc = dense_cfg(*cfg, N, cfg->M, cfg->H);
-    rc = moe::launch_dense_wgrad(*cfg, N, cfg->H, cfg->M, f + e.hden, g1, g->w2, wpart, st);
-    if (rc != MOE_OK) return rc;
-    rc = moe::launch_expert_dgrad2(fc, g1, w->w2, f + e.hden, nullptr, base + bw.dhden, nullptr, st);
-    if (rc != MOE_OK) return rc;
-    rc = moe::launch_dense_wgrad(*cfg, N, cfg->M, cfg->H, f + e.n[1], base + bw.dhden, g->w1, wpart, st);
-    if (rc != MOE_OK) return rc;
-    rc = moe::launch_expert_dgrad1(fc, base + bw.dhden, w->w1, dn, nullptr, st);
-    if (rc != MOE_OK) return rc;
-  }
+  rc = moe::launch_dense_grads(*cfg, N, cfg->H, cfg->M, f + e.hden, g1, w->w2, f + e.hden, base + bw.dhden, g->w2, wpart, st);
+  if (rc != MOE_OK) return rc;
+  rc = moe::launch_dense_grads(*cfg, N, cfg->M, cfg->H, f + e.n[1], base + bw.dhden, w->w1, nullptr, dn, g->w1, wpart, st);
+  if (rc != MOE_OK) return rc;
   rc = moe::launch_layer_norm_bwd(dt, f + e.a, dn, w->ln_gamma[1], g1, g0, partial, g->ln_gamma[1],
                                   g->ln_beta[1], N, cfg->M, st);
   if (rc != MOE_OK) return rc;

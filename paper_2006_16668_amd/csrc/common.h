@@ -250,6 +250,12 @@ int launch_expert_dgrad1(const moe_config& c, const void* dh, const void* wi, vo
 int launch_expert_wgrad1(const moe_config& c, const void* buf, const void* dh, void* dwi,
                          const int32_t* kept, hipStream_t st);
 
+//   grads2 = dgrad2 and wgrad2, grads1 = dgrad1 and wgrad1, in one launch where that is faster
+int launch_expert_grads2(const moe_config& c, const void* dout, const void* wo, const void* h, const void* signbits, void* dh,
+                         void* dwo, const int32_t* kept, hipStream_t st);
+int launch_expert_grads1(const moe_config& c, const void* dh, const void* wi, void* dbuf, const void* buf, void* dwi,
+                         const int32_t* kept, hipStream_t st);
+
 // batched bf16 MFMA GEMM with an fp32 result (expert_gemm.hip): transposed_a ? C = A^T.B with
 // A [batch,K,R], B [batch,K,N] : C = A.B^T with A [batch,R,K], B [batch,N,K]; C [batch,R,N]
 bool gemm_bf16_f32out_ok(int R, int N, int K);
@@ -287,8 +293,11 @@ DenseWgradPlan dense_wgrad_plan(long long rows, int in, int out);     // expert_
 int launch_dense_wgrad_ranges(const DenseWgradPlan& p, long long rows, int in, int out, const void* X, const void* dY,
                               float* partial, hipStream_t st);
 size_t dense_wgrad_partial_bytes(int act_dtype, long long rows, int in, int out);
-int launch_dense_wgrad(const moe_config& c, long long rows, int in, int out, const void* X,
-                       const void* dY, void* dW, float* partial, hipStream_t st);
+int launch_dense_grads_pair(const DenseWgradPlan& p, long long rows, int in, int out, const void* X, const void* dY,
+                            const void* W, const void* mask, void* dX, void* dW, float* partial, hipStream_t st, bool* done);
+// dW, and dX [rows,in] = dY W^T (W [in,out]; zero where mask, of dX's shape, is <= 0, unless mask is NULL)
+int launch_dense_grads(const moe_config& c, long long rows, int in, int out, const void* X, const void* dY, const void* W,
+                       const void* mask, void* dX, void* dW, float* partial, hipStream_t st);
 // MFMA form (attention_mfma.hip): bf16, d = 64 or 128
 bool attention_mfma_ok(int act_dtype, int L, int heads, int d);
 int launch_attention_mfma(const void* qkv, void* ctx, float* lse, long long B, int L, int heads, int d, hipStream_t st);

@@ -302,21 +302,37 @@ size_t dense_wgrad_partial_bytes(int act_dtype, long long rows, int in, int out)
   return sp > 1 ? (size_t)sp * in * out * sizeof(float) : 0;
 }
 
-int launch_dense_wgrad(const moe_config& c, long long rows, int in, int out, const void* X,
-                       const void* dY, void* dW, float* partial, hipStream_t st) {
+int launch_dense_grads(const moe_config& c, long long rows, int in, int out, const void* X, const void* dY, const void* W,
+                       const void* mask, void* dX, void* dW, float* partial, hipStream_t st) {
   if (rows > 0x7fffffffLL) return MOE_EUNSUPPORTED;
-  const DenseWgradPlan plan = c.act_dtype == MOE_BF16 ? dense_wgrad_plan(rows, in, out) : DenseWgradPlan{1, (int)rows};
-  if (plan.splits <= 1 || partial == nullptr) {
+  DenseWgradPlan plan{1, (int)rows};
+  if (c.act_dtype == MOE_BF16 && partial != nullptr) plan = dense_wgrad_plan(rows, in, out);
+  bool done = false;
+  int rc = MOE_OK;
+  if (c.act_dtype == MOE_BF16)
+    rc = launch_dense_grads_pair(plan, rows, in, out, X, dY, W, mask, dX, dW, partial, st, &done);
+  if (rc != MOE_OK) return rc;
+  if (!done) {
     moe_config g = c;
     g.E = 1; g.G = 1; g.C = (int)rows; g.M = in; g.H = out;
-    return launch_expert_wgrad1(g, X, dY, dW, nullptr, st);
+    rc = plan.splits > 1 ? launch_dense_wgrad_ranges(plan, rows, in, out, X, dY, partial, st)
+                         : launch_expert_wgrad1(g, X, dY, dW, nullptr, st);
   }
-  const int rc = launch_dense_wgrad_ranges(plan, rows, in, out, X, dY, partial, st);
   if (rc != MOE_OK) return rc;
-  const long long elems = (long long)in * out;
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((elems / 8 + 255) / 256)), dim3(256), 0, st,
-                     partial, plan.splits, elems, static_cast<uint4*>(dW));
-  return check_launch();
+  if (plan.splits > 1) {
+    const long long elems = (long long)in * out;
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((elems / 8 + 255) / 256)), dim3(256), 0, st,
+                       partial, plan.splits, elems, static_cast<uint4*>(dW));
+    if ((rc = check_launch()) != MOE_OK) return rc;
+  }
+  if (done) return MOE_OK;
+  // (the second product of a feed-forward layer is its transpose in the expert's naming)
+  moe_config g = c;
+  g.E = 1; g.G = 1; g.S = g.C = (int)rows;
+  g.M = mask != nullptr ? out : in;
+  g.H = mask != nullptr ? in : out;
+  return mask != nullptr ? launch_expert_dgrad2(g, dY, W, mask, nullptr, dX, nullptr, st)
+                         : launch_expert_dgrad1(g, dY, W, dX, nullptr, st);
 }
 
 int layer_norm_bwd_parts(long long rows) {

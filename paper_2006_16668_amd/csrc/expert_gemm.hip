@@ -15,8 +15,9 @@
 //   expert_gemm_bf16_edge_kernel  every other shape, and outputs of few tiles: one block per
 //     tile of 128 x 256 down to 64 x 64, two to four blocks per CU, the same register-bypassing
 //     copies with per-lane source addresses (pieces past an edge come from a zero line).
+//     expert_gemm_bf16_pair_kernel runs the tiles of two such products in one launch.
 //
-// In both, activation tiles (K contiguous) sit in LDS as [m][k] and are read with
+// In all, activation tiles (K contiguous) sit in LDS as [m][k] and are read with
 // 16-byte loads; weight tiles are [k][n] in memory (N contiguous), stay that way in
 // LDS and are read with ds_read_b64_tr_b16, which hands every lane the 4 consecutive
 // k of its column that the MFMA operand wants.  Blocks of one XCD (own L2) take
@@ -614,12 +615,32 @@ __device__ __forceinline__ constexpr int edge_swizzle(int k) {
   return COLS == 64 ? 4 * ((k >> 1) & 1) : 4 * (k & 3);
 }
 
+// The arguments of a product, of one launch or of one of the two of a pair (below).
+struct EdgeArgs {
+  const bf16_t *A, *B;
+  bf16_t* C;
+  const bf16_t* mask;
+  int R, N, K, tiles_m, tiles_n, nblk;
+  const int32_t *gather, *kept;
+  int row_pad;
+  const int32_t* scatter;
+  int k_total;
+};
+// EPI of the products of a pair: decided by their arguments
+constexpr int kEpiMaskIfAny = 6;       // 2 with a mask, else 0
+constexpr int kEpiRangesIfAny = 7;     // 3 with a k_total, else 0; kept is K_KEPT's
+
 template <int BM, int BN, int BK, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
-__global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert_gemm_bf16_edge_kernel(
-    const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ Cout,
-    const bf16_t* __restrict__ mask, int R, int N, int K, int tiles_m, int tiles_n, int nblk,
-    const int32_t* __restrict__ gather, const int32_t* __restrict__ kept,
-    int row_pad, const int32_t* __restrict__ scatter, int k_total) {
+__device__ __forceinline__ void edge_tile(const EdgeArgs& arg, const int logical) {
+  const bf16_t *const __restrict__ A = arg.A, *const __restrict__ B = arg.B, *const __restrict__ mask = arg.mask;
+  bf16_t* const __restrict__ Cout = arg.C;
+  const int R = arg.R, N = arg.N, K = arg.K, tiles_m = arg.tiles_m, tiles_n = arg.tiles_n, row_pad = arg.row_pad;
+  const int32_t *const __restrict__ gather = arg.gather, *const __restrict__ kept = arg.kept, *const __restrict__ scatter = arg.scatter;
+  const int k_total = arg.k_total;
+  const bool masked = EPI == 2 || (EPI == kEpiMaskIfAny && mask != nullptr);
+  const bool ranges = EPI == 3 || (EPI == kEpiRangesIfAny && k_total != 0);
+  const bool k_kept = K_KEPT || (EPI == kEpiRangesIfAny && kept != nullptr);
+  constexpr bool MASKS = EPI == 2 || EPI == kEpiMaskIfAny, RANGES = EPI == 3 || EPI == kEpiRangesIfAny;
   static_assert(EPI != 3 || (A_MNC && !B_KC && !K_KEPT), "ranges of k: of row-of-k operands");
   using SM = EdgeSmem<BM, BN, BK, ST>;
   constexpr int TM = BM / 64, TN = BN / 64;
@@ -636,7 +657,6 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
 
   // Neighbouring tiles on one XCD; inside an expert bands of 8 row tiles, row tile fastest, so
   // that the tiles an XCD works on at a time share row and column panels in its L2.
-  const int logical = xcd_remap(blockIdx.x, nblk);
   const int per_e = tiles_m * tiles_n;
   const int e = logical / per_e;
   const int t = logical - e * per_e;
@@ -646,14 +666,14 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
   const int ct = rem / brows, rt = band * kBand + (rem - ct * brows);
   const int m0 = rt * BM, n0 = ct * BN;
   int rows = R, rows_out = R;                                  // rows of A that count, of C that are stored
-  if (kept != nullptr && !K_KEPT) {
+  if (kept != nullptr && !k_kept) {
     rows = kept[e];
     rows_out = (rows + row_pad) & ~row_pad;
     rows_out = rows_out < R ? rows_out : R;
   }
   if (m0 >= rows_out) return;                                  // block-uniform
-  int KE = K_KEPT ? kept[e] : K;                               // length of the sum
-  if (EPI == 3) KE = k_total - e * K < K ? k_total - e * K : K;
+  int KE = k_kept ? kept[e] : K;                               // length of the sum
+  if (ranges) KE = k_total - e * K < K ? k_total - e * K : K;
   const int KT = (KE + BK - 1) / BK;
 
   // Per-lane source addresses of the copies and their advance per K step (0 for a lane that reads
@@ -783,16 +803,7 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
     ++pstage;
   }
   int stage = 0;
-  auto step = [&](int g) __attribute__((always_inline)) {
-    // own copies of step g landed (the steps started after it may still fly), then everybody's; the
-    // stage of step g - 1 is free after the barrier
-    wait_copies<AC + BC, ST - 2>(KT - 1 - g);
-    __syncthreads();
-    if (p < KT) {
-      start_step(p, pstage);
-      pstage = pstage + 1 == ST ? 0 : pstage + 1;
-      ++p;
-    }
+  auto multiply = [&]() __attribute__((always_inline)) {
     const uint32_t sb = lds0 + stage * SM::kStage;
     stage = stage + 1 == ST ? 0 : stage + 1;
 #pragma unroll
@@ -809,27 +820,43 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
     }
   };
-  constexpr int CH = WN / 8, RPP = 64 / CH;                    // chunks per row of the wavefront tile, rows per store
-  u32x4_t mk[EPI == 2 ? TM : 1][EPI == 2 ? 32 / RPP : 1];
-  if (EPI == 2) {
-    // The masks of a tile, all at once and under the last step: fetched store by store, they wait for one another
-    // (training step of 76 experts of 309 rows, M 512, H 4096 1072 / 1058 us, of 12 of 669, M 520, H 2056 266.0 / 263.8).
-    // Those of rows and columns that are not stored come from the last ones.
-    for (int g = 0; g < KT - 1; ++g) step(g);
-#pragma unroll
-    for (int i = 0; i < (EPI == 2 ? TM : 0); ++i)
-#pragma unroll
-      for (int ps = 0; ps < 32 / RPP; ++ps) {
-        const int row = m0 + wm0 + 32 * i + RPP * ps + lane / CH, col = n0 + wn0 + 8 * (lane % CH);
-        mk[i][ps] = *reinterpret_cast<const u32x4_t*>(mask + ((size_t)e * R + (row < rows_out ? row : rows_out - 1)) * N +
-                                                      (col < N ? col : N - 8));
-      }
-    __builtin_amdgcn_sched_barrier(0);
-    step(KT - 1);
-  } else {
-    for (int g = 0; g < KT; ++g) step(g);
+  // The last step of a masked tile stands by itself (k is never empty there): a loop that the masks' loads may have
+  // preceded waits for them in every turn.
+  const int loop_steps = MASKS ? KT - 1 : KT;
+  for (int g = 0; g < loop_steps; ++g) {
+    // own copies of step g landed (the steps started after it may still fly), then everybody's; the
+    // stage of step g - 1 is free after the barrier
+    wait_copies<AC + BC, ST - 2>(KT - 1 - g);
+    __syncthreads();
+    if (p < KT) {
+      start_step(p, pstage);
+      pstage = pstage + 1 == ST ? 0 : pstage + 1;
+      ++p;
+    }
+    multiply();
   }
-  if (EPI == 3) {                                              // a lane owns four consecutive columns of a row
+  constexpr int CH = WN / 8, RPP = 64 / CH;                    // chunks per row of the wavefront tile, rows per store
+  u32x4_t mk[MASKS ? TM : 1][MASKS ? 32 / RPP : 1];
+  if constexpr (MASKS) {
+    wait_copies<0, 0>(0);
+    __syncthreads();
+    if (masked) {
+      // The masks of a tile, all at once and under the last step: fetched store by store, they wait for one another
+      // (training step of 76 experts of 309 rows, M 512, H 4096 1072 / 1058 us, of 12 of 669, M 520, H 2056 266.0 / 263.8).
+      // Those of rows and columns that are not stored come from the last ones.
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int ps = 0; ps < 32 / RPP; ++ps) {
+          const int row = m0 + wm0 + 32 * i + RPP * ps + lane / CH, col = n0 + wn0 + 8 * (lane % CH);
+          mk[i][ps] = *reinterpret_cast<const u32x4_t*>(mask + ((size_t)e * R + (row < rows_out ? row : rows_out - 1)) * N +
+                                                        (col < N ? col : N - 8));
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    multiply();
+  }
+  if (RANGES && ranges) {                                      // a lane owns four consecutive columns of a row
     typedef float f32x4_t __attribute__((ext_vector_type(4)));
     float* const Cf = reinterpret_cast<float*>(Cout) + (size_t)e * R * N;
 #pragma unroll
@@ -877,7 +904,7 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
       const int row = m0 + wm0 + 32 * i + rr, col = n0 + wn0 + 8 * c;
       if (row < rows_out && col < N) {
         const size_t o = ((size_t)e * R + row) * N + col;
-        if (EPI == 2) {
+        if (MASKS && masked) {
 #pragma unroll
           for (int w = 0; w < 4; ++w)          // a bf16 is positive iff its bits, as an integer, are
             d[w] &= ((int16_t)(mk[i][ps][w] & 0xffffu) > 0 ? 0xffffu : 0u) |
@@ -891,6 +918,23 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : BM == 128 ? 3 : 4) void expert
     }
   }
 #undef MOE_EDGE_COPY
+}
+
+template <int BM, int BN> constexpr int kEdgeBlocks = BN == 256 ? 2 : BM == 128 ? 3 : 4;      // per compute unit
+template <int BM, int BN, int BK, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
+__global__ __launch_bounds__(256, (kEdgeBlocks<BM, BN>)) void expert_gemm_bf16_edge_kernel(EdgeArgs arg) {
+  edge_tile<BM, BN, BK, ST, EPI, A_MNC, B_KC, K_KEPT>(arg, xcd_remap(blockIdx.x, arg.nblk));
+}
+
+// The data gradient and the weight gradient of one linear layer in one launch: both read the layer's upstream gradient,
+// neither needs the other (pair_ok below says when).  The arguments decide what the forms of a launch of its own know when
+// they are compiled (masks, ranges, kept rows), which keeps them at nine kernels; a tile does the same arithmetic either way.
+template <int BMD, int BND, int STD, int BMW, int BNW, int STW>
+__global__ __launch_bounds__(256, (kEdgeBlocks<BMD, BND> < kEdgeBlocks<BMW, BNW> ? kEdgeBlocks<BMD, BND> : kEdgeBlocks<BMW, BNW>))
+void expert_gemm_bf16_pair_kernel(EdgeArgs data, EdgeArgs weight) {
+  const int id = blockIdx.x;
+  if (id < data.nblk) edge_tile<BMD, BND, 64, STD, kEpiMaskIfAny, false, true, false>(data, xcd_remap(id, data.nblk));
+  else edge_tile<BMW, BNW, 32, STW, kEpiRangesIfAny, true, false, false>(weight, xcd_remap(id - data.nblk, weight.nblk));
 }
 
 // LDS limit of one instantiation of the persistent kernel on the current device (all of the
@@ -1073,21 +1117,21 @@ bool persistent_h(int E, int R, int H, int M, int cus) {
 }
 // the form of this shape on the current device; k_kept: the sum over k runs over packed rows, of
 // which the persistent kernel takes whole 256-row tiles
-int choose_form(int E, int R, int N, int K, GemmLayout layout, GemmForm* form, bool k_kept = false) {
+int choose_form(int E, int R, int N, int K, GemmLayout layout, GemmForm* form, bool k_kept = false, double* us = nullptr) {
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
   const bool persistent = dma_shape_ok(R, N, K) || (layout != kLayoutWeightGrad && dma_columns_ok(R, N, K));
-  *form = gemm_form(persistent && (!k_kept || K % 256 == 0), E, R, N, K, layout, cus);
+  *form = gemm_form(persistent && (!k_kept || K % 256 == 0), E, R, N, K, layout, cus, us);
   return MOE_OK;
 }
 // h and dh of a training pass over packed rows
-int choose_train_forms(const moe_config& c, GemmForm* h, GemmForm* dh) {
+int choose_train_forms(const moe_config& c, GemmForm* h, GemmForm* dh, double* dh_us = nullptr) {
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
   const int R = c.G * c.C;
   const bool bits = (dma_shape_ok(R, c.H, c.M) || dma_columns_ok(R, c.H, c.M)) && persistent_h(c.E, R, c.H, c.M, cus);
   *h = bits ? kPersistent : gemm_form(false, c.E, R, c.H, c.M, kLayoutForward, cus);
-  *dh = gemm_form(bits, c.E, R, c.H, c.M, kLayoutMaskedDataGrad, cus);
+  *dh = gemm_form(bits, c.E, R, c.H, c.M, kLayoutMaskedDataGrad, cus, dh_us);
   return MOE_OK;
 }
 
@@ -1099,18 +1143,23 @@ int prepare_edge() {
       (int)EdgeSmem<BM, BN, BK, ST>::kBytes);
 }
 
+inline bool edge_args(EdgeArgs* out, int BM, int BN, const GemmArgs& a, int E, int R, int N, int K, int k_total) {
+  const int tiles_m = (R + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const long long nblk = (long long)E * tiles_m * tiles_n;
+  if (nblk > 0x7fffffffLL) return false;
+  *out = EdgeArgs{static_cast<const bf16_t*>(a.A), static_cast<const bf16_t*>(a.B), static_cast<bf16_t*>(a.C),
+                  static_cast<const bf16_t*>(a.mask), R, N, K, tiles_m, tiles_n, (int)nblk, a.gather, a.kept, a.row_pad,
+                  a.scatter, k_total};
+  return true;
+}
 template <int BM, int BN, int BK, int ST, int EPI, bool A_MNC, bool B_KC, bool K_KEPT>
 int launch_edge(const GemmArgs& a, int E, int R, int N, int K, hipStream_t st, int k_total = 0) {
   if (prepare_edge<BM, BN, BK, ST, EPI, A_MNC, B_KC, K_KEPT>() != MOE_OK) return MOE_EHIP;
   constexpr size_t kLds = EdgeSmem<BM, BN, BK, ST>::kBytes;
-  const int tiles_m = (R + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  const long long nblk = (long long)E * tiles_m * tiles_n;
-  if (nblk > 0x7fffffffLL || (K_KEPT && a.kept == nullptr)) return MOE_EUNSUPPORTED;
-  hipLaunchKernelGGL((expert_gemm_bf16_edge_kernel<BM, BN, BK, ST, EPI, A_MNC, B_KC, K_KEPT>), dim3((unsigned)nblk),
-                     dim3(256), kLds, st, static_cast<const bf16_t*>(a.A),
-                     static_cast<const bf16_t*>(a.B), static_cast<bf16_t*>(a.C),
-                     static_cast<const bf16_t*>(a.mask), R, N, K, tiles_m, tiles_n, (int)nblk, a.gather,
-                     a.kept, a.row_pad, a.scatter, k_total);
+  EdgeArgs arg;
+  if (!edge_args(&arg, BM, BN, a, E, R, N, K, k_total) || (K_KEPT && a.kept == nullptr)) return MOE_EUNSUPPORTED;
+  hipLaunchKernelGGL((expert_gemm_bf16_edge_kernel<BM, BN, BK, ST, EPI, A_MNC, B_KC, K_KEPT>), dim3((unsigned)arg.nblk),
+                     dim3(256), kLds, st, arg);
   return check_launch();
 }
 
@@ -1135,6 +1184,77 @@ int gemm_bf16_edge(GemmForm form, const GemmArgs& a, int E, int R, int N, int K,
       case kEdge128x128Deep: return launch_edge<128, 128, 64, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
       default: return launch_edge<128, 256, 32, 3, EPI, A_MNC, B_KC, K_KEPT>(a, E, R, N, K, st);
     }
+  }
+}
+
+// One product of a pair: its operands and sizes as for gemm_bf16_edge, its form and the rule's time (us).
+struct PairProduct {
+  GemmArgs a;
+  int E, R, N, K;
+  GemmForm form;
+  double us;
+  int k_total = 0;
+};
+template <int BMD, int BND, int STD, int BMW, int BNW, int STW>
+int prepare_pair() {
+  static LdsLimitOnce once;
+  constexpr size_t d = EdgeSmem<BMD, BND, 64, STD>::kBytes, w = EdgeSmem<BMW, BNW, 32, STW>::kBytes;
+  return ensure_lds_limit(once, reinterpret_cast<const void*>(expert_gemm_bf16_pair_kernel<BMD, BND, STD, BMW, BNW, STW>),
+                          (int)(d > w ? d : w));
+}
+template <int BMD, int BND, int STD, int BMW, int BNW, int STW>
+int launch_pair_as(const PairProduct& d, const PairProduct& w, hipStream_t st) {
+  if (prepare_pair<BMD, BND, STD, BMW, BNW, STW>() != MOE_OK) return MOE_EHIP;
+  constexpr size_t kLdsD = EdgeSmem<BMD, BND, 64, STD>::kBytes, kLdsW = EdgeSmem<BMW, BNW, 32, STW>::kBytes;
+  EdgeArgs da, wa;
+  if (!edge_args(&da, BMD, BND, d.a, d.E, d.R, d.N, d.K, 0) || !edge_args(&wa, BMW, BNW, w.a, w.E, w.R, w.N, w.K, w.k_total) ||
+      (long long)da.nblk + wa.nblk > 0x7fffffffLL)
+    return MOE_EUNSUPPORTED;
+  hipLaunchKernelGGL((expert_gemm_bf16_pair_kernel<BMD, BND, STD, BMW, BNW, STW>), dim3((unsigned)(da.nblk + wa.nblk)), dim3(256),
+                     kLdsD > kLdsW ? kLdsD : kLdsW, st, da, wa);
+  return check_launch();
+}
+// as many stages as leave a unit the blocks that its larger tiles would have alone
+template <int BMD, int BND>
+int launch_pair_weight(const PairProduct& d, const PairProduct& w, hipStream_t st) {
+  constexpr int kDeep = BND == 64 ? 4 : 2, kFlat = BND == 64 ? 3 : 2;
+  switch (w.form) {
+    case kEdge64x64: return launch_pair_as<BMD, BND, kDeep, 64, 64, 5>(d, w, st);
+    case kEdge64x128: return launch_pair_as<BMD, BND, kDeep, 64, 128, 4>(d, w, st);
+    default: return launch_pair_as<BMD, BND, kFlat, 128, 128, 3>(d, w, st);
+  }
+}
+// Which pairs of gradients share a launch.  A small product leaves units idle at its start and end and its successor waits
+// for the last of its tiles; in one launch the second product's tiles fill the units that the first leaves, and one launch
+// and its gap go away.  With 160 products of 60 drawn training steps and encoder backward passes (us, two launches / one,
+// without the gap): 64 x 64 tiles 13.9 / 8.3, 18.1 / 12.0, 25.5 / 24.5, mixed ones 24.5 / 19.9, 60.5 / 53.8,
+// 162 / 147, 128 x 128 tiles 31.1 / 22.4, 57.8 / 52.4, 121 / 101, at worst 64.3 / 69.7.  The line is drawn where pairs of more
+// (70 + 70 us) were no faster as often as they were: both products then fill the chip alone.  The persistent kernel and
+// 128 x 256 tiles take a unit's whole LDS for shapes that fill it.
+// What one product writes the other must not read: a caller may pass a gradient's buffer that is also an operand (wi as dwi),
+// which one launch after the other allows.
+bool disjoint(const void* p, size_t pn, const void* q, size_t qn) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+  return p == nullptr || q == nullptr || a + pn <= b || b + qn <= a;
+}
+bool independent(const PairProduct& writer, const PairProduct& reader) {
+  auto bytes = [](long long e, long long r, long long n, size_t elt) { return (size_t)(e * r * n) * elt; };
+  const PairProduct &w = writer, &r = reader;
+  const size_t out = bytes(w.E, w.R, w.N, w.k_total != 0 ? sizeof(float) : sizeof(bf16_t));
+  const long long k = r.k_total != 0 ? r.k_total : (long long)r.E * r.K;        // of all experts or ranges
+  return disjoint(w.a.C, out, r.a.A, bytes(k, r.R, 1, sizeof(bf16_t))) &&
+         disjoint(w.a.C, out, r.a.B, bytes(k, r.N, 1, sizeof(bf16_t))) &&
+         disjoint(w.a.C, out, r.a.mask, bytes(r.E, r.R, r.N, sizeof(bf16_t)));
+}
+bool pair_ok(const PairProduct& d, const PairProduct& w) {
+  if (d.form == kPersistent || d.form == kEdge128x256 || w.form == kPersistent || w.form == kEdge128x256) return false;
+  return d.us + w.us < 120.0 && independent(d, w) && independent(w, d);
+}
+int launch_pair(const PairProduct& d, const PairProduct& w, hipStream_t st) {
+  switch (d.form) {
+    case kEdge64x64: case kEdge64x64Deep: return launch_pair_weight<64, 64>(d, w, st);
+    case kEdge64x128: case kEdge64x128Deep: return launch_pair_weight<64, 128>(d, w, st);
+    default: return launch_pair_weight<128, 128>(d, w, st);
   }
 }
 
@@ -1193,7 +1313,11 @@ int prepare_expert_gemm() {
       prepare_edge<64, 128, 32, 4, __VA_ARGS__>(), prepare_edge<64, 64, 32, 5, __VA_ARGS__>()
       MOE_EDGE_KC(1, false, false, false), MOE_EDGE_KC(0, false, false, false), MOE_EDGE_KC(0, false, true, false),
       MOE_EDGE_KC(2, false, true, false), MOE_EDGE_MNC(0, true, false, false), MOE_EDGE_MNC(0, true, false, true),
-      MOE_EDGE_MNC(3, true, false, false)};
+      MOE_EDGE_MNC(3, true, false, false),
+#define MOE_PAIR(BM, BN, DEEP, FLAT) \
+  prepare_pair<BM, BN, DEEP, 64, 64, 5>(), prepare_pair<BM, BN, DEEP, 64, 128, 4>(), prepare_pair<BM, BN, FLAT, 128, 128, 3>()
+      MOE_PAIR(64, 64, 4, 3), MOE_PAIR(64, 128, 2, 2), MOE_PAIR(128, 128, 2, 2)};
+#undef MOE_PAIR
 #undef MOE_EDGE_KC
 #undef MOE_EDGE_MNC
   int cus = 0;
@@ -1436,6 +1560,64 @@ int launch_expert_dgrad1(const moe_config& c, const void* dh, const void* wi, vo
 int launch_expert_wgrad1(const moe_config& c, const void* buf, const void* dh, void* dwi,
                          const int32_t* kept, hipStream_t st) {
   return wgrad(c, buf, dh, dwi, c.M, c.H, kept, st);
+}
+
+// The gradients of out = h . wo (dh, dwo) and of h = relu(x . wi) (dbuf, dwi), in one launch where that is faster.
+static int pair_or_none(const moe_config& c, const GemmArgs& data, GemmLayout layout, const GemmArgs& weight, int N, int K,
+                        const int32_t* kept, hipStream_t st, bool* done) {
+  // upstream [R,K], weight [N,K]: [R,K] . [N,K]^T -> [R,N] and [R,N]^T . [R,K] -> [N,K]
+  const int R = c.G * c.C;
+  PairProduct d{data, c.E, R, N, K, kPersistent, 0}, w{weight, c.E, N, K, R, kPersistent, 0};
+  GemmForm h;
+  const bool train = kept != nullptr && layout == kLayoutMaskedDataGrad;
+  if ((train ? choose_train_forms(c, &h, &d.form, &d.us) : choose_form(c.E, R, N, K, layout, &d.form, false, &d.us)) != MOE_OK ||
+      choose_form(c.E, w.R, w.N, R, kLayoutWeightGrad, &w.form, kept != nullptr, &w.us) != MOE_OK)
+    return MOE_EHIP;
+  *done = pair_ok(d, w);
+  return *done ? launch_pair(d, w, st) : MOE_OK;
+}
+
+int launch_expert_grads2(const moe_config& c, const void* dout, const void* wo, const void* h, const void* signbits, void* dh,
+                         void* dwo, const int32_t* kept, hipStream_t st) {
+  if (c.act_dtype == MOE_BF16 && (long long)c.G * c.C <= 0x7fffffffLL) {
+    GemmArgs d{dout, wo, dh, h}, w{h, dout, dwo};
+    d.kept = w.kept = kept;
+    if (kept != nullptr) d.row_pad = packed_row_pad(c);
+    bool done = false;
+    const int rc = pair_or_none(c, d, kLayoutMaskedDataGrad, w, c.H, c.M, kept, st, &done);
+    if (rc != MOE_OK || done) return rc;
+  }
+  const int rc = launch_expert_dgrad2(c, dout, wo, h, signbits, dh, kept, st);
+  return rc != MOE_OK ? rc : launch_expert_wgrad2(c, h, dout, dwo, kept, st);
+}
+
+int launch_expert_grads1(const moe_config& c, const void* dh, const void* wi, void* dbuf, const void* buf, void* dwi,
+                         const int32_t* kept, hipStream_t st) {
+  if (c.act_dtype == MOE_BF16 && (long long)c.G * c.C <= 0x7fffffffLL) {
+    GemmArgs d{dh, wi, dbuf}, w{buf, dh, dwi};
+    d.kept = w.kept = kept;
+    bool done = false;
+    const int rc = pair_or_none(c, d, kLayoutDataGrad, w, c.M, c.H, kept, st, &done);
+    if (rc != MOE_OK || done) return rc;
+  }
+  const int rc = launch_expert_dgrad1(c, dh, wi, dbuf, kept, st);
+  return rc != MOE_OK ? rc : launch_expert_wgrad1(c, buf, dh, dwi, kept, st);
+}
+
+// dX [rows,in] = dY . W^T (0 where mask <= 0) and dW [in,out] = X^T . dY of a dense layer in one launch, dW in the plan's
+// ranges (partial); false: to be launched one after the other
+int launch_dense_grads_pair(const DenseWgradPlan& p, long long rows, int in, int out, const void* X, const void* dY,
+                            const void* W, const void* mask, void* dX, void* dW, float* partial, hipStream_t st, bool* done) {
+  *done = false;
+  PairProduct d{GemmArgs{dY, W, dX, mask}, 1, (int)rows, in, out, kPersistent, 0};
+  PairProduct w{GemmArgs{X, dY, p.splits > 1 ? static_cast<void*>(partial) : dW}, p.splits, in, out, p.splits > 1 ? p.k : (int)rows, kPersistent, 0};
+  w.k_total = p.splits > 1 ? (int)rows : 0;
+  const bool persistent = dma_shape_ok(in, out, w.K) && (long long)p.splits * w.K == rows;
+  if (choose_form(1, (int)rows, in, out, mask != nullptr ? kLayoutMaskedDataGrad : kLayoutDataGrad, &d.form, false, &d.us) != MOE_OK)
+    return MOE_EHIP;
+  w.form = gemm_form(persistent, p.splits, in, out, w.K, kLayoutWeightGrad, 256, &w.us);
+  *done = pair_ok(d, w);
+  return *done ? launch_pair(d, w, st) : MOE_OK;
 }
 
 }  // namespace moe
