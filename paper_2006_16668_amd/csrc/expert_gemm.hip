@@ -803,21 +803,44 @@ __device__ __forceinline__ void edge_tile(const EdgeArgs& arg, const int logical
     ++pstage;
   }
   int stage = 0;
+  // A step: the fragments of its first kAhead pieces of 16 k are asked for at once and each product is followed by the fetch
+  // of the piece kAhead on, so that a step waits for LDS once and not once per piece: it is this chain of waits that bounds
+  // tiles alone on their unit (48 tiles of K 3072, 0.24 us a step of 64 k, of which 0.05 are products).
+  // The copies of a later step are started under that wait; with two stages they go first, since the next step needs them,
+  // and so they do for the dense layers' 128 x 128 weight gradients, whose long sums lost 5 % otherwise.
+  // Over the products of 60 drawn training and encoder steps, sums of us before / after: 64 x 64 deep 1129 / 1062, pairs of
+  // 64 x 64 tiles 1501 / 1389, weight gradients of 64 x 64 tiles 269 / 245, of 128 x 128 of kept rows 411 / 392, data products
+  // 128 x 128 deep 569 / 534.  No gain and so as it was: 128 x 256 tiles (two blocks of 128 accumulators fill the
+  // unit) and the forward products in two stages (276 / 284: the read-ahead delays their copies).
+  constexpr int kAhead = BN == 256 || (ST == 2 && !B_KC) ? 0 : BM == 128 && KK > 2 ? 2 : KK;
+  constexpr bool kReadFirst = ST > 2 && (!A_MNC || BM == 64 || K_KEPT || EPI == kEpiRangesIfAny);
+  bf16x8_t fa[KK][TM], fb[KK][TN];
+  auto fetch = [&](uint32_t sb, int kk) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) fa[kk][i] = A_MNC ? read_mnc(sb, a_rd[i], kk, BM * 2) : read_kc(sb, a_rd[kk], i);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) fb[kk][j] = B_KC ? read_kc(sb, b_rd[kk], j) : read_mnc(sb, b_rd[j], kk, BN * 2);
+  };
+  auto begin = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < kAhead; ++kk) fetch(lds0 + stage * SM::kStage, kk);
+    if (kAhead > 0) __builtin_amdgcn_sched_barrier(0);
+  };
   auto multiply = [&]() __attribute__((always_inline)) {
     const uint32_t sb = lds0 + stage * SM::kStage;
     stage = stage + 1 == ST ? 0 : stage + 1;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      bf16x8_t fa[TM], fb[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) fa[i] = A_MNC ? read_mnc(sb, a_rd[i], kk, BM * 2) : read_kc(sb, a_rd[kk], i);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fb[j] = B_KC ? read_kc(sb, b_rd[kk], j) : read_mnc(sb, b_rd[j], kk, BN * 2);
+      if (kAhead == 0) fetch(sb, kk);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kk][j], fa[kk][i], acc[i][j], 0, 0, 0);
+      if (kAhead > 0 && kk + kAhead < KK) {
+        fetch(sb, kk + kAhead);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   };
   // The last step of a masked tile stands by itself (k is never empty there): a loop that the masks' loads may have
@@ -828,11 +851,13 @@ __device__ __forceinline__ void edge_tile(const EdgeArgs& arg, const int logical
     // stage of step g - 1 is free after the barrier
     wait_copies<AC + BC, ST - 2>(KT - 1 - g);
     __syncthreads();
+    if (kReadFirst) begin();
     if (p < KT) {
       start_step(p, pstage);
       pstage = pstage + 1 == ST ? 0 : pstage + 1;
       ++p;
     }
+    if (!kReadFirst) begin();
     multiply();
   }
   constexpr int CH = WN / 8, RPP = 64 / CH;                    // chunks per row of the wavefront tile, rows per store
@@ -840,6 +865,7 @@ __device__ __forceinline__ void edge_tile(const EdgeArgs& arg, const int logical
   if constexpr (MASKS) {
     wait_copies<0, 0>(0);
     __syncthreads();
+    begin();
     if (masked) {
       // The masks of a tile, all at once and under the last step: fetched store by store, they wait for one another
       // (training step of 76 experts of 309 rows, M 512, H 4096 1072 / 1058 us, of 12 of 669, M 520, H 2056 266.0 / 263.8).
