@@ -313,8 +313,8 @@ int moe_backward(const moe_config* cfg, const void* x, const float* wg, const vo
 /*
  * moe_backward with stage timing marks (see moe_forward_events): MOE_BACKWARD_EVENTS
  * caller-owned events recorded on `stream`:
- *   [0] start  [1] after dout, dweight (includes re-dispatching x)  [2] after dh  [3] after dwo
- *   [4] after dbuf  [5] after dwi  [6] after dz and the partial sums of dwg  [7] after dx, dwg.
+ *   [0] start  [1] after dout, dz (includes re-dispatching x)  [2] after dh  [3] after dwo
+ *   [4] after dbuf  [5] after dwi  [6] after the partial sums of dwg  [7] after dx, dwg.
  * events == NULL is exactly moe_backward.
  */
 #define MOE_BACKWARD_EVENTS 8

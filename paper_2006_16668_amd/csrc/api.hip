@@ -80,11 +80,11 @@ ForwardWs carve(const moe_config& c, bool train) {
 
 // Layout of the moe_backward workspace.
 struct BackwardWs {
-  size_t dout, dh, dbuf, buf, dweight, dz, dzp, wgp, dxg, dwg_partial, total;
+  size_t dout, dh, dbuf, buf, dz, dzp, wgp, dxg, dwg_partial, total;
 };
 
 BackwardWs carve_bwd(const moe_config& c) {
-  const size_t N = (size_t)c.G * c.S, rows = (size_t)c.E * c.G * c.C;
+  const size_t rows = (size_t)c.E * c.G * c.C;
   const size_t elt = c.act_dtype == MOE_F32 ? 4 : 2;
   BackwardWs w{};
   size_t off = 0;
@@ -93,7 +93,6 @@ BackwardWs carve_bwd(const moe_config& c) {
   w.dh = take(rows * c.H * elt);
   w.dbuf = take(rows * c.M * elt);
   w.buf = take(rows * c.M * elt);
-  w.dweight = take(N * 2 * 4);
   const moe::GateBwdPlan p = moe::gate_bwd_plan(c);
   w.dz = take(p.dz_bytes);
   w.dzp = take(p.dzp_bytes);
@@ -567,7 +566,6 @@ int moe_backward_events(const moe_config* cfg, const void* x, const float* wg, c
   const int32_t* slot = reinterpret_cast<const int32_t*>(fb + f.slot);
   const float* weight = reinterpret_cast<const float*>(fb + f.weight);
   const int32_t* src_token = reinterpret_cast<const int32_t*>(fb + f.src_token);
-  float* dweight = reinterpret_cast<float*>(base + b.dweight);
   const moe::GateBwdWs gw{reinterpret_cast<float*>(base + b.dz),
                           reinterpret_cast<moe::bf16_t*>(base + b.dzp),
                           reinterpret_cast<moe::bf16_t*>(base + b.wgp),
@@ -578,10 +576,11 @@ int moe_backward_events(const moe_config* cfg, const void* x, const float* wg, c
   const bool packed = moe::expert_ffn_can_pack(*cfg);
   const moe::RowPacking pk = moe::carve_row_packing(*cfg, const_cast<char*>(fb) + f.packing);
   const int32_t* kept = packed ? pk.kept : nullptr;
-  const int32_t* rows_src = packed ? pk.packed_src : src_token;
+  const int32_t* row_base = packed ? pk.row_base : nullptr;
   if (!mark(0)) return MOE_EHIP;
-  rc = moe::launch_combine_bwd(*cfg, dy, fb + f.out, x, rows_src, expert_idx, weight, base + b.dout,
-                               base + b.buf, dweight, kept, st);
+  rc = moe::launch_combine_bwd(*cfg, dy, fb + f.out, x, src_token, expert_idx, slot, weight, base + b.dout, base + b.buf,
+                               kept, row_base, reinterpret_cast<const float*>(fb + f.gates),
+                               reinterpret_cast<const int32_t*>(fb + f.c1), daux, gw, st);
   if (rc != MOE_OK) return rc;
   if (!mark(1)) return MOE_EHIP;
   const void* const signbits = packed ? fb + f.signbits : nullptr;
@@ -604,13 +603,10 @@ int moe_backward_events(const moe_config* cfg, const void* x, const float* wg, c
     if (rc != MOE_OK) return rc;
     if (!mark(5)) return MOE_EHIP;
   }
-  rc = moe::launch_gate_bwd(*cfg, x, wg, reinterpret_cast<const float*>(fb + f.gates), expert_idx,
-                            slot, dweight, reinterpret_cast<const int32_t*>(fb + f.c1), daux, gw,
-                            dwg, st);
+  rc = moe::launch_dwg(*cfg, x, gw, dwg, st);
   if (rc != MOE_OK) return rc;
   if (!mark(6)) return MOE_EHIP;
-  rc = moe::launch_dx(*cfg, wg, base + b.dbuf, expert_idx, slot, gw, dx, dwg,
-                      packed ? pk.row_base : nullptr, st);
+  rc = moe::launch_dx(*cfg, wg, base + b.dbuf, expert_idx, slot, gw, dx, dwg, row_base, st);
   if (rc != MOE_OK) return rc;
   return mark(7) ? MOE_OK : MOE_EHIP;
 }

@@ -7,7 +7,7 @@
 //
 //   combine_bwd   dout[e,g,c,:] = weight[g,s,k] * dy[g,s,:]          (Eq. 3 transposed)
 //                 dweight[g,s,k] = <dy[g,s,:], out[e,g,c,:]>
-//   gate_bwd      weight_1 = g1/(g1+g2), weight_2 = g2/(g1+g2)  (Algorithm 1) =>
+//                 and, in the same kernel: weight_1 = g1/(g1+g2), weight_2 = g2/(g1+g2)  (Algorithm 1) =>
 //                 dgate[e1] = (dw1 - dw2) g2 / (g1+g2)^2,  dgate[e2] = (dw2 - dw1) g1 / (g1+g2)^2
 //                 l_aux = (1/E) sum_e (c_e/S) m_e  =>  dgate[e] += daux[g] c_e / (E S^2)
 //                 softmax: dz[e] = g[e] (dgate[e] - sum_e' g[e'] dgate[e'])
@@ -20,116 +20,129 @@ namespace moe {
 namespace {
 
 constexpr int kRowsPerBlock = 4;  // one wavefront per row / token
+constexpr int kZeroRows = 64;     // rows that a block of combine_bwd_kernel checks and clears
 
-// One wavefront per expert row: its gradient row dout, dweight of the choice that fills it, and its row of
-// the dispatched activations (buf, the first weight gradient's operand; the forward pass of packed layers
-// never writes one).  Bound: HBM, x, dy and out rows in, buf and dout rows out.  The copy into buf was a
-// launch of its own, as was the sum of dwg that dx_kernel's launch now makes: without the two, training
-// steps of 4 x 1024 tokens, M 512, E 16: 234.7 -> 228.5 us; 3 x 1333 tokens, M 520, E 12: 292.2 -> 286.9;
-// 32 768 tokens, M 1024, E 32: 6373 -> 6363.
+// One wavefront per token: the gradient rows dout of its kept choices, their rows of the dispatched activations
+// (buf, the first weight gradient's operand; the forward pass of packed layers never writes one), and the gradient of
+// its gate logits, for which the choices' dweight stay in registers.  The blocks behind those of the tokens clear the
+// rows that no token fills: of packed rows (kept != NULL) the ones from kept[e] to the end of that 256-row tile, which enter
+// the weight gradients' sums.
+// dz: NULL, or [tokens, ez] fp32 with zeros behind the E columns; dzp: NULL, or the three bf16 terms side by side
+// in `cols` columns.
+// Bound: HBM, x and dy rows once, out rows in, buf and dout rows out; for few tokens the chain routing -> rows -> sum -> gates.
+// One wavefront per expert row read x and dy once per choice, and the gates were a launch of their own behind it:
+// us of both, before / now: 4 x 1024 tokens, M 512, E 16 14.6 / 8.5; 3 x 1333 tokens, M 520, E 12 14.9 / 9.8; fp32,
+// 4 x 1024 tokens, M 1024, E 16 31.7 / 27.9.
+struct GateGrad {
+  const float* gates;
+  const int32_t* c1;
+  const float* daux;
+  float* dz;
+  bf16_t* dzp;
+  int ez, cols;
+};
 template <typename T>
 __global__ __launch_bounds__(256) void combine_bwd_kernel(
     const uint4* __restrict__ dy, const uint4* __restrict__ out, const uint4* __restrict__ x,
-    const int32_t* __restrict__ src_token, const int32_t* __restrict__ expert_idx,
-    const float* __restrict__ weight, uint4* __restrict__ dout, uint4* __restrict__ buf,
-    float* __restrict__ dweight,
-    int S, int G, int C, int vec_per_row, long long rows, const int32_t* __restrict__ kept) {
-  const long long r = (long long)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  const int lane = threadIdx.x & 63;
-  const int g = (int)((r / C) % G);
-  const int e = (int)(r / ((long long)G * C));
-  // kept != NULL: packed rows.  src_token then holds the token row g*S + s of packed row p of
-  // expert e for p < kept[e]; the rows up to the end of the last occupied 256-row tile become
-  // zero rows (they enter the weight gradients' sums), later rows are nobody's business.
-  int t = src_token[r];
-  if (kept != nullptr) {
-    const long long p = r - (long long)e * G * C;
-    const int ke = kept[e];
-    if (p >= ((ke + 255) & ~255)) return;
-    if (p >= ke) t = -1;
-  }
-  uint4* dst = dout + r * vec_per_row;
-  uint4* bufr = buf + r * vec_per_row;
-  if (t < 0) {
+    const int32_t* __restrict__ expert_idx, const int32_t* __restrict__ slot, const float* __restrict__ weight,
+    uint4* __restrict__ dout, uint4* __restrict__ buf, int S, int G, int C, int E, int vec_per_row, long long tokens,
+    unsigned token_blocks, const int32_t* __restrict__ src_token, const int32_t* __restrict__ kept,
+    const int32_t* __restrict__ row_base, GateGrad gate) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (blockIdx.x >= token_blocks) {
+    const long long per_expert = (long long)G * C;
+    const unsigned zb = blockIdx.x - token_blocks;
+    constexpr int kPerWave = kZeroRows / 4;
+    long long r0;
+    bool empty = false;
+    if (kept != nullptr) {
+      constexpr int kBlocks = 256 / kZeroRows;                   // per expert
+      const int e = zb / kBlocks, ke = kept[e];
+      const long long p0 = ke + (long long)(zb % kBlocks) * kZeroRows + wave * kPerWave;
+      const long long end = (ke + 255) & ~255;
+      r0 = e * per_expert + p0;
+      empty = lane < kPerWave && p0 + lane < end && p0 + lane < per_expert;
+    } else {
+      r0 = (long long)zb * kZeroRows + wave * kPerWave;
+      if (lane < kPerWave && r0 + lane < E * per_expert) empty = src_token[r0 + lane] < 0;
+    }
     const uint4 zero = {0u, 0u, 0u, 0u};
-    for (int v = lane; v < vec_per_row; v += 64) dst[v] = bufr[v] = zero;
+    for (unsigned long long left = __ballot(empty); left != 0; left &= left - 1) {
+      const long long o = (r0 + __builtin_ctzll(left)) * vec_per_row;
+      for (int v = lane; v < vec_per_row; v += 64) dout[o + v] = buf[o + v] = zero;
+    }
     return;
   }
-  const long long n = kept != nullptr ? (long long)t : (long long)g * S + t;
-  const int k = expert_idx[2 * n] == e ? 0 : 1;        // the two experts of a token differ
-  const float w = weight[2 * n + k];
-  const uint4* dyr = dy + n * vec_per_row;
-  const uint4* outr = out + r * vec_per_row;
-  const uint4* xr = x + n * vec_per_row;
-  constexpr int K = Vec16<T>::kElts;
-  float dot = 0.f;
-  for (int v = lane; v < vec_per_row; v += 64) {
-    float f[K], o[K];
-    Vec16<T>::unpack(dyr[v], f);
-    Vec16<T>::unpack(outr[v], o);
-    bufr[v] = xr[v];
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      dot = fmaf(f[i], o[i], dot);
-      f[i] *= w;
-    }
-    dst[v] = Vec16<T>::pack(f);
-  }
-  dot = wave_sum(dot);
-  if (lane == 0) dweight[2 * n + k] = dot;
-}
-
-// LPT lanes per token (16, 32 or 64: no more than the experts need); dweight of a choice that is not
-// kept is never read.  dz: NULL, or [tokens, ez] fp32 with zeros behind the E columns; dzp: NULL, or the
-// three bf16 terms side by side in `cols` columns.
-template <int LPT>
-__global__ __launch_bounds__(256) void gate_bwd_kernel(
-    const float* __restrict__ gates, const int32_t* __restrict__ expert_idx,
-    const int32_t* __restrict__ slot, const float* __restrict__ dweight,
-    const int32_t* __restrict__ c1, const float* __restrict__ daux, float* __restrict__ dz, int ez,
-    bf16_t* __restrict__ dzp, int cols, int S, int E, long long tokens) {
-  const long long n0 = (long long)blockIdx.x * (256 / LPT) + threadIdx.x / LPT;
-  const bool live = n0 < tokens;
-  const long long n = live ? n0 : tokens - 1;            // idle lanes take part in the shuffles
-  const int lane = threadIdx.x % LPT;
+  const long long n = (long long)blockIdx.x * kRowsPerBlock + wave;
+  if (n >= tokens) return;
   const int g = (int)(n / S);
-  const float* p = gates + n * E;
+  const float* const p = gate.gates + n * E;
+  const int32_t* const cg = gate.c1 + (long long)g * E;
   const int e1 = expert_idx[2 * n], e2 = expert_idx[2 * n + 1];
+  const int s1 = slot[2 * n], s2 = slot[2 * n + 1];
+  const float w1 = weight[2 * n], w2 = weight[2 * n + 1];
   const float g1 = p[e1], g2 = p[e2];
-  const float d1 = slot[2 * n] >= 0 ? dweight[2 * n] : 0.f;
-  const float d2 = slot[2 * n + 1] >= 0 ? dweight[2 * n + 1] : 0.f;
+  // row of a kept choice: (e G + g) C + slot, or e G C + row_base[g,e] + slot when packed
+  auto row_of = [&](int e, int s) {
+    return row_base != nullptr ? (long long)e * G * C + row_base[(size_t)g * E + e] + s : ((long long)e * G + g) * C + s;
+  };
+  const uint4 *const dyr = dy + n * vec_per_row, *const xr = x + n * vec_per_row;
+  const long long o1 = s1 >= 0 ? row_of(e1, s1) * vec_per_row : 0, o2 = s2 >= 0 ? row_of(e2, s2) * vec_per_row : 0;
+  float d1 = 0.f, d2 = 0.f;
+  if (s1 >= 0 || s2 >= 0) {
+    for (int v = lane; v < vec_per_row; v += 64) {
+      constexpr int K = Vec16<T>::kElts;
+      const uint4 dv = dyr[v], xv = xr[v];
+      uint4 ov1 = {0u, 0u, 0u, 0u}, ov2 = ov1;
+      if (s1 >= 0) ov1 = out[o1 + v];
+      if (s2 >= 0) ov2 = out[o2 + v];
+      float f[K], o[K];
+      Vec16<T>::unpack(dv, f);
+      auto choice = [&](const uint4& ov, float w, float* d, long long at) {
+        float h[K];
+        Vec16<T>::unpack(ov, o);
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+          *d = fmaf(f[i], o[i], *d);
+          h[i] = f[i] * w;
+        }
+        buf[at + v] = xv;
+        dout[at + v] = Vec16<T>::pack(h);
+      };
+      if (s1 >= 0) choice(ov1, w1, &d1, o1);
+      if (s2 >= 0) choice(ov2, w2, &d2, o2);
+    }
+    d1 = wave_sum(d1);
+    d2 = wave_sum(d2);
+  }
   const float inv = 1.f / ((g1 + g2) * (g1 + g2));
   const float t1 = (d1 - d2) * g2 * inv, t2 = (d2 - d1) * g1 * inv;
-  const float scale = daux[g] / ((float)E * (float)S * (float)S);
-  const int32_t* cg = c1 + (long long)g * E;
+  const float scale = gate.daux[g] / ((float)E * (float)S * (float)S);
   float dot = 0.f;
-  for (int e = lane; e < E; e += LPT) {
+  for (int e = lane; e < E; e += 64) {
     const float dp = scale * (float)cg[e] + (e == e1 ? t1 : 0.f) + (e == e2 ? t2 : 0.f);
     dot = fmaf(p[e], dp, dot);
   }
-#pragma unroll
-  for (int o = LPT / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, 64);
-  if (!live) return;
-  for (int e = lane; e < E; e += LPT) {
+  dot = wave_sum(dot);
+  for (int e = lane; e < E; e += 64) {
     const float dp = scale * (float)cg[e] + (e == e1 ? t1 : 0.f) + (e == e2 ? t2 : 0.f);
     const float v = p[e] * (dp - dot);
-    if (dz != nullptr) dz[n * ez + e] = v;
-    if (dzp != nullptr) {
+    if (gate.dz != nullptr) gate.dz[n * gate.ez + e] = v;
+    if (gate.dzp != nullptr) {
       // v = hi + mid + lo exactly (three bf16 terms cover the 24 mantissa bits), stored side
       // by side so that a bf16 matrix product over these columns is an fp32-faithful one
       const bf16_t hi = f32_to_bf16(v);
       const float r1 = v - bf16_to_f32(hi);
       const bf16_t mid = f32_to_bf16(r1);
       const bf16_t lo = f32_to_bf16(r1 - bf16_to_f32(mid));
-      bf16_t* d = dzp + n * cols + 3 * e;
+      bf16_t* d = gate.dzp + n * gate.cols + 3 * e;
       d[0] = hi; d[1] = mid; d[2] = lo;
     }
   }
-  if (dz != nullptr)
-    for (int e = E + lane; e < ez; e += LPT) dz[n * ez + e] = 0.f;
-  if (dzp != nullptr)
-    for (int cidx = 3 * E + lane; cidx < cols; cidx += LPT) dzp[n * cols + cidx] = 0;
+  if (gate.dz != nullptr)
+    for (int e = E + lane; e < gate.ez; e += 64) gate.dz[n * gate.ez + e] = 0.f;
+  if (gate.dzp != nullptr)
+    for (int cidx = 3 * E + lane; cidx < gate.cols; cidx += 64) gate.dzp[n * gate.cols + cidx] = 0;
 }
 
 // wgp[m, 3e+p] = bf16(wg[m,e]) for the three terms p of dz, zero in the padding columns
@@ -479,25 +492,25 @@ __global__ __launch_bounds__(256) void dx_kernel(
 
 }  // namespace
 
-int launch_combine_bwd(const moe_config& c, const void* dy, const void* out, const void* x,
-                       const int32_t* src_token, const int32_t* expert_idx, const float* weight,
-                       void* dout, void* buf, float* dweight, const int32_t* kept, hipStream_t st) {
+int launch_combine_bwd(const moe_config& c, const void* dy, const void* out, const void* x, const int32_t* src_token,
+                       const int32_t* expert_idx, const int32_t* slot, const float* weight, void* dout, void* buf,
+                       const int32_t* kept, const int32_t* row_base, const float* gates, const int32_t* c1,
+                       const float* daux, const GateBwdWs& w, hipStream_t st) {
+  const GateBwdPlan p = gate_bwd_plan(c);
   const int elt = c.act_dtype == MOE_F32 ? 4 : 2;
   const int vec_per_row = c.M * elt / 16;
-  const long long rows = (long long)c.E * c.G * c.C;
-  const unsigned grid = (unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock);
-  if (c.act_dtype == MOE_F32)
-    hipLaunchKernelGGL(combine_bwd_kernel<float>, dim3(grid), dim3(256), 0, st,
-                       static_cast<const uint4*>(dy), static_cast<const uint4*>(out),
-                       static_cast<const uint4*>(x), src_token, expert_idx, weight,
-                       static_cast<uint4*>(dout), static_cast<uint4*>(buf), dweight, c.S, c.G, c.C,
-                       vec_per_row, rows, kept);
-  else
-    hipLaunchKernelGGL(combine_bwd_kernel<bf16_t>, dim3(grid), dim3(256), 0, st,
-                       static_cast<const uint4*>(dy), static_cast<const uint4*>(out),
-                       static_cast<const uint4*>(x), src_token, expert_idx, weight,
-                       static_cast<uint4*>(dout), static_cast<uint4*>(buf), dweight, c.S, c.G, c.C,
-                       vec_per_row, rows, kept);
+  const long long tokens = (long long)c.G * c.S, rows = (long long)c.E * c.G * c.C;
+  const long long tblocks = (tokens + kRowsPerBlock - 1) / kRowsPerBlock;
+  const long long zblocks = kept != nullptr ? (long long)c.E * (256 / kZeroRows) : (rows + kZeroRows - 1) / kZeroRows;
+  const GateGrad gate{gates, c1, daux, p.mfma ? nullptr : w.dz, p.mfma ? w.dzp : nullptr, p.ez, p.cols};
+#define MOE_COMBINE_BWD(T)                                                                                              \
+  hipLaunchKernelGGL(combine_bwd_kernel<T>, dim3((unsigned)(tblocks + zblocks)), dim3(256), 0, st,                      \
+                     static_cast<const uint4*>(dy), static_cast<const uint4*>(out), static_cast<const uint4*>(x),       \
+                     expert_idx, slot, weight, static_cast<uint4*>(dout), static_cast<uint4*>(buf), c.S, c.G, c.C, c.E, \
+                     vec_per_row, tokens, (unsigned)tblocks, src_token, kept, row_base, gate)
+  if (c.act_dtype == MOE_F32) MOE_COMBINE_BWD(float);
+  else MOE_COMBINE_BWD(bf16_t);
+#undef MOE_COMBINE_BWD
   return check_launch();
 }
 
@@ -552,21 +565,9 @@ GateBwdPlan gate_bwd_plan(const moe_config& c) {
   return p;
 }
 
-int launch_gate_bwd(const moe_config& c, const void* x, const float* wg, const float* gates,
-                    const int32_t* expert_idx, const int32_t* slot, const float* dweight,
-                    const int32_t* c1, const float* daux, const GateBwdWs& w, float* dwg,
-                    hipStream_t st) {
+int launch_dwg(const moe_config& c, const void* x, const GateBwdWs& w, float* dwg, hipStream_t st) {
   const GateBwdPlan p = gate_bwd_plan(c);
   const long long tokens = (long long)c.G * c.S;
-#define MOE_GATE_BWD(LPT)                                                                              \
-  hipLaunchKernelGGL(gate_bwd_kernel<LPT>, dim3((unsigned)((tokens + 256 / LPT - 1) / (256 / LPT))),   \
-                     dim3(256), 0, st, gates, expert_idx, slot, dweight, c1, daux,                     \
-                     p.mfma ? nullptr : w.dz, p.ez, p.mfma ? w.dzp : nullptr, p.cols, c.S, c.E, tokens)
-  if (c.E <= 16) MOE_GATE_BWD(16);
-  else if (c.E <= 32) MOE_GATE_BWD(32);
-  else MOE_GATE_BWD(64);
-#undef MOE_GATE_BWD
-  if (check_launch() != MOE_OK) return MOE_EHIP;
   const long long size = (long long)c.M * c.E;
   if (p.mfma) {
     // dwg = x^T . dz as one batched MFMA GEMM over the token ranges, the three bf16 terms of

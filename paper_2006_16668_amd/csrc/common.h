@@ -203,11 +203,6 @@ int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPackin
 size_t expert_signbits_bytes(const moe_config& c);
 
 // backward pass (backward.hip)
-// dout, dweight and the dispatched rows of x (buf); kept: NULL, or the packed layout's row counts
-// (src_token is then its packed_src)
-int launch_combine_bwd(const moe_config& c, const void* dy, const void* out, const void* x,
-                       const int32_t* src_token, const int32_t* expert_idx, const float* weight,
-                       void* dout, void* buf, float* dweight, const int32_t* kept, hipStream_t st);
 // Gate gradients: the two projections (dwg = x^T dz, dz . wg^T) in full fp32, or, for bf16 layers of more
 // than 128 experts whose token count and M are multiples of 256, as bf16 GEMMs over three terms of dz.
 struct GateBwdPlan {
@@ -225,11 +220,13 @@ struct GateBwdWs {
   float* dxg;       // [N,M] fp32 gate part of dx (MFMA path)
   float* partial;   // [splits,M,ez or cols] fp32
 };
-int launch_gate_bwd(const moe_config& c, const void* x, const float* wg, const float* gates,
-                    const int32_t* expert_idx, const int32_t* slot, const float* dweight,
-                    const int32_t* c1, const float* daux, const GateBwdWs& w, float* dwg,
-                    hipStream_t st);
-// dx, and the sum of launch_gate_bwd's partial dwg (without the bf16 GEMMs, which leave dwg finished)
+// dout, buf and dz (or dzp); kept and row_base: NULL, or those of packed rows, whose src_token is not read
+int launch_combine_bwd(const moe_config& c, const void* dy, const void* out, const void* x, const int32_t* src_token,
+                       const int32_t* expert_idx, const int32_t* slot, const float* weight, void* dout, void* buf,
+                       const int32_t* kept, const int32_t* row_base, const float* gates, const int32_t* c1,
+                       const float* daux, const GateBwdWs& w, hipStream_t st);
+int launch_dwg(const moe_config& c, const void* x, const GateBwdWs& w, float* dwg, hipStream_t st);
+// dx, and the sum of launch_dwg's partial dwg (without the bf16 GEMMs, which leave dwg finished)
 int launch_dx(const moe_config& c, const float* wg, const void* dbuf, const int32_t* expert_idx,
               const int32_t* slot, const GateBwdWs& w, void* dx, float* dwg, const int32_t* row_base,
               hipStream_t st);
