@@ -1255,8 +1255,11 @@ int launch_pair_weight(const PairProduct& d, const PairProduct& w, hipStream_t s
 // and its gap go away.  With 160 products of 60 drawn training steps and encoder backward passes (us, two launches / one,
 // without the gap): 64 x 64 tiles 13.9 / 8.3, 18.1 / 12.0, 25.5 / 24.5, mixed ones 24.5 / 19.9, 60.5 / 53.8,
 // 162 / 147, 128 x 128 tiles 31.1 / 22.4, 57.8 / 52.4, 121 / 101, at worst 64.3 / 69.7.  The line is drawn where pairs of more
-// (70 + 70 us) were no faster as often as they were: both products then fill the chip alone.  The persistent kernel and
-// 128 x 256 tiles take a unit's whole LDS for shapes that fill it.
+// (70 + 70 us) were no faster as often as they were: both products then fill the chip alone.
+// The persistent kernel and 128 x 256 tiles take too much of a unit's LDS to share it.  Products that the rule would give to
+// them are paired in their best other form unless that looks more than kPairGain slower, which a shared launch is worth
+// (us, with such a form / paired, 7 of 90 drawn layers: 69.8 / 62.2, 66.2 / 58.2, 60.0 / 56.6, 49.0 / 44.4, 48.8 / 47.4,
+// 42.2 / 35.8, 62.1 / 62.7; at 4 us instead of 12 only one of them was paired).
 // What one product writes the other must not read: a caller may pass a gradient's buffer that is also an operand (wi as dwi),
 // which one launch after the other allows.
 bool disjoint(const void* p, size_t pn, const void* q, size_t qn) {
@@ -1272,9 +1275,20 @@ bool independent(const PairProduct& writer, const PairProduct& reader) {
          disjoint(w.a.C, out, r.a.B, bytes(k, r.N, 1, sizeof(bf16_t))) &&
          disjoint(w.a.C, out, r.a.mask, bytes(r.E, r.R, r.N, sizeof(bf16_t)));
 }
-bool pair_ok(const PairProduct& d, const PairProduct& w) {
-  if (d.form == kPersistent || d.form == kEdge128x256 || w.form == kPersistent || w.form == kEdge128x256) return false;
-  return d.us + w.us < 120.0 && independent(d, w) && independent(w, d);
+constexpr double kPairGain = 12.0;                             // us
+// sets the forms that the pair runs in
+bool pair_ok(PairProduct* d, GemmLayout data, PairProduct* w, int cus) {
+  const double alone = d->us + w->us;
+  for (PairProduct* p : {d, w})
+    if (p->form == kPersistent || p->form == kEdge128x256) {
+      p->us = 1e30;
+      for (int f = kEdge64x64Deep; f >= kEdge128x128; --f) {
+        const double us = form_time((GemmForm)f, p->E, p->R, p->N, p->K, p == d ? data : kLayoutWeightGrad, cus);
+        if (us > 0 && us < p->us) { p->us = us; p->form = (GemmForm)f; }
+      }
+    }
+  const double us = d->us + w->us;
+  return us < 120.0 && us < alone + kPairGain && independent(*d, *w) && independent(*w, *d);
 }
 int launch_pair(const PairProduct& d, const PairProduct& w, hipStream_t st) {
   switch (d.form) {
@@ -1599,7 +1613,9 @@ static int pair_or_none(const moe_config& c, const GemmArgs& data, GemmLayout la
   if ((train ? choose_train_forms(c, &h, &d.form, &d.us) : choose_form(c.E, R, N, K, layout, &d.form, false, &d.us)) != MOE_OK ||
       choose_form(c.E, w.R, w.N, R, kLayoutWeightGrad, &w.form, kept != nullptr, &w.us) != MOE_OK)
     return MOE_EHIP;
-  *done = pair_ok(d, w);
+  int cus = 0;
+  if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
+  *done = pair_ok(&d, layout, &w, cus);
   return *done ? launch_pair(d, w, st) : MOE_OK;
 }
 
@@ -1642,7 +1658,7 @@ int launch_dense_grads_pair(const DenseWgradPlan& p, long long rows, int in, int
   if (choose_form(1, (int)rows, in, out, mask != nullptr ? kLayoutMaskedDataGrad : kLayoutDataGrad, &d.form, false, &d.us) != MOE_OK)
     return MOE_EHIP;
   w.form = gemm_form(persistent, p.splits, in, out, w.K, kLayoutWeightGrad, 256, &w.us);
-  *done = pair_ok(d, w);
+  *done = pair_ok(&d, mask != nullptr ? kLayoutMaskedDataGrad : kLayoutDataGrad, &w, 256);
   return *done ? launch_pair(d, w, st) : MOE_OK;
 }
 

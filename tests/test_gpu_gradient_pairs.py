@@ -29,6 +29,8 @@ CASES = [
     _cfg(1, 3000, 256, 512, 6, 1000),              # 128 x 128 rows
     _cfg(4, 627, 800, 3232, 46, 28),
     _cfg(2, 1500, 136, 904, 24, 195, 0.5),
+    _cfg(4, 1024, 512, 2048, 16, 128, 0.5),        # dh of the persistent kernel, with its mask bits, by itself
+    _cfg(2, 1318, 512, 2048, 9, 293),
 ]
 
 
