@@ -942,7 +942,7 @@ template <int D> constexpr int kLdsQShort = 2 * ShortGeom<D>::kRowBlock + ShortG
 template <int D, int CT> constexpr int kLdsKV = 2 * (2 * AttGeom<D>::kBlock + 512) + 128 * CT * AttGeom<D>::kRow;
 
 template <int D, bool RAGGED>
-int prepare() {
+int prepare_kernels() {
   static LdsLimitOnce once, once_q, once_short, once_kv1, once_kv2;
   int rc = ensure_lds_limit(once, reinterpret_cast<const void*>(attention_mfma_kernel<D, RAGGED>), kLdsForward<D>);
   if (rc == MOE_OK) rc = ensure_lds_limit(once_q, reinterpret_cast<const void*>(attention_bwd_dq_mfma_kernel<D, RAGGED>), kLdsQ<D>);
@@ -956,7 +956,7 @@ int prepare() {
 
 template <int D, bool RAGGED>
 int launch(const bf16_t* qkv, bf16_t* ctx, float* lse, long long B, int L, int heads, hipStream_t st) {
-  if (prepare<D, RAGGED>() != MOE_OK) return MOE_EHIP;
+  if (prepare_kernels<D, RAGGED>() != MOE_OK) return MOE_EHIP;
   const long long blocks = B * heads * ((L + 127) / 128);
   if (blocks > 0x7fffffffLL) return MOE_EUNSUPPORTED;
   hipLaunchKernelGGL((attention_mfma_kernel<D, RAGGED>), dim3((unsigned)blocks), dim3(256), kLdsForward<D>, st, qkv, ctx, lse, L, heads);
@@ -966,7 +966,7 @@ template <int D, bool RAGGED>
 int launch_bwd(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse, bf16_t* dqkv, float* dvec,
                long long B, int L, int heads, hipStream_t st) {
   int cus = 0;
-  if (prepare<D, RAGGED>() != MOE_OK || compute_units(&cus) != MOE_OK) return MOE_EHIP;
+  if (prepare_kernels<D, RAGGED>() != MOE_OK || compute_units(&cus) != MOE_OK) return MOE_EHIP;
   const long long blocks = B * heads * ((L + 127) / 128), blocks2 = B * heads * ((L + 255) / 256);
   if (blocks > 0x7fffffffLL) return MOE_EUNSUPPORTED;
   if constexpr (RAGGED) {
@@ -993,7 +993,7 @@ int launch_bwd(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const f
 }  // namespace
 
 int prepare_attention_mfma() {
-  const int rcs[] = {prepare<64, false>(), prepare<64, true>(), prepare<128, false>(), prepare<128, true>()};
+  const int rcs[] = {prepare_kernels<64, false>(), prepare_kernels<64, true>(), prepare_kernels<128, false>(), prepare_kernels<128, true>()};
   for (int rc : rcs)
     if (rc != MOE_OK) return rc;
   return MOE_OK;
