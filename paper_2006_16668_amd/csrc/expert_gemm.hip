@@ -806,14 +806,16 @@ __device__ __forceinline__ void edge_tile(const EdgeArgs& arg, const int logical
   // A step: the fragments of its first kAhead pieces of 16 k are asked for at once and each product is followed by the fetch
   // of the piece kAhead on, so that a step waits for LDS once and not once per piece: it is this chain of waits that bounds
   // tiles alone on their unit (48 tiles of K 3072, 0.24 us a step of 64 k, of which 0.05 are products).
-  // The copies of a later step are started under that wait; with two stages they go first, since the next step needs them,
-  // and so they do for the dense layers' 128 x 128 weight gradients, whose long sums lost 5 % otherwise.
+  // Where three stages or more leave them time the copies of a later step are started under that wait.  They go first with two
+  // stages, in the forward products, whose weights may come from memory (128 x 128 deep 213 / 201 reads first, 194 copies
+  // first; 64 x 128 deep of 40 us and more lost 2 % otherwise), and in the dense layers' 128 x 128 weight gradients,
+  // whose long sums lost 5 %.
   // Over the products of 60 drawn training and encoder steps, sums of us before / after: 64 x 64 deep 1129 / 1062, pairs of
   // 64 x 64 tiles 1501 / 1389, weight gradients of 64 x 64 tiles 269 / 245, of 128 x 128 of kept rows 411 / 392, data products
   // 128 x 128 deep 569 / 534.  No gain and so as it was: 128 x 256 tiles (two blocks of 128 accumulators fill the
   // unit) and the forward products in two stages (276 / 284: the read-ahead delays their copies).
   constexpr int kAhead = BN == 256 || (ST == 2 && !B_KC) ? 0 : BM == 128 && KK > 2 ? 2 : KK;
-  constexpr bool kReadFirst = ST > 2 && (!A_MNC || BM == 64 || K_KEPT || EPI == kEpiRangesIfAny);
+  constexpr bool kReadFirst = ST > 2 && (A_MNC ? BM == 64 || K_KEPT || EPI == kEpiRangesIfAny : B_KC);
   bf16x8_t fa[KK][TM], fb[KK][TN];
   auto fetch = [&](uint32_t sb, int kk) __attribute__((always_inline)) {
 #pragma unroll
