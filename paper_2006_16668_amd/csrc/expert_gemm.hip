@@ -807,14 +807,13 @@ __device__ __forceinline__ void edge_tile(const EdgeArgs& arg, const int logical
   // of the piece kAhead on, so that a step waits for LDS once and not once per piece: it is this chain of waits that bounds
   // tiles alone on their unit (48 tiles of K 3072, 0.24 us a step of 64 k, of which 0.05 are products).
   // Where three stages or more leave them time the copies of a later step are started under that wait.  They go first with two
-  // stages, in the forward products, whose weights may come from memory (128 x 128 deep 213 / 201 reads first, 194 copies
-  // first; 64 x 128 deep of 40 us and more lost 2 % otherwise), and in the dense layers' 128 x 128 weight gradients,
-  // whose long sums lost 5 %.
+  // stages, in the forward products, whose weights may come from memory (64 x 128 deep of 40 us and more lost 3 %), and in the
+  // dense layers' 128 x 128 weight gradients, whose long sums lost 5 %.
   // Over the products of 60 drawn training and encoder steps, sums of us before / after: 64 x 64 deep 1129 / 1062, pairs of
-  // 64 x 64 tiles 1501 / 1389, weight gradients of 64 x 64 tiles 269 / 245, of 128 x 128 of kept rows 411 / 392, data products
-  // 128 x 128 deep 569 / 534.  No gain and so as it was: 128 x 256 tiles (two blocks of 128 accumulators fill the
-  // unit) and the forward products in two stages (276 / 284: the read-ahead delays their copies).
-  constexpr int kAhead = BN == 256 || (ST == 2 && !B_KC) ? 0 : BM == 128 && KK > 2 ? 2 : KK;
+  // 64 x 64 tiles 1501 / 1389, weight gradients of 64 x 64 tiles 269 / 245, of 128 x 128 of kept rows 411 / 392.
+  // As before: 128 x 256 tiles (two blocks of 128 accumulators fill the unit) and the forward products on 128 x 128 tiles or in
+  // two stages: 64 tokens through 32 experts of M 1024, H 8192, whose weights stream, took 200 us with it instead of 194.
+  constexpr int kAhead = BN == 256 || (!A_MNC && !B_KC && (ST == 2 || BM == 128)) ? 0 : BM == 128 && KK > 2 ? 2 : KK;
   constexpr bool kReadFirst = ST > 2 && (A_MNC ? BM == 64 || K_KEPT || EPI == kEpiRangesIfAny : B_KC);
   bf16x8_t fa[KK][TM], fb[KK][TN];
   auto fetch = [&](uint32_t sb, int kk) __attribute__((always_inline)) {
@@ -833,7 +832,19 @@ __device__ __forceinline__ void edge_tile(const EdgeArgs& arg, const int logical
     stage = stage + 1 == ST ? 0 : stage + 1;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      if (kAhead == 0) fetch(sb, kk);
+      if constexpr (kAhead == 0) {
+        bf16x8_t ga[TM], gb[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) ga[i] = A_MNC ? read_mnc(sb, a_rd[i], kk, BM * 2) : read_kc(sb, a_rd[kk], i);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) gb[j] = B_KC ? read_kc(sb, b_rd[kk], j) : read_mnc(sb, b_rd[j], kk, BN * 2);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gb[j], ga[i], acc[i][j], 0, 0, 0);
+        continue;
+      }
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
