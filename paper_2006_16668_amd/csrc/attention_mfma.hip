@@ -134,6 +134,12 @@ __device__ __forceinline__ void fragment_terms(const V& v, int first, bf16x8_bit
   if constexpr (TERMS == 3) split_bf16x8(v, first, t);
   else t[0] = pack8(v, first);
 }
+// dS = p (dp - D), rounded.  The compiler fused it with the subtractions of split_bf16x8 in some kernels and not in others: the
+// terms were then those of the unrounded product, and a sequence's dq would depend on the kernel that forms it.
+__device__ __forceinline__ float dscore(float p, float dp, float D) {
+#pragma clang fp contract(off)
+  return p * (dp - D);
+}
 // Every XCD (own L2) takes a contiguous range of work items: the blocks of one (sequence, head) read the same rows.
 __device__ __forceinline__ unsigned xcd_contiguous(unsigned block, unsigned blocks) {
   const unsigned per_xcd = blocks / 8;
@@ -590,7 +596,7 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
               constexpr int w = CT * (u - KS) + p - 1, all = CT * KS - 1;      // (not right behind dP's last product)
               if constexpr (w >= 0) {
 #pragma unroll
-                for (int j = w * 16 * CT / all; j < (w + 1) * 16 * CT / all; ++j) sacc[j % CT][j / CT] *= dpacc[j % CT][j / CT] - dd[j % CT];
+                for (int j = w * 16 * CT / all; j < (w + 1) * 16 * CT / all; ++j) sacc[j % CT][j / CT] = dscore(sacc[j % CT][j / CT], dpacc[j % CT][j / CT], dd[j % CT]);
               }
               if constexpr (u == KS + KS / 2 + 1) fragment_terms(sacc[p], 0, dsf[0][p]);
             } else if constexpr (u == 2 * KS && p < CT) {
@@ -614,9 +620,8 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
 
 // ---------------------------------------------------------------- dq (and D) of short ragged sequences
 // K and V blocks through registers into one LDS stage, K once more in the order of the transposing read: more traffic
-// in LDS, but a shorter way to the first product, which is what counts for a few blocks of keys.  us, this kernel / the one above:
-// d 128, 64 sequences and heads of 48 tokens 7.8 / 10.5, 500 of 100 43.3 / 45.0, 200 of 300 33.5 / 32.1; d 64, 64 of
-// 48 6.1 / 7.4, 500 of 100 25.8 / 26.8, 30 of 192 10.6 / 11.1, 200 of 192 15.3 / 14.8.
+// in LDS, but a shorter way to the first product, which is what counts for a few blocks of keys, and for d 64 three
+// blocks on a unit instead of two (attention_dq_short below says which calls take it).
 template <int D> struct ShortGeom {          // row pitches: 16-byte row reads 4 banks apart, transposing reads 16
   static constexpr int kRowPitch = D * 2 + 16, kTrPitch = D * 2 + 64;
   static constexpr int kRowBlock = 64 * kRowPitch, kTrBlock = 64 * kTrPitch;
@@ -737,7 +742,7 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_short_kernel(
       float ds[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        ds[i] = __builtin_amdgcn_exp2f(fmaf(sacc[i], sl2, -lse2)) * (dpacc[i] - dd);
+        ds[i] = dscore(__builtin_amdgcn_exp2f(fmaf(sacc[i], sl2, -lse2)), dpacc[i], dd);
       if (kb * 64 + 64 > L) {
 #pragma unroll
         for (int i = 0; i < 16; ++i)
@@ -936,6 +941,23 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
   store_own<D, CT>(dv, 1.f, lds0 + own, out + A, ld, w.col0, L, lane);
 }
 
+}  // namespace
+
+// Which dq kernel a ragged length takes, from 680 calls of both (us, short kernel / the other; sequence-heads of L tokens).
+// Under 256 tokens the short one: d 128, 64 of 48 7.8 / 9.9, 400 of 100 21.5 / 21.9; d 64, 64 of 48 6.0 / 6.7, 1000 of 100
+// 25.5 / 26.2, 32 of 193 11.6 / 12.7 (three blocks of keys of d 64 are as often faster with either: 96 of 191 11.0 / 12.1, 96 of
+// 192 11.8 / 10.9).  For d 128 and more than two blocks of keys only while units have one block each: 96 of 191 15.6 / 16.0, 200 of 200
+// 29.5 / 29.0, 152 of 200 28.2 / 27.1; then 132 of 300 34.4 / 32.4, 128 of 700 95 / 90.  For d 64 three short blocks share a
+// unit, or two of the others: past one round of those the short kernel has fewer rounds or, up to 896 tokens, shorter ones: 88 of 700
+// 46.8 / 52.1, 248 of 700 88.8 / 91.6, 80 of 900 58 / 62, 80 of 1000 64 / 69, but with as many rounds 112 of 1000 88.9 / 86.9.
+bool attention_dq_short(int d, int L, long long blocks, int cus) {
+  if (d == 128) return L <= 128 || (L < 256 && blocks <= cus);
+  auto rounds = [&](long long per_unit) { return (blocks + per_unit * cus - 1) / (per_unit * cus); };
+  return L < 256 || (rounds(2) > 1 && (L <= 896 || rounds(3) < rounds(2)));
+}
+
+namespace {
+
 template <int D> constexpr int kLdsForward = 4 * AttGeom<D>::kBlock;
 template <int D> constexpr int kLdsQ = 5 * AttGeom<D>::kBlock;
 template <int D> constexpr int kLdsQShort = 2 * ShortGeom<D>::kRowBlock + ShortGeom<D>::kTrBlock;
@@ -969,11 +991,12 @@ int launch_bwd(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const f
   if (prepare_kernels<D, RAGGED>() != MOE_OK || compute_units(&cus) != MOE_OK) return MOE_EHIP;
   const long long blocks = B * heads * ((L + 127) / 128), blocks2 = B * heads * ((L + 255) / 256);
   if (blocks > 0x7fffffffLL) return MOE_EUNSUPPORTED;
+  const bool dq_short = RAGGED && attention_dq_short(D, L, blocks, cus);
   if constexpr (RAGGED) {
-    if (L < 256) hipLaunchKernelGGL((attention_bwd_dq_short_kernel<D>), dim3((unsigned)blocks), dim3(256), kLdsQShort<D>, st, qkv, ctx,
-                                    dctx, lse, dqkv, dvec, L, heads);
+    if (dq_short) hipLaunchKernelGGL((attention_bwd_dq_short_kernel<D>), dim3((unsigned)blocks), dim3(256), kLdsQShort<D>, st, qkv, ctx,
+                                     dctx, lse, dqkv, dvec, L, heads);
   }
-  if (!RAGGED || L >= 256)
+  if (!dq_short)
     hipLaunchKernelGGL((attention_bwd_dq_mfma_kernel<D, RAGGED>), dim3((unsigned)blocks), dim3(256), kLdsQ<D>, st, qkv, ctx, dctx,
                      lse, dqkv, dvec, L, heads);
   // dk, dv of d 128: one block per compute unit, and 256 keys of a block take 1.46 times as long as 128 (L 1024, 192 blocks
