@@ -248,6 +248,28 @@ __device__ __forceinline__ void store_own(const f32x16_t (&acc)[CT][D / 32], flo
   }
 }
 
+// ---------------------------------------------------------------- staging of the short ragged kernels
+// Blocks of 64 rows through registers into LDS, the rows of a transposing read in an order of their own.
+template <int D> struct ShortGeom {          // row pitches: 16-byte row reads 4 banks apart, transposing reads 16
+  static constexpr int kRowPitch = D * 2 + 16, kTrPitch = D * 2 + 64;
+  static constexpr int kRowBlock = 64 * kRowPitch, kTrBlock = 64 * kTrPitch;
+};
+__device__ __forceinline__ int swap_bits_2_3(int row) {
+  return (row & ~12) | ((row & 4) << 1) | ((row & 8) >> 1);
+}
+// first operand fragment [32 d-rows x 16 staged rows] of a block staged [rows][d] with the
+// transposing pitch: lane needs (d = 32 dt + lane%32, 8 consecutive staged rows of its half)
+template <int PITCH>
+__device__ __forceinline__ bf16x8_t read_transposed(uint32_t block, int row16, int dt, int lane) {
+  const int p16 = lane & 15, bb = lane >> 4;
+  const int krow0 = 8 * (bb >> 1) + (p16 >> 2);
+  const int col = 32 * dt + 16 * (bb & 1) + 4 * (p16 & 3);
+  const uint32_t pv = block + (row16 + krow0) * PITCH + 2 * col;
+  const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)pv);
+  const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(pv + 4 * PITCH));
+  return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 // ---------------------------------------------------------------- forward
 template <int D, bool RAGGED>
 __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx,
@@ -427,6 +449,99 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const bf16_t* __
   if (lse != nullptr && hf == 0 && q < L) lse[(size_t)w.bh * L + q] = (m_run + log2f(l_run)) * 0.6931471805599453f;
   const f32x16_t (&tiles)[1][DT] = reinterpret_cast<const f32x16_t (&)[1][DT]>(o);
   store_own<D, CT>(tiles, 1.0f / l_run, lds0 + own, ctx + (size_t)w.b * L * A + (size_t)w.h * D, A, w.col0, L, lane);
+}
+
+// ---------------------------------------------------------------- forward of one block of keys (L <= 64)
+// The sums of the kernel above without its loop: K and V through registers, the queries' rows straight from memory and
+// the results straight to it.  What counts here is the way to the first product, and room for more blocks on a unit (91 or
+// 127 registers instead of 182 or 250).  us, the kernel above / this one: d 64, 8 sequence-heads of 16 tokens 4.9 / 4.3, 520 of 48
+// 9.2 / 5.8, 2200 of 64 21.2 / 17.7; d 128, 64 of 48 6.9 / 6.4, 1000 of 48 16.7 / 13.9, but 4000 of 48 51.7 / 50.9, 400 of 64
+// 9.6 / 10.1 and 4000 of 64 55.6 / 65.8: rows of 256 bytes read and written piece by piece are what it waits for then.
+template <int D>
+__global__ __launch_bounds__(256, 2) void attention_short_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx,
+                                                                 float* __restrict__ lse, int L, int heads) {
+  using GM = ShortGeom<D>;
+  constexpr int KS = D / 16, DT = D / 32, VV = 64 * D / 8 / 256, VPR = D / 8;
+  __shared__ __attribute__((aligned(256))) unsigned char kv[GM::kRowBlock + GM::kTrBlock];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 31, hf = lane >> 5;
+  const unsigned bh = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int h = (int)(bh % heads);
+  const long long b = bh / heads;
+  const int A = heads * D;
+  const size_t ld = (size_t)3 * A;
+  const bf16_t* const base = qkv + (size_t)b * L * ld + (size_t)h * D;
+  const int q = wave * 32 + r;
+
+  u32x4_t qf[KS], kreg[VV], vreg[VV];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) qf[s] = *reinterpret_cast<const u32x4_t*>(base + (size_t)(q < L ? q : L - 1) * ld + 16 * s + 8 * hf);
+#pragma unroll
+  for (int i = 0; i < VV; ++i) {
+    const int f = tid + 256 * i, key = f / VPR;
+    const bf16_t* const row = base + (size_t)(key < L ? key : L - 1) * ld + 8 * (f % VPR);
+    kreg[i] = *reinterpret_cast<const u32x4_t*>(row + A);
+    vreg[i] = *reinterpret_cast<const u32x4_t*>(row + 2 * A);
+  }
+#pragma unroll
+  for (int i = 0; i < VV; ++i) {
+    const int f = tid + 256 * i, key = f / VPR, c = f % VPR;
+    *reinterpret_cast<u32x4_t*>(kv + key * GM::kRowPitch + 16 * c) = kreg[i];
+    *reinterpret_cast<u32x4_t*>(kv + GM::kRowBlock + swap_bits_2_3(key) * GM::kTrPitch + 16 * c) = key < L ? vreg[i] : u32x4_t{0u, 0u, 0u, 0u};
+  }
+  __syncthreads();
+  if (wave * 32 >= L) return;
+  const uint32_t kst = (uint32_t)(uintptr_t)((lds_ptr)kv), vst = kst + GM::kRowBlock;
+  const float sl2 = 1.4426950408889634f / sqrtf((float)D);
+  f32x16_t sacc[2], o[DT];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const u32x4_t kf = *(lds_u4_ptr)(uintptr_t)(kst + (32 * t + r) * GM::kRowPitch + 32 * s + 16 * hf);
+      sacc[t] = MOE_MFMA(kf, qf[s], s == 0 ? f32x16_t{} : sacc[t]);
+    }
+  float mx = -INFINITY, psum = 0.f;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (32 * t + 8 * (i >> 2) + 4 * hf + (i & 3) >= L) sacc[t][i] = -INFINITY;
+      mx = fmaxf(mx, sacc[t][i]);
+    }
+  const float m = fmaxf(-FLT_MAX, fmaxf(mx, __shfl_xor(mx, 32, 64)) * sl2);
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      sacc[t][i] = __builtin_amdgcn_exp2f(fmaf(sacc[t][i], sl2, -m));
+      psum += sacc[t][i];
+    }
+  psum += __shfl_xor(psum, 32, 64);
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) o[dt] = f32x16_t{};
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    bf16x8_bits_t pf[3];
+    split_bf16x8(sacc[s / 2], 8 * (s % 2), pf);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const bf16x8_t vt = read_transposed<GM::kTrPitch>(vst, 16 * s, dt, lane);
+#pragma unroll
+      for (int k = 2; k >= 0; --k) o[dt] = MOE_MFMA(vt, pf[k], o[dt]);
+    }
+  }
+  if (q >= L) return;
+  const float inv = 1.0f / psum;
+  if (lse != nullptr && hf == 0) lse[(size_t)bh * L + q] = (m + log2f(psum)) * 0.6931471805599453f;
+  // o[dt][i]: d = 32 dt + 8 (i/4) + 4 hf + i%4 of query r
+  bf16_t* const row = ctx + ((size_t)b * L + q) * A + (size_t)h * D;
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<u32x2_t*>(row + 32 * dt + 8 * g + 4 * hf) =
+          u32x2_t{pack_bf16x2(o[dt][4 * g] * inv, o[dt][4 * g + 1] * inv), pack_bf16x2(o[dt][4 * g + 2] * inv, o[dt][4 * g + 3] * inv)};
 }
 
 // ---------------------------------------------------------------- dq (and D)
@@ -622,26 +737,6 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dq_mfma_kernel(
 // K and V blocks through registers into one LDS stage, K once more in the order of the transposing read: more traffic
 // in LDS, but a shorter way to the first product, which is what counts for a few blocks of keys, and for d 64 three
 // blocks on a unit instead of two (attention_dq_short below says which calls take it).
-template <int D> struct ShortGeom {          // row pitches: 16-byte row reads 4 banks apart, transposing reads 16
-  static constexpr int kRowPitch = D * 2 + 16, kTrPitch = D * 2 + 64;
-  static constexpr int kRowBlock = 64 * kRowPitch, kTrBlock = 64 * kTrPitch;
-};
-__device__ __forceinline__ int swap_bits_2_3(int row) {
-  return (row & ~12) | ((row & 4) << 1) | ((row & 8) >> 1);
-}
-// first operand fragment [32 d-rows x 16 staged rows] of a block staged [rows][d] with the
-// transposing pitch: lane needs (d = 32 dt + lane%32, 8 consecutive staged rows of its half)
-template <int PITCH>
-__device__ __forceinline__ bf16x8_t read_transposed(uint32_t block, int row16, int dt, int lane) {
-  const int p16 = lane & 15, bb = lane >> 4;
-  const int krow0 = 8 * (bb >> 1) + (p16 >> 2);
-  const int col = 32 * dt + 16 * (bb & 1) + 4 * (p16 & 3);
-  const uint32_t pv = block + (row16 + krow0) * PITCH + 2 * col;
-  const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)pv);
-  const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(pv + 4 * PITCH));
-  return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
 template <int D>
 __global__ __launch_bounds__(256, 2) void attention_bwd_dq_short_kernel(
     const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
@@ -981,6 +1076,11 @@ int launch(const bf16_t* qkv, bf16_t* ctx, float* lse, long long B, int L, int h
   if (prepare_kernels<D, RAGGED>() != MOE_OK) return MOE_EHIP;
   const long long blocks = B * heads * ((L + 127) / 128);
   if (blocks > 0x7fffffffLL) return MOE_EUNSUPPORTED;
+  if constexpr (RAGGED)
+    if (L <= (D == 64 ? 64 : 48)) {                            // (figures at the kernel)
+      hipLaunchKernelGGL((attention_short_kernel<D>), dim3((unsigned)blocks), dim3(256), 0, st, qkv, ctx, lse, L, heads);
+      return check_launch();
+    }
   hipLaunchKernelGGL((attention_mfma_kernel<D, RAGGED>), dim3((unsigned)blocks), dim3(256), kLdsForward<D>, st, qkv, ctx, lse, L, heads);
   return check_launch();
 }
