@@ -935,7 +935,8 @@ __device__ __forceinline__ void gate_single_chunk_finish(
 // tokens, M 1024, E 32: 16.9 -> 10.6 us.
 // TAIL: fp32 and M % 32 != 0.  RAW: bf16 and wg as it is, split into its three terms on the way to the products: a
 // chunk's wavefronts together read each weight once, so packing them first (a launch of 4 to 5 us) does not
-// pay for one call.  Training step of 4 x 1024 tokens, M 512, H 2048, E 16 211.0 -> 203.3 us.
+// pay for one call (gate_splits_wg says where it does).  Training step of 4 x 1024 tokens, M 512, H 2048, E 16
+// 211.0 -> 203.3 us.
 template <typename T, int ETW, int KW, bool TAIL, bool RAW>
 __global__ __launch_bounds__(512) void gate_chunk_kernel(
     const T* __restrict__ x, const uint4* __restrict__ wgP, const float* __restrict__ wg,
@@ -1737,6 +1738,13 @@ static bool gate_route_form(const moe_config& c, long long chunks) {
 // 75.6; 1000 x 20, 32 318 / 76.
 constexpr int kSumGroups = 16;
 
+// Whether a bf16 gate of few chunks without packed weights splits wg itself.  A block's chain of loads, splits and products
+// grows with M, and with two tiles of columns per wavefront it has half the loads in flight: then the launch that
+// packs is the shorter way from 2560 on.  Layer of H 64, us, packed first / split here (tokens, M, E): 64, 4096, 32 67.7 / 59.9;
+// 64, 1024, 33 33.0 / 32.0; 700, 1536, 64 48.3 / 47.1; 4 x 1024, 2048, 64 65.7 / 64.7; 64, 2048, 33 46.8 / 47.4; 700, 2560, 33
+// 63.1 / 65.3; 64, 3072, 64 65.2 / 69.3; 64, 4096, 33 78.3 / 84.2.
+bool gate_splits_wg(int E, int M) { return E <= 32 || M <= 2048; }
+
 int launch_gate(const moe_config& c, const void* x, const float* wg, const float* u,
                 int32_t* expert_idx, int32_t* slot, float* weight, int32_t* fill,
                 int32_t* src_token, int32_t* c1, float* mean_gate, float* aux,
@@ -1759,7 +1767,7 @@ int launch_gate(const moe_config& c, const void* x, const float* wg, const float
   const bool single = chunk_form && chunks == 1;
   const int zero_words = zero_row != nullptr ? c.M / 2 : 0;
   const RowPacking pk = packing != nullptr ? *packing : RowPacking{nullptr, nullptr, nullptr};
-  const bool raw = chunk_form && c.act_dtype == MOE_BF16 && wg_prepacked == nullptr;
+  const bool raw = chunk_form && c.act_dtype == MOE_BF16 && wg_prepacked == nullptr && gate_splits_wg(c.E, c.M);
   if (wg_prepacked == nullptr && !raw && (rc = launch_gate_pack(c, wg, own, st)) != MOE_OK) return rc;
   if (chunk_form) {
 #define MOE_GATE_CHUNK(T, ETW, KW, TAIL, RAW)                                                           \

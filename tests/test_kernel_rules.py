@@ -24,3 +24,11 @@ def _rule(mangled, *types):
 def test_dq_of_ragged_sequences(d, L, n, short, other):
     rule = _rule("_ZN3moe18attention_dq_shortEiixi", ctypes.c_int, ctypes.c_int, ctypes.c_longlong, ctypes.c_int)
     assert rule(d, L, n * ((L + 127) // 128), UNITS) == (short < other)
+
+
+# tokens, M, E, us of a layer of H 64 that packs wg first and of one whose gate splits it
+@pytest.mark.parametrize("tokens,M,E,packed,split", [
+    (64, 4096, 32, 67.7, 59.9), (64, 1024, 33, 33.0, 32.0), (700, 1536, 64, 48.3, 47.1), (4096, 2048, 64, 65.7, 64.7),
+    (700, 2560, 33, 63.1, 65.3), (64, 3072, 64, 65.2, 69.3), (64, 4096, 33, 78.3, 84.2), (700, 4096, 64, 88.9, 93.2)])
+def test_gate_weights_of_one_call(tokens, M, E, packed, split):
+    assert _rule("_ZN3moe14gate_splits_wgEii", ctypes.c_int, ctypes.c_int)(E, M) == (split < packed)
