@@ -22,6 +22,7 @@ def _cfg(dt, G, S, M, H, E, C, bias=0.0):
 CASES = [
     _cfg("f32", 1, 17, 8, 8, 2, 3),                    # one piece of a row; most choices dropped
     _cfg("f32", 3, 43, 264, 40, 7, 64, 1.0),           # rows of two rounds of a wavefront; many empty rows
+    _cfg("f32", 2, 33, 776, 40, 5, 16, 0.5),           # of three rounds, taken two at a time, and a bit
     _cfg("bf16", 1, 65, 512, 64, 3, 63),
     _cfg("bf16", 2, 64, 520, 64, 16, 32, 1.0),         # one lane more than a row of 512; empty experts' rows
     _cfg("bf16", 5, 51, 72, 136, 33, 13),              # 255 tokens, more gate columns than half a wavefront
