@@ -1122,9 +1122,10 @@ int prepare_attention_mfma() {
   return MOE_OK;
 }
 
-// copies address rows of a block by 32-bit byte offsets
+// Copies address the rows of a block by unsigned 32-bit byte offsets, and the row statistics of a head by signed ones.  The
+// widths that the calls accept (heads . d below 2^23) stay below the first.
 bool attention_mfma_ok(int act_dtype, int L, int heads, int d) {
-  return act_dtype == MOE_BF16 && (d == 64 || d == 128) && (long long)64 * 3 * heads * d * 2 < 1LL << 31 && L < 1 << 29;
+  return act_dtype == MOE_BF16 && (d == 64 || d == 128) && (long long)64 * 3 * heads * d * 2 < 1LL << 32 && L < 1 << 29;
 }
 
 int launch_attention_mfma(const void* qkv, void* ctx, float* lse, long long B, int L, int heads, int d, hipStream_t st) {

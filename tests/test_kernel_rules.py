@@ -32,3 +32,12 @@ def test_dq_of_ragged_sequences(d, L, n, short, other):
     (700, 2560, 33, 63.1, 65.3), (64, 3072, 64, 65.2, 69.3), (64, 4096, 33, 78.3, 84.2), (700, 4096, 64, 88.9, 93.2)])
 def test_gate_weights_of_one_call(tokens, M, E, packed, split):
     assert _rule("_ZN3moe14gate_splits_wgEii", ctypes.c_int, ctypes.c_int)(E, M) == (split < packed)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_widest_attention_takes_the_matrix_cores(d):
+    """The plain kernels, for other widths, refuse sequences of about 4000 tokens (2000 backward)."""
+    ok = _rule("_ZN3moe17attention_mfma_okEiiii", *[ctypes.c_int] * 4)
+    bf16, f32 = 1, 0
+    for heads in (1, 43690 * 128 // d, 43691 * 128 // d, 0x7fffff // d):       # up to the limit of heads . d
+        assert ok(bf16, 5000, heads, d) and not ok(f32, 5000, heads, d)
