@@ -253,6 +253,9 @@ int launch_expert_grads2(const moe_config& c, const void* dout, const void* wo, 
 int launch_expert_grads1(const moe_config& c, const void* dh, const void* wi, void* dbuf, const void* buf, void* dwi,
                          const int32_t* kept, hipStream_t st);
 
+// Whether the rule pairs these two (masked: grads2) on a device of `cus` units, and in which forms (host only)
+bool gradient_pair_forms(const moe_config& c, bool masked, int cus, int* data, int* weight);
+
 // batched bf16 MFMA GEMM with an fp32 result (expert_gemm.hip): transposed_a ? C = A^T.B with
 // A [batch,K,R], B [batch,K,N] : C = A.B^T with A [batch,R,K], B [batch,N,K]; C [batch,R,N]
 bool gemm_bf16_f32out_ok(int R, int N, int K);

@@ -1154,23 +1154,29 @@ bool persistent_h(int E, int R, int H, int M, int cus) {
   const double both = hp + (dhp < dh ? dhp : dh);
   return hp < h ? both < h + dh : both < 0.96 * (h + dh) && 0.85 * 2 * E * R * H > 80e6;
 }
-// the form of this shape on the current device; k_kept: the sum over k runs over packed rows, of
+// the form of this shape on a device of `cus` units, or the current one; k_kept: the sum over k runs over packed rows, of
 // which the persistent kernel takes whole 256-row tiles
-int choose_form(int E, int R, int N, int K, GemmLayout layout, GemmForm* form, bool k_kept = false, double* us = nullptr) {
+GemmForm form_of(int E, int R, int N, int K, GemmLayout layout, bool k_kept, int cus, double* us = nullptr) {
+  const bool persistent = dma_shape_ok(R, N, K) || (layout != kLayoutWeightGrad && dma_columns_ok(R, N, K));
+  return gemm_form(persistent && (!k_kept || K % 256 == 0), E, R, N, K, layout, cus, us);
+}
+int choose_form(int E, int R, int N, int K, GemmLayout layout, GemmForm* form, bool k_kept = false) {
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
-  const bool persistent = dma_shape_ok(R, N, K) || (layout != kLayoutWeightGrad && dma_columns_ok(R, N, K));
-  *form = gemm_form(persistent && (!k_kept || K % 256 == 0), E, R, N, K, layout, cus, us);
+  *form = form_of(E, R, N, K, layout, k_kept, cus);
   return MOE_OK;
 }
 // h and dh of a training pass over packed rows
-int choose_train_forms(const moe_config& c, GemmForm* h, GemmForm* dh, double* dh_us = nullptr) {
-  int cus = 0;
-  if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
+void train_forms_of(const moe_config& c, int cus, GemmForm* h, GemmForm* dh, double* dh_us = nullptr) {
   const int R = c.G * c.C;
   const bool bits = (dma_shape_ok(R, c.H, c.M) || dma_columns_ok(R, c.H, c.M)) && persistent_h(c.E, R, c.H, c.M, cus);
   *h = bits ? kPersistent : gemm_form(false, c.E, R, c.H, c.M, kLayoutForward, cus);
   *dh = gemm_form(bits, c.E, R, c.H, c.M, kLayoutMaskedDataGrad, cus, dh_us);
+}
+int choose_train_forms(const moe_config& c, GemmForm* h, GemmForm* dh) {
+  int cus = 0;
+  if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
+  train_forms_of(c, cus, h, dh);
   return MOE_OK;
 }
 
@@ -1267,14 +1273,15 @@ int launch_pair_weight(const PairProduct& d, const PairProduct& w, hipStream_t s
 // for the last of its tiles; in one launch the second product's tiles fill the units that the first leaves, and one launch
 // and its gap go away.  With 160 products of 60 drawn training steps and encoder backward passes (us, two launches / one,
 // without the gap): 64 x 64 tiles 13.9 / 8.3, 18.1 / 12.0, 25.5 / 24.5, mixed ones 24.5 / 19.9, 60.5 / 53.8,
-// 162 / 147, 128 x 128 tiles 31.1 / 22.4, 57.8 / 52.4, 121 / 101, at worst 64.3 / 69.7.  The line is drawn where pairs of more
-// (70 + 70 us) were no faster as often as they were: both products then fill the chip alone.
+// 162 / 147, 128 x 128 tiles 31.1 / 22.4, 57.8 / 52.4, 121 / 101, at worst 64.3 / 69.7.  The line is drawn (kPairMost, both
+// products by the rule) under the sizes from which pairs were as often slower as faster, 140 us: both then fill the chip alone.
 // The persistent kernel and 128 x 256 tiles take too much of a unit's LDS to share it.  Products that the rule would give to
 // them are paired in their best other form unless that looks more than kPairGain slower, which a shared launch is worth
 // (us, with such a form / paired, 7 of 90 drawn layers: 69.8 / 62.2, 66.2 / 58.2, 60.0 / 56.6, 49.0 / 44.4, 48.8 / 47.4,
 // 42.2 / 35.8, 62.1 / 62.7; at 4 us instead of 12 only one of them was paired).
-// What one product writes the other must not read: a caller may pass a gradient's buffer that is also an operand (wi as dwi),
-// which one launch after the other allows.
+// What one product writes the other must not read: a caller may pass a gradient's buffer that is also an operand of the
+// product that comes first otherwise (wi as dwi: an expert's data gradient; a dense layer's comes second), which one launch
+// after the other allows.
 bool disjoint(const void* p, size_t pn, const void* q, size_t qn) {
   const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
   return p == nullptr || q == nullptr || a + pn <= b || b + qn <= a;
@@ -1288,8 +1295,8 @@ bool independent(const PairProduct& writer, const PairProduct& reader) {
          disjoint(w.a.C, out, r.a.B, bytes(k, r.N, 1, sizeof(bf16_t))) &&
          disjoint(w.a.C, out, r.a.mask, bytes(r.E, r.R, r.N, sizeof(bf16_t)));
 }
-constexpr double kPairGain = 12.0;                             // us
-// sets the forms that the pair runs in
+constexpr double kPairMost = 120.0, kPairGain = 12.0;          // us
+// sets the forms that the pair runs in; both products' times are for `cus` units
 bool pair_ok(PairProduct* d, GemmLayout data, PairProduct* w, int cus) {
   const double alone = d->us + w->us;
   for (PairProduct* p : {d, w})
@@ -1301,9 +1308,12 @@ bool pair_ok(PairProduct* d, GemmLayout data, PairProduct* w, int cus) {
       }
     }
   const double us = d->us + w->us;
-  return us < 120.0 && us < alone + kPairGain && independent(*d, *w) && independent(*w, *d);
+  return us < kPairMost && us < alone + kPairGain;
 }
-int launch_pair(const PairProduct& d, const PairProduct& w, hipStream_t st) {
+// one launch, unless the products are not independent
+int launch_pair(const PairProduct& d, const PairProduct& w, hipStream_t st, bool* done) {
+  *done = independent(d, w) && independent(w, d);
+  if (!*done) return MOE_OK;
   switch (d.form) {
     case kEdge64x64: case kEdge64x64Deep: return launch_pair_weight<64, 64>(d, w, st);
     case kEdge64x128: case kEdge64x128Deep: return launch_pair_weight<64, 128>(d, w, st);
@@ -1498,7 +1508,8 @@ int launch_expert_ffn_packed(const moe_config& c, const void* a, const RowPackin
 
 // dW [in,out] = X^T dY over rows tokens: few tiles and a long sum.  The ranges run as a batch with fp32 results,
 // at the rule's time for that batch, and adding them up costs a launch and their bytes at about 6 TB/s (they
-// are in the last-level cache).
+// are in the last-level cache).  The ranges size a workspace, so they are those of a whole device on any partition.
+constexpr int kPlanUnits = 256;
 DenseWgradPlan dense_wgrad_plan(long long rows, int in, int out) {
   DenseWgradPlan best{1, (int)rows};
   double best_us = 0;
@@ -1507,7 +1518,7 @@ DenseWgradPlan dense_wgrad_plan(long long rows, int in, int out) {
     if (want > 1 && (k < 128 || sp < want)) continue;
     const bool persistent = dma_shape_ok(in, out, k) && (long long)sp * k == rows;
     double us = 0;
-    gemm_form(persistent, sp, in, out, sp == 1 ? (int)rows : k, kLayoutWeightGrad, 256, &us);
+    gemm_form(persistent, sp, in, out, sp == 1 ? (int)rows : k, kLayoutWeightGrad, kPlanUnits, &us);
     if (sp > 1) us += 3.0 + 4e-6 * sp * in * out / 6.0;
     if (want == 1 || us < best_us) { best_us = us; best = DenseWgradPlan{sp, sp == 1 ? (int)rows : k}; }
   }
@@ -1518,7 +1529,7 @@ DenseWgradPlan dense_wgrad_plan(long long rows, int in, int out) {
 int launch_dense_wgrad_ranges(const DenseWgradPlan& p, long long rows, int in, int out, const void* X, const void* dY,
                               float* partial, hipStream_t st) {
   const bool persistent = dma_shape_ok(in, out, p.k) && (long long)p.splits * p.k == rows;
-  const GemmForm form = gemm_form(persistent, p.splits, in, out, p.k, kLayoutWeightGrad, 256);
+  const GemmForm form = gemm_form(persistent, p.splits, in, out, p.k, kLayoutWeightGrad, kPlanUnits);
   if (form == kPersistent) return launch_gemm_bf16_f32out(true, X, dY, partial, p.splits, in, out, p.k, st);
   return gemm_bf16_edge<3, true, false>(form, GemmArgs{X, dY, partial}, p.splits, in, out, p.k, st, (int)rows);
 }
@@ -1615,21 +1626,32 @@ int launch_expert_wgrad1(const moe_config& c, const void* buf, const void* dh, v
   return wgrad(c, buf, dh, dwi, c.M, c.H, kept, st);
 }
 
-// The gradients of out = h . wo (dh, dwo) and of h = relu(x . wi) (dbuf, dwi), in one launch where that is faster.
-static int pair_or_none(const moe_config& c, const GemmArgs& data, GemmLayout layout, const GemmArgs& weight, int N, int K,
-                        const int32_t* kept, hipStream_t st, bool* done) {
-  // upstream [R,K], weight [N,K]: [R,K] . [N,K]^T -> [R,N] and [R,N]^T . [R,K] -> [N,K]
-  const int R = c.G * c.C;
-  PairProduct d{data, c.E, R, N, K, kPersistent, 0}, w{weight, c.E, N, K, R, kPersistent, 0};
+// The gradients of out = h . wo (dh, dwo; masked) and of h = relu(x . wi) (dbuf, dwi), in one launch where that is faster.
+// upstream [R,K], weight [N,K]: [R,K] . [N,K]^T -> [R,N] and [R,N]^T . [R,K] -> [N,K]
+static bool expert_pair(const moe_config& c, bool masked, bool packed, int cus, PairProduct* d, PairProduct* w) {
+  const int R = c.G * c.C, N = masked ? c.H : c.M, K = masked ? c.M : c.H;
+  const GemmLayout layout = masked ? kLayoutMaskedDataGrad : kLayoutDataGrad;
+  d->E = w->E = c.E;
+  d->R = w->K = R; d->N = w->R = N; d->K = w->N = K;
   GemmForm h;
-  const bool train = kept != nullptr && layout == kLayoutMaskedDataGrad;
-  if ((train ? choose_train_forms(c, &h, &d.form, &d.us) : choose_form(c.E, R, N, K, layout, &d.form, false, &d.us)) != MOE_OK ||
-      choose_form(c.E, w.R, w.N, R, kLayoutWeightGrad, &w.form, kept != nullptr, &w.us) != MOE_OK)
-    return MOE_EHIP;
+  if (masked && packed) train_forms_of(c, cus, &h, &d->form, &d->us);
+  else d->form = form_of(c.E, R, N, K, layout, false, cus, &d->us);
+  w->form = form_of(c.E, N, K, R, kLayoutWeightGrad, packed, cus, &w->us);
+  return pair_ok(d, layout, w, cus);
+}
+static int pair_or_none(const moe_config& c, bool masked, const GemmArgs& data, const GemmArgs& weight, const int32_t* kept,
+                        hipStream_t st, bool* done) {
   int cus = 0;
   if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
-  *done = pair_ok(&d, layout, &w, cus);
-  return *done ? launch_pair(d, w, st) : MOE_OK;
+  PairProduct d{data}, w{weight};
+  return expert_pair(c, masked, kept != nullptr, cus, &d, &w) ? launch_pair(d, w, st, done) : MOE_OK;
+}
+bool gradient_pair_forms(const moe_config& c, bool masked, int cus, int* data, int* weight) {
+  PairProduct d{}, w{};
+  if (c.act_dtype != MOE_BF16 || !expert_pair(c, masked, expert_ffn_can_pack(c), cus, &d, &w)) return false;
+  *data = d.form;
+  *weight = w.form;
+  return true;
 }
 
 int launch_expert_grads2(const moe_config& c, const void* dout, const void* wo, const void* h, const void* signbits, void* dh,
@@ -1639,7 +1661,7 @@ int launch_expert_grads2(const moe_config& c, const void* dout, const void* wo, 
     d.kept = w.kept = kept;
     if (kept != nullptr) d.row_pad = packed_row_pad(c);
     bool done = false;
-    const int rc = pair_or_none(c, d, kLayoutMaskedDataGrad, w, c.H, c.M, kept, st, &done);
+    const int rc = pair_or_none(c, true, d, w, kept, st, &done);
     if (rc != MOE_OK || done) return rc;
   }
   const int rc = launch_expert_dgrad2(c, dout, wo, h, signbits, dh, kept, st);
@@ -1652,7 +1674,7 @@ int launch_expert_grads1(const moe_config& c, const void* dh, const void* wi, vo
     GemmArgs d{dh, wi, dbuf}, w{buf, dh, dwi};
     d.kept = w.kept = kept;
     bool done = false;
-    const int rc = pair_or_none(c, d, kLayoutDataGrad, w, c.M, c.H, kept, st, &done);
+    const int rc = pair_or_none(c, false, d, w, kept, st, &done);
     if (rc != MOE_OK || done) return rc;
   }
   const int rc = launch_expert_dgrad1(c, dh, wi, dbuf, kept, st);
@@ -1667,12 +1689,13 @@ int launch_dense_grads_pair(const DenseWgradPlan& p, long long rows, int in, int
   PairProduct d{GemmArgs{dY, W, dX, mask}, 1, (int)rows, in, out, kPersistent, 0};
   PairProduct w{GemmArgs{X, dY, p.splits > 1 ? static_cast<void*>(partial) : dW}, p.splits, in, out, p.splits > 1 ? p.k : (int)rows, kPersistent, 0};
   w.k_total = p.splits > 1 ? (int)rows : 0;
+  int cus = 0;
+  if (compute_units(&cus) != MOE_OK) return MOE_EHIP;
+  const GemmLayout layout = mask != nullptr ? kLayoutMaskedDataGrad : kLayoutDataGrad;
   const bool persistent = dma_shape_ok(in, out, w.K) && (long long)p.splits * w.K == rows;
-  if (choose_form(1, (int)rows, in, out, mask != nullptr ? kLayoutMaskedDataGrad : kLayoutDataGrad, &d.form, false, &d.us) != MOE_OK)
-    return MOE_EHIP;
-  w.form = gemm_form(persistent, p.splits, in, out, w.K, kLayoutWeightGrad, 256, &w.us);
-  *done = pair_ok(&d, mask != nullptr ? kLayoutMaskedDataGrad : kLayoutDataGrad, &w, 256);
-  return *done ? launch_pair(d, w, st) : MOE_OK;
+  d.form = form_of(1, (int)rows, in, out, layout, false, cus, &d.us);
+  w.form = gemm_form(persistent, p.splits, in, out, w.K, kLayoutWeightGrad, cus, &w.us);
+  return pair_ok(&d, layout, &w, cus) ? launch_pair(d, w, st, done) : MOE_OK;
 }
 
 }  // namespace moe

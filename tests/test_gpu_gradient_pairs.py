@@ -1,6 +1,7 @@
 """The data and the weight gradient of a linear layer in one launch.  moe_backward_events, which marks each product, launches
 them one after the other with the same arithmetic: every gradient equal bit for bit, at the edges of the tiles of the nine
-pairs, and with the weights' own memory as that of their gradients."""
+pairs, and with the weights' own memory as that of their gradients.  Which pair each case takes is pinned by
+test_kernel_rules.py."""
 import pytest
 import torch
 
@@ -29,8 +30,10 @@ CASES = [
     _cfg(1, 3000, 256, 512, 6, 1000),              # 128 x 128 rows
     _cfg(4, 627, 800, 3232, 46, 28),
     _cfg(2, 1500, 136, 904, 24, 195, 0.5),
-    _cfg(4, 1024, 512, 2048, 16, 128, 0.5),        # dh of the persistent kernel, with its mask bits, by itself
+    _cfg(4, 1024, 512, 2048, 16, 128, 0.5),        # dh of the persistent kernel, with its mask bits, when alone
     _cfg(2, 1318, 512, 2048, 9, 293),
+    _cfg(8, 595, 168, 504, 99, 13),                # 128 x 128 rows beside weights of 64 x 64 tiles
+    _cfg(1, 3464, 256, 1024, 21, 330),             # and of 64 x 128
 ]
 
 

@@ -5,6 +5,8 @@ import ctypes
 import pytest
 
 import paper_2006_16668_amd as moe
+from paper_2006_16668_amd.binding import _Config
+from test_gpu_gradient_pairs import CASES as PAIR_CASES
 
 UNITS = 256                                     # of the device that was measured
 
@@ -41,3 +43,32 @@ def test_widest_attention_takes_the_matrix_cores(d):
     bf16, f32 = 1, 0
     for heads in (1, 43690 * 128 // d, 43691 * 128 // d, 0x7fffff // d):       # up to the limit of heads . d
         assert ok(bf16, 5000, heads, d) and not ok(f32, 5000, heads, d)
+
+
+# the tiles of the data and the weight gradient that share a launch, for dh with dwo and dbuf with dwi; None: two launches
+SMALL, FLAT, LARGE = "64x64", "64x128", "128x128"
+PAIRS = [((SMALL, SMALL), (SMALL, SMALL)), ((SMALL, SMALL), (SMALL, SMALL)), ((SMALL, SMALL), (SMALL, SMALL)),
+         ((SMALL, FLAT), (SMALL, FLAT)), ((SMALL, LARGE), (SMALL, LARGE)), ((SMALL, LARGE), (FLAT, LARGE)),
+         ((FLAT, SMALL), (SMALL, SMALL)), ((SMALL, SMALL), (FLAT, SMALL)), ((LARGE, LARGE), None), ((FLAT, FLAT), (SMALL, FLAT)),
+         ((LARGE, LARGE), (LARGE, LARGE)), ((FLAT, LARGE), (LARGE, LARGE)), ((LARGE, SMALL), (SMALL, FLAT)),
+         ((LARGE, FLAT), (FLAT, FLAT))]
+FORMS = {2: LARGE, 3: LARGE, 4: FLAT, 5: FLAT, 6: SMALL, 7: SMALL}
+
+
+def _pair(cfg, masked):
+    rule = _rule("_ZN3moe19gradient_pair_formsERK10moe_configbiPiS3_", ctypes.c_void_p, ctypes.c_bool, ctypes.c_int,
+                 ctypes.c_void_p, ctypes.c_void_p)
+    c, data, weight = _Config(cfg.G, cfg.S, cfg.M, cfg.H, cfg.E, cfg.C, 1), ctypes.c_int(), ctypes.c_int()
+    if not rule(ctypes.byref(c), masked, UNITS, ctypes.byref(data), ctypes.byref(weight)):
+        return None
+    return FORMS[data.value], FORMS[weight.value]
+
+
+@pytest.mark.parametrize("cfg,want", list(zip(PAIR_CASES, PAIRS)), ids=lambda v: getattr(v, "name", ""))
+def test_pairs_of_gradients(cfg, want):
+    assert (_pair(cfg, True), _pair(cfg, False)) == want
+
+
+def test_every_pair_kernel_is_launched_by_a_case():
+    assert len(PAIRS) == len(PAIR_CASES)
+    assert len({p for case in PAIRS for p in case if p is not None}) == 9
