@@ -70,10 +70,12 @@ __device__ __forceinline__ constexpr int att_swizzle(int row) {
 #define MOE_MFMA(a, b, c)                                                                      \
   __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),                      \
                                           __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0)
-// acc += a . b with acc in accumulation registers (gradients, whose tiles no vector instruction touches).  Score tiles, which vector instructions read, stay in vector
-// registers (builtin above, and see the build's flag for this file): left to itself the compiler puts all results of a
-// kernel into one kind and copies.  It does not see what this instruction asks for: wait states after a vector
-// instruction that wrote b (fresh_operand) and before acc is read (settle_all).
+// acc += a . b with acc in accumulation registers (gradients, whose tiles no vector instruction touches).  Score tiles, which
+// vector instructions read, stay in vector registers (builtin above, and see the build's flag for this file): left to
+// itself the compiler puts all results of a kernel into one kind and copies.  It does not see what this instruction asks
+// for: 2 wait states after a vector instruction that wrote a or b (fresh_operand) and 11 before anything but the next product
+// into it touches acc (settle_all; 19 for longer products).  Both stand where the source needs them; that the compiler
+// puts no copy or spill in between is read from the compiled code by tests/test_attention_wait_states.py.
 __device__ __forceinline__ void mfma_acc(f32x16_t& acc, const u32x4_t& a, const u32x4_t& b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
