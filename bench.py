@@ -271,14 +271,14 @@ def time_backward(moe, cfg, sh, inp, ws, y, aux, K, W, kept_rows, peak):
         moe.moe_backward_events(*args, events[k])
     torch.cuda.synchronize()
     t1 = time.perf_counter()
-    names = ["combine_bwd", "dgrad2_dh", "wgrad2_dwo", "dgrad1_dbuf", "wgrad1_dwi", "gate_bwd_dwg", "dx"]
+    names = ["combine_bwd_dz", "dgrad2_dh", "wgrad2_dwo", "dgrad1_dbuf", "wgrad1_dwi", "dwg", "dx"]
     stage_ms = {n: sum(events[k][i].elapsed_time(events[k][i + 1]) for k in range(K)) / K
                 for i, n in enumerate(names)}
     gemm_ms = sum(stage_ms[n] for n in names[1:5])
     flops = 4 * 2.0 * cfg.M * cfg.H * kept_rows          # four GEMMs over the kept rows
     return {"ms_per_step": (t1 - t0) * 1e3 / K, "stages_ms": stage_ms,
             "gemm_mfma_frac": flops / (gemm_ms * 1e-3) / 1e12 / peak,
-            "note": "moe_backward after moe_forward_train on the same inputs; not part of value"}
+            "note": "moe_backward_events after moe_forward_train on the same inputs, one launch per product; not part of value"}
 
 
 def time_f32_layer(moe, cfg, K, W):

@@ -315,7 +315,9 @@ int moe_backward(const moe_config* cfg, const void* x, const float* wg, const vo
  * caller-owned events recorded on `stream`:
  *   [0] start  [1] after dout, dz (includes re-dispatching x)  [2] after dh  [3] after dwo
  *   [4] after dbuf  [5] after dwi  [6] after the partial sums of dwg  [7] after dx, dwg.
- * events == NULL is exactly moe_backward.
+ * events == NULL is exactly moe_backward.  With events each product is a launch of its own, where moe_backward
+ * runs the data and the weight gradient of a layer in one launch if both are small: the results are the same bit
+ * for bit, but the stages' sum is then not that call's time.
  */
 #define MOE_BACKWARD_EVENTS 8
 int moe_backward_events(const moe_config* cfg, const void* x, const float* wg, const void* wi,

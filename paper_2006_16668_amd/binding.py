@@ -437,7 +437,7 @@ def moe_backward(shape: MoEShape, x, wg, wi, wo, dy, daux, fwd_ws, dx, dwg, dwi,
 
 
 def moe_backward_events(shape: MoEShape, x, wg, wi, wo, dy, daux, fwd_ws, dx, dwg, dwi, dwo, ws, events):
-    """moe_backward that records BACKWARD_EVENTS torch.cuda.Event objects at its stage boundaries."""
+    """moe_backward, one launch per product, that records BACKWARD_EVENTS torch.cuda.Event objects between them."""
     if len(events) != BACKWARD_EVENTS:
         raise ValueError(f"need {BACKWARD_EVENTS} events")
     handles = (ctypes.c_void_p * BACKWARD_EVENTS)(*[ctypes.c_void_p(e.cuda_event) for e in events])
