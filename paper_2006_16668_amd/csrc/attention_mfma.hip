@@ -1040,6 +1040,14 @@ __global__ __launch_bounds__(256, 1) void attention_bwd_dkv_mfma_kernel(
 
 }  // namespace
 
+// dk, dv of d 128, L % 128 == 0: two tiles of 32 keys per wavefront.  One block shares a compute unit with no other, and 256 keys of
+// a block take 1.46 times as long as 128 (L 1024, 192 blocks of 128 35.4 us, 96 of 256 51.7; with the three terms of ragged
+// lengths 1.75 times, and never worth it).
+bool attention_dkv_wide(long long sequence_heads, int L, int cus) {
+  const long long rounds = (sequence_heads * (L / 128) + cus - 1) / cus, rounds2 = (sequence_heads * ((L + 255) / 256) + cus - 1) / cus;
+  return 1.46 * (double)rounds2 < (double)rounds;
+}
+
 // Which dq kernel a ragged length takes, from 680 calls of both (us, short kernel / the other; sequence-heads of L tokens).
 // Under 256 tokens the short one: d 128, 64 of 48 7.8 / 9.9, 400 of 100 21.5 / 21.9; d 64, 64 of 48 6.0 / 6.7, 1000 of 100
 // 25.5 / 26.2, 32 of 193 11.6 / 12.7 (three blocks of keys of d 64 are as often faster with either: 96 of 191 11.0 / 12.1, 96 of
@@ -1101,11 +1109,8 @@ int launch_bwd(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const f
   if (!dq_short)
     hipLaunchKernelGGL((attention_bwd_dq_mfma_kernel<D, RAGGED>), dim3((unsigned)blocks), dim3(256), kLdsQ<D>, st, qkv, ctx, dctx,
                      lse, dqkv, dvec, L, heads);
-  // dk, dv of d 128: one block per compute unit, and 256 keys of a block take 1.46 times as long as 128 (L 1024, 192 blocks
-  // of 128 35.4 us, 96 of 256 51.7; with three terms of P and dS 1.75 times, and never worth it)
-  const long long rounds = (blocks + cus - 1) / cus, rounds2 = (blocks2 + cus - 1) / cus;
   if constexpr (D == 128 && !RAGGED)
-    if (1.46 * (double)rounds2 < (double)rounds) {
+    if (attention_dkv_wide(B * heads, L, cus)) {
       hipLaunchKernelGGL((attention_bwd_dkv_mfma_kernel<D, 2, RAGGED>), dim3((unsigned)blocks2), dim3(256), (kLdsKV<D, 2>), st, qkv,
                          dctx, lse, dvec, dqkv, L, heads);
       return check_launch();

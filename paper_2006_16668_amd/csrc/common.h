@@ -300,6 +300,7 @@ int launch_dense_grads(const moe_config& c, long long rows, int in, int out, con
                        const void* mask, void* dX, void* dW, float* partial, hipStream_t st);
 // MFMA form (attention_mfma.hip): bf16, d = 64 or 128
 bool attention_mfma_ok(int act_dtype, int L, int heads, int d);
+bool attention_dkv_wide(long long sequence_heads, int L, int cus);
 bool attention_dq_short(int d, int L, long long blocks, int cus);      // L % 128 != 0; blocks of 128 queries
 int launch_attention_mfma(const void* qkv, void* ctx, float* lse, long long B, int L, int heads, int d, hipStream_t st);
 int launch_attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, const float* lse,

@@ -16,7 +16,6 @@ DEV = "cuda:0"
 
 
 def step(B, L, heads, d, x, dy, w, u):
-    cfg = MoEConfig("blocks", G=B, S=L, M=256, H=256, E=2, C=L, act_dtype="bf16")
     sh = moe.MoEShape(B, L, 256, 256, 2, L, "bf16")
     dims = moe.EncoderDims(B, L, heads, d)
     new = lambda n: torch.empty(n, dtype=torch.uint8, device=DEV)
@@ -27,12 +26,17 @@ def step(B, L, heads, d, x, dy, w, u):
     grads, dx = {k: like(v) for k, v in w.items()}, torch.empty_like(x)
     moe.moe_encoder_pair_backward(sh, dims, x, w, dy, torch.zeros(B, device=DEV), fws, dx, grads,
                                   new(moe.moe_encoder_backward_workspace_bytes(sh, dims)))
-    assert cfg.G == B
     return y, dx
 
 
-@pytest.mark.parametrize("d,heads,L,B", [(128, 8, 256, 40), (128, 8, 512, 24), (128, 8, 384, 40), (64, 8, 256, 40), (64, 8, 128, 70),
-                                         (128, 8, 129, 24), (128, 8, 200, 40), (128, 8, 321, 24), (64, 8, 257, 24), (64, 8, 449, 24)])
+# two of each are the few.  WIDE: the many take the dk, dv kernel of 64 keys per wavefront (L 384 and 640: its last block has
+# wavefronts without keys, which only stage)
+WIDE = [(128, 8, 256, 40), (128, 8, 512, 24), (128, 8, 384, 16), (128, 8, 640, 8)]
+OTHERS = [(128, 8, 384, 40), (64, 8, 256, 40), (64, 8, 128, 70), (128, 8, 129, 24), (128, 8, 200, 40), (128, 8, 321, 24),
+          (64, 8, 257, 24), (64, 8, 449, 24)]
+
+
+@pytest.mark.parametrize("d,heads,L,B", WIDE + OTHERS)
 def test_many_sequences_give_the_bits_of_few(d, heads, L, B):
     cfg = MoEConfig("blocks", G=B, S=L, M=256, H=256, E=2, C=L, act_dtype="bf16", seed=5)
     inp = make_inputs(cfg, device=DEV, condition=False, with_experts=True)

@@ -6,6 +6,7 @@ import pytest
 
 import paper_2006_16668_amd as moe
 from paper_2006_16668_amd.binding import _Config
+from test_gpu_attention_blocks import OTHERS, WIDE
 from test_gpu_gradient_pairs import CASES as PAIR_CASES
 
 UNITS = 256                                     # of the device that was measured
@@ -26,6 +27,19 @@ def _rule(mangled, *types):
 def test_dq_of_ragged_sequences(d, L, n, short, other):
     rule = _rule("_ZN3moe18attention_dq_shortEiixi", ctypes.c_int, ctypes.c_int, ctypes.c_longlong, ctypes.c_int)
     assert rule(d, L, n * ((L + 127) // 128), UNITS) == (short < other)
+
+
+def test_attention_gradients_of_few_and_many_sequences():
+    """The bit-for-bit test's few and many take different kernels where it says so."""
+    wide = _rule("_ZN3moe18attention_dkv_wideExii", ctypes.c_longlong, ctypes.c_int, ctypes.c_int)
+    short = _rule("_ZN3moe18attention_dq_shortEiixi", ctypes.c_int, ctypes.c_int, ctypes.c_longlong, ctypes.c_int)
+    for cases, many in ((WIDE, True), ([c for c in OTHERS if c[0] == 128 and c[2] % 128 == 0], False)):
+        for _, heads, L, B in cases:
+            assert wide(B * heads, L, UNITS) is many and not wide(2 * heads, L, UNITS)
+    assert any(L % 256 == 128 for _, _, L, _ in WIDE)
+    took = [(short(d, L, 2 * heads * ((L + 127) // 128), UNITS), short(d, L, B * heads * ((L + 127) // 128), UNITS))
+            for d, heads, L, B in OTHERS if L % 128]
+    assert (True, False) in took and (False, True) in took
 
 
 # tokens, M, E, us of a layer of H 64 that packs wg first and of one whose gate splits it
