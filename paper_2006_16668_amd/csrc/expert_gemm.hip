@@ -832,7 +832,7 @@ __device__ __forceinline__ void edge_tile(const EdgeArgs& arg, const int logical
     stage = stage + 1 == ST ? 0 : stage + 1;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      if constexpr (kAhead == 0) {
+      if constexpr (kAhead == 0) {                             // (by itself: fa and fb in their place cost address arithmetic)
         bf16x8_t ga[TM], gb[TN];
 #pragma unroll
         for (int i = 0; i < TM; ++i) ga[i] = A_MNC ? read_mnc(sb, a_rd[i], kk, BM * 2) : read_kc(sb, a_rd[kk], i);
@@ -850,7 +850,7 @@ __device__ __forceinline__ void edge_tile(const EdgeArgs& arg, const int logical
 #pragma unroll
         for (int j = 0; j < TN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kk][j], fa[kk][i], acc[i][j], 0, 0, 0);
-      if (kAhead > 0 && kk + kAhead < KK) {
+      if (kk + kAhead < KK) {
         fetch(sb, kk + kAhead);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -1138,7 +1138,8 @@ GemmForm gemm_form(bool persistent_ok, int E, int R, int N, int K, GemmLayout la
 }
 // h of a training pass over packed rows: the persistent kernel takes relu' of dh from the bits that only it records
 // with h, so the two products are chosen together.  A dh that reads h leaves it in the last-level cache for dwo, unless it
-// is too large to stay there: an h that is slower persistent has to be that large, and gain 4 % of both.  us of h / dh / dwo,
+// is too large to stay there: an h that is slower persistent has to be that large, and gain 4 % of both.  A dh that shares its
+// launch with dwo (pair_ok, below: small layers) masks by h after all and leaves the bits unread.  us of h / dh / dwo,
 // each by its own best form, then h and dh persistent (MB of h at 0.85 full):
 //   E 12 R 4352 M 256  H 2048 (182)   80 / 162 /  83    97 /  93 /  91
 //   E 51 R 862  M 512  H 4096 (306)  234 / 346 / 198   259 / 265 / 205
