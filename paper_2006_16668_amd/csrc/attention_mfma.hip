@@ -28,8 +28,13 @@
 // scheduling hints; they were busy multiplying a quarter of the time.  us before / now: forward, dq, dk and dv of 16 x 1024
 // tokens, 16 heads of 128 180 / 155, 307 / 198, 487 / 268 (0.89, 1.04 and 1.03 PFLOP/s now); of 2 x 1024, 4 heads of 128
 // 28.6 / 23.2, 49.4 / 26.4, 47.6 / 31.5; of 62 x 1024, 4 heads of 64 57.4 / 47.2, 69.1 / 59.3, 145 / 75; of 42 x 700, 4 heads
-// of 128 98 / 88, 118 / 113, 263 / 187.  What bounds them now: the products (two thirds of the time; with random operands
-// power leaves the chip 0.7 of its peak) and, for dk and dv, the first rows of a block, which nothing overlaps.
+// of 128 98 / 88, 118 / 113, 263 / 187.  What bounds them now (32 x 1024 tokens, 16 heads): the matrix
+// pipes are busy 47, 62 and 53 % of forward, dq, dk and dv, at the 1.6 to 1.9 of 2.4 GHz that power leaves, the vector ALU
+// 66, 55 and 39 %; for dk and dv also the first rows of a block, which nothing overlaps.
+//
+// Short ragged sequences have kernels of their own with less on the way to the first product: attention_short_kernel,
+// attention_bwd_dq_short_kernel.  Without one: dk and dv of up to 33 tokens, d 64, in up to 192 blocks took 0.2 us of 6 less in
+// the kernels before these (1.4 to 2.1 times as long in more blocks), forward of 65 to 80 tokens 0.3 of 7.
 //
 // RAGGED: L is no multiple of 128.  Rows past the end are staged as zeros; their scores become -inf (forward), their part
 // of P and dS 0; columns past the end are computed from row L - 1 and not stored, and a wavefront without
